@@ -9,6 +9,7 @@
 // a K that is not a multiple of 64 takes the older path through registers, which can zero-fill the tail.
 #include "kernels.h"
 #include <algorithm>
+#include <type_traits>
 
 namespace {
 
@@ -43,20 +44,23 @@ __device__ __forceinline__ void tile_of_block(int tiles_m, int tiles_n, int spli
   tn = in_group / gsz;
 }
 
-// erf by the rational-exponential form of Abramowitz & Stegun 7.1.26 (absolute error < 1.5e-7, far below the
-// fp16 rounding of the result): a third of the instructions of the library erff, which matters in an epilogue.
-__device__ __forceinline__ float erf_as(float x) {
-  const float ax = fabsf(x);
-  const float t = __frcp_rn(1.0f + 0.3275911f * ax);
+// gelu(v) = v/2 (1 + erf(v / sqrt 2)) = v/2 + |v|/2 erf(|v| / sqrt 2), with erf by the rational-exponential form of Abramowitz &
+// Stegun 7.1.26 (absolute error < 1.5e-7, far below the 16-bit rounding of the result).  The epilogue of the widest layer is
+// bound by this arithmetic: 15 instructions and two transcendentals a value, sqrt 2 and log2 e folded into the constants.
+__device__ __forceinline__ float gelu_erf(float v) {
+  const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752f, fabsf(v), 1.0f));
   const float poly = t * (0.254829592f + t * (-0.284496736f + t * (1.421413741f + t * (-1.453152027f + t * 1.061405429f))));
-  const float r = 1.0f - poly * __expf(-ax * ax);
-  return copysignf(r, x);
+  const float z = v * 0.84932180028801907f;                   // sqrt(log2(e) / 2) v
+  const float r = fmaf(-poly, __builtin_amdgcn_exp2f(-z * z), 1.0f);
+  const float h = 0.5f * v;
+  return fmaf(fabsf(h), r, h);
 }
-__device__ __forceinline__ float gelu_erf(float v) { return 0.5f * v * (1.0f + erf_as(v * 0.70710678118654752f)); }
-__device__ __forceinline__ float silu(float v) { return v / (1.0f + __expf(-v)); }
-
-// nothing may be scheduled across this point
-#define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
+__device__ __forceinline__ float silu(float v) { return v * __builtin_amdgcn_rcpf(1.0f + __expf(-v)); }
+// v / t for one divisor t and its reciprocal: the quotient with its residual folded back in
+__device__ __forceinline__ float div_by(float v, float t, float inv_t) {
+  const float q = v * inv_t;
+  return fmaf(fmaf(-q, t, v), inv_t, q);
+}
 
 template <int N>
 __device__ __forceinline__ void wait_loads_then_barrier() {
@@ -64,300 +68,59 @@ __device__ __forceinline__ void wait_loads_then_barrier() {
   asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-// NS = 0: tiles travel global -> registers -> LDS (two LDS stages).  NS >= 2: NS LDS stages filled by direct
-// global -> LDS loads, issued NS - 1 K steps ahead (needs K % 64 == 0).
-// PR: precise mode (see GemmArgs): bf16 operands, A as hi/lo pairs; every K block of W meets the hi and then the lo
-// block of A in two consecutive steps of the K loop.
-template <int BM, int BN, int WM, int WN, int EPI, bool KTAIL, int NS = 0, bool PR = false>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_f16_kernel(GemmArgs g) {
-  constexpr int NT = WM * WN * 64;               // threads
-  constexpr int TM = BM / WM / 32, TN = BN / WN / 32;   // 32x32 MFMA tiles per wave in each direction
-  constexpr int RPP = NT / 8;                    // rows covered by one pass of 16-byte loads
-  constexpr int PA = BM / RPP, PB = BN / RPP;
-  static_assert(PA >= 1 && PB >= 1 && TM >= 1 && TN >= 1, "tile too small for the thread count");
-  static_assert(NS == 0 || (NS >= 2 && NS <= 4 && !KTAIL), "direct loads need whole K tiles");
-  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];   // max(2, NS) x (BM + BN) x BK
-  // GEMM waves issue ahead of whatever shares their SIMD: in a decode step that is the other half's attention, whose
-  // waves mostly wait for memory (measured: the GEMMs' time in that company -10 %, the decode phase -0.8 %)
-  __builtin_amdgcn_s_setprio(3);
-  constexpr int STAGE = (BM + BN) * BK;
+// nothing may be scheduled across this point
+#define SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  int tile_m, tile_n, split;
-  const int splits = EPI == EPI_PARTIAL ? g.splits : 1;
-  tile_of_block(tiles_m, tiles_n, splits, tile_m, tile_n, split);
-  const int row0 = tile_m * BM, col0 = tile_n * BN;
-
-  // ---- global -> register staging: thread t covers chunk (t % 8) of rows (t / 8) + RPP i
-  const int ld_chunk = tid & 7, ld_row = tid >> 3;
-  const uint16_t* __restrict__ A = (const uint16_t*)g.A;
-  const uint16_t* __restrict__ W = (const uint16_t*)g.W;
-  // operands are K-block major: K tile kt of rows r0.. is the contiguous run starting at (kt * rows + r0) * 64,
-  // and thread t reads bytes [16 t, 16 t + 16) of it (rows past the end repeat the last row)
-  u32x4 ra[PA], rb[PB];
-  const uint16_t* pa[PA];
-  const uint16_t* pb[PB];
-#pragma unroll
-  for (int i = 0; i < PA; ++i) {
-    int r = min(row0 + ld_row + RPP * i, g.M - 1);
-    pa[i] = A + (size_t)r * 64 + ld_chunk * 8;
-  }
-#pragma unroll
-  for (int i = 0; i < PB; ++i) {
-    int r = min(col0 + ld_row + RPP * i, g.N - 1);
-    pb[i] = W + (size_t)r * 64 + ld_chunk * 8;
-  }
-  const size_t ka = (size_t)g.M * 64, kw = (size_t)g.N * 64;    // elements between K tiles
-  const int nkb = (g.K + BK - 1) / BK;                          // K blocks of W (and of each half of a hi/lo A)
-  // K tile kt of the loop reads block ak(kt) of A and block wk(kt) of W.  Precise mode takes the hi and the lo block of A
-  // against the same block of W in consecutive steps (A holds its nkb hi blocks, then its nkb lo blocks): the second
-  // request for the W block finds it in L2, so the weights cross HBM once
-  auto wk = [&](int kt) { return PR ? kt >> 1 : kt; };
-  auto ak = [&](int kt) { return PR ? (kt >> 1) + (kt & 1) * nkb : kt; };
-  auto load_global = [&](int kt) {
-    if constexpr (KTAIL) {     // K is not a multiple of BK: chunks beyond K read as zero
-      const bool ok = wk(kt) * BK + ld_chunk * 8 < g.K;
-#pragma unroll
-      for (int i = 0; i < PA; ++i) ra[i] = ok ? *(const u32x4*)(pa[i] + ak(kt) * ka) : u32x4{0, 0, 0, 0};
-#pragma unroll
-      for (int i = 0; i < PB; ++i) rb[i] = ok ? *(const u32x4*)(pb[i] + wk(kt) * kw) : u32x4{0, 0, 0, 0};
-    } else {
-#pragma unroll
-      for (int i = 0; i < PA; ++i) ra[i] = *(const u32x4*)(pa[i] + ak(kt) * ka);
-#pragma unroll
-      for (int i = 0; i < PB; ++i) rb[i] = *(const u32x4*)(pb[i] + wk(kt) * kw);
-    }
-  };
-  // one 32x32x16 matrix instruction on 16-bit fragments: fp16, or bf16 in precise mode
-  auto mfma = [](f16x8 b, f16x8 a, f32x16 c) {
-    if constexpr (PR) return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b), __builtin_bit_cast(bf16x8, a), c, 0, 0, 0);
-    else return __builtin_amdgcn_mfma_f32_32x32x16_f16(b, a, c, 0, 0, 0);
-  };
-  auto store_lds = [&](int buf) {
-    uint16_t* la = lds + buf * STAGE;
-    uint16_t* lb = la + BM * BK;
-#pragma unroll
-    for (int i = 0; i < PA; ++i) {
-      int r = ld_row + RPP * i;
-      *(u32x4*)(la + r * BK + ((ld_chunk ^ swz(r)) * 8)) = ra[i];
-    }
-#pragma unroll
-    for (int i = 0; i < PB; ++i) {
-      int r = ld_row + RPP * i;
-      *(u32x4*)(lb + r * BK + ((ld_chunk ^ swz(r)) * 8)) = rb[i];
-    }
-  };
-
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-  const int nk_all = PR ? 2 * nkb : nkb;
-  const int kt0 = (int)((long long)split * nk_all / splits);          // this block's share of the K tiles
-  const int nk = (int)((long long)(split + 1) * nk_all / splits);
-  const int frow = lane & 31, fhalf = lane >> 5;
-  // one K step on the LDS stage `buf`; `mid` runs between the last two MFMA groups
-  auto k_step = [&](int buf, auto&& mid) {
-    const uint16_t* la = lds + buf * STAGE + (wm * (BM / WM)) * BK;
-    const uint16_t* lb = lds + buf * STAGE + BM * BK + (wn * (BN / WN)) * BK;
-    // fragments of step kk + 1 are fetched from LDS while the MFMAs of step kk run
-    f16x8 fa[2][TM], fb[2][TN];
-    auto load_frags = [&](int kk, int slot) {
-      const int chunk = kk * 2 + fhalf;
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        int r = i * 32 + frow;
-        fa[slot][i] = *(const f16x8*)(la + r * BK + ((chunk ^ swz(r)) * 8));
-      }
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        int r = j * 32 + frow;
-        fb[slot][j] = *(const f16x8*)(lb + r * BK + ((chunk ^ swz(r)) * 8));
-      }
-    };
-    load_frags(0, 0);
-#pragma unroll
-    for (int kk = 0; kk < BK / 16; ++kk) {
-      if (kk + 1 < BK / 16) load_frags(kk + 1, (kk + 1) & 1);
-      if (kk == BK / 16 - 2) mid();
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = mfma(fb[kk & 1][j], fa[kk & 1][i], acc[i][j]);
-    }
-  };
-
-  if constexpr (NS == 0) {
-    load_global(kt0);
-    store_lds(kt0 & 1);
-    __syncthreads();
-    for (int kt = kt0; kt < nk; ++kt) {
-      const int cur = kt & 1;
-      if (kt + 1 < nk) load_global(kt + 1);
-      // the next tile moves from registers to the other LDS buffer under the last MFMAs of this one
-      k_step(cur, [&] { if (kt + 1 < nk) store_lds(cur ^ 1); });
-      __syncthreads();
-    }
-  } else {
-    // Direct loads: a wave instruction moves 64 16-byte chunks = 8 tile rows into 1 KB of LDS in lane order, so
-    // the XOR swizzle is applied on the source side: the lane that fills chunk position p of row r fetches chunk
-    // p ^ swz(r).  Rows advance by a multiple of 16 per pass, which leaves swz(r) unchanged.
-    static_assert(RPP % 16 == 0, "the swizzle must not depend on the pass");
-    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    const int lrow = wave_u * 8 + (lane >> 3);
-    const int schunk = (lane & 7) ^ swz(lrow);
-    const uint16_t* qa[PA];
-    const uint16_t* qb[PB];
-#pragma unroll
-    for (int i = 0; i < PA; ++i) qa[i] = A + (size_t)min(row0 + lrow + RPP * i, g.M - 1) * 64 + schunk * 8;
-#pragma unroll
-    for (int i = 0; i < PB; ++i) qb[i] = W + (size_t)min(col0 + lrow + RPP * i, g.N - 1) * 64 + schunk * 8;
-    typedef const __attribute__((address_space(1))) void* gptr_t;
-    typedef __attribute__((address_space(3))) void* lptr_t;
-    auto issue = [&](int kt, int buf) {
-      uint16_t* la = lds + buf * STAGE + wave_u * 8 * BK;
-#pragma unroll
-      for (int i = 0; i < PA; ++i)
-        __builtin_amdgcn_global_load_lds((gptr_t)(qa[i] + ak(kt) * ka), (lptr_t)(la + i * RPP * BK), 16, 0, 0);
-#pragma unroll
-      for (int i = 0; i < PB; ++i)
-        __builtin_amdgcn_global_load_lds((gptr_t)(qb[i] + wk(kt) * kw), (lptr_t)(la + (BM + i * RPP) * BK), 16, 0, 0);
-    };
-    constexpr int L = PA + PB;                      // loads per wave and stage
-    if constexpr (NS == 2) {
-      // Skewed by a quarter of a K step: the wait for the next stage and the barrier sit before the last of the four
-      // MFMA groups of a stage, whose fragments are in registers by then.  Behind the barrier nobody reads this
-      // stage's LDS any more, so its buffer is refilled at once, and the first fragments of the next stage are
-      // fetched while the last MFMA group runs: the matrix pipe does not drain at the stage boundary.
-      f16x8 fa[2][TM], fb[2][TN];
-      auto frags = [&](int buf, int kk, int slot) {
-        const uint16_t* la = lds + buf * STAGE + (wm * (BM / WM)) * BK;
-        const uint16_t* lb = lds + buf * STAGE + BM * BK + (wn * (BN / WN)) * BK;
-        const int chunk = kk * 2 + fhalf;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          int r = i * 32 + frow;
-          fa[slot][i] = *(const f16x8*)(la + r * BK + ((chunk ^ swz(r)) * 8));
-        }
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          int r = j * 32 + frow;
-          fb[slot][j] = *(const f16x8*)(lb + r * BK + ((chunk ^ swz(r)) * 8));
-        }
-      };
-      constexpr int HEAD = TM * TN >= 8 ? 2 : 1;
-      auto mma = [&](int slot, int lo, int hi) {     // MFMAs lo .. hi - 1 of the group, row-major over the wave's tiles
-#pragma unroll
-        for (int t = 0; t < TM * TN; ++t)
-          if (t >= lo && t < hi)
-            acc[t / TN][t % TN] = mfma(fb[slot][t % TN], fa[slot][t / TN], acc[t / TN][t % TN]);
-      };
-      issue(kt0, 0);
-      wait_loads_then_barrier<0>();
-      if (kt0 + 1 < nk) issue(kt0 + 1, 1);
-      frags(0, 0, 0);
-      for (int kt = kt0; kt < nk; ++kt) {
-        const int buf = (kt - kt0) & 1;
-        // Per MFMA group: the first MFMAs, then the LDS reads of the next group's fragments, then the rest, in exactly
-        // this order (the fences stop the compiler from sinking the reads behind the MFMAs, where the wait for them
-        // would sit directly in front of their first use).
-        mma(0, 0, HEAD);
-        SCHED_FENCE();
-        frags(buf, 1, 1);
-        SCHED_FENCE();
-        mma(0, HEAD, TM * TN);
-        SCHED_FENCE();
-        mma(1, 0, HEAD);
-        SCHED_FENCE();
-        frags(buf, 2, 0);
-        SCHED_FENCE();
-        mma(1, HEAD, TM * TN);
-        SCHED_FENCE();
-        mma(0, 0, HEAD);
-        SCHED_FENCE();
-        frags(buf, 3, 1);
-        SCHED_FENCE();
-        mma(0, HEAD, TM * TN);
-        SCHED_FENCE();
-        mma(1, 0, HEAD);
-        SCHED_FENCE();
-        if (kt + 1 < nk) {
-          // stage kt + 1 has landed, and every wave holds its last fragments of stage kt in registers
-          asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-          if (kt + 2 < nk) issue(kt + 2, buf);
-          frags(buf ^ 1, 0, 0);
-          SCHED_FENCE();
-        }
-        mma(1, HEAD, TM * TN);
-        SCHED_FENCE();
-      }
-    } else {
-#pragma unroll
-    for (int s = 0; s < NS - 1; ++s)
-      if (kt0 + s < nk) issue(kt0 + s, s);
-    for (int kt = kt0; kt < nk; ++kt) {
-      // stage kt must have landed; up to NS - 2 younger stages may still be in flight
-      const int younger = min(nk - 1 - kt, NS - 2);
-      if (younger >= 2) wait_loads_then_barrier<2 * L>();
-      else if (younger == 1) wait_loads_then_barrier<L>();
-      else wait_loads_then_barrier<0>();
-      // every wave has left stage kt - 1: its buffer takes stage kt + NS - 1
-      if (kt + NS - 1 < nk) issue(kt + NS - 1, (kt - kt0 + NS - 1) % NS);
-      k_step((kt - kt0) % NS, [] {});
-    }
-    }
-  }
-
-  // ---- epilogue.  The products were issued as W_tile . A_tile^T, so acc[i][j][e] is C[m][n] with
-  // m = lane % 32 (row of the 32x32 tile) and n = 8 (e / 4) + 4 (lane / 32) + e % 4: every lane holds runs of four
-  // consecutive columns of one row, which makes outputs, bias and residual 16-byte accesses and turns the
-  // row-wise softmax statistics of the LM head into in-register reductions.
-  const int wrow0 = row0 + wm * (BM / WM), wcol0 = col0 + wn * (BN / WN);
+// What becomes of a wave's accumulators.  The products were issued as W_tile . A_tile^T, so acc[i][j][r] is C[m][n] with
+// m = 16 i + lane % 16 and n = 16 j + 4 (lane / 16) + r: every lane holds runs of four consecutive columns of one row,
+// which makes outputs, bias and residual 16-byte accesses and turns the row-wise softmax statistics of the LM head into
+// in-register reductions.  (wrow0, wcol0): the wave's first row and column.  FULL: every row and column of the wave exists
+// and rows start on 16-byte boundaries, so that no access needs a condition of its own (a wave that runs alone on its SIMD
+// waits out every branch: the epilogue of a whole 256x256 tile is a third shorter without them).
+template <int TM, int TN, int EPI, bool PR, bool FULL>
+__device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 (&acc)[TM][TN], int wrow0, int wcol0, int lane, int split) {
+  const int frow = lane & 15, fq = lane >> 4;
   if constexpr (EPI == EPI_LMHEAD) {
     // per row and per 64-column group: max and sum of exp of the tempered logits; optional capture
     // of the target column's tempered logit.  Nothing of size [M, N] is written.
-    static_assert(TN % 2 == 0, "a wave must own whole 64-column groups");
+    static_assert(TN % 4 == 0, "a wave must own whole 64-column groups");
     const int ngroups = (g.N + 63) >> 6;
+    const float inv_t = 1.0f / g.temperature;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-      const int row = wrow0 + i * 32 + frow;
-      const int tgt = (g.target != nullptr && row < g.M) ? g.target[row] : -1;
+      const int row = wrow0 + i * 16 + frow;
+      const int tgt = (g.target != nullptr && (FULL || row < g.M)) ? g.target[row] : -1;
 #pragma unroll
-      for (int gi = 0; gi < TN / 2; ++gi) {
+      for (int gi = 0; gi < TN / 4; ++gi) {
         const int group = (wcol0 >> 6) + gi;
-        float l[32];
+        float l[16];
         float mx = -INFINITY;
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
+        for (int jj = 0; jj < 4; ++jj)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int col = wcol0 + (2 * gi + jj) * 32 + 8 * (e >> 2) + 4 * fhalf + (e & 3);
-            const float v = col < g.N ? acc[i][2 * gi + jj][e] / g.temperature : -INFINITY;
-            l[jj * 16 + e] = v;
+          for (int r = 0; r < 4; ++r) {
+            const int col = wcol0 + (4 * gi + jj) * 16 + 4 * fq + r;
+            const float v = FULL || col < g.N ? div_by(acc[i][4 * gi + jj][r], g.temperature, inv_t) : -INFINITY;
+            l[jj * 4 + r] = v;
             mx = fmaxf(mx, v);
             if (col == tgt) g.target_logit[row] = v;
           }
+        mx = fmaxf(mx, __shfl_xor(mx, 16, WAVE));
         mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
         float sum = 0.f;
 #pragma unroll
-        for (int e = 0; e < 32; ++e) sum += (l[e] == -INFINITY) ? 0.f : __expf(l[e] - mx);
+        for (int e = 0; e < 16; ++e) sum += (!FULL && l[e] == -INFINITY) ? 0.f : __expf(l[e] - mx);
+        sum += __shfl_xor(sum, 16, WAVE);
         sum += __shfl_xor(sum, 32, WAVE);
-        if (fhalf == 0 && row < g.M && group < ngroups) g.partial[(size_t)row * ngroups + group] = make_float2(mx, sum);
+        if (fq == 0 && (FULL || (row < g.M && group < ngroups))) g.partial[(size_t)row * ngroups + group] = make_float2(mx, sum);
       }
     }
-  } else {
+  } else if constexpr (EPI == EPI_QKV) {
     [[maybe_unused]] bool sat = false;        // an fp16 output was clamped
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-      const int row = wrow0 + i * 32 + frow;
-      if (row >= g.M) continue;
+      const int row = wrow0 + i * 16 + frow;
+      if (!FULL && row >= g.M) continue;
       // EPI_QKV: this row's rotary table row, its q and staging rows, and where its key / value start inside
       // kv head 0's stream of its cache sequence (the parts of KvLayout::k_elem / v_elem that depend on the
       // slot alone; kv heads are per_head elements apart)
@@ -383,35 +146,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_f16_kernel(GemmArgs g) {
       }
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int col = wcol0 + j * 32 + 8 * q + 4 * fhalf;       // first of four consecutive columns
-          if (col >= g.N) continue;
-          const bool full = col + 3 < g.N;
-          f32x4 v;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) v[r] = acc[i][j][4 * q + r];
-          if constexpr (EPI == EPI_PARTIAL) {
-            float* p = g.ws + ((size_t)split * g.M + row) * g.N + col;
-            if (full && (g.N & 3) == 0) *(f32x4*)p = v;
-            else
-              for (int r = 0; r < 4 && col + r < g.N; ++r) p[r] = v[r];
-            continue;
-          }
-          if (g.bias) {
-            if (full) v += *(const f32x4*)(g.bias + col);
-            else
-              for (int r = 0; r < 4 && col + r < g.N; ++r) v[r] += g.bias[col + r];
-          }
-          if constexpr (EPI == EPI_F32 || EPI == EPI_RESID) {
-            float* p = (float*)g.out + (size_t)row * g.ldo + col;
-            if (full && (g.ldo & 3) == 0) {
-              if constexpr (EPI == EPI_RESID) v += *(const f32x4*)p;
-              *(f32x4*)p = v;
-            } else {
-              for (int r = 0; r < 4 && col + r < g.N; ++r) p[r] = (EPI == EPI_RESID ? p[r] : 0.f) + v[r];
-            }
-          } else if constexpr (EPI == EPI_QKV) {
+        const int col = wcol0 + j * 16 + 4 * fq;       // first of four consecutive columns
+        if (!FULL && col >= g.N) continue;
+        f32x4 v = acc[i][j];
+        if (g.bias) v += *(const f32x4*)(g.bias + col);
+        {
             // head dims of a group of four packed columns: a rotary group holds the pairs (d0, d0 + r/2) and
             // (d0 + 1, d0 + 1 + r/2) as (v0, v2) and (v1, v3); any other group holds four consecutive dims
             const QkvEpi& e = g.qe;
@@ -481,66 +220,488 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_f16_kernel(GemmArgs g) {
               for (int r = 0; r < 4; ++r) st[r << 3] = f32_to_bf16_bits(v[r]);
             }
             }
-          } else if constexpr (EPI == EPI_GELU_F16) {
-            uint16_t* p = (uint16_t*)g.out + kblk_off(row, col, g.M);     // four columns never straddle a K block
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              v[r] = gelu_erf(v[r]);
-              if constexpr (!PR) sat |= f16_out_of_range(v[r]) && col + r < g.N;
-            }
-            if constexpr (PR) {
-              u32x2 wh, wl;
-              SPLIT_BF16X2(v[0], v[1], wh[0], wl[0]);
-              SPLIT_BF16X2(v[2], v[3], wh[1], wl[1]);
-              if (full) {
-                *(u32x2*)p = wh;
-                *(u32x2*)(p + g.out_lo_off) = wl;
-              } else {
-                for (int r = 0; r < 4 && col + r < g.N; ++r) {
-                  p[r] = (uint16_t)(wh[r >> 1] >> (16 * (r & 1)));
-                  p[g.out_lo_off + r] = (uint16_t)(wl[r >> 1] >> (16 * (r & 1)));
-                }
-              }
-            } else if (full) {
-              u32x2 w;
-              w[0] = pack_f16x2(v[0], v[1]);
-              w[1] = pack_f16x2(v[2], v[3]);
-              *(u32x2*)p = w;
-            } else {
-              for (int r = 0; r < 4 && col + r < g.N; ++r) p[r] = f32_to_f16_bits(v[r]);
-            }
-          } else if constexpr (EPI == EPI_SWIGLU_F16) {
-            // weight rows come in blocks of 32: block 2b = gate rows [32b, 32b+32), block 2b+1 = the
-            // matching up rows, so tile j (even) and tile j+1 hold gate and up of the same features.
-            static_assert(TN % 2 == 0, "a wave must own gate and up of the same features");
-            if ((j & 1) == 0) {
-              const int f = ((wcol0 + j * 32) >> 1) + 8 * q + 4 * fhalf;
-              u32x2 w;
-              const int ju = j + 1 < TN ? j + 1 : j;
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                v[r] = silu(v[r]) * acc[i][ju][4 * q + r];
-                if constexpr (!PR) sat |= f16_out_of_range(v[r]);
-              }
-              uint16_t* p = (uint16_t*)g.out + kblk_off(row, f, g.M);
-              if constexpr (PR) {
-                u32x2 wl;
-                SPLIT_BF16X2(v[0], v[1], w[0], wl[0]);
-                SPLIT_BF16X2(v[2], v[3], w[1], wl[1]);
-                *(u32x2*)(p + g.out_lo_off) = wl;
-              } else {
-                w[0] = pack_f16x2(v[0], v[1]);
-                w[1] = pack_f16x2(v[2], v[3]);
-              }
-              *(u32x2*)p = w;
-            }
-          }
         }
       }
     }
-    if constexpr (EPI == EPI_QKV || EPI == EPI_GELU_F16 || EPI == EPI_SWIGLU_F16) flag_f16_range(sat, g.status);
+    if constexpr (!PR) flag_f16_range(sat, g.status);
+  } else {
+    // The place of (i, j) is a distance common to the wave plus one 32-bit distance of the lane: a scalar base and one
+    // register address every access.  Column tiles outside, so that a bias is read once.
+    [[maybe_unused]] bool sat = false;
+    constexpr bool F32OUT = EPI == EPI_F32 || EPI == EPI_RESID || EPI == EPI_PARTIAL;
+    const int ld = EPI == EPI_PARTIAL ? g.N : g.ldo;
+    const uint32_t lane_off = F32OUT ? (uint32_t)(frow * ld + 4 * fq) * 4 : (uint32_t)(frow * 64 + 4 * fq) * 2;
+    auto place = [&](int i, int j) -> char* {
+      const size_t row = wrow0 + i * 16;
+      // first output column of the tile (SwiGLU: weight rows come in blocks of 32, gates and then the matching ups)
+      const int col = EPI == EPI_SWIGLU_F16 ? (wcol0 >> 1) + (j >> 2) * 32 + (j & 1) * 16 : wcol0 + j * 16;
+      if constexpr (EPI == EPI_PARTIAL) return (char*)(g.ws + ((size_t)split * g.M + row) * g.N + col);
+      else if constexpr (F32OUT) return (char*)((float*)g.out + row * g.ldo + col);
+      else return (char*)((uint16_t*)g.out + ((size_t)(col >> 6) * g.M + row) * 64 + (col & 63));
+    };
+    auto live = [&](int i) { return FULL || wrow0 + i * 16 + frow < g.M; };
+    // the residual's values travel one column tile ahead: with one wave per SIMD nothing else covers their latency
+    [[maybe_unused]] f32x4 old[TM];
+    auto fetch = [&](int j) {
+      if (!FULL && wcol0 + j * 16 + 4 * fq >= g.N) return;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+        if (live(i)) old[i] = *(const f32x4*)(place(i, j) + lane_off);
+    };
+    if constexpr (EPI == EPI_RESID) fetch(0);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      if (EPI == EPI_SWIGLU_F16 && (j & 2)) continue;       // the ups, taken along with their gates
+      const int col4 = wcol0 + j * 16 + 4 * fq;             // first of the lane's four columns
+      if (!FULL && col4 >= g.N) continue;
+      // only plain fp32 outputs (logits of any vocabulary) have widths or rows that break up the groups of four
+      const bool four = FULL || EPI != EPI_F32 || (col4 + 3 < g.N && (ld & 3) == 0);
+      f32x4 bias = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (EPI != EPI_PARTIAL && g.bias) {
+        if (four) bias = *(const f32x4*)((const char*)(g.bias + wcol0 + j * 16) + (uint32_t)(fq * 16));
+        else
+          for (int r = 0; r < 4; ++r) bias[r] = col4 + r < g.N ? g.bias[col4 + r] : 0.f;
+      }
+      auto at = [&](int i) -> char* { return place(i, j); };
+      f32x4 v[TM];
+      if constexpr (EPI == EPI_RESID) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) v[i] = old[i];
+        if (j + 1 < TN) fetch(j + 1);
+      }
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        if (!live(i)) continue;
+        if constexpr (EPI == EPI_PARTIAL) v[i] = acc[i][j];
+        else if constexpr (EPI == EPI_F32) v[i] = acc[i][j] + bias;
+        else if constexpr (EPI == EPI_RESID) v[i] += acc[i][j] + bias;
+        else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            if constexpr (EPI == EPI_GELU_F16) v[i][r] = gelu_erf(acc[i][j][r] + bias[r]);
+            else v[i][r] = silu(acc[i][j][r] + bias[r]) * acc[i][(j + 2) % TN][r];
+            if constexpr (!PR) sat |= f16_out_of_range(v[i][r]);
+          }
+        }
+        if constexpr (F32OUT) {
+          if (four) *(f32x4*)(at(i) + lane_off) = v[i];
+          else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (col4 + r < g.N) ((float*)(at(i) + lane_off))[r] = v[i][r];
+          }
+        } else {
+          u32x2 w;
+          if constexpr (PR) {
+            u32x2 wl;
+            SPLIT_BF16X2(v[i][0], v[i][1], w[0], wl[0]);
+            SPLIT_BF16X2(v[i][2], v[i][3], w[1], wl[1]);
+            *(u32x2*)(at(i) + g.out_lo_off * 2 + lane_off) = wl;
+          } else {
+            w[0] = pack_f16x2(v[i][0], v[i][1]);
+            w[1] = pack_f16x2(v[i][2], v[i][3]);
+          }
+          *(u32x2*)(at(i) + lane_off) = w;
+        }
+      }
+      SCHED_FENCE();
+    }
+    if constexpr ((EPI == EPI_GELU_F16 || EPI == EPI_SWIGLU_F16) && !PR) flag_f16_range(sat, g.status);
   }
 }
+template <int TM, int TN, int EPI, bool PR>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, const f32x4 (&acc)[TM][TN], int wrow0, int wcol0, int lane, int split) {
+  const bool fits = wrow0 + TM * 16 <= g.M && wcol0 + TN * 16 <= g.N && (EPI != EPI_F32 || (g.ldo & 3) == 0);
+  if (fits) gemm_epilogue_as<TM, TN, EPI, PR, true>(g, acc, wrow0, wcol0, lane, split);
+  else gemm_epilogue_as<TM, TN, EPI, PR, false>(g, acc, wrow0, wcol0, lane, split);
+}
+
+// One 16x16x32 matrix instruction on 16-bit fragments: fp16, or bf16 in precise mode.  (The 32x32x16 form reads half the
+// operand bits per product and yet costs more power: on random operands the chip sustains 1960 TFLOP/s with this one and
+// 1700 with that one, at 1.92 and 1.62 GHz.)
+template <bool PR>
+__device__ __forceinline__ f32x4 mfma16(f16x8 b, f16x8 a, f32x4 c) {
+  if constexpr (PR) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, b), __builtin_bit_cast(bf16x8, a), c, 0, 0, 0);
+  else return __builtin_amdgcn_mfma_f32_16x16x32_f16(b, a, c, 0, 0, 0);
+}
+
+// NS = 0: tiles travel global -> registers -> LDS (two LDS stages).  NS >= 2: NS LDS stages filled by direct
+// global -> LDS loads, issued NS - 1 K steps ahead (needs K % 64 == 0).
+// PR: precise mode (see GemmArgs): bf16 operands, A as hi/lo pairs; every K block of W meets the hi and then the lo
+// block of A in two consecutive steps of the K loop.
+template <int BM, int BN, int WM, int WN, int EPI, bool KTAIL, int NS = 0, bool PR = false>
+__global__ __launch_bounds__(WM * WN * 64) void gemm_f16_kernel(GemmArgs g) {
+  constexpr int NT = WM * WN * 64;               // threads
+  constexpr int TM = BM / WM / 16, TN = BN / WN / 16;   // 16x16 MFMA tiles per wave in each direction
+  constexpr int RPP = NT / 8;                    // rows covered by one pass of 16-byte loads
+  constexpr int PA = BM / RPP, PB = BN / RPP;
+  static_assert(PA >= 1 && PB >= 1 && TM >= 1 && TN >= 1, "tile too small for the thread count");
+  static_assert(NS == 0 || (NS >= 2 && NS <= 4 && !KTAIL), "direct loads need whole K tiles");
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];   // max(2, NS) x (BM + BN) x BK
+  // GEMM waves issue ahead of whatever shares their SIMD: in a decode step that is the other half's attention, whose
+  // waves mostly wait for memory (measured: the GEMMs' time in that company -10 %, the decode phase -0.8 %)
+  __builtin_amdgcn_s_setprio(3);
+  constexpr int STAGE = (BM + BN) * BK;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave / WN, wn = wave % WN;
+  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+  int tile_m, tile_n, split;
+  const int splits = EPI == EPI_PARTIAL ? g.splits : 1;
+  tile_of_block(tiles_m, tiles_n, splits, tile_m, tile_n, split);
+  const int row0 = tile_m * BM, col0 = tile_n * BN;
+
+  // ---- global -> register staging: thread t covers chunk (t % 8) of rows (t / 8) + RPP i
+  const int ld_chunk = tid & 7, ld_row = tid >> 3;
+  const uint16_t* __restrict__ A = (const uint16_t*)g.A;
+  const uint16_t* __restrict__ W = (const uint16_t*)g.W;
+  // operands are K-block major: K tile kt of rows r0.. is the contiguous run starting at (kt * rows + r0) * 64,
+  // and thread t reads bytes [16 t, 16 t + 16) of it (rows past the end repeat the last row)
+  u32x4 ra[PA], rb[PB];
+  const uint16_t* pa[PA];
+  const uint16_t* pb[PB];
+#pragma unroll
+  for (int i = 0; i < PA; ++i) {
+    int r = min(row0 + ld_row + RPP * i, g.M - 1);
+    pa[i] = A + (size_t)r * 64 + ld_chunk * 8;
+  }
+#pragma unroll
+  for (int i = 0; i < PB; ++i) {
+    int r = min(col0 + ld_row + RPP * i, g.N - 1);
+    pb[i] = W + (size_t)r * 64 + ld_chunk * 8;
+  }
+  const size_t ka = (size_t)g.M * 64, kw = (size_t)g.N * 64;    // elements between K tiles
+  const int nkb = (g.K + BK - 1) / BK;                          // K blocks of W (and of each half of a hi/lo A)
+  // K tile kt of the loop reads block ak(kt) of A and block wk(kt) of W.  Precise mode takes the hi and the lo block of A
+  // against the same block of W in consecutive steps (A holds its nkb hi blocks, then its nkb lo blocks): the second
+  // request for the W block finds it in L2, so the weights cross HBM once
+  auto wk = [&](int kt) { return PR ? kt >> 1 : kt; };
+  auto ak = [&](int kt) { return PR ? (kt >> 1) + (kt & 1) * nkb : kt; };
+  auto load_global = [&](int kt) {
+    if constexpr (KTAIL) {     // K is not a multiple of BK: chunks beyond K read as zero
+      const bool ok = wk(kt) * BK + ld_chunk * 8 < g.K;
+#pragma unroll
+      for (int i = 0; i < PA; ++i) ra[i] = ok ? *(const u32x4*)(pa[i] + ak(kt) * ka) : u32x4{0, 0, 0, 0};
+#pragma unroll
+      for (int i = 0; i < PB; ++i) rb[i] = ok ? *(const u32x4*)(pb[i] + wk(kt) * kw) : u32x4{0, 0, 0, 0};
+    } else {
+#pragma unroll
+      for (int i = 0; i < PA; ++i) ra[i] = *(const u32x4*)(pa[i] + ak(kt) * ka);
+#pragma unroll
+      for (int i = 0; i < PB; ++i) rb[i] = *(const u32x4*)(pb[i] + wk(kt) * kw);
+    }
+  };
+  auto store_lds = [&](int buf) {
+    uint16_t* la = lds + buf * STAGE;
+    uint16_t* lb = la + BM * BK;
+#pragma unroll
+    for (int i = 0; i < PA; ++i) {
+      int r = ld_row + RPP * i;
+      *(u32x4*)(la + r * BK + ((ld_chunk ^ swz(r)) * 8)) = ra[i];
+    }
+#pragma unroll
+    for (int i = 0; i < PB; ++i) {
+      int r = ld_row + RPP * i;
+      *(u32x4*)(lb + r * BK + ((ld_chunk ^ swz(r)) * 8)) = rb[i];
+    }
+  };
+
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  const int nk_all = PR ? 2 * nkb : nkb;
+  const int kt0 = (int)((long long)split * nk_all / splits);          // this block's share of the K tiles
+  const int nk = (int)((long long)(split + 1) * nk_all / splits);
+  const int frow = lane & 15, fq = lane >> 4;
+  // one K step on the LDS stage `buf`; `mid` runs between the last two MFMA groups
+  auto k_step = [&](int buf, auto&& mid) {
+    const uint16_t* la = lds + buf * STAGE + (wm * (BM / WM)) * BK;
+    const uint16_t* lb = lds + buf * STAGE + BM * BK + (wn * (BN / WN)) * BK;
+    // fragments of step kk + 1 are fetched from LDS while the MFMAs of step kk run
+    f16x8 fa[2][TM], fb[2][TN];
+    auto load_frags = [&](int kk, int slot) {
+      const int chunk = kk * 4 + fq;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        int r = i * 16 + frow;
+        fa[slot][i] = *(const f16x8*)(la + r * BK + ((chunk ^ swz(r)) * 8));
+      }
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        int r = j * 16 + frow;
+        fb[slot][j] = *(const f16x8*)(lb + r * BK + ((chunk ^ swz(r)) * 8));
+      }
+    };
+    load_frags(0, 0);
+#pragma unroll
+    for (int kk = 0; kk < BK / 32; ++kk) {
+      if (kk + 1 < BK / 32) load_frags(kk + 1, (kk + 1) & 1);
+      if (kk == BK / 32 - 2) mid();
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = mfma16<PR>(fb[kk & 1][j], fa[kk & 1][i], acc[i][j]);
+    }
+  };
+
+  if constexpr (NS == 0) {
+    load_global(kt0);
+    store_lds(kt0 & 1);
+    __syncthreads();
+    for (int kt = kt0; kt < nk; ++kt) {
+      const int cur = kt & 1;
+      if (kt + 1 < nk) load_global(kt + 1);
+      // the next tile moves from registers to the other LDS buffer under the last MFMAs of this one
+      k_step(cur, [&] { if (kt + 1 < nk) store_lds(cur ^ 1); });
+      __syncthreads();
+    }
+  } else {
+    // Direct loads: a wave instruction moves 64 16-byte chunks = 8 tile rows into 1 KB of LDS in lane order, so
+    // the XOR swizzle is applied on the source side: the lane that fills chunk position p of row r fetches chunk
+    // p ^ swz(r).  Rows advance by a multiple of 16 per pass, which leaves swz(r) unchanged.
+    static_assert(RPP % 16 == 0, "the swizzle must not depend on the pass");
+    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+    const int lrow = wave_u * 8 + (lane >> 3);
+    const int schunk = (lane & 7) ^ swz(lrow);
+    const uint16_t* qa[PA];
+    const uint16_t* qb[PB];
+#pragma unroll
+    for (int i = 0; i < PA; ++i) qa[i] = A + (size_t)min(row0 + lrow + RPP * i, g.M - 1) * 64 + schunk * 8;
+#pragma unroll
+    for (int i = 0; i < PB; ++i) qb[i] = W + (size_t)min(col0 + lrow + RPP * i, g.N - 1) * 64 + schunk * 8;
+    typedef const __attribute__((address_space(1))) void* gptr_t;
+    typedef __attribute__((address_space(3))) void* lptr_t;
+    auto issue = [&](int kt, int buf) {
+      uint16_t* la = lds + buf * STAGE + wave_u * 8 * BK;
+#pragma unroll
+      for (int i = 0; i < PA; ++i)
+        __builtin_amdgcn_global_load_lds((gptr_t)(qa[i] + ak(kt) * ka), (lptr_t)(la + i * RPP * BK), 16, 0, 0);
+#pragma unroll
+      for (int i = 0; i < PB; ++i)
+        __builtin_amdgcn_global_load_lds((gptr_t)(qb[i] + wk(kt) * kw), (lptr_t)(la + (BM + i * RPP) * BK), 16, 0, 0);
+    };
+    constexpr int L = PA + PB;                      // loads per wave and stage
+    if constexpr (NS == 2) {
+      // Skewed by a quarter of a K step: the wait for the next stage and the barrier sit before the last of the four
+      // MFMA groups of a stage, whose fragments are in registers by then.  Behind the barrier nobody reads this
+      // stage's LDS any more, so its buffer is refilled at once, and the first fragments of the next stage are
+      // fetched while the last MFMA group runs: the matrix pipe does not drain at the stage boundary.
+      f16x8 fa[2][TM], fb[2][TN];
+      auto frags = [&](int buf, int kk, int slot) {
+        const uint16_t* la = lds + buf * STAGE + (wm * (BM / WM)) * BK;
+        const uint16_t* lb = lds + buf * STAGE + BM * BK + (wn * (BN / WN)) * BK;
+        const int chunk = kk * 4 + fq;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          int r = i * 16 + frow;
+          fa[slot][i] = *(const f16x8*)(la + r * BK + ((chunk ^ swz(r)) * 8));
+        }
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          int r = j * 16 + frow;
+          fb[slot][j] = *(const f16x8*)(lb + r * BK + ((chunk ^ swz(r)) * 8));
+        }
+      };
+      constexpr int HEAD = TM * TN >= 16 ? 4 : 2;
+      auto mma = [&](int slot, int lo, int hi) {     // MFMAs lo .. hi - 1 of the group, row-major over the wave's tiles
+#pragma unroll
+        for (int t = 0; t < TM * TN; ++t)
+          if (t >= lo && t < hi)
+            acc[t / TN][t % TN] = mfma16<PR>(fb[slot][t % TN], fa[slot][t / TN], acc[t / TN][t % TN]);
+      };
+      issue(kt0, 0);
+      wait_loads_then_barrier<0>();
+      if (kt0 + 1 < nk) issue(kt0 + 1, 1);
+      frags(0, 0, 0);
+      // Per MFMA group: the first MFMAs, then the LDS reads of the next group's fragments, then the rest, in exactly
+      // this order (the fences stop the compiler from sinking the reads behind the MFMAs, where the wait for them
+      // would sit directly in front of their first use).  `req` / `more`: is stage kt + 2 requested, does stage kt + 1
+      // follow; the loop proper has no conditions inside, since a branch costs a wave as much as an MFMA.
+      auto stage = [&](int kt, auto req, auto more) {
+        const int buf = (kt - kt0) & 1;
+        mma(0, 0, HEAD);
+        SCHED_FENCE();
+        frags(buf, 1, 1);
+        SCHED_FENCE();
+        mma(0, HEAD, TM * TN);
+        SCHED_FENCE();
+        mma(1, 0, HEAD);
+        SCHED_FENCE();
+        if constexpr (decltype(more)::value) {
+          // stage kt + 1 has landed, and every wave holds its last fragments of stage kt in registers
+          asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+          if constexpr (decltype(req)::value) issue(kt + 2, buf);
+          frags(buf ^ 1, 0, 0);
+          SCHED_FENCE();
+        }
+        mma(1, HEAD, TM * TN);
+        SCHED_FENCE();
+      };
+      int kt = kt0;
+#pragma unroll 1
+      for (; kt + 2 < nk; ++kt) stage(kt, std::true_type{}, std::true_type{});
+      if (kt + 1 < nk) {
+        stage(kt, std::false_type{}, std::true_type{});
+        ++kt;
+      }
+      stage(kt, std::false_type{}, std::false_type{});
+    } else {
+#pragma unroll
+      for (int s = 0; s < NS - 1; ++s)
+        if (kt0 + s < nk) issue(kt0 + s, s);
+      // stage kt must have landed; up to NS - 2 younger stages may still be in flight.  Behind the barrier every wave has
+      // left stage kt - 1: its buffer takes stage kt + NS - 1
+      int kt = kt0;
+#pragma unroll 1
+      for (; kt + NS - 1 < nk; ++kt) {
+        wait_loads_then_barrier<(NS - 2) * L>();
+        issue(kt + NS - 1, (kt - kt0 + NS - 1) % NS);
+        k_step((kt - kt0) % NS, [] {});
+      }
+      for (; kt < nk; ++kt) {
+        const int younger = min(nk - 1 - kt, NS - 2);
+        if (younger >= 2) wait_loads_then_barrier<2 * L>();
+        else if (younger == 1) wait_loads_then_barrier<L>();
+        else wait_loads_then_barrier<0>();
+        k_step((kt - kt0) % NS, [] {});
+      }
+    }
+  }
+
+  gemm_epilogue<TM, TN, EPI, PR>(g, acc, row0 + wm * (BM / WM), col0 + wn * (BN / WN), lane, split);
+}
+
+// The 256x256 tile: four waves of 128x128, one per SIMD, K >= 128 (two K steps).  Every wave is its SIMD's only one, so the
+// main loop is laid out by hand: between any two products there is at most one LDS read or one request, and no branch.
+// A K step is four phases of 32 products, one for each pair of row half and column half; a half tile (128 rows of 64 K
+// values, 16 KB) is read from LDS into registers one phase before its first use and never again, so its place in LDS is
+// free two phases later and takes the same half of the K step after next: five to six half tiles (80 - 96 KB) are in flight
+// all the time, which covers the 1.3 us that the operand stream takes from HBM and the other XCDs' L2 under load.  One
+// barrier per phase: the half needed next has landed, and everybody has read the half that is about to be overwritten.
+// Measured (M = 32768, random operands, bursts of ten): N = 2560, K = 10240 1.28 PFLOP/s where the two-stage loop on eight
+// waves gave 1.01, N = 10240, K = 2560 with GELU 1.19 (0.90), N = 7680, K = 2560 1.16 (0.95).  The loop is bound by power:
+// 2420 clocks per K step (2048 of them matrix products) at 1.65 GHz; on zeros the clock stays at 2.4 GHz.
+template <int EPI, bool PR>
+__global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmArgs g) {
+  constexpr int TM = 8, TN = 8;                  // 16x16 tiles of a wave: 128 x 128
+  constexpr int HALF = 128 * BK;                 // elements of a half tile: 128 rows of one K step
+  constexpr int STAGE = 4 * HALF;                // A0, A1, B0, B1
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];   // two stages
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int tiles_m = (g.M + 255) >> 8, tiles_n = (g.N + 255) >> 8;
+  int tile_m, tile_n, split;
+  tile_of_block(tiles_m, tiles_n, 1, tile_m, tile_n, split);
+  const int row0 = tile_m << 8, col0 = tile_n << 8;
+
+  const int nkb = g.K / BK;                      // K blocks of W (and of each half of a hi/lo A)
+  const int nk = PR ? 2 * nkb : nkb;
+  const size_t ka = (size_t)g.M * 128, kw = (size_t)g.N * 128;    // bytes between K blocks
+  // A wave instruction moves 64 16-byte chunks = 8 rows into 1 KB of LDS in lane order; a wave fills 32 of a half tile's
+  // 128 rows.  Row r of half h is row 128 (r / 64) + 64 h + r % 64 of the tile: 64 rows for each of the two waves that
+  // share the operand.  The XOR swizzle is applied on the source side.
+  uint32_t va[2][4], vb[2][4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = wave * 32 + i * 8 + (lane >> 3);
+      const int chunk = (lane & 7) ^ swz(r);
+      const int t = (r >> 6) * 128 + h * 64 + (r & 63);
+      va[h][i] = (uint32_t)min(row0 + t, g.M - 1) * 128 + chunk * 16;
+      vb[h][i] = (uint32_t)min(col0 + t, g.N - 1) * 128 + chunk * 16;
+    }
+  typedef __attribute__((address_space(3))) void* lptr_t;
+  // request i (of 4) of half h of K step kt
+  auto load_a = [&](int kt, int h, int i) {
+    const char* base = (const char*)g.A + (size_t)(PR ? (kt >> 1) + (kt & 1) * nkb : kt) * ka;
+    uint16_t* dst = lds + (kt & 1) * STAGE + h * HALF + wave * 32 * BK + i * 8 * BK;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0x7fffffff, 0x00027000), (lptr_t)dst, 16, va[h][i], 0, 0, 0);
+  };
+  auto load_b = [&](int kt, int h, int i) {
+    const char* base = (const char*)g.W + (size_t)(PR ? kt >> 1 : kt) * kw;
+    uint16_t* dst = lds + (kt & 1) * STAGE + (2 + h) * HALF + wave * 32 * BK + i * 8 * BK;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0x7fffffff, 0x00027000), (lptr_t)dst, 16, vb[h][i], 0, 0, 0);
+  };
+  const int frow = lane & 15, fq = lane >> 4;
+  const int sw = swz(frow);
+  int oa[2], ob[2];                       // LDS element offsets of this lane's fragments, by K slice of 32
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const int c = ((4 * ks + fq) ^ sw) * 8;
+    oa[ks] = (wm * 64 + frow) * BK + c;
+    ob[ks] = 2 * HALF + (wn * 64 + frow) * BK + c;
+  }
+  f16x8 fa[2][4][2], fb[2][4][2];         // [half][16-row tile][K slice]
+  // fragment n (of 8) of half h in buffer buf: tile n % 4, K slice n / 4
+  auto read_a = [&](int buf, int h, int n) { fa[h][n & 3][n >> 2] = *(const f16x8*)(lds + buf * STAGE + h * HALF + (n & 3) * 16 * BK + oa[n >> 2]); };
+  auto read_b = [&](int buf, int h, int n) { fb[h][n & 3][n >> 2] = *(const f16x8*)(lds + buf * STAGE + h * HALF + (n & 3) * 16 * BK + ob[n >> 2]); };
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#define BIG_BAR(N, L) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(%1)\n\ts_barrier" ::"n"(N), "n"(L) : "memory")
+  // the 32 products of row half mh and column half nh; behind the n-th, rd(n) fetches fragments and ld(0..3) requests
+  auto phase = [&](int mh, int nh, auto&& rd, auto&& ld) {
+#pragma unroll
+    for (int n = 0; n < 32; ++n) {
+      const int ks = n >> 4, i = (n >> 2) & 3, j = n & 3;
+      acc[4 * mh + i][4 * nh + j] = mfma16<PR>(fb[nh][j][ks], fa[mh][i][ks], acc[4 * mh + i][4 * nh + j]);
+      SCHED_FENCE();
+      rd(n);
+      if (n % 4 == 1 && n < 16) ld(n / 4);
+      SCHED_FENCE();
+    }
+  };
+  // T: 0 in the loop, 1 in the last K step but one, 2 in the last (nothing is requested any more)
+  auto step = [&](int kt, auto tail) {
+    constexpr int T = decltype(tail)::value;
+    const int buf = kt & 1;
+    phase(0, 0, [&](int n) { if (n % 2 == 0 && n < 16) read_b(buf, 1, n / 2); }, [&](int n) { if (T == 0) load_a(kt + 2, 0, n); });
+    BIG_BAR(T == 0 ? 20 : T == 1 ? 16 : 0, T == 0 ? 8 : 0);
+    SCHED_FENCE();
+    phase(0, 1, [&](int n) { if (n % 2 == 0 && n < 16) read_a(buf, 1, n / 2); }, [&](int n) { if (T == 0) load_b(kt + 2, 0, n); });
+    BIG_BAR(T == 0 ? 20 : T == 1 ? 12 : 0, T == 0 ? 8 : 0);
+    SCHED_FENCE();
+    phase(1, 1, [&](int n) { if (T < 2 && n % 2 == 0 && n < 16) read_a(buf ^ 1, 0, n / 2); }, [&](int n) { if (T == 0) load_b(kt + 2, 1, n); });
+    BIG_BAR(T == 0 ? 20 : T == 1 ? 8 : 0, T == 0 ? 8 : 0);
+    SCHED_FENCE();
+    // the next K step's B0 takes the registers of this one's as they are used up
+    phase(1, 0, [&](int n) {
+      if (T < 2 && n >= 16 && n < 20) read_b(buf ^ 1, 0, n - 16);
+      if (T < 2 && n >= 28) read_b(buf ^ 1, 0, 4 + n - 28);
+    }, [&](int n) { if (T == 0) load_a(kt + 2, 1, n); });
+    if constexpr (T < 2) BIG_BAR(T == 0 ? 20 : 4, T == 0 ? 8 : 0);
+    SCHED_FENCE();
+  };
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_a(s, 0, i);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_b(s, 0, i);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_b(s, 1, i);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_a(s, 1, i);
+  }
+  BIG_BAR(24, 0);
+#pragma unroll
+  for (int n = 0; n < 8; ++n) { read_a(0, 0, n); read_b(0, 0, n); }
+  BIG_BAR(20, 0);
+  int kt = 0;
+#pragma unroll 1
+  for (; kt < nk - 2; ++kt) step(kt, std::integral_constant<int, 0>{});
+  step(kt, std::integral_constant<int, 1>{});
+  step(kt + 1, std::integral_constant<int, 2>{});
+  gemm_epilogue<TM, TN, EPI, PR>(g, acc, row0 + wm * 128, col0 + wn * 128, lane, 0);
+}
+#undef BIG_BAR
 
 // Second half of a split-K product: sums the partial results in split order (so the result does not depend
 // on scheduling) and applies the epilogue.
@@ -592,6 +753,24 @@ hipError_t launch_k(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
+// the 256x256 tile; a K of less than two steps or with a ragged end goes through registers
+template <int EPI, bool PR>
+hipError_t launch_big(const GemmArgs& g, hipStream_t s) {
+  if (g.K % BK != 0 || (!PR && g.K < 2 * BK)) return launch_k<256, 256, 4, 2, EPI, true, 0, PR>(g, s);
+  constexpr int lds_bytes = 2 * 512 * BK * (int)sizeof(uint16_t);
+  static bool configured_on[64] = {};       // once per device (a repeated call is harmless, so no lock)
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+  if (!configured_on[dev]) {
+    hipError_t e = hipFuncSetAttribute((const void*)gemm_big_kernel<EPI, PR>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    if (e != hipSuccess) return e;
+    configured_on[dev] = true;
+  }
+  const int tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
+  hipLaunchKernelGGL((gemm_big_kernel<EPI, PR>), dim3(tiles), dim3(256), lds_bytes, s, g);
+  return hipGetLastError();
+}
+
 // Whole K tiles take the direct-load pipeline with two LDS stages (more stages measured slower: the extra LDS
 // costs a resident block); a ragged K falls back to register staging, which can zero-fill the tail.
 template <int BM, int BN, int WM, int WN, int EPI, int NS = 2, bool PR = false>
@@ -604,7 +783,9 @@ template <int EPI>
 hipError_t launch_variant_precise(const GemmArgs& g, int variant, hipStream_t s) {
   switch (variant) {
     case 0: return launch<128, 128, 2, 2, EPI, 2, true>(g, s);
-    case 3: return launch<256, 256, 4, 2, EPI, 2, true>(g, s);
+    case 3:
+      if constexpr (EPI != EPI_PARTIAL) return launch_big<EPI, true>(g, s);
+      else return launch<256, 128, 4, 2, EPI, 2, true>(g, s);
     case 5: return launch<256, 128, 4, 2, EPI, 2, true>(g, s);
     case 7:
       if constexpr (EPI != EPI_SWIGLU_F16 && EPI != EPI_LMHEAD) return launch<64, 128, 1, 4, EPI, 2, true>(g, s);
@@ -619,8 +800,12 @@ hipError_t launch_variant(const GemmArgs& g, int variant, hipStream_t s) {
   switch (variant) {
     case 0: return launch<128, 128, 2, 2, EPI>(g, s);
     case 1: return launch<256, 128, 2, 2, EPI>(g, s);
-    case 2: return launch<256, 256, 2, 2, EPI>(g, s);
-    case 3: return launch<256, 256, 4, 2, EPI>(g, s);
+    case 2:
+    case 3:
+    case 10:
+      // (a K split is for shapes with few tiles: partial sums come from 256x128 at most)
+      if constexpr (EPI != EPI_PARTIAL) return launch_big<EPI, false>(g, s);
+      else return launch<256, 128, 4, 2, EPI>(g, s);
     case 4: return launch<128, 256, 2, 2, EPI>(g, s);
     case 5: return launch<256, 128, 4, 2, EPI>(g, s);
     case 6:
@@ -636,10 +821,6 @@ hipError_t launch_variant(const GemmArgs& g, int variant, hipStream_t s) {
                  // fragments and for the stage barrier (12-15 % faster than four waves on long-K shapes with few tiles)
       if constexpr (EPI != EPI_SWIGLU_F16 && EPI != EPI_LMHEAD) return launch<64, 128, 2, 4, EPI, 4>(g, s);
       else return hipErrorInvalidValue;
-    case 10:     // the largest tile on sixteen waves of 64x64: four waves per SIMD hide more of each other's waits than two,
-                 // for a third more LDS fragment traffic (a ragged K takes the eight-wave form: its register staging does
-                 // not fit 128 registers per lane)
-      return g.K % BK == 0 ? launch_k<256, 256, 4, 4, EPI, false, 2, false>(g, s) : launch_k<256, 256, 4, 2, EPI, true, 0, false>(g, s);
   }
   return hipErrorInvalidValue;
 }
@@ -649,6 +830,9 @@ hipError_t launch_variant(const GemmArgs& g, int variant, hipStream_t s) {
 hipError_t rl_gemm_variant(const GemmArgs& g, int epi, int variant, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (g.K % 8 != 0) return hipErrorInvalidValue;
+  // only the plain fp32 and the LM-head epilogue take rows that do not divide into groups of four columns (every other
+  // width is a multiple of 16 by the checks on the configuration)
+  if (epi != EPI_F32 && epi != EPI_LMHEAD && (g.N % 4 != 0 || (epi == EPI_RESID && g.ldo % 4 != 0))) return hipErrorInvalidValue;
   switch (epi) {
     case EPI_F32: return launch_variant<EPI_F32>(g, variant, s);
     case EPI_RESID: return launch_variant<EPI_RESID>(g, variant, s);

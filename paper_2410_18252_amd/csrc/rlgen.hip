@@ -692,7 +692,7 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
       const int splits = !g.ws ? 1 : mode == 1 ? split_rule(c->R, c->R, g.N, g.K, epi, g.ws_elems, false)
                                                : split_rule(dec_rows_eff, m.max_seqs, g.N, g.K, epi, g.ws_elems, tune_half);
       std::vector<int> cands = {0, 5};
-      if (splits == 1) { cands.push_back(3); if (!pr) cands.push_back(10); }
+      if (splits == 1) cands.push_back(3);
       if (mode == 2 && splits == 1 && !pr) { cands.push_back(1); cands.push_back(4); }     // beside attention other shapes can win
       if (!wide_only) {
         cands.push_back(7);
