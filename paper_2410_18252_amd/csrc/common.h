@@ -25,18 +25,17 @@ __host__ __device__ __forceinline__ size_t kblk_off(int row, int col, int rows) 
 }
 __host__ __device__ __forceinline__ size_t kblk_elems(size_t rows, size_t K) { return ((K + 63) / 64) * rows * 64; }
 
-// fp32 -> bf16, round to nearest even (finite inputs; NaN stays NaN).
-__device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+// fp32 -> bf16, round to nearest even (NaN stays NaN): the hardware's conversion, two values in one instruction.
+__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  f32x2 v;
+  v[0] = lo; v[1] = hi;
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
+__device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t b) {
   return __uint_as_float(((uint32_t)b) << 16);
-}
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-  return (uint32_t)f32_to_bf16_bits(lo) | ((uint32_t)f32_to_bf16_bits(hi) << 16);
 }
 
 // Sticky device-detected input faults (bit flags in ctx->status word).
@@ -53,12 +52,9 @@ __device__ __forceinline__ void split_bf16(float f, uint16_t& hi, uint16_t& lo) 
 }
 // the same for two values, packed for 32-bit stores: returns (hi, lo) with hi = (bf16 a, bf16 b) and lo likewise
 __device__ __forceinline__ u32x2 split_bf16x2(float a, float b) {
-  uint16_t ah, al, bh, bl;
-  split_bf16(a, ah, al);
-  split_bf16(b, bh, bl);
   u32x2 r;
-  r[0] = (uint32_t)ah | ((uint32_t)bh << 16);
-  r[1] = (uint32_t)al | ((uint32_t)bl << 16);
+  r[0] = pack_bf16x2(a, b);
+  r[1] = pack_bf16x2(a - __uint_as_float(r[0] << 16), b - __uint_as_float(r[0] & 0xffff0000u));
   return r;
 }
 #define SPLIT_BF16X2(a, b, hi, lo) do { const u32x2 t_ = split_bf16x2(a, b); (hi) = t_[0]; (lo) = t_[1]; } while (0)

@@ -115,6 +115,73 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
         if (fq == 0 && (FULL || (row < g.M && group < ngroups))) g.partial[(size_t)row * ngroups + group] = make_float2(mx, sum);
       }
     }
+  } else if (EPI == EPI_QKV && FULL && g.qe.kvstage) {
+    // Prompt pass, a wave whose rows and columns all exist: what depends on the column (head, rotary pair, which of the two
+    // outputs it belongs to) is found once per column tile, outside the loop over the rows, and a tile of which no column
+    // is rotated is stored in 8-byte pieces.
+    if constexpr (EPI == EPI_QKV) {
+    const QkvEpi& e = g.qe;
+    [[maybe_unused]] bool sat = false;
+    uint32_t rope[TM];       // byte offset of the row's angles: at most 2^20 positions of 128 pairs
+#pragma unroll
+    for (int i = 0; i < TM; ++i) rope[i] = (uint32_t)(e.pos[wrow0 + i * 16 + frow] + e.pos_add) * (uint32_t)(e.r >> 1) * 8u;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int col = wcol0 + j * 16 + 4 * fq;
+      const int head = (int)(((float)col + 0.5f) * e.inv_h);
+      const int p0 = col - head * e.h;
+      const bool isq = head < e.Hq, rot = head < e.Hq + e.Hkv && p0 < e.r;
+      const bool any_rot = __ballot(rot) != 0;
+      const int d0 = rot ? p0 >> 1 : p0, d1 = rot ? d0 + (e.r >> 1) : p0 + 2;       // dims of (v0, v1) and of (v2, v3)
+      f32x4 bias = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (g.bias) bias = *(const f32x4*)(g.bias + col);
+      const int ld = isq ? e.Hq * e.h : 2 * e.Hkv * e.h;
+      // 16-bit outputs: q rows, or staged k | v rows (precise: q rows are fp32, addressed below)
+      uint16_t* out = (isq ? e.q : e.kvstage) + (size_t)(wrow0 + frow) * ld + (isq ? head : head - e.Hq) * e.h;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        f32x4 v = acc[i][j] + bias;
+        if (any_rot) {
+          f32x4 cs = f32x4{1.f, 0.f, 1.f, 0.f};
+          if (rot) cs = *(const f32x4*)((const char*)e.table + (rope[i] + (uint32_t)d0 * 8u));
+          const float lo0 = v[0] * cs[0] - v[2] * cs[1], hi0 = v[2] * cs[0] + v[0] * cs[1];
+          const float lo1 = v[1] * cs[2] - v[3] * cs[3], hi1 = v[3] * cs[2] + v[1] * cs[3];
+          v[0] = lo0; v[1] = lo1; v[2] = hi0; v[3] = hi1;
+        }
+        uint32_t w01, w23;
+        if constexpr (PR) {
+          u32x2 wl;
+          SPLIT_BF16X2(v[0], v[1], w01, wl[0]);
+          SPLIT_BF16X2(v[2], v[3], w23, wl[1]);
+          if (isq) {
+            float* qp = (float*)e.q + (size_t)(wrow0 + i * 16 + frow) * ld + head * e.h;
+            *(float2*)(qp + d0) = make_float2(v[0], v[1]);
+            *(float2*)(qp + d1) = make_float2(v[2], v[3]);
+            continue;
+          }
+          *(uint32_t*)(out + (size_t)i * 16 * ld + e.stage_lo_off + d0) = wl[0];
+          *(uint32_t*)(out + (size_t)i * 16 * ld + e.stage_lo_off + d1) = wl[1];
+        } else {
+          // q is fp16; cached keys and values are bf16 but enter the attention products as fp16
+#pragma unroll
+          for (int r = 0; r < 4; ++r) sat |= f16_out_of_range(v[r]);
+          w01 = isq ? pack_f16x2(v[0], v[1]) : pack_bf16x2(v[0], v[1]);
+          w23 = isq ? pack_f16x2(v[2], v[3]) : pack_bf16x2(v[2], v[3]);
+        }
+        uint16_t* p = out + (size_t)i * 16 * ld;
+        if (any_rot) {
+          *(uint32_t*)(p + d0) = w01;
+          *(uint32_t*)(p + d1) = w23;
+        } else {
+          u32x2 w;
+          w[0] = w01; w[1] = w23;
+          *(u32x2*)(p + d0) = w;
+        }
+      }
+      SCHED_FENCE();
+    }
+    if constexpr (!PR) flag_f16_range(sat, g.status);
+    }
   } else if constexpr (EPI == EPI_QKV) {
     [[maybe_unused]] bool sat = false;        // an fp16 output was clamped
 #pragma unroll
