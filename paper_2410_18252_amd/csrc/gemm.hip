@@ -76,8 +76,9 @@ __device__ __forceinline__ void wait_loads_then_barrier() {
 // which makes outputs, bias and residual 16-byte accesses and turns the row-wise softmax statistics of the LM head into
 // in-register reductions.  (wrow0, wcol0): the wave's first row and column.  FULL: every row and column of the wave exists
 // and rows start on 16-byte boundaries, so that no access needs a condition of its own (a wave that runs alone on its SIMD
-// waits out every branch: the epilogue of a whole 256x256 tile is a third shorter without them).
-template <int TM, int TN, int EPI, bool PR, bool FULL>
+// waits out every branch: the epilogue of a whole 256x256 tile is a third shorter without them).  STAGED: a QKV projection
+// of the prompt pass only (the kernel has no code for a decode step's cache writes).
+template <int TM, int TN, int EPI, bool PR, bool FULL, bool STAGED>
 __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 (&acc)[TM][TN], int wrow0, int wcol0, int lane, int split) {
   const int frow = lane & 15, fq = lane >> 4;
   if constexpr (EPI == EPI_LMHEAD) {
@@ -115,60 +116,87 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
         if (fq == 0 && (FULL || (row < g.M && group < ngroups))) g.partial[(size_t)row * ngroups + group] = make_float2(mx, sum);
       }
     }
-  } else if (EPI == EPI_QKV && FULL && g.qe.kvstage) {
-    // Prompt pass, a wave whose rows and columns all exist: what depends on the column (head, rotary pair, which of the two
-    // outputs it belongs to) is found once per column tile, outside the loop over the rows, and a tile of which no column
-    // is rotated is stored in 8-byte pieces.
+  } else if (EPI == EPI_QKV && (STAGED || g.qe.kvstage)) {
+    // Prompt pass: what depends on the column (head, rotary pair, which of the two outputs it belongs to) is found once per
+    // column tile, outside the loop over the rows, and a tile of which no column is rotated is stored in 8-byte pieces.
+    // The next tile's bias and angles are requested in front of this one's stores: loads and stores return in order, so
+    // that a load behind a store waits for the store (per 256x256 tile of four waves: 53 us with, 18 us without such waits).
     if constexpr (EPI == EPI_QKV) {
     const QkvEpi& e = g.qe;
     [[maybe_unused]] bool sat = false;
+    auto live = [&](int i) { return FULL || wrow0 + i * 16 + frow < g.M; };
     uint32_t rope[TM];       // byte offset of the row's angles: at most 2^20 positions of 128 pairs
 #pragma unroll
-    for (int i = 0; i < TM; ++i) rope[i] = (uint32_t)(e.pos[wrow0 + i * 16 + frow] + e.pos_add) * (uint32_t)(e.r >> 1) * 8u;
+    for (int i = 0; i < TM; ++i) rope[i] = (uint32_t)(live(i) ? e.pos[wrow0 + i * 16 + frow] + e.pos_add : 0) * (uint32_t)(e.r >> 1) * 8u;
+    struct Col { int head, p0; bool isq, rot; };
+    auto column = [&](int j) {
+      Col c;
+      const int col = FULL ? wcol0 + j * 16 + 4 * fq : min(wcol0 + j * 16 + 4 * fq, g.N - 4);
+      c.head = (int)(((float)col + 0.5f) * e.inv_h);
+      c.p0 = col - c.head * e.h;
+      c.isq = c.head < e.Hq;
+      c.rot = c.head < e.Hq + e.Hkv && c.p0 < e.r;
+      return c;
+    };
+    f32x4 bias_n = f32x4{0.f, 0.f, 0.f, 0.f}, cs_n[TM];
+    auto fetch = [&](int j) {
+      const Col c = column(j);
+      if (g.bias) bias_n = *(const f32x4*)(g.bias + (c.head * e.h + c.p0));
+      if (__ballot(c.rot) != 0) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          cs_n[i] = f32x4{1.f, 0.f, 1.f, 0.f};
+          if (c.rot) cs_n[i] = *(const f32x4*)((const char*)e.table + (rope[i] + (uint32_t)(c.p0 >> 1) * 8u));
+        }
+      }
+    };
+    fetch(0);
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      const int col = wcol0 + j * 16 + 4 * fq;
-      const int head = (int)(((float)col + 0.5f) * e.inv_h);
-      const int p0 = col - head * e.h;
-      const bool isq = head < e.Hq, rot = head < e.Hq + e.Hkv && p0 < e.r;
-      const bool any_rot = __ballot(rot) != 0;
-      const int d0 = rot ? p0 >> 1 : p0, d1 = rot ? d0 + (e.r >> 1) : p0 + 2;       // dims of (v0, v1) and of (v2, v3)
-      f32x4 bias = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (g.bias) bias = *(const f32x4*)(g.bias + col);
-      const int ld = isq ? e.Hq * e.h : 2 * e.Hkv * e.h;
-      // 16-bit outputs: q rows, or staged k | v rows (precise: q rows are fp32, addressed below)
-      uint16_t* out = (isq ? e.q : e.kvstage) + (size_t)(wrow0 + frow) * ld + (isq ? head : head - e.Hq) * e.h;
+      const Col c = column(j);
+      const bool in_n = FULL || wcol0 + j * 16 + 4 * fq < g.N;
+      const bool any_rot = __ballot(c.rot) != 0;
+      const int d0 = c.rot ? c.p0 >> 1 : c.p0, d1 = c.rot ? d0 + (e.r >> 1) : c.p0 + 2;       // dims of (v0, v1) and of (v2, v3)
+      f32x4 v[TM];
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        f32x4 v = acc[i][j] + bias;
+        v[i] = acc[i][j] + bias_n;
         if (any_rot) {
-          f32x4 cs = f32x4{1.f, 0.f, 1.f, 0.f};
-          if (rot) cs = *(const f32x4*)((const char*)e.table + (rope[i] + (uint32_t)d0 * 8u));
-          const float lo0 = v[0] * cs[0] - v[2] * cs[1], hi0 = v[2] * cs[0] + v[0] * cs[1];
-          const float lo1 = v[1] * cs[2] - v[3] * cs[3], hi1 = v[3] * cs[2] + v[1] * cs[3];
-          v[0] = lo0; v[1] = lo1; v[2] = hi0; v[3] = hi1;
+          const f32x4 cs = cs_n[i];
+          const float lo0 = v[i][0] * cs[0] - v[i][2] * cs[1], hi0 = v[i][2] * cs[0] + v[i][0] * cs[1];
+          const float lo1 = v[i][1] * cs[2] - v[i][3] * cs[3], hi1 = v[i][3] * cs[2] + v[i][1] * cs[3];
+          v[i][0] = lo0; v[i][1] = lo1; v[i][2] = hi0; v[i][3] = hi1;
         }
+      }
+      if (j + 1 < TN) fetch(j + 1);
+      SCHED_FENCE();
+      // 16-bit outputs: q rows, or staged k | v rows (precise: q rows are fp32, addressed apart)
+      const int ld = c.isq ? e.Hq * e.h : 2 * e.Hkv * e.h;
+      uint16_t* out = (c.isq ? e.q : e.kvstage) + (size_t)(wrow0 + frow) * ld + (c.isq ? c.head : c.head - e.Hq) * e.h;
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        if (!live(i) || !in_n) continue;
+        uint16_t* p = out + (size_t)i * 16 * ld;
         uint32_t w01, w23;
         if constexpr (PR) {
           u32x2 wl;
-          SPLIT_BF16X2(v[0], v[1], w01, wl[0]);
-          SPLIT_BF16X2(v[2], v[3], w23, wl[1]);
-          if (isq) {
-            float* qp = (float*)e.q + (size_t)(wrow0 + i * 16 + frow) * ld + head * e.h;
-            *(float2*)(qp + d0) = make_float2(v[0], v[1]);
-            *(float2*)(qp + d1) = make_float2(v[2], v[3]);
+          SPLIT_BF16X2(v[i][0], v[i][1], w01, wl[0]);
+          SPLIT_BF16X2(v[i][2], v[i][3], w23, wl[1]);
+          if (c.isq) {
+            float* qp = (float*)e.q + (size_t)(wrow0 + i * 16 + frow) * ld + c.head * e.h;
+            *(float2*)(qp + d0) = make_float2(v[i][0], v[i][1]);
+            *(float2*)(qp + d1) = make_float2(v[i][2], v[i][3]);
             continue;
           }
-          *(uint32_t*)(out + (size_t)i * 16 * ld + e.stage_lo_off + d0) = wl[0];
-          *(uint32_t*)(out + (size_t)i * 16 * ld + e.stage_lo_off + d1) = wl[1];
+          *(uint32_t*)(p + e.stage_lo_off + d0) = wl[0];
+          *(uint32_t*)(p + e.stage_lo_off + d1) = wl[1];
         } else {
           // q is fp16; cached keys and values are bf16 but enter the attention products as fp16
 #pragma unroll
-          for (int r = 0; r < 4; ++r) sat |= f16_out_of_range(v[r]);
-          w01 = isq ? pack_f16x2(v[0], v[1]) : pack_bf16x2(v[0], v[1]);
-          w23 = isq ? pack_f16x2(v[2], v[3]) : pack_bf16x2(v[2], v[3]);
+          for (int r = 0; r < 4; ++r) sat |= f16_out_of_range(v[i][r]);
+          w01 = c.isq ? pack_f16x2(v[i][0], v[i][1]) : pack_bf16x2(v[i][0], v[i][1]);
+          w23 = c.isq ? pack_f16x2(v[i][2], v[i][3]) : pack_bf16x2(v[i][2], v[i][3]);
         }
-        uint16_t* p = out + (size_t)i * 16 * ld;
         if (any_rot) {
           *(uint32_t*)(p + d0) = w01;
           *(uint32_t*)(p + d1) = w23;
@@ -182,7 +210,7 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
     }
     if constexpr (!PR) flag_f16_range(sat, g.status);
     }
-  } else if constexpr (EPI == EPI_QKV) {
+  } else if constexpr (EPI == EPI_QKV && !STAGED) {
     [[maybe_unused]] bool sat = false;        // an fp16 output was clamped
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
@@ -192,16 +220,14 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
       // kv head 0's stream of its cache sequence (the parts of KvLayout::k_elem / v_elem that depend on the
       // slot alone; kv heads are per_head elements apart)
       [[maybe_unused]] const float2* rope_row = nullptr;
-      [[maybe_unused]] uint16_t *q_row = nullptr, *stage_row = nullptr, *k_row = nullptr, *v_row = nullptr;
+      [[maybe_unused]] uint16_t *q_row = nullptr, *k_row = nullptr, *v_row = nullptr;
       [[maybe_unused]] int per_head = 0;
       if constexpr (EPI == EPI_QKV) {
         const QkvEpi& e = g.qe;
         const int qpos = e.pos[row] + e.pos_add;
         rope_row = e.table + (size_t)qpos * (e.r >> 1);
         q_row = e.q + (size_t)row * (e.Hq * e.h) * (PR ? 2 : 1);         // precise: a row of floats
-        if (e.kvstage) {
-          stage_row = e.kvstage + (size_t)row * (2 * e.Hkv * e.h);
-        } else {
+        {
           const int seq = e.dst_seq[row];
           const int slot = qpos - (e.slot_sub ? e.slot_sub[row] : 0);
           const int cap = e.kv_cap[seq];
@@ -244,13 +270,7 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
                 uint32_t h01, l01, h23, l23;
                 SPLIT_BF16X2(v[0], v[1], h01, l01);
                 SPLIT_BF16X2(v[2], v[3], h23, l23);
-                if (e.kvstage) {
-                  uint16_t* sp = stage_row + (head - e.Hq) * e.h;
-                  *(uint32_t*)(sp + d0) = h01;
-                  *(uint32_t*)(sp + d1) = h23;
-                  *(uint32_t*)(sp + e.stage_lo_off + d0) = l01;
-                  *(uint32_t*)(sp + e.stage_lo_off + d1) = l23;
-                } else if (!is_v) {
+                if (!is_v) {
                   uint16_t* st = k_row + (size_t)(head - e.Hq) * per_head;
                   *(uint32_t*)(st + ((d0 >> 3) << 7) + (d0 & 7)) = h01;
                   *(uint32_t*)(st + ((d1 >> 3) << 7) + (d1 & 7)) = h23;
@@ -271,12 +291,6 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
               uint16_t* qp = q_row + head * e.h;
               *(uint32_t*)(qp + d0) = pack_f16x2(v[0], v[1]);
               *(uint32_t*)(qp + d1) = pack_f16x2(v[2], v[3]);
-            } else if (e.kvstage) {
-              // prompt pass: keys (rotated) and values as bf16 rows [k heads | v heads]; a second kernel moves them
-              // into the cache layout, to every copy, in 16-byte units
-              uint16_t* sp = stage_row + (head - e.Hq) * e.h;
-              *(uint32_t*)(sp + d0) = pack_bf16x2(v[0], v[1]);
-              *(uint32_t*)(sp + d1) = pack_bf16x2(v[2], v[3]);
             } else if (!is_v) {
               uint16_t* st = k_row + (size_t)(head - e.Hq) * per_head;
               *(uint32_t*)(st + ((d0 >> 3) << 7) + (d0 & 7)) = pack_bf16x2(v[0], v[1]);
@@ -307,35 +321,44 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
       else return (char*)((uint16_t*)g.out + ((size_t)(col >> 6) * g.M + row) * 64 + (col & 63));
     };
     auto live = [&](int i) { return FULL || wrow0 + i * 16 + frow < g.M; };
-    // the residual's values travel one column tile ahead: with one wave per SIMD nothing else covers their latency
+    // only plain fp32 outputs (logits of any vocabulary) have widths or rows that break up the groups of four
+    auto whole = [&](int j) { return FULL || EPI != EPI_F32 || (wcol0 + j * 16 + 4 * fq + 3 < g.N && (ld & 3) == 0); };
+    // Bias and residual travel one column tile ahead, in front of the stores: loads and stores return in order, so that a
+    // load behind a store waits for the store, and with one wave per SIMD nothing else covers that.
     [[maybe_unused]] f32x4 old[TM];
+    f32x4 bias_n = f32x4{0.f, 0.f, 0.f, 0.f};
     auto fetch = [&](int j) {
-      if (!FULL && wcol0 + j * 16 + 4 * fq >= g.N) return;
+      const int col4 = wcol0 + j * 16 + 4 * fq;
+      if (!FULL && col4 >= g.N) return;
+      if (EPI != EPI_PARTIAL && g.bias) {
+        if (whole(j)) bias_n = *(const f32x4*)((const char*)(g.bias + wcol0 + j * 16) + (uint32_t)(fq * 16));
+        else
+          for (int r = 0; r < 4; ++r) bias_n[r] = col4 + r < g.N ? g.bias[col4 + r] : 0.f;
+      }
+      if constexpr (EPI == EPI_RESID) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
-        if (live(i)) old[i] = *(const f32x4*)(place(i, j) + lane_off);
+        for (int i = 0; i < TM; ++i)
+          if (live(i)) old[i] = *(const f32x4*)(place(i, j) + lane_off);
+      }
     };
-    if constexpr (EPI == EPI_RESID) fetch(0);
+    fetch(0);
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       if (EPI == EPI_SWIGLU_F16 && (j & 2)) continue;       // the ups, taken along with their gates
       const int col4 = wcol0 + j * 16 + 4 * fq;             // first of the lane's four columns
       if (!FULL && col4 >= g.N) continue;
-      // only plain fp32 outputs (logits of any vocabulary) have widths or rows that break up the groups of four
-      const bool four = FULL || EPI != EPI_F32 || (col4 + 3 < g.N && (ld & 3) == 0);
-      f32x4 bias = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (EPI != EPI_PARTIAL && g.bias) {
-        if (four) bias = *(const f32x4*)((const char*)(g.bias + wcol0 + j * 16) + (uint32_t)(fq * 16));
-        else
-          for (int r = 0; r < 4; ++r) bias[r] = col4 + r < g.N ? g.bias[col4 + r] : 0.f;
-      }
+      const bool four = whole(j);
+      const f32x4 bias = bias_n;
       auto at = [&](int i) -> char* { return place(i, j); };
       f32x4 v[TM];
       if constexpr (EPI == EPI_RESID) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) v[i] = old[i];
-        if (j + 1 < TN) fetch(j + 1);
       }
+      // column tile whose turn is next (SwiGLU: gates only, 0, 1, 4, 5, ...)
+      const int jn = EPI == EPI_SWIGLU_F16 && (j & 1) ? j + 3 : j + 1;
+      if (jn < TN) fetch(jn);
+      SCHED_FENCE();
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         if (!live(i)) continue;
@@ -376,11 +399,11 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
     if constexpr ((EPI == EPI_GELU_F16 || EPI == EPI_SWIGLU_F16) && !PR) flag_f16_range(sat, g.status);
   }
 }
-template <int TM, int TN, int EPI, bool PR>
+template <int TM, int TN, int EPI, bool PR, bool STAGED = false>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, const f32x4 (&acc)[TM][TN], int wrow0, int wcol0, int lane, int split) {
   const bool fits = wrow0 + TM * 16 <= g.M && wcol0 + TN * 16 <= g.N && (EPI != EPI_F32 || (g.ldo & 3) == 0);
-  if (fits) gemm_epilogue_as<TM, TN, EPI, PR, true>(g, acc, wrow0, wcol0, lane, split);
-  else gemm_epilogue_as<TM, TN, EPI, PR, false>(g, acc, wrow0, wcol0, lane, split);
+  if (fits) gemm_epilogue_as<TM, TN, EPI, PR, true, STAGED>(g, acc, wrow0, wcol0, lane, split);
+  else gemm_epilogue_as<TM, TN, EPI, PR, false, STAGED>(g, acc, wrow0, wcol0, lane, split);
 }
 
 // One 16x16x32 matrix instruction on 16-bit fragments: fp16, or bf16 in precise mode.  (The 32x32x16 form reads half the
@@ -766,7 +789,7 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmArgs g) {
   for (; kt < nk - 2; ++kt) step(kt, std::integral_constant<int, 0>{});
   step(kt, std::integral_constant<int, 1>{});
   step(kt + 1, std::integral_constant<int, 2>{});
-  gemm_epilogue<TM, TN, EPI, PR>(g, acc, row0 + wm * 128, col0 + wn * 128, lane, 0);
+  gemm_epilogue<TM, TN, EPI, PR, true>(g, acc, row0 + wm * 128, col0 + wn * 128, lane, 0);
 }
 #undef BIG_BAR
 
@@ -851,8 +874,9 @@ hipError_t launch_variant_precise(const GemmArgs& g, int variant, hipStream_t s)
   switch (variant) {
     case 0: return launch<128, 128, 2, 2, EPI, 2, true>(g, s);
     case 3:
+      if (EPI == EPI_PARTIAL || (EPI == EPI_QKV && !g.qe.kvstage)) return launch<256, 128, 4, 2, EPI, 2, true>(g, s);
       if constexpr (EPI != EPI_PARTIAL) return launch_big<EPI, true>(g, s);
-      else return launch<256, 128, 4, 2, EPI, 2, true>(g, s);
+      break;
     case 5: return launch<256, 128, 4, 2, EPI, 2, true>(g, s);
     case 7:
       if constexpr (EPI != EPI_SWIGLU_F16 && EPI != EPI_LMHEAD) return launch<64, 128, 1, 4, EPI, 2, true>(g, s);
@@ -870,9 +894,10 @@ hipError_t launch_variant(const GemmArgs& g, int variant, hipStream_t s) {
     case 2:
     case 3:
     case 10:
-      // (a K split is for shapes with few tiles: partial sums come from 256x128 at most)
+      // (a K split is for shapes with few tiles: partial sums come from 256x128 at most, and so do a decode step's cache writes)
+      if (EPI == EPI_PARTIAL || (EPI == EPI_QKV && !g.qe.kvstage)) return launch<256, 128, 4, 2, EPI>(g, s);
       if constexpr (EPI != EPI_PARTIAL) return launch_big<EPI, false>(g, s);
-      else return launch<256, 128, 4, 2, EPI>(g, s);
+      break;
     case 4: return launch<128, 256, 2, 2, EPI>(g, s);
     case 5: return launch<256, 128, 4, 2, EPI>(g, s);
     case 6:
