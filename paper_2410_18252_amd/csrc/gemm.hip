@@ -116,18 +116,44 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
         if (fq == 0 && (FULL || (row < g.M && group < ngroups))) g.partial[(size_t)row * ngroups + group] = make_float2(mx, sum);
       }
     }
-  } else if (EPI == EPI_QKV && (STAGED || g.qe.kvstage)) {
-    // Prompt pass: what depends on the column (head, rotary pair, which of the two outputs it belongs to) is found once per
-    // column tile, outside the loop over the rows, and a tile of which no column is rotated is stored in 8-byte pieces.
-    // The next tile's bias and angles are requested in front of this one's stores: loads and stores return in order, so
-    // that a load behind a store waits for the store (per 256x256 tile of four waves: 53 us with, 18 us without such waits).
-    if constexpr (EPI == EPI_QKV) {
+  } else if constexpr (EPI == EPI_QKV) {
+    // What depends on the row (angles, place in the cache) is found before anything is stored, what depends on the column
+    // (head, rotary pair, destination) once per column tile, and the next tile's bias and angles are requested in front of
+    // this one's stores: loads and stores return in order, so that a load behind a store waits for the store (a 256x256 tile
+    // of the prompt pass on four waves: 53 us with, 18 us without such waits).  A column tile of which no column is rotated
+    // is stored in 8-byte pieces.
     const QkvEpi& e = g.qe;
     [[maybe_unused]] bool sat = false;
+    const bool staged = STAGED || e.kvstage != nullptr;
     auto live = [&](int i) { return FULL || wrow0 + i * 16 + frow < g.M; };
     uint32_t rope[TM];       // byte offset of the row's angles: at most 2^20 positions of 128 pairs
+    [[maybe_unused]] long long k_at[STAGED ? 1 : TM], v_at[STAGED ? 1 : TM];     // the row's first key / value element in the cache
+    [[maybe_unused]] int per_head[STAGED ? 1 : TM];                              // elements between kv heads
+    {
+      int pos[TM];
+      [[maybe_unused]] int seq[TM], sub[TM];
 #pragma unroll
-    for (int i = 0; i < TM; ++i) rope[i] = (uint32_t)(live(i) ? e.pos[wrow0 + i * 16 + frow] + e.pos_add : 0) * (uint32_t)(e.r >> 1) * 8u;
+      for (int i = 0; i < TM; ++i) {
+        const int row = FULL ? wrow0 + i * 16 + frow : min(wrow0 + i * 16 + frow, g.M - 1);
+        pos[i] = e.pos[row] + e.pos_add;
+        if (!staged) {
+          seq[i] = e.dst_seq[row];
+          sub[i] = e.slot_sub ? e.slot_sub[row] : 0;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        rope[i] = (uint32_t)pos[i] * (uint32_t)(e.r >> 1) * 8u;
+        if constexpr (!STAGED) {
+          if (!staged) {
+            const long long base = e.lay.seq_base(e.kv_off[seq[i]]);
+            per_head[i] = 2 * e.kv_cap[seq[i]] * e.h;
+            k_at[i] = base + e.lay.k_elem(pos[i] - sub[i], 0);
+            v_at[i] = base + e.lay.v_elem(pos[i] - sub[i], 0);
+          }
+        }
+      }
+    }
     struct Col { int head, p0; bool isq, rot; };
     auto column = [&](int j) {
       Col c;
@@ -156,7 +182,9 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
       const Col c = column(j);
       const bool in_n = FULL || wcol0 + j * 16 + 4 * fq < g.N;
       const bool any_rot = __ballot(c.rot) != 0;
-      const int d0 = c.rot ? c.p0 >> 1 : c.p0, d1 = c.rot ? d0 + (e.r >> 1) : c.p0 + 2;       // dims of (v0, v1) and of (v2, v3)
+      // head dims of the lane's four columns: a rotary group holds the pairs (d0, d0 + r/2) and (d0 + 1, d0 + 1 + r/2) as
+      // (v0, v2) and (v1, v3); any other group holds four consecutive dims.  d0, d1: dims of (v0, v1) and of (v2, v3)
+      const int d0 = c.rot ? c.p0 >> 1 : c.p0, d1 = c.rot ? d0 + (e.r >> 1) : c.p0 + 2;
       f32x4 v[TM];
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
@@ -170,7 +198,7 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
       }
       if (j + 1 < TN) fetch(j + 1);
       SCHED_FENCE();
-      // 16-bit outputs: q rows, or staged k | v rows (precise: q rows are fp32, addressed apart)
+      // 16-bit outputs in rows: q, or staged k | v (precise: q rows are fp32, addressed apart)
       const int ld = c.isq ? e.Hq * e.h : 2 * e.Hkv * e.h;
       uint16_t* out = (c.isq ? e.q : e.kvstage) + (size_t)(wrow0 + frow) * ld + (c.isq ? c.head : c.head - e.Hq) * e.h;
 #pragma unroll
@@ -178,8 +206,8 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
         if (!live(i) || !in_n) continue;
         uint16_t* p = out + (size_t)i * 16 * ld;
         uint32_t w01, w23;
+        [[maybe_unused]] u32x2 wl;
         if constexpr (PR) {
-          u32x2 wl;
           SPLIT_BF16X2(v[i][0], v[i][1], w01, wl[0]);
           SPLIT_BF16X2(v[i][2], v[i][3], w23, wl[1]);
           if (c.isq) {
@@ -188,8 +216,6 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
             *(float2*)(qp + d1) = make_float2(v[i][2], v[i][3]);
             continue;
           }
-          *(uint32_t*)(p + e.stage_lo_off + d0) = wl[0];
-          *(uint32_t*)(p + e.stage_lo_off + d1) = wl[1];
         } else {
           // q is fp16; cached keys and values are bf16 but enter the attention products as fp16
 #pragma unroll
@@ -197,112 +223,40 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
           w01 = c.isq ? pack_f16x2(v[i][0], v[i][1]) : pack_bf16x2(v[i][0], v[i][1]);
           w23 = c.isq ? pack_f16x2(v[i][2], v[i][3]) : pack_bf16x2(v[i][2], v[i][3]);
         }
-        if (any_rot) {
-          *(uint32_t*)(p + d0) = w01;
-          *(uint32_t*)(p + d1) = w23;
-        } else {
-          u32x2 w;
-          w[0] = w01; w[1] = w23;
-          *(u32x2*)(p + d0) = w;
+        if (staged || c.isq) {
+          if constexpr (PR) {
+            *(uint32_t*)(p + e.stage_lo_off + d0) = wl[0];
+            *(uint32_t*)(p + e.stage_lo_off + d1) = wl[1];
+          }
+          if (any_rot) {
+            *(uint32_t*)(p + d0) = w01;
+            *(uint32_t*)(p + d1) = w23;
+          } else {
+            u32x2 w;
+            w[0] = w01; w[1] = w23;
+            *(u32x2*)(p + d0) = w;
+          }
+        } else if constexpr (!STAGED) {
+          if (c.head < e.Hq + e.Hkv) {
+            // eight dims of a key are 16 bytes, the next eight 256 bytes further
+            uint16_t* st = e.kv + k_at[i] + (long long)(c.head - e.Hq) * per_head[i];
+            *(uint32_t*)(st + ((d0 >> 3) << 7) + (d0 & 7)) = w01;
+            *(uint32_t*)(st + ((d1 >> 3) << 7) + (d1 & 7)) = w23;
+            if constexpr (PR) {
+              *(uint32_t*)(st + e.kv_lo_off + ((d0 >> 3) << 7) + (d0 & 7)) = wl[0];
+              *(uint32_t*)(st + e.kv_lo_off + ((d1 >> 3) << 7) + (d1 & 7)) = wl[1];
+            }
+          } else {
+            uint16_t* st = e.kv + v_at[i] + (long long)(c.head - e.Hq - e.Hkv) * per_head[i] + ((c.p0 >> 4) << 9) + ((c.p0 & 15) << 3);
+            st[0] = (uint16_t)w01; st[8] = (uint16_t)(w01 >> 16); st[16] = (uint16_t)w23; st[24] = (uint16_t)(w23 >> 16);
+            if constexpr (PR) {
+              st += e.kv_lo_off;
+              st[0] = (uint16_t)wl[0]; st[8] = (uint16_t)(wl[0] >> 16); st[16] = (uint16_t)wl[1]; st[24] = (uint16_t)(wl[1] >> 16);
+            }
+          }
         }
       }
       SCHED_FENCE();
-    }
-    if constexpr (!PR) flag_f16_range(sat, g.status);
-    }
-  } else if constexpr (EPI == EPI_QKV && !STAGED) {
-    [[maybe_unused]] bool sat = false;        // an fp16 output was clamped
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int row = wrow0 + i * 16 + frow;
-      if (!FULL && row >= g.M) continue;
-      // EPI_QKV: this row's rotary table row, its q and staging rows, and where its key / value start inside
-      // kv head 0's stream of its cache sequence (the parts of KvLayout::k_elem / v_elem that depend on the
-      // slot alone; kv heads are per_head elements apart)
-      [[maybe_unused]] const float2* rope_row = nullptr;
-      [[maybe_unused]] uint16_t *q_row = nullptr, *k_row = nullptr, *v_row = nullptr;
-      [[maybe_unused]] int per_head = 0;
-      if constexpr (EPI == EPI_QKV) {
-        const QkvEpi& e = g.qe;
-        const int qpos = e.pos[row] + e.pos_add;
-        rope_row = e.table + (size_t)qpos * (e.r >> 1);
-        q_row = e.q + (size_t)row * (e.Hq * e.h) * (PR ? 2 : 1);         // precise: a row of floats
-        {
-          const int seq = e.dst_seq[row];
-          const int slot = qpos - (e.slot_sub ? e.slot_sub[row] : 0);
-          const int cap = e.kv_cap[seq];
-          uint16_t* base = e.kv + e.lay.seq_base(e.kv_off[seq]);
-          k_row = base + e.lay.k_elem(slot, 0);
-          v_row = base + e.lay.v_elem(slot, 0);
-          per_head = 2 * cap * e.h;
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int col = wcol0 + j * 16 + 4 * fq;       // first of four consecutive columns
-        if (!FULL && col >= g.N) continue;
-        f32x4 v = acc[i][j];
-        if (g.bias) v += *(const f32x4*)(g.bias + col);
-        {
-            // head dims of a group of four packed columns: a rotary group holds the pairs (d0, d0 + r/2) and
-            // (d0 + 1, d0 + 1 + r/2) as (v0, v2) and (v1, v3); any other group holds four consecutive dims
-            const QkvEpi& e = g.qe;
-            const int head = (int)(((float)col + 0.5f) * e.inv_h);
-            const int p0 = col - head * e.h;
-            const bool is_v = head >= e.Hq + e.Hkv;
-            int d0 = p0, d1 = p0 + 2;                         // dims of (v0, v1) and of (v2, v3)
-            if (!is_v && p0 < e.r) {
-              d0 = p0 >> 1;
-              d1 = d0 + (e.r >> 1);
-              const f32x4 cs = *(const f32x4*)(rope_row + d0);     // cos, sin of pairs d0 and d0 + 1
-              const float lo0 = v[0] * cs[0] - v[2] * cs[1], hi0 = v[2] * cs[0] + v[0] * cs[1];
-              const float lo1 = v[1] * cs[2] - v[3] * cs[3], hi1 = v[3] * cs[2] + v[1] * cs[3];
-              v[0] = lo0; v[1] = lo1; v[2] = hi0; v[3] = hi1;
-            }
-            if constexpr (PR) {
-              // precise mode: q stays fp32; keys and values are stored as bf16 hi/lo pairs (the lo halves a fixed
-              // distance behind the hi halves)
-              if (head < e.Hq) {
-                float* qp = (float*)q_row + head * e.h;
-                *(float2*)(qp + d0) = make_float2(v[0], v[1]);
-                *(float2*)(qp + d1) = make_float2(v[2], v[3]);
-              } else {
-                uint32_t h01, l01, h23, l23;
-                SPLIT_BF16X2(v[0], v[1], h01, l01);
-                SPLIT_BF16X2(v[2], v[3], h23, l23);
-                if (!is_v) {
-                  uint16_t* st = k_row + (size_t)(head - e.Hq) * per_head;
-                  *(uint32_t*)(st + ((d0 >> 3) << 7) + (d0 & 7)) = h01;
-                  *(uint32_t*)(st + ((d1 >> 3) << 7) + (d1 & 7)) = h23;
-                  *(uint32_t*)(st + e.kv_lo_off + ((d0 >> 3) << 7) + (d0 & 7)) = l01;
-                  *(uint32_t*)(st + e.kv_lo_off + ((d1 >> 3) << 7) + (d1 & 7)) = l23;
-                } else {
-                  uint16_t* st = v_row + (size_t)(head - e.Hq - e.Hkv) * per_head + ((p0 >> 4) << 9) + ((p0 & 15) << 3);
-                  st[0] = (uint16_t)h01; st[8] = (uint16_t)(h01 >> 16); st[16] = (uint16_t)h23; st[24] = (uint16_t)(h23 >> 16);
-                  st += e.kv_lo_off;
-                  st[0] = (uint16_t)l01; st[8] = (uint16_t)(l01 >> 16); st[16] = (uint16_t)l23; st[24] = (uint16_t)(l23 >> 16);
-                }
-              }
-            } else {
-            // q is fp16; cached keys and values are bf16 but enter the attention products as fp16
-#pragma unroll
-            for (int r = 0; r < 4; ++r) sat |= f16_out_of_range(v[r]);
-            if (head < e.Hq) {
-              uint16_t* qp = q_row + head * e.h;
-              *(uint32_t*)(qp + d0) = pack_f16x2(v[0], v[1]);
-              *(uint32_t*)(qp + d1) = pack_f16x2(v[2], v[3]);
-            } else if (!is_v) {
-              uint16_t* st = k_row + (size_t)(head - e.Hq) * per_head;
-              *(uint32_t*)(st + ((d0 >> 3) << 7) + (d0 & 7)) = pack_bf16x2(v[0], v[1]);
-              *(uint32_t*)(st + ((d1 >> 3) << 7) + (d1 & 7)) = pack_bf16x2(v[2], v[3]);
-            } else {
-              uint16_t* st = v_row + (size_t)(head - e.Hq - e.Hkv) * per_head + ((p0 >> 4) << 9) + ((p0 & 15) << 3);
-#pragma unroll
-              for (int r = 0; r < 4; ++r) st[r << 3] = f32_to_bf16_bits(v[r]);
-            }
-            }
-        }
-      }
     }
     if constexpr (!PR) flag_f16_range(sat, g.status);
   } else {
@@ -793,6 +747,105 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmArgs g) {
 }
 #undef BIG_BAR
 
+// Few rows (a decode step of a small batch): the product is bound by the time the weights take to arrive, and a 64x128
+// tile per block leaves most CUs without one.  Here a block owns a tile of 16 TM x 16 TN (16 to 64 on a side) and its eight
+// waves divide K among themselves, wave w taking the K blocks w, w + 8, ... straight from memory into matrix operands; the
+// eight partial tiles meet in LDS and are added in the order of the waves.  One launch with any epilogue, where the K split
+// over blocks takes a second one and has no form for QKV.  A sum's order depends on K alone, not on the tile or the rows.
+// Measured (weights from HBM, us): 16 rows, N x K = 3072 x 1024 4.2 (64x128 tiles 7.4), 6144 x 2048 8.7 (13.8), 8192 x 2048
+// 9.0 (split-K 12.9), 2560 x 10240 21.5 (23.2); 128 rows, 1024 x 1024 4.9 (8.6).  Operands that go to registers arrive at
+// about 34 bytes a nanosecond and CU, a third of what the direct loads to LDS reach, so the tiles win where a block has
+// more than 256 KB to fetch: 64 rows, 2560 x 10240 38 (split-K 24).
+template <int TM, int TN, int EPI>
+__global__ __launch_bounds__(SKINNY_WAVES * 64) void gemm_skinny_kernel(GemmArgs g) {
+  constexpr int NW = SKINNY_WAVES;
+  __builtin_amdgcn_s_setprio(3);       // as the other products: beside another half's attention the GEMM goes first
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
+  f32x4 (*red)[TM * TN][64] = (f32x4 (*)[TM * TN][64])lds;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tiles_m = (g.M + 16 * TM - 1) / (16 * TM), tiles_n = (g.N + 16 * TN - 1) / (16 * TN);
+  int tile_m, tile_n, split;
+  tile_of_block(tiles_m, tiles_n, 1, tile_m, tile_n, split);
+  const int row0 = tile_m * 16 * TM, col0 = tile_n * 16 * TN;
+  const int frow = lane & 15, fq = lane >> 4;
+  uint32_t va[TM], vb[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) va[i] = (uint32_t)min(row0 + i * 16 + frow, g.M - 1) * 128 + fq * 16;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) vb[j] = (uint32_t)min(col0 + j * 16 + frow, g.N - 1) * 128 + fq * 16;
+  const size_t ka = (size_t)g.M * 128, kw = (size_t)g.N * 128;
+  const int nkb = g.K / BK;
+  f16x8 fa[2][TM][2], fb[2][TN][2];
+  auto load = [&](int kb, int slot) {
+    const char* a = (const char*)g.A + (size_t)kb * ka;
+    const char* w = (const char*)g.W + (size_t)kb * kw;
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) fb[slot][j][s] = *(const f16x8*)(w + vb[j] + s * 64);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int i = 0; i < TM; ++i) fa[slot][i][s] = *(const f16x8*)(a + va[i] + s * 64);
+  };
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto mma = [&](int slot) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = mfma16<false>(fb[slot][j][s], fa[slot][i][s], acc[i][j]);
+  };
+  if (wave < nkb) {
+    load(wave, 0);
+    int kb = wave;
+#pragma unroll 1
+    for (; kb + 2 * NW < nkb; kb += 2 * NW) {
+      load(kb + NW, 1);
+      mma(0);
+      load(kb + 2 * NW, 0);
+      mma(1);
+    }
+    if (kb + NW < nkb) {
+      load(kb + NW, 1);
+      mma(0);
+      mma(1);
+    } else {
+      mma(0);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) red[wave][i * TN + j][lane] = acc[i][j];
+  __syncthreads();
+  if constexpr (EPI == EPI_SWIGLU_F16) {
+    for (int i = wave; i < TM; i += NW) {
+      f32x4 v[1][TN];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        v[0][j] = red[0][i * TN + j][lane];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) v[0][j] += red[w][i * TN + j][lane];
+      }
+      if (row0 + i * 16 < g.M) gemm_epilogue<1, TN, EPI, false>(g, v, row0 + i * 16, col0, lane, 0);
+    }
+  } else {
+    for (int t = wave; t < TM * TN; t += NW) {
+      f32x4 v[1][1];
+      v[0][0] = red[0][t][lane];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) v[0][0] += red[w][t][lane];
+      if (row0 + t / TN * 16 < g.M && col0 + t % TN * 16 < g.N) gemm_epilogue<1, 1, EPI, false>(g, v, row0 + t / TN * 16, col0 + t % TN * 16, lane, 0);
+    }
+  }
+}
+
 // Second half of a split-K product: sums the partial results in split order (so the result does not depend
 // on scheduling) and applies the epilogue.
 template <int EPI>
@@ -861,6 +914,56 @@ hipError_t launch_big(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int TM, int TN, int EPI>
+hipError_t launch_skinny(const GemmArgs& g, hipStream_t s) {
+  constexpr int lds_bytes = SKINNY_WAVES * TM * TN * 64 * 16;
+  static bool configured_on[64] = {};       // once per device (a repeated call is harmless, so no lock)
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+  if (lds_bytes > 65536 && !configured_on[dev]) {
+    hipError_t e = hipFuncSetAttribute((const void*)gemm_skinny_kernel<TM, TN, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    if (e != hipSuccess) return e;
+    configured_on[dev] = true;
+  }
+  const int tiles = ((g.M + 16 * TM - 1) / (16 * TM)) * ((g.N + 16 * TN - 1) / (16 * TN));
+  hipLaunchKernelGGL((gemm_skinny_kernel<TM, TN, EPI>), dim3(tiles), dim3(SKINNY_WAVES * 64), lds_bytes, s, g);
+  return hipGetLastError();
+}
+
+// The tile that leaves the busiest CU the fewest rows and columns to fetch; of equals the largest.
+struct SkinnyTile { int tm, tn; long long cost; };      // cost: rows + columns over all blocks of the busiest CU
+SkinnyTile skinny_tile(int M, int N, int epi) {
+  SkinnyTile best{0, 0, 1LL << 60};
+  for (int tm = 1; tm <= 4; tm *= 2)
+    for (int tn = epi == EPI_SWIGLU_F16 ? 4 : 1; tn <= 4; tn *= 2) {      // SwiGLU: gates and ups of 32 features
+      const long long blocks = (long long)((M + 16 * tm - 1) / (16 * tm)) * ((N + 16 * tn - 1) / (16 * tn));
+      const long long cost = (blocks + 255) / 256 * 16 * (tm + tn);
+      if (cost <= best.cost) best = {tm, tn, cost};
+    }
+  return best;
+}
+
+template <int EPI>
+hipError_t launch_skinny_tile(const GemmArgs& g, hipStream_t s) {
+  const SkinnyTile t = skinny_tile(g.M, g.N, EPI);
+  switch (t.tm * 8 + t.tn) {
+    case 12: return launch_skinny<1, 4, EPI>(g, s);
+    case 20: return launch_skinny<2, 4, EPI>(g, s);
+    case 36: return launch_skinny<4, 4, EPI>(g, s);
+  }
+  if constexpr (EPI != EPI_SWIGLU_F16) {
+    switch (t.tm * 8 + t.tn) {
+      case 9: return launch_skinny<1, 1, EPI>(g, s);
+      case 10: return launch_skinny<1, 2, EPI>(g, s);
+      case 17: return launch_skinny<2, 1, EPI>(g, s);
+      case 18: return launch_skinny<2, 2, EPI>(g, s);
+      case 33: return launch_skinny<4, 1, EPI>(g, s);
+      case 34: return launch_skinny<4, 2, EPI>(g, s);
+    }
+  }
+  return hipErrorInvalidValue;
+}
+
 // Whole K tiles take the direct-load pipeline with two LDS stages (more stages measured slower: the extra LDS
 // costs a resident block); a ragged K falls back to register staging, which can zero-fill the tail.
 template <int BM, int BN, int WM, int WN, int EPI, int NS = 2, bool PR = false>
@@ -919,6 +1022,11 @@ hipError_t launch_variant(const GemmArgs& g, int variant, hipStream_t s) {
 
 }  // namespace
 
+static bool valid_qkv(const GemmArgs& g) {
+  const QkvEpi& e = g.qe;
+  return e.r % 4 == 0 && e.h % 16 == 0 && g.N == (e.Hq + 2 * e.Hkv) * e.h && e.q && e.pos && (e.r == 0 || e.table) &&
+         (e.kvstage || (e.kv && e.dst_seq && e.kv_off && e.kv_cap));
+}
 hipError_t rl_gemm_variant(const GemmArgs& g, int epi, int variant, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (g.K % 8 != 0) return hipErrorInvalidValue;
@@ -935,12 +1043,27 @@ hipError_t rl_gemm_variant(const GemmArgs& g, int epi, int variant, hipStream_t 
     case EPI_LMHEAD: return launch_variant<EPI_LMHEAD>(g, variant, s);
     case EPI_PARTIAL: return launch_variant<EPI_PARTIAL>(g, variant, s);
     case EPI_QKV: {
-      const QkvEpi& e = g.qe;
-      if (e.r % 4 != 0 || e.h % 16 != 0 || g.N != (e.Hq + 2 * e.Hkv) * e.h || !e.q || !e.pos || (e.r > 0 && !e.table) ||
-          (!e.kvstage && (!e.kv || !e.dst_seq || !e.kv_off || !e.kv_cap)))
-        return hipErrorInvalidValue;
-      return launch_variant<EPI_QKV>(g, variant, s);
+      return valid_qkv(g) ? launch_variant<EPI_QKV>(g, variant, s) : hipErrorInvalidValue;
     }
+  }
+  return hipErrorInvalidValue;
+}
+
+bool rl_gemm_skinny_pays(int cap_rows, int N, int K, int epi) {
+  if (K % BK != 0 || N % 16 != 0 || (epi == EPI_SWIGLU_F16 && N % 64 != 0)) return false;
+  if (epi != EPI_F32 && epi != EPI_RESID && epi != EPI_GELU_F16 && epi != EPI_SWIGLU_F16 && epi != EPI_QKV) return false;
+  // up to 16 rows on every width that was measured, beyond while a CU fetches no more than 256 KB (see the kernel)
+  return cap_rows <= 16 || (cap_rows <= 128 && skinny_tile(cap_rows, N, epi).cost * K * 2 <= 256 * 1024);
+}
+hipError_t rl_gemm_skinny(const GemmArgs& g, int epi, hipStream_t s) {
+  if (g.M <= 0 || g.N <= 0) return hipSuccess;
+  if (g.precise || g.K % BK != 0 || g.N % 16 != 0 || (epi == EPI_RESID && g.ldo % 4 != 0)) return hipErrorInvalidValue;
+  switch (epi) {
+    case EPI_F32: return launch_skinny_tile<EPI_F32>(g, s);
+    case EPI_RESID: return launch_skinny_tile<EPI_RESID>(g, s);
+    case EPI_GELU_F16: return launch_skinny_tile<EPI_GELU_F16>(g, s);
+    case EPI_SWIGLU_F16: return g.N % 64 == 0 ? launch_skinny_tile<EPI_SWIGLU_F16>(g, s) : hipErrorInvalidValue;
+    case EPI_QKV: return valid_qkv(g) ? launch_skinny_tile<EPI_QKV>(g, s) : hipErrorInvalidValue;
   }
   return hipErrorInvalidValue;
 }

@@ -95,6 +95,12 @@ hipError_t rl_gemm(const GemmArgs& g, int epi, hipStream_t s);
 hipError_t rl_gemm_variant(const GemmArgs& g, int epi, int variant, hipStream_t s);
 hipError_t rl_gemm_splitk(const GemmArgs& g, int epi, int variant, hipStream_t s);   // needs g.ws, g.splits >= 2
 
+// Few rows: K divided among the SKINNY_WAVES waves of a block (K a multiple of 64, N of 16; not in precise mode).  Whether a
+// layer of a context with room for cap_rows rows takes this form follows from its shape: the sums' order is the form's.
+constexpr int SKINNY_WAVES = 8;
+bool rl_gemm_skinny_pays(int cap_rows, int N, int K, int epi);
+hipError_t rl_gemm_skinny(const GemmArgs& g, int epi, hipStream_t s);
+
 // ------------------------------------------------------------------ attention
 // prefill: 16 queries [16 qblock, 16 qblock + 16) of one sequence.  pre_len > 0: the sequence continues a prefix held
 // by cache sequence pre_seq (pre_len keys, all visible to every query) -- the shared prompt of grouped scoring

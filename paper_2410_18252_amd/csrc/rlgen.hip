@@ -128,6 +128,7 @@ struct rlgen_ctx {
   // tile shape and K split of each linear layer, measured at creation: [decode | prompt pass][which GEMM]
   // [decode of max_seqs rows | prompt pass | decode of half of max_seqs rows][which GEMM]
   struct GemmChoice { int variant, splits; } tuned[3][5];
+  bool skinny[5];         // decode steps take this linear layer with K divided inside the block (by rule: rl_gemm_skinny_pays)
   bool half_rows;         // the decode steps being enqueued cover half of the batch
   // precise mode (cfg.precise): 16-bit activations and cached keys/values are bf16 hi/lo pairs.  pw = 2 then (else 1):
   // 16-bit values per activation element; kv_plane = elements between the hi and the lo plane of the cache
@@ -385,6 +386,7 @@ hipError_t run_choice(const GemmArgs& g, int epi, int variant, int splits, hipSt
 }
 hipError_t gemm(rlgen_ctx* c, int which, bool decode, const GemmArgs& g, int epi, hipStream_t st) {
   const int mode = decode ? (c->half_rows ? 2 : 0) : 1;
+  if (decode && c->skinny[which]) return rl_gemm_skinny(g, epi, st);
   // the K split is that of the mode's family (decode / prompt pass) even where a mode was not tuned
   return run_choice(g, epi, c->tuned[mode][which].variant, c->tuned[decode ? 0 : 1][which].splits, st);
 }
@@ -691,6 +693,12 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
       // the K split: by rule, the same for every decode mode
       const int splits = !g.ws ? 1 : mode == 1 ? split_rule(c->R, c->R, g.N, g.K, epi, g.ws_elems, false)
                                                : split_rule(dec_rows_eff, m.max_seqs, g.N, g.K, epi, g.ws_elems, tune_half);
+      if (mode != 1 && which != G_LMHEAD && !pr && rl_gemm_skinny_pays(m.max_seqs, g.N, g.K, epi)) {
+        // decode steps of every row count divide K inside the block: there is no tile shape to time
+        c->skinny[which] = true;
+        c->tuned[mode][which] = {0, SKINNY_WAVES};
+        continue;
+      }
       std::vector<int> cands = {0, 5};
       if (splits == 1) cands.push_back(3);
       if (mode == 2 && splits == 1 && !pr) { cands.push_back(1); cands.push_back(4); }     // beside attention other shapes can win
