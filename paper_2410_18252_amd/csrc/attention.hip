@@ -50,11 +50,15 @@
 
 namespace {
 
+// SPLIT > 1 (decode): the waves of a block share one job, wave w taking the super-blocks w, w + SPLIT, ... of every segment; their
+// maxima, sums and outputs meet in LDS and are added in the order of the waves.  For contexts whose batches cannot give every
+// CU several jobs: a wave's walk over its keys is a serial chain of loads and products, 2.8 us a super-block at head size 256.
 // QB = query blocks of 16 columns a wave carries through one pass over the keys (prompt pass only: two blocks halve
 // the key / value traffic per query; a.jobs then counts blocks of 16 QB tokens).
-template <int HD, bool DECODE, int QB = 1, bool PR = false>
-__global__ __launch_bounds__(256, (!DECODE && HD <= 128 && !PR) ? ATTN_PROMPT_BLOCKS : 1) void attention_kernel(AttnArgs a) {
+template <int HD, bool DECODE, int QB = 1, bool PR = false, int SPLIT = 1>
+__global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= 128 && !PR) ? ATTN_PROMPT_BLOCKS : 1) void attention_kernel(AttnArgs a) {
   static_assert(!DECODE || QB == 1, "decode has one query block");
+  static_assert(SPLIT == 1 || (DECODE && SPLIT >= 4), "only decode jobs are shared, by all waves of a block");
   constexpr int NCH = HD / 8;            // 16-byte chunks per key row
   constexpr int KSTEPS = (HD + 31) / 32; // MFMA steps over head_dim for the scores
   constexpr int VT = HD / 16;            // 16-row tiles of V^T / O^T
@@ -62,10 +66,11 @@ __global__ __launch_bounds__(256, (!DECODE && HD <= 128 && !PR) ? ATTN_PROMPT_BL
   // and loads them at the top of the iteration instead)
   constexpr bool PF = (DECODE || !ATTN_PROMPT_NOPF) && !PR;
   constexpr int NP = PR ? 2 : 1;         // cache planes: hi, lo
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 15, g = lane >> 4;
   const int Hkv = a.lay.Hkv, G = a.Hq / Hkv;
-  const int job = blockIdx.x * 4 + wave;
+  const int job = SPLIT > 1 ? blockIdx.x : blockIdx.x * 4 + wave;
+  const int sb0 = SPLIT > 1 ? wave : 0;                 // first super-block of this wave
 
   // A job streams one or more segments.  Segment i is the stream of cache sequence seg_seq(i) with seg_len(i)
   // keys; column c takes part in it if seg_col(i) < 0 or seg_col(i) == c / G (its sample).
@@ -203,26 +208,26 @@ __global__ __launch_bounds__(256, (!DECODE && HD <= 128 && !PR) ? ATTN_PROMPT_BL
   [[maybe_unused]] u32x4 kraw_lo[NP - 1 ? 2 : 1][KSTEPS], vraw_lo[VT];
 #if ATTN_PREFETCH
   u32x4 knext[2][KSTEPS], vnext[VT];
-  if (PF && nsb > 0) load_sb(0, kraw, vraw);
+  if (PF && sb0 < nsb) load_sb(sb0, kraw, vraw);
 #endif
 #if ATTN_PREFETCH2
   // decode: a second super-block in flight (the kernel is bound by bytes in flight, and registers allow it)
   u32x4 knext2[2][KSTEPS], vnext2[VT];
   // measured: head size 128 gains 4 % from it, head sizes 64 and 80 lose (fewer waves fit), 256 would spill
   constexpr bool P2 = DECODE && HD > 96 && HD <= 128 && !PR;
-  if (P2 && nsb > 1) load_sb(1, knext, vnext);
+  if (P2 && sb0 + SPLIT < nsb) load_sb(sb0 + SPLIT, knext, vnext);
 #endif
-  for (int sb = 0; sb < nsb; ++sb) {
+  for (int sb = sb0; sb < nsb; sb += SPLIT) {
 #if ATTN_PREFETCH2
     if (P2) {
-      if (sb + 2 < nsb) load_sb(sb + 2, knext2, vnext2);
-    } else if (PF) { if (sb + 1 < nsb) load_sb(sb + 1, knext, vnext); }
+      if (sb + 2 * SPLIT < nsb) load_sb(sb + 2 * SPLIT, knext2, vnext2);
+    } else if (PF) { if (sb + SPLIT < nsb) load_sb(sb + SPLIT, knext, vnext); }
     else {
       load_sb(sb, kraw, vraw);
       if constexpr (PR) load_sb(sb, kraw_lo, vraw_lo, 1);
     }
 #elif ATTN_PREFETCH
-    if (sb + 1 < nsb) load_sb(sb + 1, knext, vnext);
+    if (sb + SPLIT < nsb) load_sb(sb + SPLIT, knext, vnext);
 #else
     load_sb(sb, kraw, vraw);
 #endif
@@ -325,52 +330,102 @@ __global__ __launch_bounds__(256, (!DECODE && HD <= 128 && !PR) ? ATTN_PROMPT_BL
 #endif
   }
   }   // segments
+  // column c's 4 VT values of head dims 16 t + 4 g .. + 3 leave for row qrow
+  auto store = [&](int b, int t, f32x4 y) {
+    u32x2 w;
+    uint16_t* dst = a.out + kblk_off(qrow[b], qhead * HD + 16 * t + 4 * g, a.out_rows);
+    if constexpr (PR) {
+      u32x2 wl;
+      SPLIT_BF16X2(y[0], y[1], w[0], wl[0]);
+      SPLIT_BF16X2(y[2], y[3], w[1], wl[1]);
+      *(u32x2*)(dst + a.out_lo_off) = wl;
+    } else {
+      w[0] = pack_f16x2(y[0], y[1]);
+      w[1] = pack_f16x2(y[2], y[3]);
+    }
+    *(u32x2*)dst = w;
+  };
 #pragma unroll
   for (int b = 0; b < QB; ++b) {
     float ls = lsum[b];
     ls += __shfl_xor(ls, 16, WAVE);
     ls += __shfl_xor(ls, 32, WAVE);
-    const float inv = 1.0f / ls;
-    if (store_col[b]) {
+    if constexpr (SPLIT > 1) {
+      extern __shared__ __attribute__((aligned(16))) unsigned char shared[];
+      f32x4 (*part)[VT][64] = (f32x4 (*)[VT][64])shared;                       // [wave][16-dim tile][lane]
+      float2 (*ml)[16] = (float2 (*)[16])(shared + (size_t)SPLIT * VT * 64 * 16);   // [wave][column] maximum and sum
+      if (g == 0) ml[wave][c] = make_float2(m[b], ls);
+      __syncthreads();
+      float M = -INFINITY, L = 0.f;
 #pragma unroll
-      for (int t = 0; t < VT; ++t) {
-        u32x2 w;
-        uint16_t* dst = a.out + kblk_off(qrow[b], qhead * HD + 16 * t + 4 * g, a.out_rows);
-        if constexpr (PR) {
-          u32x2 wl;
-          SPLIT_BF16X2(o[b][t][0] * inv, o[b][t][1] * inv, w[0], wl[0]);
-          SPLIT_BF16X2(o[b][t][2] * inv, o[b][t][3] * inv, w[1], wl[1]);
-          *(u32x2*)(dst + a.out_lo_off) = wl;
-        } else {
-          w[0] = pack_f16x2(o[b][t][0] * inv, o[b][t][1] * inv);
-          w[1] = pack_f16x2(o[b][t][2] * inv, o[b][t][3] * inv);
-        }
-        *(u32x2*)dst = w;
+      for (int w = 0; w < SPLIT; ++w) M = fmaxf(M, ml[w][c].x);
+#pragma unroll
+      for (int w = 0; w < SPLIT; ++w) L += ml[w][c].y * __expf(ml[w][c].x - M);
+      // a wave without keys has a maximum of -inf and contributes nothing (some wave has keys: M is finite)
+      const float mine = __expf(m[b] - M);
+#pragma unroll
+      for (int t = 0; t < VT; ++t) part[wave][t][lane] = o[b][t] * mine;
+      __syncthreads();
+      const float inv = 1.0f / L;
+      for (int t = wave; t < VT; t += SPLIT) {
+        f32x4 y = part[0][t][lane];
+#pragma unroll
+        for (int w = 1; w < SPLIT; ++w) y += part[w][t][lane];
+        if (store_col[b]) store(b, t, y * inv);
+      }
+    } else {
+      const float inv = 1.0f / ls;
+      if (store_col[b]) {
+#pragma unroll
+        for (int t = 0; t < VT; ++t) store(b, t, o[b][t] * inv);
       }
     }
   }
 }
 
+template <int HD, bool DECODE, int QB, bool PR, int SPLIT>
+hipError_t launch(const AttnArgs& a, int jobs, hipStream_t s) {
+  constexpr int lds_bytes = SPLIT > 1 ? SPLIT * (HD / 16 * 64 * 16 + 16 * (int)sizeof(float2)) : 0;
+  if constexpr (lds_bytes > 65536) {
+    static bool configured_on[64] = {};       // once per device (a repeated call is harmless, so no lock)
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+    if (!configured_on[dev]) {
+      hipError_t e = hipFuncSetAttribute((const void*)attention_kernel<HD, DECODE, QB, PR, SPLIT>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+      if (e != hipSuccess) return e;
+      configured_on[dev] = true;
+    }
+  }
+  const dim3 grid(SPLIT > 1 ? jobs : (jobs + 3) / 4), block(SPLIT > 4 ? SPLIT * 64 : 256);
+  hipLaunchKernelGGL((attention_kernel<HD, DECODE, QB, PR, SPLIT>), grid, block, lds_bytes, s, a);
+  return hipGetLastError();
+}
+template <int HD, bool DECODE, int QB, bool PR>
+hipError_t launch_split(const AttnArgs& a, int jobs, hipStream_t s) {
+  if constexpr (DECODE) {
+    // (eight waves to a job leave a wave 256 registers: too few for the widest head and for precise mode)
+    if (a.split >= 8 && HD <= 128 && !PR) return launch<HD, DECODE, QB, PR, (HD <= 128 && !PR) ? 8 : 4>(a, jobs, s);
+    if (a.split >= 4) return launch<HD, DECODE, QB, PR, 4>(a, jobs, s);
+  }
+  return launch<HD, DECODE, QB, PR, 1>(a, jobs, s);
+}
 template <bool DECODE, int QB>
 hipError_t dispatch(const AttnArgs& a, int jobs, hipStream_t s) {
   if (jobs <= 0) return hipSuccess;
-  dim3 grid((jobs + 3) / 4), block(256);
   if (a.precise) {
     switch (a.lay.h) {
-#define CASE(H) case H: hipLaunchKernelGGL((attention_kernel<H, DECODE, (QB > 1 && H > 80) ? 1 : QB, true>), grid, block, 0, s, a); break;
+#define CASE(H) case H: return launch_split<H, DECODE, (QB > 1 && H > 80) ? 1 : QB, true>(a, jobs, s);
       CASE(16) CASE(32) CASE(48) CASE(64) CASE(80) CASE(96) CASE(112) CASE(128)
 #undef CASE
       default: return hipErrorInvalidValue;     // head size 256 would not fit the register file with two planes
     }
-    return hipGetLastError();
   }
   switch (a.lay.h) {
-#define CASE(H) case H: hipLaunchKernelGGL((attention_kernel<H, DECODE, (QB > 1 && H > 80) ? 1 : QB>), grid, block, 0, s, a); break;
+#define CASE(H) case H: return launch_split<H, DECODE, (QB > 1 && H > 80) ? 1 : QB, false>(a, jobs, s);
     CASE(16) CASE(32) CASE(48) CASE(64) CASE(80) CASE(96) CASE(112) CASE(128) CASE(256)
 #undef CASE
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace
@@ -379,6 +434,9 @@ hipError_t rl_attention_decode(const AttnArgs& a, hipStream_t s) {
   if (a.share_k && (a.S % a.share_k != 0 || a.share_k * (a.Hq / a.lay.Hkv) > 16)) return hipErrorInvalidValue;
   return dispatch<true, 1>(a, (a.share_k ? a.S / a.share_k : a.S) * a.lay.Hkv, s);
 }
+// Waves to a decode job: by what the context can hold, so that a sequence's sums do not depend on the batch it is in.  With up to
+// 512 jobs a CU gets at most two, with up to 2048 at most eight waves: too few to keep the memory busy.
+int rl_attention_decode_split(long long cap_jobs) { return cap_jobs <= 512 ? 8 : cap_jobs <= 2048 ? 4 : 1; }
 // a.jobs: 16-token blocks; every sequence must contribute a multiple of rl_attention_prefill_qb(h) of them (blocks
 // past its end are allowed), since a wave takes that many consecutive blocks
 int rl_attention_prefill_qb(int h) { return h <= 80 ? 2 : 1; }

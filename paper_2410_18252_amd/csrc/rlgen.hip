@@ -471,6 +471,7 @@ int run_layers(rlgen_ctx* c, int rows, bool decode, int t, int ncopy, bool use_c
       const int u0 = c->share_k ? dv.b0 : dv.g0;
       a.kv_off = c->d_kv_off + u0; a.kv_cap = c->d_kv_cap + u0;
       a.ctx_base = c->d_ctx_base + dv.g0; a.ctx_add = t; a.S = rows; a.order = c->use_order ? c->d_order + u0 : nullptr;
+      a.split = rl_attention_decode_split((long long)m.max_seqs * m.n_kv_heads);
       a.share_k = c->share_k; a.sfx_first = c->share_k ? dv.B + dv.g0 - dv.b0 : 0;
       a.finished = c->eos_token >= 0 ? c->d_finished + dv.g0 : nullptr;
       if (dv.row_seq) {
@@ -643,7 +644,7 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
       bool ok = hipMemcpyAsync(nb_meta, meta, (size_t)3 * Sh * sizeof(int), hipMemcpyHostToDevice, st) == hipSuccess &&
                 rl_fill_zero(c->kv, (size_t)Sh * cap * 2 * m.n_kv_heads * m.head_dim * 2, st) == hipSuccess;
       nb.q = c->q; nb.q_ld = qd; nb.out = (uint16_t*)c->qkv; nb.out_rows = Sh; nb.kv = c->kv; nb.lay = c->lay;
-      nb.kv_off = nb_meta; nb.kv_cap = nb_meta + Sh; nb.ctx_base = nb_meta + 2 * Sh; nb.ctx_add = 1; nb.S = Sh;
+      nb.kv_off = nb_meta; nb.kv_cap = nb_meta + Sh; nb.ctx_base = nb_meta + 2 * Sh; nb.ctx_add = 1; nb.S = Sh; nb.split = rl_attention_decode_split((long long)m.max_seqs * m.n_kv_heads);
       nb.Hq = m.n_q_heads; nb.scale = 1.0f / sqrtf((float)m.head_dim);
       nb.precise = pr; nb.kv_lo_off = c->kv_plane; nb.out_lo_off = pr ? kblk_elems(Sh, qd) : 0;
       if (pr && ok) ok = rl_fill_zero(c->kv + c->kv_plane, (size_t)Sh * cap * 2 * m.n_kv_heads * m.head_dim * 2, st) == hipSuccess;
