@@ -66,7 +66,11 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= 128
   // and loads them at the top of the iteration instead)
   constexpr bool PF = (DECODE || !ATTN_PROMPT_NOPF) && !PR;
   constexpr int NP = PR ? 2 : 1;         // cache planes: hi, lo
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  // A wave number known to be common to the wave makes the job's addresses scalar.  Not for the two-block prompt pass: there
+  // the compiler then keeps more in registers (181 instead of 162 at head size 80: two waves per SIMD instead of three; at
+  // head size 64 109 -> 128 us), while wide heads gain (256: 163 -> 142 us).
+  const int wave = DECODE || HD >= 112 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : (int)(threadIdx.x >> 6);
   const int c = lane & 15, g = lane >> 4;
   const int Hkv = a.lay.Hkv, G = a.Hq / Hkv;
   const int job = SPLIT > 1 ? blockIdx.x : blockIdx.x * 4 + wave;
@@ -434,9 +438,14 @@ hipError_t rl_attention_decode(const AttnArgs& a, hipStream_t s) {
   if (a.share_k && (a.S % a.share_k != 0 || a.share_k * (a.Hq / a.lay.Hkv) > 16)) return hipErrorInvalidValue;
   return dispatch<true, 1>(a, (a.share_k ? a.S / a.share_k : a.S) * a.lay.Hkv, s);
 }
-// Waves to a decode job: by what the context can hold, so that a sequence's sums do not depend on the batch it is in.  With up to
-// 512 jobs a CU gets at most two, with up to 2048 at most eight waves: too few to keep the memory busy.
-int rl_attention_decode_split(long long cap_jobs) { return cap_jobs <= 512 ? 8 : cap_jobs <= 2048 ? 4 : 1; }
+// Waves to a decode job: by what the context can hold, so that a sequence's sums do not depend on the batch it is in.  Where
+// the jobs alone give a SIMD a wave or two (wide heads need fewer, they hold more in registers), sharing one only costs the
+// meeting in LDS.  Measured, one wave / four waves to a job: 128 jobs at head size 256 50 / 21 us, 2048 at head size 64 37.8 /
+// 35.9 us, 2048 at head size 128 125 / 148 us.
+int rl_attention_decode_split(long long cap_jobs, int h) {
+  const long long size = cap_jobs * (h > 64 ? h : 64);
+  return size <= 32768 ? 8 : size <= 131072 ? 4 : 1;
+}
 // a.jobs: 16-token blocks; every sequence must contribute a multiple of rl_attention_prefill_qb(h) of them (blocks
 // past its end are allowed), since a wave takes that many consecutive blocks
 int rl_attention_prefill_qb(int h) { return h <= 80 ? 2 : 1; }

@@ -380,7 +380,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_f16_kernel(GemmArgs g) {
   constexpr int RPP = NT / 8;                    // rows covered by one pass of 16-byte loads
   constexpr int PA = BM / RPP, PB = BN / RPP;
   static_assert(PA >= 1 && PB >= 1 && TM >= 1 && TN >= 1, "tile too small for the thread count");
-  static_assert(NS == 0 || (NS >= 2 && NS <= 4 && !KTAIL), "direct loads need whole K tiles");
+  static_assert(NS == 0 || (NS == 2 && !KTAIL), "direct loads need whole K tiles");
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];   // max(2, NS) x (BM + BN) x BK
   // GEMM waves issue ahead of whatever shares their SIMD: in a decode step that is the other half's attention, whose
   // waves mostly wait for memory (measured: the GEMMs' time in that company -10 %, the decode phase -0.8 %)
@@ -528,8 +528,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_f16_kernel(GemmArgs g) {
       for (int i = 0; i < PB; ++i)
         __builtin_amdgcn_global_load_lds((gptr_t)(qb[i] + wk(kt) * kw), (lptr_t)(la + (BM + i * RPP) * BK), 16, 0, 0);
     };
-    constexpr int L = PA + PB;                      // loads per wave and stage
-    if constexpr (NS == 2) {
+    {
       // Skewed by a quarter of a K step: the wait for the next stage and the barrier sit before the last of the four
       // MFMA groups of a stage, whose fragments are in registers by then.  Behind the barrier nobody reads this
       // stage's LDS any more, so its buffer is refilled at once, and the first fragments of the next stage are
@@ -593,26 +592,6 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_f16_kernel(GemmArgs g) {
         ++kt;
       }
       stage(kt, std::false_type{}, std::false_type{});
-    } else {
-#pragma unroll
-      for (int s = 0; s < NS - 1; ++s)
-        if (kt0 + s < nk) issue(kt0 + s, s);
-      // stage kt must have landed; up to NS - 2 younger stages may still be in flight.  Behind the barrier every wave has
-      // left stage kt - 1: its buffer takes stage kt + NS - 1
-      int kt = kt0;
-#pragma unroll 1
-      for (; kt + NS - 1 < nk; ++kt) {
-        wait_loads_then_barrier<(NS - 2) * L>();
-        issue(kt + NS - 1, (kt - kt0 + NS - 1) % NS);
-        k_step((kt - kt0) % NS, [] {});
-      }
-      for (; kt < nk; ++kt) {
-        const int younger = min(nk - 1 - kt, NS - 2);
-        if (younger >= 2) wait_loads_then_barrier<2 * L>();
-        else if (younger == 1) wait_loads_then_barrier<L>();
-        else wait_loads_then_barrier<0>();
-        k_step((kt - kt0) % NS, [] {});
-      }
     }
   }
 
@@ -746,6 +725,134 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmArgs g) {
   gemm_epilogue<TM, TN, EPI, PR, true>(g, acc, row0 + wm * 128, col0 + wn * 128, lane, 0);
 }
 #undef BIG_BAR
+
+// Tiles for launches with few blocks to a CU (decode steps, short prompt passes): a ring of NS stages of 64 K values, requested
+// NS - 1 stages ahead, and fragments one K slice of 32 ahead of the products, across the stage boundary too.  The wait for
+// the next stage and the only barrier of a K step sit between its two slices, where every wave holds fragments for the
+// second; behind the barrier nobody reads the stage before any more, whose slot is requested anew.  No branch in the loop.
+// What bounds these launches is the latency of the weights (1 us from another XCD's side of the chip, 1.8 us from HBM) over
+// the bytes a CU has in flight, so the ring takes most of LDS.  Measured with weights from HBM (us, the two-stage loop's best
+// tile in parentheses): 64x64 on four waves, 128 rows, N x K = 2560 x 2560 9.2 (15.2), 6144 x 2048 8.8 (13.6); 128x128 on
+// eight waves, 512 rows, 7680 x 2560 23.5 (29.8), 6144 x 4096 38.0 (54.7), 1024 rows, 2560 x 2560 19.5 (24.4); 256x128, 1024
+// rows, 7680 x 2560 43.9 (48.8); 64x128 on four waves as the parts of a K split, 128 rows, 2560 x 10240 21.7 (26.2).
+template <int BM, int BN, int WM, int WN, int NS, int EPI, bool PR = false>
+__global__ __launch_bounds__(WM * WN * 64) void gemm_ring_kernel(GemmArgs g) {
+  constexpr int NW = WM * WN;                            // waves
+  constexpr int TM = BM / WM / 16, TN = BN / WN / 16;    // 16x16 tiles of a wave
+  constexpr int LA = BM / 8 / NW, LB = BN / 8 / NW, L = LA + LB;     // requests per wave and stage, 8 rows each
+  constexpr int STAGE = (BM + BN) * BK;
+  static_assert(NS >= 3 && NS <= 6 && LA >= 1 && LB >= 1, "whole requests");
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];   // NS stages
+  __builtin_amdgcn_s_setprio(3);       // ahead of the other half's attention (see gemm_f16_kernel)
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+  int tile_m, tile_n, split;
+  const int splits = EPI == EPI_PARTIAL ? g.splits : 1;
+  tile_of_block(tiles_m, tiles_n, splits, tile_m, tile_n, split);
+  const int row0 = tile_m * BM, col0 = tile_n * BN;
+  const int nkb = g.K / BK;
+  const int nk_all = PR ? 2 * nkb : nkb;
+  const int kt0 = (int)((long long)split * nk_all / splits);
+  const int nk = (int)((long long)(split + 1) * nk_all / splits) - kt0;       // this block's K steps
+  const size_t ka = (size_t)g.M * 128, kw = (size_t)g.N * 128;
+  uint32_t va[LA], vb[LB];
+#pragma unroll
+  for (int i = 0; i < LA; ++i) {
+    const int r = (wave * LA + i) * 8 + (lane >> 3);
+    va[i] = (uint32_t)min(row0 + r, g.M - 1) * 128 + ((lane & 7) ^ swz(r)) * 16;
+  }
+#pragma unroll
+  for (int i = 0; i < LB; ++i) {
+    const int r = (wave * LB + i) * 8 + (lane >> 3);
+    vb[i] = (uint32_t)min(col0 + r, g.N - 1) * 128 + ((lane & 7) ^ swz(r)) * 16;
+  }
+  typedef __attribute__((address_space(3))) void* lptr_t;
+  // request n of stage kt (counted from kt0) into slot s: first the rows of A, then those of W
+  auto request = [&](int kt, int s, int n) {
+    kt += kt0;
+    const bool is_a = n < LA;
+    const char* base = is_a ? (const char*)g.A + (size_t)(PR ? (kt >> 1) + (kt & 1) * nkb : kt) * ka : (const char*)g.W + (size_t)(PR ? kt >> 1 : kt) * kw;
+    uint16_t* dst = lds + s * STAGE + (is_a ? wave * LA + n : BM / 8 + wave * LB + n - LA) * 8 * BK;
+    const uint32_t off = is_a ? va[is_a ? n : 0] : vb[is_a ? 0 : n - LA];
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0x7fffffff, 0x00027000), (lptr_t)dst, 16, off, 0, 0, 0);
+  };
+  const int frow = lane & 15, fq = lane >> 4;
+  int oa[2], ob[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const int c = ((4 * ks + fq) ^ swz(frow)) * 8;
+    oa[ks] = (wm * (BM / WM) + frow) * BK + c;
+    ob[ks] = (BM + wn * (BN / WN) + frow) * BK + c;
+  }
+  f16x8 fa[2][TM], fb[2][TN];
+  auto read = [&](int s, int ks, int n) {      // fragment n of K slice ks of the stage in slot s
+    const uint16_t* st = lds + s * STAGE;
+    if (n < TN) fb[ks][n < TN ? n : 0] = *(const f16x8*)(st + ob[ks] + n * 16 * BK);
+    else fa[ks][n < TN ? 0 : n - TN] = *(const f16x8*)(st + oa[ks] + (n - TN) * 16 * BK);
+  };
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  constexpr int T = TM * TN, R = TM + TN;
+  static_assert(R <= T, "at most one read and one request behind a product");
+  static_assert(L <= T, "at most one request");
+  auto slice = [&](int ks, auto&& rd, auto&& rq) {
+#pragma unroll
+    for (int n = 0; n < T; ++n) {
+      acc[n / TN][n % TN] = mfma16<PR>(fb[ks][n % TN], fa[ks][n / TN], acc[n / TN][n % TN]);
+      SCHED_FENCE();
+      if ((n + 1) * R / T > n * R / T) rd(n * R / T);
+      if ((n + 1) * L / T > n * L / T) rq(n * L / T);
+      SCHED_FENCE();
+    }
+  };
+#define RING_WAIT(N) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory")
+  auto wait_younger = [&](int stages) {     // all but the `stages` youngest stages of this wave have landed; then everybody is here
+    if (stages >= 4) RING_WAIT(4 * L);
+    else if (stages == 3) RING_WAIT(3 * L);
+    else if (stages == 2) RING_WAIT(2 * L);
+    else if (stages == 1) RING_WAIT(L);
+    else RING_WAIT(0);
+  };
+#pragma unroll
+  for (int s = 0; s < NS - 1; ++s)
+    if (s < nk) {
+#pragma unroll
+      for (int n = 0; n < L; ++n) request(s, s, n);
+    }
+  wait_younger(min(nk, NS - 1) - 1);
+#pragma unroll
+  for (int n = 0; n < R; ++n) read(0, 0, n);
+  int kt = 0, s = 0;
+  auto next = [](int x) { return x + 1 == NS ? 0 : x + 1; };
+#pragma unroll 1
+  for (; kt + NS - 1 < nk; ++kt) {
+    const int s1 = next(s), sp = s == 0 ? NS - 1 : s - 1;
+    slice(0, [&](int n) { read(s, 1, n); }, [](int) {});
+    RING_WAIT((NS - 3) * L);
+    SCHED_FENCE();
+    slice(1, [&](int n) { read(s1, 0, n); }, [&](int n) { request(kt + NS - 1, sp, n); });
+    s = s1;
+  }
+#pragma unroll 1
+  for (; kt + 1 < nk; ++kt) {
+    const int s1 = next(s);
+    slice(0, [&](int n) { read(s, 1, n); }, [](int) {});
+    wait_younger(nk - 2 - kt);
+    SCHED_FENCE();
+    slice(1, [&](int n) { read(s1, 0, n); }, [](int) {});
+    s = s1;
+  }
+  if (nk > 0) {
+    slice(0, [&](int n) { read(s, 1, n); }, [](int) {});
+    slice(1, [](int) {}, [](int) {});
+  }
+  gemm_epilogue<TM, TN, EPI, PR>(g, acc, row0 + wm * (BM / WM), col0 + wn * (BN / WN), lane, split);
+}
+#undef RING_WAIT
 
 // Few rows (a decode step of a small batch): the product is bound by the time the weights take to arrive, and a 64x128
 // tile per block leaves most CUs without one.  Here a block owns a tile of 16 TM x 16 TN (16 to 64 on a side) and its eight
@@ -964,6 +1071,23 @@ hipError_t launch_skinny_tile(const GemmArgs& g, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
+template <int BM, int BN, int WM, int WN, int NS, int EPI, bool PR = false>
+hipError_t launch_ring(const GemmArgs& g, hipStream_t s) {
+  constexpr int lds_bytes = NS * (BM + BN) * BK * (int)sizeof(uint16_t);
+  static_assert(lds_bytes <= 160 * 1024, "LDS of one CU");
+  static bool configured_on[64] = {};       // once per device (a repeated call is harmless, so no lock)
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+  if (lds_bytes > 65536 && !configured_on[dev]) {
+    hipError_t e = hipFuncSetAttribute((const void*)gemm_ring_kernel<BM, BN, WM, WN, NS, EPI, PR>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    if (e != hipSuccess) return e;
+    configured_on[dev] = true;
+  }
+  const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * (EPI == EPI_PARTIAL ? g.splits : 1);
+  hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WM, WN, NS, EPI, PR>), dim3(tiles), dim3(WM * WN * 64), lds_bytes, s, g);
+  return hipGetLastError();
+}
+
 // Whole K tiles take the direct-load pipeline with two LDS stages (more stages measured slower: the extra LDS
 // costs a resident block); a ragged K falls back to register staging, which can zero-fill the tail.
 template <int BM, int BN, int WM, int WN, int EPI, int NS = 2, bool PR = false>
@@ -988,34 +1112,32 @@ hipError_t launch_variant_precise(const GemmArgs& g, int variant, hipStream_t s)
   return hipErrorInvalidValue;
 }
 
+// the tile shapes by number; a K that is not whole K tiles takes the register-staged form of the same or the nearest tile
 template <int EPI>
 hipError_t launch_variant(const GemmArgs& g, int variant, hipStream_t s) {
   if (g.precise) return launch_variant_precise<EPI>(g, variant, s);
+  constexpr bool WIDE = EPI == EPI_SWIGLU_F16 || EPI == EPI_LMHEAD;      // a wave must own 64 columns
+  const bool whole = g.K % BK == 0;
   switch (variant) {
     case 0: return launch<128, 128, 2, 2, EPI>(g, s);
     case 1: return launch<256, 128, 2, 2, EPI>(g, s);
-    case 2:
+    case 2: return whole ? launch_ring<128, 128, 4, 2, 4, EPI>(g, s) : launch_k<128, 128, 2, 2, EPI, true, 0>(g, s);
     case 3:
-    case 10:
       // (a K split is for shapes with few tiles: partial sums come from 256x128 at most, and so do a decode step's cache writes)
       if (EPI == EPI_PARTIAL || (EPI == EPI_QKV && !g.qe.kvstage)) return launch<256, 128, 4, 2, EPI>(g, s);
       if constexpr (EPI != EPI_PARTIAL) return launch_big<EPI, false>(g, s);
       break;
     case 4: return launch<128, 256, 2, 2, EPI>(g, s);
     case 5: return launch<256, 128, 4, 2, EPI>(g, s);
-    case 6:
-      if constexpr (EPI != EPI_SWIGLU_F16 && EPI != EPI_LMHEAD) return launch<128, 64, 2, 2, EPI>(g, s);
-      else return hipErrorInvalidValue;
-    case 7:
-      if constexpr (EPI != EPI_SWIGLU_F16 && EPI != EPI_LMHEAD) return launch<64, 128, 1, 4, EPI>(g, s);
-      else return hipErrorInvalidValue;
-    case 8:      // the smallest tile with four LDS stages: loads three K steps ahead, for launches with few blocks per CU
-      if constexpr (EPI != EPI_SWIGLU_F16 && EPI != EPI_LMHEAD) return launch<64, 128, 1, 4, EPI, 4>(g, s);
-      else return hipErrorInvalidValue;
-    case 9:      // the same tile and ring on eight waves of 32x32: two waves per SIMD cover each other's waits for LDS
-                 // fragments and for the stage barrier (12-15 % faster than four waves on long-K shapes with few tiles)
-      if constexpr (EPI != EPI_SWIGLU_F16 && EPI != EPI_LMHEAD) return launch<64, 128, 2, 4, EPI, 4>(g, s);
-      else return hipErrorInvalidValue;
+    case 10: return whole ? launch_ring<256, 128, 4, 2, 3, EPI>(g, s) : launch_k<256, 128, 4, 2, EPI, true, 0>(g, s);
+  }
+  if constexpr (!WIDE) {
+    switch (variant) {
+      case 6: return whole ? launch_ring<64, 64, 2, 2, 5, EPI>(g, s) : launch_k<64, 128, 1, 4, EPI, true, 0>(g, s);
+      case 7: return launch<64, 128, 1, 4, EPI>(g, s);
+      case 8: return whole ? launch_ring<64, 128, 2, 2, 6, EPI>(g, s) : launch_k<64, 128, 1, 4, EPI, true, 0>(g, s);
+      case 9: return whole ? launch_ring<64, 128, 2, 4, 6, EPI>(g, s) : launch_k<64, 128, 1, 4, EPI, true, 0>(g, s);
+    }
   }
   return hipErrorInvalidValue;
 }

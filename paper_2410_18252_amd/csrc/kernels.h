@@ -130,7 +130,7 @@ struct AttnArgs {
   const AttnJob* jobs; int njobs;
 };
 hipError_t rl_attention_decode(const AttnArgs& a, hipStream_t s);
-int rl_attention_decode_split(long long cap_jobs);
+int rl_attention_decode_split(long long cap_jobs, int h);
 hipError_t rl_attention_prefill(const AttnArgs& a, hipStream_t s);
 // 16-token blocks a prompt-pass attention wave takes at once for head size h; a.jobs must list a multiple of it per sequence
 int rl_attention_prefill_qb(int h);

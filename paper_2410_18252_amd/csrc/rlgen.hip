@@ -471,7 +471,7 @@ int run_layers(rlgen_ctx* c, int rows, bool decode, int t, int ncopy, bool use_c
       const int u0 = c->share_k ? dv.b0 : dv.g0;
       a.kv_off = c->d_kv_off + u0; a.kv_cap = c->d_kv_cap + u0;
       a.ctx_base = c->d_ctx_base + dv.g0; a.ctx_add = t; a.S = rows; a.order = c->use_order ? c->d_order + u0 : nullptr;
-      a.split = rl_attention_decode_split((long long)m.max_seqs * m.n_kv_heads);
+      a.split = rl_attention_decode_split((long long)m.max_seqs * m.n_kv_heads, m.head_dim);
       a.share_k = c->share_k; a.sfx_first = c->share_k ? dv.B + dv.g0 - dv.b0 : 0;
       a.finished = c->eos_token >= 0 ? c->d_finished + dv.g0 : nullptr;
       if (dv.row_seq) {
@@ -644,7 +644,7 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
       bool ok = hipMemcpyAsync(nb_meta, meta, (size_t)3 * Sh * sizeof(int), hipMemcpyHostToDevice, st) == hipSuccess &&
                 rl_fill_zero(c->kv, (size_t)Sh * cap * 2 * m.n_kv_heads * m.head_dim * 2, st) == hipSuccess;
       nb.q = c->q; nb.q_ld = qd; nb.out = (uint16_t*)c->qkv; nb.out_rows = Sh; nb.kv = c->kv; nb.lay = c->lay;
-      nb.kv_off = nb_meta; nb.kv_cap = nb_meta + Sh; nb.ctx_base = nb_meta + 2 * Sh; nb.ctx_add = 1; nb.S = Sh; nb.split = rl_attention_decode_split((long long)m.max_seqs * m.n_kv_heads);
+      nb.kv_off = nb_meta; nb.kv_cap = nb_meta + Sh; nb.ctx_base = nb_meta + 2 * Sh; nb.ctx_add = 1; nb.S = Sh; nb.split = rl_attention_decode_split((long long)m.max_seqs * m.n_kv_heads, m.head_dim);
       nb.Hq = m.n_q_heads; nb.scale = 1.0f / sqrtf((float)m.head_dim);
       nb.precise = pr; nb.kv_lo_off = c->kv_plane; nb.out_lo_off = pr ? kblk_elems(Sh, qd) : 0;
       if (pr && ok) ok = rl_fill_zero(c->kv + c->kv_plane, (size_t)Sh * cap * 2 * m.n_kv_heads * m.head_dim * 2, st) == hipSuccess;
@@ -700,23 +700,39 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
         c->tuned[mode][which] = {0, SKINNY_WAVES};
         continue;
       }
-      std::vector<int> cands = {0, 5};
-      if (splits == 1) cands.push_back(3);
-      if (mode == 2 && splits == 1 && !pr) { cands.push_back(1); cands.push_back(4); }     // beside attention other shapes can win
-      if (!wide_only) {
-        cands.push_back(7);
-        // deeper load pipeline: pays on a long K with few tiles (precise mode is compiled for four tile shapes only)
-        if (g.K % 64 == 0 && g.K >= 2048 * splits && g.M <= 2048 && !pr) { cands.push_back(8); cands.push_back(9); }
+      std::vector<int> cands;
+      if (pr) {                                   // precise mode is compiled for four tile shapes
+        cands = {0, 5};
+        if (splits == 1) cands.push_back(3);
+        if (!wide_only) cands.push_back(7);
+      } else if (splits == 1 && (long long)(g.M / 256) * (g.N / 256) >= 1024) {
+        cands = {3, 10, 5};                       // four large tiles to every CU: the small ones cannot win
+      } else {
+        cands = {0, 5, 2, 10};
+        if (splits == 1) cands.push_back(3);
+        if (mode == 2 && splits == 1) { cands.push_back(1); cands.push_back(4); }     // beside attention other shapes can win
+        if (!wide_only) { cands.push_back(7); cands.push_back(6); cands.push_back(8); cands.push_back(9); }
       }
       // clocks drift with load, so the candidates take turns: one warm-up each, then three rounds in which
       // every candidate is timed over two launches; the smallest total wins
+      // Every timed launch takes the weights of another layer, as in a pass over the model: the same ones again would
+      // come from the 256 MB cache in front of HBM, where tiles win that lose behind it.
+      int layer = 0;
+      auto next_layer = [&](GemmArgs& a) {
+        layer = layer + 1 == m.n_layers ? 0 : layer + 1;
+        const LayerW& l = c->layers[layer];
+        a.W = which == G_QKV ? l.wqkv : which == G_O ? l.wo : which == G_UP ? l.wup : which == G_DOWN ? l.wdown : c->lm_head;
+      };
       std::vector<float> total(cands.size(), 0.f);
       bool ok = true;
       for (size_t i = 0; ok && i < cands.size(); ++i) ok = run_choice(g, epi, cands[i], splits, st) == hipSuccess;
       for (int round = 0; ok && round < 3; ++round)
         for (size_t i = 0; ok && i < cands.size(); ++i) {
           ok = hipEventRecord(e0, st) == hipSuccess;
-          for (int r = 0; ok && r < 2; ++r) ok = run_choice(g, epi, cands[i], splits, st) == hipSuccess;
+          for (int r = 0; ok && r < 2; ++r) {
+            next_layer(g);
+            ok = run_choice(g, epi, cands[i], splits, st) == hipSuccess;
+          }
           if (ok) ok = hipEventRecord(e1, st) == hipSuccess && hipEventSynchronize(e1) == hipSuccess;
           float ms = 0.f;
           if (ok) ok = hipEventElapsedTime(&ms, e0, e1) == hipSuccess;
@@ -743,8 +759,10 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
                hipStreamWaitEvent(c->gstream[0], c->ev_fork, 0) == hipSuccess &&
                hipStreamWaitEvent(c->gstream[1], c->ev_fork, 0) == hipSuccess &&
                rl_attention_decode(nb, c->gstream[0]) == hipSuccess && rl_attention_decode(nb, c->gstream[0]) == hipSuccess;
-          for (int r = 0; ok && r < reps; ++r)
+          for (int r = 0; ok && r < reps; ++r) {
+            next_layer(g);
             ok = run_choice(g, epi, cands[i], splits, c->gstream[1]) == hipSuccess;
+          }
           if (ok) ok = hipEventRecord(e2, c->gstream[1]) == hipSuccess;
           for (int gi = 0; ok && gi < 2; ++gi)
             ok = hipEventRecord(c->ev_join[gi], c->gstream[gi]) == hipSuccess &&
