@@ -54,6 +54,10 @@ __global__ void rope_table_kernel(float2* tab, int max_pos, int r, double theta)
   const double ang = (double)pos * pow(theta, -2.0 * (double)k / (double)r);
   tab[i] = make_float2((float)cos(ang), (float)sin(ang));
 }
+__global__ void add_f32_kernel(float* dst, const float* src, size_t n) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) dst[i] += src[i];
+}
 __global__ void fill_zero_kernel(u32x4* p, size_t n16) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -421,6 +425,11 @@ hipError_t rl_rope_table(float2* tab, int max_pos, int rotary_dim, float theta, 
   const int n = max_pos * (rotary_dim / 2);
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(rope_table_kernel, dim3(blocks_for(n)), dim3(TPB), 0, s, tab, max_pos, rotary_dim, (double)theta);
+  return hipGetLastError();
+}
+hipError_t rl_add_f32(float* dst, const float* src, size_t n, hipStream_t s) {
+  if (!n) return hipSuccess;
+  hipLaunchKernelGGL(add_f32_kernel, dim3(blocks_for(n)), dim3(TPB), 0, s, dst, src, n);
   return hipGetLastError();
 }
 hipError_t rl_fill_zero(void* p, size_t bytes, hipStream_t s) {

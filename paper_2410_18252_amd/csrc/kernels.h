@@ -151,6 +151,8 @@ hipError_t rl_to_f32(float* dst, const void* src, int src_is_bf16, size_t n, hip
 hipError_t rl_pack_gate_up(uint16_t* dst, const void* gate, const void* up, int src_is_bf16, int F, int d, hipStream_t s, int as_bf16 = 0);
 // cos/sin table [max_pos, r/2] (float2), angles pos * theta^(-2i/r) evaluated in fp64
 hipError_t rl_rope_table(float2* tab, int max_pos, int rotary_dim, float theta, hipStream_t s);
+// dst[i] += src[i]
+hipError_t rl_add_f32(float* dst, const float* src, size_t n, hipStream_t s);
 hipError_t rl_fill_zero(void* p, size_t bytes, hipStream_t s);
 // n pseudo-random fp16 values in [-0.5, 0.5) (inputs for timing runs)
 hipError_t rl_fill_random_f16(uint16_t* p, size_t n, unsigned seed, hipStream_t s, int as_bf16 = 0);

@@ -50,7 +50,7 @@ struct SeqMeta {       // one per sequence of a call, consumed by expand_kernel
 };
 
 struct LayerW {
-  float *n1g, *n1b, *n2g, *n2b, *bqkv, *bo, *bup, *bdown;
+  float *n1g, *n1b, *n2g, *n2b, *bqkv, *bo, *bup, *bdown;      // joined_out: bdown holds the sum of both output biases
   uint16_t *wqkv, *wo, *wup, *wdown;
 };
 
@@ -84,6 +84,9 @@ struct rlgen_ctx {
   SeqMeta* d_meta;
   int *d_kv_off, *d_kv_cap, *d_ctx_base, *d_iota, *d_lastrow, *d_order;
   bool use_order;
+  // Parallel residual (NeoX): attention output and FFN-down add to the same residual, so they are one product over K = Hq h + F:
+  // the two weight matrices and the two activation matrices follow each other in memory (whole K blocks: Hq h % 64 == 0)
+  bool joined_out;
   bool fused_qkv;         // rotary_dim % 4 == 0: rotary embedding and cache writes run in the QKV GEMM's epilogue
   int score_groups;       // k > 1: rlgen_score treats every k consecutive sequences as one prompt with k completions
   int eos_token;          // -1: completions never end early (rlgen_set_eos)
@@ -187,6 +190,7 @@ size_t carve(rlgen_ctx* c, char* base) {
   c->ngroups = (int)((V + 63) / 64);
   const size_t R = c->R, LM = c->LM, S = m.max_seqs;
 
+  c->joined_out = !llama && qd % 64 == 0;
   Carve k;
   c->status = k.take<unsigned>(base, 64);
   c->embed = k.take<uint16_t>(base, V * d);
@@ -198,9 +202,10 @@ size_t carve(rlgen_ctx* c, char* base) {
     L.n1g = k.take<float>(base, d); L.n1b = k.take<float>(base, d);
     L.n2g = k.take<float>(base, d); L.n2b = k.take<float>(base, d);
     L.wqkv = k.take<uint16_t>(base, kblk_elems(nqkv, d)); L.bqkv = k.take<float>(base, nqkv);
-    L.wo = k.take<uint16_t>(base, kblk_elems(d, qd)); L.bo = k.take<float>(base, d);
+    L.wo = k.take<uint16_t>(base, kblk_elems(d, c->joined_out ? qd + F : qd)); L.bo = k.take<float>(base, d);
     L.wup = k.take<uint16_t>(base, kblk_elems((llama ? 2 : 1) * F, d)); L.bup = k.take<float>(base, F);
-    L.wdown = k.take<uint16_t>(base, kblk_elems(d, F)); L.bdown = k.take<float>(base, d);
+    L.wdown = c->joined_out ? L.wo + (base ? kblk_elems(d, qd) : 0) : k.take<uint16_t>(base, kblk_elems(d, F));
+    L.bdown = k.take<float>(base, d);
   }
   c->rope = k.take<float2>(base, (size_t)m.max_seq_len * (m.rotary_dim / 2 > 0 ? m.rotary_dim / 2 : 1));
   c->lay.Hkv = m.n_kv_heads;
@@ -229,8 +234,8 @@ size_t carve(rlgen_ctx* c, char* base) {
     b.n2 = k.take<uint16_t>(base, pw * kblk_elems(rows, d));
     b.qkv = k.take<float>(base, rows * nqkv);
     b.q = k.take<uint16_t>(base, pw * rows * qd);
-    b.attn = k.take<uint16_t>(base, pw * kblk_elems(rows, qd));
-    b.act = k.take<uint16_t>(base, pw * kblk_elems(rows, F));
+    b.attn = k.take<uint16_t>(base, pw * kblk_elems(rows, c->joined_out ? qd + F : qd));
+    b.act = c->joined_out ? nullptr : k.take<uint16_t>(base, pw * kblk_elems(rows, F));       // joined: behind attn, at a distance set by the rows of the pass
     b.hfin = k.take<uint16_t>(base, pw * kblk_elems(lm, d));
     b.partial = k.take<float2>(base, lm * (size_t)c->ngroups);
     b.target_logit = k.take<float>(base, lm);
@@ -287,6 +292,7 @@ int pack_weights(rlgen_ctx* c, const rlgen_weights* w, hipStream_t st) {
       HIPCHK(rl_to_f32(L.bo, s.bo, bf, d, st));
       HIPCHK(rl_to_f32(L.bup, s.b_up, bf, F, st));
       HIPCHK(rl_to_f32(L.bdown, s.b_down, bf, d, st));
+      if (c->joined_out) HIPCHK(rl_add_f32(L.bdown, L.bo, d, st));
     }
   }
   return RLGEN_OK;
@@ -427,6 +433,8 @@ int run_layers(rlgen_ctx* c, int rows, bool decode, int t, int ncopy, bool use_c
     const int pr = m.precise;
     // precise mode: distance between the hi and the lo halves of a 16-bit activation matrix of `rows` rows and K columns
     auto lo_off = [&](int K) { return pr ? kblk_elems(rows, K) : (size_t)0; };
+    const int attn_K = c->joined_out ? qd + F : qd, act_K = c->joined_out ? qd + F : F;      // width of the matrix each is a part of
+    uint16_t* const act = c->joined_out ? c->attn + kblk_elems(rows, qd) : c->act;
     if (llama) HIPCHK(rl_norm(c->x, nullptr, rows, d, m.norm_eps, L.n1g, nullptr, c->n1, nullptr, nullptr, nullptr, rows, 0, c->status, st, lo_off(d)));
     else HIPCHK(rl_norm(c->x, nullptr, rows, d, m.norm_eps, L.n1g, L.n1b, c->n1, L.n2g, L.n2b, c->n2, rows, 0, c->status, st, lo_off(d)));
     GemmArgs g{};
@@ -465,7 +473,7 @@ int run_layers(rlgen_ctx* c, int rows, bool decode, int t, int ncopy, bool use_c
     AttnArgs a{};
     a.q = c->q; a.q_ld = qd; a.out = c->attn; a.out_rows = rows; a.kv = kvl; a.lay = c->lay;
     a.kv_off = c->d_kv_off; a.kv_cap = c->d_kv_cap; a.Hq = m.n_q_heads; a.scale = 1.0f / sqrtf((float)h);
-    a.precise = pr; a.kv_lo_off = c->kv_plane; a.out_lo_off = lo_off(qd);
+    a.precise = pr; a.kv_lo_off = c->kv_plane; a.out_lo_off = lo_off(attn_K);
     if (decode) {
       // the kernel indexes sequences (prompts, if shared) from 0: hand it the arrays at this view's first entry
       const int u0 = c->share_k ? dv.b0 : dv.g0;
@@ -495,21 +503,23 @@ int run_layers(rlgen_ctx* c, int rows, bool decode, int t, int ncopy, bool use_c
       a.jobs = c->d_jobs; a.njobs = njobs;
       HIPCHK(rl_attention_prefill(a, st));
     }
-    g = GemmArgs{};
-    g.precise = pr;
-    g.A = c->attn; g.W = L.wo; g.M = rows; g.N = d; g.K = qd;
-    g.bias = llama ? nullptr : L.bo; g.out = c->x; g.ldo = d; g.ws = c->splitk; g.ws_elems = c->splitk_elems;
-    HIPCHK(gemm(c, G_O, decode, g, EPI_RESID, st));
+    if (!c->joined_out) {
+      g = GemmArgs{};
+      g.precise = pr;
+      g.A = c->attn; g.W = L.wo; g.M = rows; g.N = d; g.K = qd;
+      g.bias = llama ? nullptr : L.bo; g.out = c->x; g.ldo = d; g.ws = c->splitk; g.ws_elems = c->splitk_elems;
+      HIPCHK(gemm(c, G_O, decode, g, EPI_RESID, st));
+    }
     if (llama) HIPCHK(rl_norm(c->x, nullptr, rows, d, m.norm_eps, L.n2g, nullptr, c->n2, nullptr, nullptr, nullptr, rows, 0, c->status, st, lo_off(d)));
     g = GemmArgs{};
-    g.precise = pr; g.out_lo_off = lo_off(F);
+    g.precise = pr; g.out_lo_off = lo_off(act_K);
     g.A = c->n2; g.W = L.wup; g.M = rows; g.N = llama ? 2 * F : F; g.K = d;
-    g.bias = llama ? nullptr : L.bup; g.out = c->act; g.ldo = F; g.ws = c->splitk; g.ws_elems = c->splitk_elems;
+    g.bias = llama ? nullptr : L.bup; g.out = act; g.ldo = F; g.ws = c->splitk; g.ws_elems = c->splitk_elems;
     g.status = c->status;
     HIPCHK(gemm(c, G_UP, decode, g, llama ? EPI_SWIGLU_F16 : EPI_GELU_F16, st));
     g = GemmArgs{};
     g.precise = pr;
-    g.A = c->act; g.W = L.wdown; g.M = rows; g.N = d; g.K = F;
+    g.A = c->joined_out ? c->attn : act; g.W = c->joined_out ? L.wo : L.wdown; g.M = rows; g.N = d; g.K = act_K;
     g.bias = llama ? nullptr : L.bdown; g.out = c->x; g.ldo = d; g.ws = c->splitk; g.ws_elems = c->splitk_elems;
     HIPCHK(gemm(c, G_DOWN, decode, g, EPI_RESID, st));
   }
@@ -609,8 +619,9 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
   const size_t pw = c->pw;
   HIPCHK(rl_fill_random_f16(c->n1, pw * kblk_elems(c->R, d), 11, st, pr));
   HIPCHK(rl_fill_random_f16(c->n2, pw * kblk_elems(c->R, d), 12, st, pr));
-  HIPCHK(rl_fill_random_f16(c->attn, pw * kblk_elems(c->R, qd), 13, st, pr));
-  HIPCHK(rl_fill_random_f16(c->act, pw * kblk_elems(c->R, F), 14, st, pr));
+  const int down_K = c->joined_out ? qd + F : F;       // the joined output product is timed as FFN-down
+  HIPCHK(rl_fill_random_f16(c->attn, pw * kblk_elems(c->R, c->joined_out ? qd + F : qd), 13, st, pr));
+  if (!c->joined_out) HIPCHK(rl_fill_random_f16(c->act, pw * kblk_elems(c->R, F), 14, st, pr));
   HIPCHK(rl_fill_random_f16(c->hfin, pw * kblk_elems(c->LM, d), 15, st, pr));
   if (pr) HIPCHK(rl_fill_zero(c->q, align_up((size_t)c->R * qd * 4, 16), st));      // fp32 queries of the neighbour attention
   HIPCHK(rl_fill_zero(c->x, align_up((size_t)c->R * d * 4, 16), st));
@@ -660,6 +671,10 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
   for (int mi = tune_half ? 0 : 1; mi < 3 && rc == RLGEN_OK; ++mi) {
     const int mode = modes[mi];
     for (int which = 0; which < 5 && rc == RLGEN_OK; ++which) {
+      if (which == G_O && c->joined_out) {      // no launch of its own
+        c->tuned[mode][which] = {0, 1};
+        continue;
+      }
       GemmArgs g{};
       g.precise = pr;
       int epi = EPI_F32;
@@ -682,10 +697,10 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
           }
           break;
         case G_O: g.A = c->attn; g.W = L.wo; g.N = d; g.K = qd; g.bias = llama ? nullptr : L.bo; g.out = c->x; g.ldo = d; epi = EPI_RESID; break;
-        case G_UP: g.A = c->n2; g.W = L.wup; g.N = llama ? 2 * F : F; g.K = d; g.bias = llama ? nullptr : L.bup; g.out = c->act; g.ldo = F;
+        case G_UP: g.A = c->n2; g.W = L.wup; g.N = llama ? 2 * F : F; g.K = d; g.bias = llama ? nullptr : L.bup; g.out = c->joined_out ? c->attn : c->act; g.ldo = F;
                    g.out_lo_off = pr ? kblk_elems(g.M, F) : 0;
                    epi = llama ? EPI_SWIGLU_F16 : EPI_GELU_F16; break;
-        case G_DOWN: g.A = c->act; g.W = L.wdown; g.N = d; g.K = F; g.bias = llama ? nullptr : L.bdown; g.out = c->x; g.ldo = d; epi = EPI_RESID;
+        case G_DOWN: g.A = c->joined_out ? c->attn : c->act; g.W = c->joined_out ? L.wo : L.wdown; g.N = d; g.K = down_K; g.bias = llama ? nullptr : L.bdown; g.out = c->x; g.ldo = d; epi = EPI_RESID;
                      break;
         case G_LMHEAD: g.A = c->hfin; g.W = c->lm_head; g.M = mode != 1 ? dec_rows : c->LM; g.N = m.vocab; g.K = d; g.temperature = 1.f;
                        g.partial = c->partial; g.ws = nullptr; epi = EPI_LMHEAD; break;
@@ -721,7 +736,7 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
       auto next_layer = [&](GemmArgs& a) {
         layer = layer + 1 == m.n_layers ? 0 : layer + 1;
         const LayerW& l = c->layers[layer];
-        a.W = which == G_QKV ? l.wqkv : which == G_O ? l.wo : which == G_UP ? l.wup : which == G_DOWN ? l.wdown : c->lm_head;
+        a.W = which == G_QKV ? l.wqkv : which == G_O ? l.wo : which == G_UP ? l.wup : which == G_DOWN ? (c->joined_out ? l.wo : l.wdown) : c->lm_head;
       };
       std::vector<float> total(cands.size(), 0.f);
       bool ok = true;
