@@ -108,7 +108,7 @@ template <int NV, bool WIDE>
 __global__ __launch_bounds__(256) void norm_kernel(const float* x, const int* row_index, int rows, int d, float eps,
                                                    const float* g1, const float* b1, uint16_t* out1,
                                                    const float* g2, const float* b2, uint16_t* out2,
-                                                   int out_rows, int out_row0, unsigned* status, size_t lo_off) {
+                                                   int out_rows, int out_row0, unsigned* status, size_t lo_off, NormParts parts) {
   constexpr int NW = WIDE ? 1 : 4;               // waves' shares this thread holds
   __shared__ float part[2][4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -142,6 +142,22 @@ __global__ __launch_bounds__(256) void norm_kernel(const float* x, const int* ro
       const int col = col_of(i, w);
       v[i][w] = col < d ? *(const f32x4*)(xr + col) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
+  if constexpr (WIDE) {
+    if (parts.ws) {
+      // the row is still waiting for a split product: its parts in their order, the bias, the residual (as the split
+      // product's own second pass adds them), and back to the residual stream
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int col = col_of(i, 0);
+        if (col >= d) continue;
+        f32x4 y = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int sp = 0; sp < parts.splits; ++sp) y += *(const f32x4*)(parts.ws + ((size_t)sp * rows + row) * d + col);
+        if (parts.bias) y += *(const f32x4*)(parts.bias + col);
+        v[i][0] += y;
+        *(f32x4*)(parts.x + (size_t)row * d + col) = v[i][0];
+      }
+    }
+  }
   const bool rms = (b1 == nullptr);
   float mean = 0.f;
   if (!rms) {
@@ -451,13 +467,14 @@ hipError_t rl_embed(float* x, const uint16_t* E, const int* tokens, const int* t
 }
 hipError_t rl_norm(const float* x, const int* row_index, int rows, int d, float eps, const float* g1, const float* b1,
                    uint16_t* out1, const float* g2, const float* b2, uint16_t* out2, int out_rows, int out_row0,
-                   unsigned* status, hipStream_t s, size_t lo_off) {
+                   unsigned* status, hipStream_t s, size_t lo_off, NormParts parts) {
   if (rows <= 0) return hipSuccess;
+  if (parts.ws && (row_index || parts.x != x)) return hipErrorInvalidValue;
   // up to four blocks of four waves per CU the rows are few enough for a block each; beyond, a wave each (see the kernel)
-  const bool wide = rows <= 1024;
+  const bool wide = rows <= NORM_WIDE_ROWS || parts.ws;
   const dim3 grid(wide ? rows : (rows + 3) / 4), block(256);
   const int nv = (d + 1023) / 1024;
-#define NORM_AS(NV, W) hipLaunchKernelGGL((norm_kernel<NV, W>), grid, block, 0, s, x, row_index, rows, d, eps, g1, b1, out1, g2, b2, out2, out_rows, out_row0, status, lo_off)
+#define NORM_AS(NV, W) hipLaunchKernelGGL((norm_kernel<NV, W>), grid, block, 0, s, x, row_index, rows, d, eps, g1, b1, out1, g2, b2, out2, out_rows, out_row0, status, lo_off, parts)
 #define NORM(NV) do { if (wide) NORM_AS(NV, true); else NORM_AS(NV, false); } while (0)
   if (nv <= 1) NORM(1);
   else if (nv <= 2) NORM(2);

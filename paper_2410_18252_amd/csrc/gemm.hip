@@ -1192,11 +1192,14 @@ hipError_t rl_gemm_skinny(const GemmArgs& g, int epi, hipStream_t s) {
 
 // Split-K: `splits` blocks per tile each take a share of K and write fp32 partial tiles to g.ws
 // ([splits, M, N]); a second kernel adds them in order and applies the epilogue.
+hipError_t rl_gemm_parts(const GemmArgs& g, int variant, hipStream_t s) {
+  if (g.splits < 2 || !g.ws || (size_t)g.splits * g.M * g.N > g.ws_elems) return hipErrorInvalidValue;      // the partial sums must fit
+  return rl_gemm_variant(g, EPI_PARTIAL, variant, s);
+}
 hipError_t rl_gemm_splitk(const GemmArgs& g, int epi, int variant, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
-  if (g.splits < 2 || !g.ws || (epi != EPI_F32 && epi != EPI_RESID && epi != EPI_GELU_F16)) return hipErrorInvalidValue;
-  if ((size_t)g.splits * g.M * g.N > g.ws_elems) return hipErrorInvalidValue;      // the partial sums must fit
-  hipError_t e = rl_gemm_variant(g, EPI_PARTIAL, variant, s);
+  if (epi != EPI_F32 && epi != EPI_RESID && epi != EPI_GELU_F16) return hipErrorInvalidValue;
+  hipError_t e = rl_gemm_parts(g, variant, s);
   if (e != hipSuccess) return e;
   const size_t n = (size_t)g.M * g.N;
   const dim3 grid((unsigned)((n + 255) / 256)), block(256);

@@ -95,6 +95,8 @@ hipError_t rl_gemm(const GemmArgs& g, int epi, hipStream_t s);
 hipError_t rl_gemm_variant(const GemmArgs& g, int epi, int variant, hipStream_t s);
 hipError_t rl_gemm_splitk(const GemmArgs& g, int epi, int variant, hipStream_t s);   // needs g.ws, g.splits >= 2
 
+// the first half of rl_gemm_splitk alone: the parts stay in g.ws
+hipError_t rl_gemm_parts(const GemmArgs& g, int variant, hipStream_t s);
 // Few rows: K divided among the SKINNY_WAVES waves of a block (K a multiple of 64, N of 16; not in precise mode).  Whether a
 // layer of a context with room for cap_rows rows takes this form follows from its shape: the sums' order is the form's.
 constexpr int SKINNY_WAVES = 8;
@@ -165,9 +167,13 @@ hipError_t rl_embed(float* x, const uint16_t* E, const int* tokens, const int* t
 // Outputs are K-block major matrices of out_rows rows; output row i goes to row out_row0 + i.
 // status (nullable): receives RLGEN_FAULT_RANGE if a normalised value does not fit fp16 (it is clamped).
 // lo_off > 0 (precise mode): outputs are bf16 hi/lo pairs, the lo halves lo_off elements behind the hi halves.
+// parts.ws: the rows first take up a split product that is still in parts (rl_gemm_parts: [splits, rows, d]) plus its bias and
+// are written back to parts.x = x; row_index must be null then.
+struct NormParts { const float* ws = nullptr; int splits = 0; const float* bias = nullptr; float* x = nullptr; };
+constexpr int NORM_WIDE_ROWS = 1024;       // up to here four waves share a row (see norm_kernel)
 hipError_t rl_norm(const float* x, const int* row_index, int rows, int d, float eps, const float* g1,
                    const float* b1, uint16_t* out1, const float* g2, const float* b2, uint16_t* out2,
-                   int out_rows, int out_row0, unsigned* status, hipStream_t s, size_t lo_off = 0);
+                   int out_rows, int out_row0, unsigned* status, hipStream_t s, size_t lo_off = 0, NormParts parts = NormParts{});
 
 // Rotary + KV write.  qkv fp32 [rows, (Hq + 2 Hkv) h] (bias already added) ->
 //   q fp16 [rows, Hq h] rotated; k (rotated) and v written as bf16 to the cache of `ncopy` consecutive cache
