@@ -50,15 +50,15 @@
 
 namespace {
 
-// SPLIT > 1 (decode): the waves of a block share one job, wave w taking the super-blocks w, w + SPLIT, ... of every segment; their
+// SPLIT > 1: the waves of a block share one job, wave w taking the super-blocks w, w + SPLIT, ... of every segment; their
 // maxima, sums and outputs meet in LDS and are added in the order of the waves.  For contexts whose batches cannot give every
 // CU several jobs: a wave's walk over its keys is a serial chain of loads and products, 2.8 us a super-block at head size 256.
 // QB = query blocks of 16 columns a wave carries through one pass over the keys (prompt pass only: two blocks halve
 // the key / value traffic per query; a.jobs then counts blocks of 16 QB tokens).
 template <int HD, bool DECODE, int QB = 1, bool PR = false, int SPLIT = 1>
-__global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= 128 && !PR) ? ATTN_PROMPT_BLOCKS : 1) void attention_kernel(AttnArgs a) {
+__global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= 128 && !PR && SPLIT == 1) ? ATTN_PROMPT_BLOCKS : 1) void attention_kernel(AttnArgs a) {
   static_assert(!DECODE || QB == 1, "decode has one query block");
-  static_assert(SPLIT == 1 || (DECODE && SPLIT >= 4), "only decode jobs are shared, by all waves of a block");
+  static_assert(SPLIT == 1 || SPLIT == 4 || (DECODE && SPLIT == 8), "a job is shared by all waves of a block");
   constexpr int NCH = HD / 8;            // 16-byte chunks per key row
   constexpr int KSTEPS = (HD + 31) / 32; // MFMA steps over head_dim for the scores
   constexpr int VT = HD / 16;            // 16-row tiles of V^T / O^T
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= 128
   // A wave number known to be common to the wave makes the job's addresses scalar.  Not for the two-block prompt pass: there
   // the compiler then keeps more in registers (181 instead of 162 at head size 80: two waves per SIMD instead of three; at
   // head size 64 109 -> 128 us), while wide heads gain (256: 163 -> 142 us).
-  const int wave = DECODE || HD >= 112 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : (int)(threadIdx.x >> 6);
+  const int wave = DECODE || HD >= 112 || SPLIT > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : (int)(threadIdx.x >> 6);
   const int c = lane & 15, g = lane >> 4;
   const int Hkv = a.lay.Hkv, G = a.Hq / Hkv;
   const int job = SPLIT > 1 ? blockIdx.x : blockIdx.x * 4 + wave;
@@ -377,6 +377,7 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= 128
         for (int w = 1; w < SPLIT; ++w) y += part[w][t][lane];
         if (store_col[b]) store(b, t, y * inv);
       }
+      if (b + 1 < QB) __syncthreads();             // the next query block takes the same place
     } else {
       const float inv = 1.0f / ls;
       if (store_col[b]) {
@@ -409,8 +410,8 @@ hipError_t launch_split(const AttnArgs& a, int jobs, hipStream_t s) {
   if constexpr (DECODE) {
     // (eight waves to a job leave a wave 256 registers: too few for the widest head and for precise mode)
     if (a.split >= 8 && HD <= 128 && !PR) return launch<HD, DECODE, QB, PR, (HD <= 128 && !PR) ? 8 : 4>(a, jobs, s);
-    if (a.split >= 4) return launch<HD, DECODE, QB, PR, 4>(a, jobs, s);
   }
+  if (a.split >= 4) return launch<HD, DECODE, QB, PR, 4>(a, jobs, s);
   return launch<HD, DECODE, QB, PR, 1>(a, jobs, s);
 }
 template <bool DECODE, int QB>
@@ -445,6 +446,12 @@ hipError_t rl_attention_decode(const AttnArgs& a, hipStream_t s) {
 int rl_attention_decode_split(long long cap_jobs, int h) {
   const long long size = cap_jobs * (h > 64 ? h : 64);
   return size <= 32768 ? 8 : size <= 131072 ? 4 : 1;
+}
+// The same for a prompt pass of at most cap_rows rows: up to four jobs a CU (654 rows of 8 heads of size 256: 57 ->
+// 21 us a layer).
+int rl_attention_prefill_split(int cap_rows, int Hq, int h) {
+  const long long jobs = (long long)((cap_rows + 15) / 16) * Hq / rl_attention_prefill_qb(h);
+  return jobs <= 1024 ? 4 : 1;
 }
 // a.jobs: 16-token blocks; every sequence must contribute a multiple of rl_attention_prefill_qb(h) of them (blocks
 // past its end are allowed), since a wave takes that many consecutive blocks

@@ -124,7 +124,7 @@ struct AttnArgs {
   // shared prompt cache: 0 = off.  K = samples per prompt: sequence s = prompt * K + j; cache sequence `prompt`
   // holds the prompt's keys (ctx_base[prompt * K] of them), cache sequence sfx_first + s the ctx_add new tokens of s
   int share_k, sfx_first;
-  int split;                          // waves that share a (sequence, kv head): rl_attention_decode_split of the context's capacity
+  int split;                          // waves that share a job: rl_attention_decode_split / _prefill_split of the context's capacity
   const int* cache_seq_of;            // nullable [S] (not with share_k): cache sequence of row i, default i (kv_off / kv_cap index)
   const int* finished;                // nullable [S]: sequences whose completion has ended are skipped (their output rows keep
                                       // whatever they held; nothing downstream of an ended sequence is used)
@@ -133,6 +133,7 @@ struct AttnArgs {
 };
 hipError_t rl_attention_decode(const AttnArgs& a, hipStream_t s);
 int rl_attention_decode_split(long long cap_jobs, int h);
+int rl_attention_prefill_split(int cap_rows, int Hq, int h);
 hipError_t rl_attention_prefill(const AttnArgs& a, hipStream_t s);
 // 16-token blocks a prompt-pass attention wave takes at once for head size h; a.jobs must list a multiple of it per sequence
 int rl_attention_prefill_qb(int h);

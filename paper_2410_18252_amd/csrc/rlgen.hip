@@ -516,7 +516,7 @@ int run_layers(rlgen_ctx* c, int rows, bool decode, int t, int ncopy, bool use_c
       HIPCHK(rl_attention_decode(a, st));
       if (e1) HIPCHK(hipEventRecord(e1, st));
     } else {
-      a.jobs = c->d_jobs; a.njobs = njobs;
+      a.jobs = c->d_jobs; a.njobs = njobs; a.split = rl_attention_prefill_split(c->R, m.n_q_heads, h);
       HIPCHK(rl_attention_prefill(a, st));
     }
     if (!c->joined_out) {
