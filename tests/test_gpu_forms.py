@@ -1,0 +1,149 @@
+"""GPU: the kernels' forms at the sizes where they can go wrong -- whole and ragged tiles of the matrix products with two to a
+few K steps, decode steps on either side of the rules that divide a product or an attention job inside a block, norms with a
+wave or a block to a row, and a joined output product whose K is not whole K blocks."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import decoder as O
+from workloads import ModelShape
+from gpu_util import (GPU_SHAPES, TOL_LOGITS, TOL_LOGPROB, R, dev_f32, dev_i32, make_policy, padded, reference_decoder,
+                      scaled_bf16_weights)
+
+pytestmark = pytest.mark.gpu
+
+# K = d: two, three and five K steps of 64; d_ffn + d: 8 to 15 (a ring of up to six stages fills and drains); widths that are
+# no multiple of a 64-, 128- or 256-column tile; the vocabulary odd
+TILES = {
+    "neox-d128": ModelShape(0, 1, 128, 2, 2, 64, 384, 515, rotary_dim=16),
+    "neox-d192": ModelShape(0, 1, 192, 4, 4, 48, 608, 333, rotary_dim=12),
+    "llama-d320": ModelShape(1, 1, 320, 4, 2, 80, 640, 700, rotary_dim=80, rope_theta=500000.0),
+}
+
+
+@pytest.mark.parametrize("precise", [0, 1])
+@pytest.mark.parametrize("name", list(TILES))
+def test_every_tile_shape_returns_the_same_bits_on_whole_and_ragged_tiles(name, precise):
+    """One chunk of 611 rows (two whole 256-row tiles and a ragged one) through every tile shape, forced on all layers of the
+    prompt pass: the same bits for all of them, and those within tolerance of the reference."""
+    m = TILES[name]
+    W = scaled_bf16_weights(m)
+    dec = reference_decoder(W, m, precise)
+    rng = np.random.default_rng(17)
+    seqs = [rng.integers(0, m.vocab, size=n) for n in (256, 1, 255, 99)]
+    arr, lens = padded(seqs)
+    r = R()
+    pol = make_policy(W, max_seqs=4, max_seq_len=256, max_batch_tokens=1024, precise=precise)
+    outs = []
+    try:
+        for v in [0, 3, 5, 7] if precise else range(11):
+            for which in range(5):
+                wide_only = which == 4 or (which == 2 and m.arch == 1)
+                r.rlgen_debug_set_gemm(pol, 1, which, 0 if wide_only and 6 <= v <= 9 else v)
+            outs.append((r.rlgen_score(pol, dev_i32(arr), lens, 0.7).cpu(), r.rlgen_debug_logits(pol, dev_i32(arr), lens).cpu()))
+        assert r.rlgen_status(pol) == 0
+    finally:
+        pol.close()
+    for o in outs[1:]:
+        assert torch.equal(o[0], outs[0][0]) and torch.equal(o[1], outs[0][1])
+    ref = np.stack([O.last_logits(dec, s) for s in seqs])
+    assert np.abs(outs[0][1].numpy() - ref).max() < (TOL_LOGITS / 20 if precise else TOL_LOGITS)
+    for n in (0, 3):
+        assert np.abs(outs[0][0][n, :lens[n]].numpy() - O.score(dec, seqs[n], 0.7)).max() < TOL_LOGPROB
+
+
+# capacities on either side of the rules: products divide K inside a block up to 16 sequences, and up to 128 where little is
+# fetched; decode attention shares a job among eight or four waves while capacity x kv heads x max(head size, 64) is at most
+# 32768 or 131072
+@pytest.mark.parametrize("max_seqs", [6, 17, 128, 129, 300, 2100])
+@pytest.mark.parametrize("name", ["neox-h16-raggedV", "neox-h80", "neox-h256", "llama-gqa4-h16", "llama-gqa2-h128"])
+def test_decode_forms_match_the_reference(name, max_seqs):
+    m = GPU_SHAPES[name]
+    W = scaled_bf16_weights(m)
+    dec = reference_decoder(W, m)
+    rng = np.random.default_rng(23)
+    lens = [1, 31, 32, 33, 97, 150]
+    arr, lens = padded([rng.integers(0, m.vocab, size=n) for n in lens])
+    T = 5
+    forced = rng.integers(0, m.vocab, size=(6, 1, T)).astype(np.int32)
+    r = R()
+    pol = make_policy(W, max_seqs=max_seqs, max_seq_len=160, max_kv_tokens=max(6 * 160, 32 * max_seqs), max_batch_tokens=160)
+    try:
+        u = dev_f32(np.zeros((6, 1, T)))
+        _, lp = r.rlgen_generate(pol, dev_i32(arr), lens, 1, T, 0.7, u, dev_i32(forced))
+        # a smaller batch of the same context takes its sums in the same order
+        _, one = r.rlgen_generate(pol, dev_i32(arr[4:5]), lens[4:5], 1, T, 0.7, u[:1].contiguous(), dev_i32(forced[4:5]))
+        assert r.rlgen_status(pol) == 0
+        assert torch.equal(one[0], lp[4])
+        lp = lp.cpu().numpy()
+    finally:
+        pol.close()
+    for b in range(6):
+        want = O.score(dec, np.concatenate([arr[b, :lens[b]], forced[b, 0]]), 0.7, score_from=int(lens[b]))[lens[b]:]
+        assert np.abs(lp[b, 0] - want).max() < TOL_LOGPROB
+
+
+def test_norms_return_the_same_bits_with_a_wave_or_a_block_to_a_row():
+    """A sequence scored on its own (few rows: a block to each) and among others (1100 rows: a wave to each)."""
+    m = GPU_SHAPES["neox-h80"]
+    W = scaled_bf16_weights(m)
+    rng = np.random.default_rng(29)
+    arr, lens = padded([rng.integers(0, m.vocab, size=n) for n in [100] * 10 + [37, 63]])
+    r = R()
+    pol = make_policy(W, max_seqs=12, max_seq_len=100, max_batch_tokens=1200)
+    try:
+        many = r.rlgen_score(pol, dev_i32(arr), lens, 1.0)
+        one = r.rlgen_score(pol, dev_i32(arr[10:11]), lens[10:11], 1.0)
+        assert torch.equal(many[10, :37], one[0, :37])
+    finally:
+        pol.close()
+
+
+@pytest.mark.parametrize("precise", [0, 1])
+def test_joined_output_product_with_half_a_k_block(precise):
+    """d_ffn % 64 = 32: the joined attention-output and FFN-down product ends on half a K block."""
+    m = ModelShape(0, 2, 64, 4, 4, 16, 160, 200, rotary_dim=4)
+    W = scaled_bf16_weights(m)
+    dec = reference_decoder(W, m, precise)
+    rng = np.random.default_rng(37)
+    seqs = [rng.integers(0, m.vocab, size=n) for n in (5, 64, 33)]
+    arr, lens = padded(seqs)
+    r = R()
+    pol = make_policy(W, max_seqs=3, max_seq_len=70, precise=precise)
+    try:
+        z = r.rlgen_debug_logits(pol, dev_i32(arr), lens).cpu().numpy()
+        forced = rng.integers(0, m.vocab, size=(3, 1, 4)).astype(np.int32)
+        _, lp = r.rlgen_generate(pol, dev_i32(arr), lens, 1, 4, 1.0, dev_f32(np.zeros((3, 1, 4))), dev_i32(forced))
+        lp = lp.cpu().numpy()
+        assert r.rlgen_status(pol) == 0
+    finally:
+        pol.close()
+    assert np.abs(z - np.stack([O.last_logits(dec, s) for s in seqs])).max() < (TOL_LOGITS / 20 if precise else TOL_LOGITS)
+    for b in range(3):
+        want = O.score(dec, np.concatenate([seqs[b], forced[b, 0]]), 1.0, score_from=len(seqs[b]))[len(seqs[b]):]
+        assert np.abs(lp[b, 0] - want).max() < TOL_LOGPROB
+
+
+@pytest.mark.parametrize("V", [63, 131072, 131073, 200001])
+def test_sampler_draws_in_order_at_any_vocabulary(V):
+    """Up to 131072 columns a thread holds its run of column groups in registers, beyond it reads the rest again; 63 columns are
+    one group for 256 threads.  Every draw must lie in the reference's CDF bucket (up to the 1e-4 that the 16-bit rows move the
+    CDF by) and carry its log-prob."""
+    m = ModelShape(0, 1, 64, 4, 4, 16, 64, V, rotary_dim=4)
+    W = scaled_bf16_weights(m, scale=4.0)
+    dec = O.Decoder(W, m, np.float64)
+    rng = np.random.default_rng(V)
+    hidden = rng.normal(size=(9, 64)).astype(np.float32)
+    u = np.array([0.0, 1e-6, 0.1, 0.3, 0.5, 0.7, 0.9, 0.999, 0.99999994], np.float32)
+    r = R()
+    pol = make_policy(W, max_seqs=9, max_seq_len=32)
+    try:
+        tok, lp = (x.cpu().numpy() for x in r.rlgen_debug_sample(pol, dev_f32(hidden), 0.7, dev_f32(u)))
+        assert r.rlgen_status(pol) == 0
+    finally:
+        pol.close()
+    logp = O.tempered_log_softmax(dec.logits(hidden.astype(np.float64)), 0.7)
+    for i in range(9):
+        lo, hi = O.cdf_bucket(logp[i], int(tok[i]))
+        assert lo - 1e-4 <= u[i] <= hi + 1e-4, (i, tok[i])
+        assert abs(lp[i] - logp[i, tok[i]]) < TOL_LOGPROB
