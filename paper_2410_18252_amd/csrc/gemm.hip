@@ -3,10 +3,13 @@
 // represents them exactly; activations are fp16, whose 11 significant bits keep the logits within
 // the parity bound where bf16 activations do not.)  Both operands are K-block major (see kblk_off), so a
 // block's tile is one contiguous run in memory and every MFMA operand fragment is one 16-byte LDS read.
-// A block of WM x WN waves owns a BM x BN tile; each wave a (BM/WM) x (BN/WN) sub-tile built from 32x32x16
+// A block of WM x WN waves owns a BM x BN tile; each wave a (BM/WM) x (BN/WN) sub-tile built from 16x16x32
 // MFMAs.  A and W tiles of depth 64 go from global memory straight into LDS (16-byte chunks, XOR-swizzled by
-// row so that fragment reads spread over all banks), two or four stages deep, with one barrier per K step;
-// a K that is not a multiple of 64 takes the older path through registers, which can zero-fill the tail.
+// row so that fragment reads spread over all banks).  Four main loops share the epilogues and the matrix instruction,
+// which walks K front to back in all of them: gemm_f16_kernel (two stages, one barrier per K step; a K that is not a
+// multiple of 64 takes its older path through registers, which can zero-fill the tail), gemm_big_kernel (256x256 on four
+// waves, for launches that fill the chip), gemm_ring_kernel (as many stages as LDS holds, for launches that do not) and
+// gemm_skinny_kernel (K divided among the waves of a block, for the fewest rows).
 #include "kernels.h"
 #include <algorithm>
 #include <type_traits>

@@ -744,10 +744,17 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
       } else if (splits == 1 && (long long)(g.M / 256) * (g.N / 256) >= 1024) {
         cands = {3, 10, 5};                       // four large tiles to every CU: the small ones cannot win
       } else {
-        cands = {0, 5, 2, 10};
-        if (splits == 1) cands.push_back(3);
+        cands = {0, 2};
+        if (g.M > 128) {                          // 256 rows to a tile would be half padding below
+          cands.push_back(5); cands.push_back(10);
+          if (splits == 1) cands.push_back(3);
+        }
         if (mode == 2 && splits == 1) { cands.push_back(1); cands.push_back(4); }     // beside attention other shapes can win
-        if (!wide_only) { cands.push_back(7); cands.push_back(6); cands.push_back(8); cands.push_back(9); }
+        if (!wide_only) {
+          cands.push_back(7);
+          // the small rings are for launches that leave CUs short of blocks
+          if ((long long)((g.M + 63) / 64) * ((g.N + 127) / 128) < 2048) { cands.push_back(6); cands.push_back(8); cands.push_back(9); }
+        }
       }
       // clocks drift with load, so the candidates take turns: one warm-up each, then three rounds in which
       // every candidate is timed over two launches; the smallest total wins
