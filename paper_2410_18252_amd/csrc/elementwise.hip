@@ -102,7 +102,7 @@ __global__ void embed_kernel(float* x, const uint16_t* E, const int* tokens, con
 // t, t + 256, ...; otherwise a wave holds a row and lane l the pieces the lanes l of those four waves would hold, with one
 // sum for each of the four, so that both forms add in the same order and return the same bits.
 // A decode step's norms are bound by latency, not by bytes: one wave per row leaves most CUs empty and chains ten loads
-// (2.8B width, 128 rows: 10.4 us against 4.4 with four waves to a row); from a few thousand rows on the one-wave form is at
+// (64 rows at d = 2560: 11.4 us, 4.9 with four waves to a row); from a few thousand rows on the one-wave form is at
 // the rate of memory and does without the barriers.  NV: 16-byte pieces per thread of the wide form.
 template <int NV, bool WIDE>
 __global__ __launch_bounds__(256) void norm_kernel(const float* x, const int* row_index, int rows, int d, float eps,
