@@ -264,11 +264,13 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
     if constexpr (!PR) flag_f16_range(sat, g.status);
   } else {
     // The place of (i, j) is a distance common to the wave plus one 32-bit distance of the lane: a scalar base and one
-    // register address every access.  Column tiles outside, so that a bias is read once.
+    // register address every access (the rows of plain fp32 outputs are as long as a vocabulary: 64 bits there).  Column
+    // tiles outside, so that a bias is read once.
     [[maybe_unused]] bool sat = false;
     constexpr bool F32OUT = EPI == EPI_F32 || EPI == EPI_RESID || EPI == EPI_PARTIAL;
     const int ld = EPI == EPI_PARTIAL ? g.N : g.ldo;
-    const uint32_t lane_off = F32OUT ? (uint32_t)(frow * ld + 4 * fq) * 4 : (uint32_t)(frow * 64 + 4 * fq) * 2;
+    using lane_t = std::conditional_t<EPI == EPI_F32, size_t, uint32_t>;
+    const lane_t lane_off = F32OUT ? ((lane_t)frow * ld + 4 * fq) * 4 : (lane_t)(frow * 64 + 4 * fq) * 2;
     auto place = [&](int i, int j) -> char* {
       const size_t row = wrow0 + i * 16;
       // first output column of the tile (SwiGLU: weight rows come in blocks of 32, gates and then the matching ups)
@@ -629,7 +631,10 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmArgs g) {
   const size_t ka = (size_t)g.M * 128, kw = (size_t)g.N * 128;    // bytes between K blocks
   // A wave instruction moves 64 16-byte chunks = 8 rows into 1 KB of LDS in lane order; a wave fills 32 of a half tile's
   // 128 rows.  Row r of half h is row 128 (r / 64) + 64 h + r % 64 of the tile: 64 rows for each of the two waves that
-  // share the operand.  The XOR swizzle is applied on the source side.
+  // share the operand.  The XOR swizzle is applied on the source side.  The tile's first row is part of the 64-bit base, so that
+  // the 32-bit distances stay inside the tile (a matrix of 2^24 rows has 2 GiB to a K block).
+  const char* const a0 = (const char*)g.A + (size_t)row0 * 128;
+  const char* const w0 = (const char*)g.W + (size_t)col0 * 128;
   uint32_t va[2][4], vb[2][4];
 #pragma unroll
   for (int h = 0; h < 2; ++h)
@@ -638,18 +643,18 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmArgs g) {
       const int r = wave * 32 + i * 8 + (lane >> 3);
       const int chunk = (lane & 7) ^ swz(r);
       const int t = (r >> 6) * 128 + h * 64 + (r & 63);
-      va[h][i] = (uint32_t)min(row0 + t, g.M - 1) * 128 + chunk * 16;
-      vb[h][i] = (uint32_t)min(col0 + t, g.N - 1) * 128 + chunk * 16;
+      va[h][i] = (uint32_t)min(t, g.M - 1 - row0) * 128 + chunk * 16;
+      vb[h][i] = (uint32_t)min(t, g.N - 1 - col0) * 128 + chunk * 16;
     }
   typedef __attribute__((address_space(3))) void* lptr_t;
   // request i (of 4) of half h of K step kt
   auto load_a = [&](int kt, int h, int i) {
-    const char* base = (const char*)g.A + (size_t)(PR ? (kt >> 1) + (kt & 1) * nkb : kt) * ka;
+    const char* base = a0 + (size_t)(PR ? (kt >> 1) + (kt & 1) * nkb : kt) * ka;
     uint16_t* dst = lds + (kt & 1) * STAGE + h * HALF + wave * 32 * BK + i * 8 * BK;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0x7fffffff, 0x00027000), (lptr_t)dst, 16, va[h][i], 0, 0, 0);
   };
   auto load_b = [&](int kt, int h, int i) {
-    const char* base = (const char*)g.W + (size_t)(PR ? kt >> 1 : kt) * kw;
+    const char* base = w0 + (size_t)(PR ? kt >> 1 : kt) * kw;
     uint16_t* dst = lds + (kt & 1) * STAGE + (2 + h) * HALF + wave * 32 * BK + i * 8 * BK;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0x7fffffff, 0x00027000), (lptr_t)dst, 16, vb[h][i], 0, 0, 0);
   };
@@ -759,23 +764,25 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_ring_kernel(GemmArgs g) {
   const int kt0 = (int)((long long)split * nk_all / splits);
   const int nk = (int)((long long)(split + 1) * nk_all / splits) - kt0;       // this block's K steps
   const size_t ka = (size_t)g.M * 128, kw = (size_t)g.N * 128;
+  const char* const a0 = (const char*)g.A + (size_t)row0 * 128;      // 32-bit distances stay inside the tile
+  const char* const w0 = (const char*)g.W + (size_t)col0 * 128;
   uint32_t va[LA], vb[LB];
 #pragma unroll
   for (int i = 0; i < LA; ++i) {
     const int r = (wave * LA + i) * 8 + (lane >> 3);
-    va[i] = (uint32_t)min(row0 + r, g.M - 1) * 128 + ((lane & 7) ^ swz(r)) * 16;
+    va[i] = (uint32_t)min(r, g.M - 1 - row0) * 128 + ((lane & 7) ^ swz(r)) * 16;
   }
 #pragma unroll
   for (int i = 0; i < LB; ++i) {
     const int r = (wave * LB + i) * 8 + (lane >> 3);
-    vb[i] = (uint32_t)min(col0 + r, g.N - 1) * 128 + ((lane & 7) ^ swz(r)) * 16;
+    vb[i] = (uint32_t)min(r, g.N - 1 - col0) * 128 + ((lane & 7) ^ swz(r)) * 16;
   }
   typedef __attribute__((address_space(3))) void* lptr_t;
   // request n of stage kt (counted from kt0) into slot s: first the rows of A, then those of W
   auto request = [&](int kt, int s, int n) {
     kt += kt0;
     const bool is_a = n < LA;
-    const char* base = is_a ? (const char*)g.A + (size_t)(PR ? (kt >> 1) + (kt & 1) * nkb : kt) * ka : (const char*)g.W + (size_t)(PR ? kt >> 1 : kt) * kw;
+    const char* base = is_a ? a0 + (size_t)(PR ? (kt >> 1) + (kt & 1) * nkb : kt) * ka : w0 + (size_t)(PR ? kt >> 1 : kt) * kw;
     uint16_t* dst = lds + s * STAGE + (is_a ? wave * LA + n : BM / 8 + wave * LB + n - LA) * 8 * BK;
     const uint32_t off = is_a ? va[is_a ? n : 0] : vb[is_a ? 0 : n - LA];
     __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0x7fffffff, 0x00027000), (lptr_t)dst, 16, off, 0, 0, 0);
@@ -878,17 +885,19 @@ __global__ __launch_bounds__(SKINNY_WAVES * 64) void gemm_skinny_kernel(GemmArgs
   tile_of_block(tiles_m, tiles_n, 1, tile_m, tile_n, split);
   const int row0 = tile_m * 16 * TM, col0 = tile_n * 16 * TN;
   const int frow = lane & 15, fq = lane >> 4;
+  const char* const a0 = (const char*)g.A + (size_t)row0 * 128;      // 32-bit distances stay inside the tile
+  const char* const w0 = (const char*)g.W + (size_t)col0 * 128;
   uint32_t va[TM], vb[TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) va[i] = (uint32_t)min(row0 + i * 16 + frow, g.M - 1) * 128 + fq * 16;
+  for (int i = 0; i < TM; ++i) va[i] = (uint32_t)min(i * 16 + frow, g.M - 1 - row0) * 128 + fq * 16;
 #pragma unroll
-  for (int j = 0; j < TN; ++j) vb[j] = (uint32_t)min(col0 + j * 16 + frow, g.N - 1) * 128 + fq * 16;
+  for (int j = 0; j < TN; ++j) vb[j] = (uint32_t)min(j * 16 + frow, g.N - 1 - col0) * 128 + fq * 16;
   const size_t ka = (size_t)g.M * 128, kw = (size_t)g.N * 128;
   const int nkb = g.K / BK;
   f16x8 fa[2][TM][2], fb[2][TN][2];
   auto load = [&](int kb, int slot) {
-    const char* a = (const char*)g.A + (size_t)kb * ka;
-    const char* w = (const char*)g.W + (size_t)kb * kw;
+    const char* a = a0 + (size_t)kb * ka;
+    const char* w = w0 + (size_t)kb * kw;
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll

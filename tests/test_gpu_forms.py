@@ -147,3 +147,47 @@ def test_sampler_draws_in_order_at_any_vocabulary(V):
         lo, hi = O.cdf_bucket(logp[i], int(tok[i]))
         assert lo - 1e-4 <= u[i] <= hi + 1e-4, (i, tok[i])
         assert abs(lp[i] - logp[i, tok[i]]) < TOL_LOGPROB
+
+
+def test_a_vocabulary_beyond_two_to_the_24():
+    """A weight row of 64 K values is 128 bytes: from row 2^24 on a K block's rows lie past the 2 GiB that a 32-bit distance with a
+    buffer's bounds reaches.  The LM head repeats with a period that divides no power of two, the rows from 2^24 on sixteen
+    times as large (exact in fp16 and fp32), so every logit is known from those of the first period bit for bit, and the last
+    columns decide log Z: every tile shape must return the log-probs that the logits give, and the same bits."""
+    r = R()
+    V, P, d = (1 << 24) + 777, 4099, 128
+    m = ModelShape(0, 1, d, 2, 2, 64, 128, V, rotary_dim=16)
+    small = scaled_bf16_weights(ModelShape(0, 1, d, 2, 2, 64, 128, P, rotary_dim=16), scale=2.5)
+    dev = r.upload_weights(small.tensors)
+    scale = torch.ones(V, 1, dtype=torch.bfloat16, device="cuda")
+    scale[1 << 24:] = 16.0
+    head = ((dev["lm_head"].float() * 64).round() / 64).to(torch.bfloat16)       # no value is subnormal in fp16
+    dev["lm_head"] = head.repeat((V + P - 1) // P, 1)[:V] * scale
+    dev["embed_in"] = dev["embed_in"].repeat((V + P - 1) // P, 1)[:V].contiguous()
+    rng = np.random.default_rng(3)
+    seqs = rng.integers(0, V, size=(3, 9)).astype(np.int32)
+    seqs[:, -1] = (5, V - 1, (1 << 24) + 3)
+    lens = [9, 9, 9]
+    cfg = r.make_cfg(m, weight_dtype=r.DTYPE_BF16, max_seqs=3, max_seq_len=32, max_kv_tokens=96)
+    pol = r.Policy(cfg, dev)
+    del dev
+    try:
+        z = r.rlgen_debug_logits(pol, dev_i32(seqs), [8, 8, 8])
+        want = torch.cat([z[:, :P].repeat(1, (V + P - 1) // P)[:, :1 << 24],
+                          16 * z[:, torch.arange(1 << 24, V, device="cuda") % P]], dim=1)
+        assert torch.equal(z, want)
+        want_lp = torch.log_softmax(z.double() / 0.7, dim=1)[torch.arange(3), torch.from_numpy(seqs[:, -1]).cuda().long()]
+        hidden = dev_f32(rng.normal(size=(3, d)))
+        u = dev_f32(np.array([0.1, 0.5, 0.9]))
+        outs = []
+        for v in (0, 1, 2, 3, 4, 5, 10):
+            for mode in (0, 1):
+                r.rlgen_debug_set_gemm(pol, mode, 4, v)
+            score = r.rlgen_score(pol, dev_i32(seqs), lens, 0.7)
+            assert (score[:, -1].double() - want_lp).abs().max() < 1e-4, v       # fp32 sums of the same logits
+            outs.append((score, *r.rlgen_debug_sample(pol, hidden, 0.7, u)))
+        for o in outs[1:]:
+            assert all(torch.equal(a, b) for a, b in zip(o, outs[0])), o
+        assert r.rlgen_status(pol) == 0
+    finally:
+        pol.close()
