@@ -59,11 +59,18 @@ __device__ __forceinline__ float gelu_erf(float v) {
   return fmaf(fabsf(h), r, h);
 }
 __device__ __forceinline__ float silu(float v) { return v * __builtin_amdgcn_rcpf(1.0f + __expf(-v)); }
-// v / t for one divisor t and its reciprocal: the quotient with its residual folded back in
+// v / t for one divisor t >= 2^-60 and its reciprocal: the quotient with its residual folded back in (equal to v / t on a million
+// random pairs; 3 instructions where a division takes 11).  An infinite quotient would turn into NaN there; INF: kept below
+// infinity until the residual is added, which then restores it.
+template <bool INF>
 __device__ __forceinline__ float div_by(float v, float t, float inv_t) {
-  const float q = v * inv_t;
+  const float q = INF ? __builtin_amdgcn_fmed3f(v * inv_t, -3.402823466e38f, 3.402823466e38f) : v * inv_t;
   return fmaf(fmaf(-q, t, v), inv_t, q);
 }
+// Temperatures below are divided by as they stand, in kernels of their own (EPI_LMHEAD_EXACT).  Above, the logits of the default
+// formats (at most 65504^2 x 8192 < 2^46) have finite quotients; those of precise mode, whose operands have fp32's range, may
+// overflow (a test of every value costs the default formats 3 % of the sampling stage: 64 rows at 2.8B width 75.6 -> 78.1 us).
+constexpr float MIN_FAST_TEMPERATURE = 0x1p-60f;
 
 template <int N>
 __device__ __forceinline__ void wait_loads_then_barrier() {
@@ -84,11 +91,13 @@ __device__ __forceinline__ void wait_loads_then_barrier() {
 template <int TM, int TN, int EPI, bool PR, bool FULL, bool STAGED>
 __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 (&acc)[TM][TN], int wrow0, int wcol0, int lane, int split) {
   const int frow = lane & 15, fq = lane >> 4;
-  if constexpr (EPI == EPI_LMHEAD) {
+  if constexpr (EPI == EPI_LMHEAD || EPI == EPI_LMHEAD_EXACT) {
     // per row and per 64-column group: max and sum of exp of the tempered logits; optional capture
     // of the target column's tempered logit.  Nothing of size [M, N] is written.
     static_assert(TN % 4 == 0, "a wave must own whole 64-column groups");
     const int ngroups = (g.N + 63) >> 6;
+    constexpr bool EXACT = EPI == EPI_LMHEAD_EXACT;
+    constexpr bool INF = EXACT || PR || !FULL;           // logits, and then whole groups of them, may be -inf
     const float inv_t = 1.0f / g.temperature;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
@@ -104,7 +113,8 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const int col = wcol0 + (4 * gi + jj) * 16 + 4 * fq + r;
-            const float v = FULL || col < g.N ? div_by(acc[i][4 * gi + jj][r], g.temperature, inv_t) : -INFINITY;
+            const float a = acc[i][4 * gi + jj][r];
+            const float v = !FULL && col >= g.N ? -INFINITY : EXACT ? a / g.temperature : div_by<PR>(a, g.temperature, inv_t);
             l[jj * 4 + r] = v;
             mx = fmaxf(mx, v);
             if (col == tgt) g.target_logit[row] = v;
@@ -113,7 +123,7 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
         mx = fmaxf(mx, __shfl_xor(mx, 32, WAVE));
         float sum = 0.f;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) sum += (!FULL && l[e] == -INFINITY) ? 0.f : __expf(l[e] - mx);
+        for (int e = 0; e < 16; ++e) sum += (INF && l[e] == -INFINITY) ? 0.f : __expf(l[e] - mx);
         sum += __shfl_xor(sum, 16, WAVE);
         sum += __shfl_xor(sum, 32, WAVE);
         if (fq == 0 && (FULL || (row < g.M && group < ngroups))) g.partial[(size_t)row * ngroups + group] = make_float2(mx, sum);
@@ -1174,7 +1184,10 @@ hipError_t rl_gemm_variant(const GemmArgs& g, int epi, int variant, hipStream_t 
     case EPI_SWIGLU_F16:
       if (g.N % 64 != 0) return hipErrorInvalidValue;
       return launch_variant<EPI_SWIGLU_F16>(g, variant, s);
-    case EPI_LMHEAD: return launch_variant<EPI_LMHEAD>(g, variant, s);
+    case EPI_LMHEAD:
+      if (!(g.temperature >= MIN_FAST_TEMPERATURE))
+        return g.precise ? launch<128, 128, 2, 2, EPI_LMHEAD_EXACT, 2, true>(g, s) : launch<128, 128, 2, 2, EPI_LMHEAD_EXACT>(g, s);
+      return launch_variant<EPI_LMHEAD>(g, variant, s);
     case EPI_PARTIAL: return launch_variant<EPI_PARTIAL>(g, variant, s);
     case EPI_QKV: {
       return valid_qkv(g) ? launch_variant<EPI_QKV>(g, variant, s) : hipErrorInvalidValue;

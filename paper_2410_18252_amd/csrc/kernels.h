@@ -34,7 +34,8 @@ struct KvLayout {
 };
 
 // ------------------------------------------------------------------ GEMM
-enum { EPI_F32 = 0, EPI_RESID = 1, EPI_GELU_F16 = 2, EPI_SWIGLU_F16 = 3, EPI_LMHEAD = 4, EPI_PARTIAL = 5, EPI_QKV = 6 };
+enum { EPI_F32 = 0, EPI_RESID = 1, EPI_GELU_F16 = 2, EPI_SWIGLU_F16 = 3, EPI_LMHEAD = 4, EPI_PARTIAL = 5, EPI_QKV = 6,
+       EPI_LMHEAD_EXACT = 7 };      // EPI_LMHEAD at temperatures near the end of fp32's range, chosen inside rl_gemm_variant
 
 // Epilogue of the fused QKV projection (EPI_QKV): bias, rotary embedding and the writes of q (fp16) and of k, v
 // (bf16, into the cache) happen on the accumulators.  For that the weight rows of every query and key head are

@@ -191,3 +191,31 @@ def test_a_vocabulary_beyond_two_to_the_24():
         assert r.rlgen_status(pol) == 0
     finally:
         pol.close()
+
+
+@pytest.mark.parametrize("temperature,precise", [(0.7, 1), (1e-38, 0), (1e-38, 1), (1e-40, 0), (1e-40, 1)])
+def test_lm_head_statistics_with_infinite_logits(temperature, precise):
+    """Logits of -infinity (a precise-mode weight row whose product overflows, or any negative logit over a tiny temperature)
+    have probability zero, also where they fill whole groups of 64 columns and whole tiles.  Columns 37 and 700 have logit 0, and
+    a row's draw is one of the two at log-prob -log 2."""
+    from workloads import f32_to_bf16_bits
+    r = R()
+    V, d, rows = 1000, 64, 300
+    m = ModelShape(0, 1, d, 4, 4, 16, 64, V, rotary_dim=4)
+    W = scaled_bf16_weights(m)
+    low = -3e38 if temperature > 0.1 else -0.05
+    head = np.full((V, d), low, np.float32)
+    head[[37, 700]] = 0.0
+    W.tensors.update({"final_norm_g": f32_to_bf16_bits(np.full(d, 0.1, np.float32)),
+                      "final_norm_b": f32_to_bf16_bits(np.full(d, 3.0, np.float32)), "lm_head": f32_to_bf16_bits(head)})
+    rng = np.random.default_rng(5)
+    u = rng.random(rows, dtype=np.float32)
+    pol = make_policy(W, max_seqs=rows, max_seq_len=32, precise=precise)
+    try:
+        for v in (0, 3, 5) if precise else (0, 1, 2, 3, 4, 5, 10):
+            r.rlgen_debug_set_gemm(pol, 0, 4, v)
+            tok, lp = (x.cpu().numpy() for x in r.rlgen_debug_sample(pol, dev_f32(rng.normal(size=(rows, d))), temperature, dev_f32(u)))
+            np.testing.assert_array_equal(tok, np.where(u < 0.5, 37, 700), err_msg=str(v))
+            assert np.abs(lp + np.log(2.0)).max() < 1e-6, v
+    finally:
+        pol.close()
