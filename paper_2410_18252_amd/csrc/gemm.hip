@@ -49,16 +49,26 @@ __device__ __forceinline__ void tile_of_block(int tiles_m, int tiles_n, int spli
 
 // gelu(v) = v/2 (1 + erf(v / sqrt 2)) = v/2 + |v|/2 erf(|v| / sqrt 2), with erf by the rational-exponential form of Abramowitz &
 // Stegun 7.1.26 (absolute error < 1.5e-7, far below the 16-bit rounding of the result).  The epilogue of the widest layer is
-// bound by this arithmetic: 15 instructions and two transcendentals a value, sqrt 2 and log2 e folded into the constants.
+// bound by this arithmetic: 17 instructions and two transcendentals a value, sqrt 2 and log2 e folded into the constants, the
+// hardware's reciprocal (1 ulp) corrected once.  Against 64 bits on [-4, 4] at most 3.8e-7 off, and 1.2e-7 in the mean square.
 __device__ __forceinline__ float gelu_erf(float v) {
-  const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752f, fabsf(v), 1.0f));
+  const float b = fmaf(0.3275911f * 0.70710678118654752f, fabsf(v), 1.0f);
+  const float t0 = __builtin_amdgcn_rcpf(b), t = fmaf(fmaf(-b, t0, 1.0f), t0, t0);
   const float poly = t * (0.254829592f + t * (-0.284496736f + t * (1.421413741f + t * (-1.453152027f + t * 1.061405429f))));
   const float z = v * 0.84932180028801907f;                   // sqrt(log2(e) / 2) v
   const float r = fmaf(-poly, __builtin_amdgcn_exp2f(-z * z), 1.0f);
   const float h = 0.5f * v;
   return fmaf(fabsf(h), r, h);
 }
-__device__ __forceinline__ float silu(float v) { return v * __builtin_amdgcn_rcpf(1.0f + __expf(-v)); }
+// v / (1 + exp(-v)), the division by a reciprocal with its residual folded back in; an eighth of both keeps the reciprocal in
+// fp32's normal range, and the fix-up sets what the residual cannot (infinite operands).  The values are those of a true division
+// (four million random arguments on [-90, 90]): at most 3.5e-7 from 64 bits on [-4, 4], where the bare reciprocal is up to 4.9e-7
+// off.  Over that one it costs 0.5 % of a generate call at the 8B shape, the true division 0.8 %.
+__device__ __forceinline__ float silu(float v) {
+  const float w = 0.125f * v, b = fmaf(__expf(-v), 0.125f, 0.125f);
+  const float y = __builtin_amdgcn_rcpf(b), q = w * y;
+  return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-q, b, w), y, q), b, w);
+}
 // v / t for one divisor t >= 2^-60 and its reciprocal: the quotient with its residual folded back in (equal to v / t on a million
 // random pairs; 3 instructions where a division takes 11).  An infinite quotient would turn into NaN there; INF: kept below
 // infinity until the residual is added, which then restores it.

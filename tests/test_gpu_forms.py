@@ -219,3 +219,34 @@ def test_lm_head_statistics_with_infinite_logits(temperature, precise):
             assert np.abs(lp + np.log(2.0)).max() < 1e-6, v
     finally:
         pol.close()
+
+
+@pytest.mark.parametrize("precise", [0, 1])
+def test_swiglu_at_large_gates(precise):
+    """Gates from where exp(-gate) overflows to where it vanishes.  Every token embeds to ones, attention adds nothing, gate f is
+    the f-th value and its activation, scaled to order one, reaches residual f, which the LM head reads out."""
+    from workloads import f32_to_bf16_bits
+    gates = [-6e4, -1e3, -103.5, -89.0, -88.5, -88.0, -87.0, -40.0, -9.0, -1.0, -0.01, 0.0, 0.01, 1.0, 9.0, 40.0, 88.5, 1e3, 6e4]
+    d, F = 64, 32
+    m = ModelShape(1, 1, d, 4, 2, 16, F, d, rotary_dim=16)
+    W = scaled_bf16_weights(m)
+    g = np.zeros(F, np.float32)
+    g[:len(gates)] = gates
+    down = np.zeros((d, F), np.float32)
+    down[np.arange(F), np.arange(F)] = 1.0 / np.maximum(np.abs(g), 0.25)
+    ones = f32_to_bf16_bits(np.ones(d, np.float32))
+    W.tensors.update({"embed_in": f32_to_bf16_bits(np.ones((d, d), np.float32)), "lm_head": f32_to_bf16_bits(4 * np.eye(d, dtype=np.float32)),
+                      "layers.0.wo": f32_to_bf16_bits(np.zeros((d, d), np.float32)), "layers.0.norm2_g": ones, "final_norm_g": ones,
+                      "layers.0.w_gate": f32_to_bf16_bits(np.repeat(g[:, None] / d, d, 1)),
+                      "layers.0.w_up": f32_to_bf16_bits(np.full((F, d), 1.0 / d, np.float32)), "layers.0.w_down": f32_to_bf16_bits(down)})
+    dec = reference_decoder(W, m, precise)
+    r = R()
+    pol = make_policy(W, max_seqs=2, max_seq_len=32, precise=precise)
+    try:
+        z = r.rlgen_debug_logits(pol, dev_i32(np.array([[1, 2, 3]])), [3]).cpu().numpy()
+        assert r.rlgen_status(pol) == 0
+    finally:
+        pol.close()
+    with np.errstate(over="ignore"):
+        want = O.last_logits(dec, np.array([1, 2, 3]))
+    assert np.abs(z[0] - want).max() < (TOL_LOGITS / 20 if precise else TOL_LOGITS)
