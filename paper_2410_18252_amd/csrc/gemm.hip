@@ -1228,7 +1228,9 @@ hipError_t rl_gemm_skinny(const GemmArgs& g, int epi, hipStream_t s) {
 // Split-K: `splits` blocks per tile each take a share of K and write fp32 partial tiles to g.ws
 // ([splits, M, N]); a second kernel adds them in order and applies the epilogue.
 hipError_t rl_gemm_parts(const GemmArgs& g, int variant, hipStream_t s) {
-  if (g.splits < 2 || !g.ws || (size_t)g.splits * g.M * g.N > g.ws_elems) return hipErrorInvalidValue;      // the partial sums must fit
+  // the partial sums must fit, and every part must have a K tile: the two-stage loop takes its last one without asking
+  if (g.splits < 2 || !g.ws || (size_t)g.splits * g.M * g.N > g.ws_elems) return hipErrorInvalidValue;
+  if (g.splits > (g.K + BK - 1) / BK * (g.precise ? 2 : 1)) return hipErrorInvalidValue;
   return rl_gemm_variant(g, EPI_PARTIAL, variant, s);
 }
 hipError_t rl_gemm_splitk(const GemmArgs& g, int epi, int variant, hipStream_t s) {

@@ -94,7 +94,8 @@ struct GemmArgs {
 hipError_t rl_gemm(const GemmArgs& g, int epi, hipStream_t s);
 // the same with an explicit tile shape (tuning and tests): 0 = 128x128, 1 = 256x128, 2 = 256x256, ...
 hipError_t rl_gemm_variant(const GemmArgs& g, int epi, int variant, hipStream_t s);
-hipError_t rl_gemm_splitk(const GemmArgs& g, int epi, int variant, hipStream_t s);   // needs g.ws, g.splits >= 2
+// needs g.ws and 2 <= g.splits <= K tiles of 64 (precise mode: twice as many)
+hipError_t rl_gemm_splitk(const GemmArgs& g, int epi, int variant, hipStream_t s);
 
 // the first half of rl_gemm_splitk alone: the parts stay in g.ws
 hipError_t rl_gemm_parts(const GemmArgs& g, int variant, hipStream_t s);

@@ -80,3 +80,28 @@ def test_all_five_configs_have_a_valid_cfg():
         cfg = R.make_cfg(w.model, weight_dtype=R.DTYPE_BF16 if w.bf16_weights else R.DTYPE_F32,
                          max_seqs=w.n_prompts * w.k, max_seq_len=cap, max_kv_tokens=w.n_prompts * w.k * (cap + 31))
         assert R.rlgen_workspace_bytes(cfg) > w.model.n_params * 2, i
+
+
+class GemmArgs(C.Structure):
+    """The library's internal description of a matrix product, up to its fused QKV epilogue (zeros here)."""
+    _fields_ = [("A", C.c_void_p), ("W", C.c_void_p), ("M", C.c_int), ("N", C.c_int), ("K", C.c_int), ("precise", C.c_int),
+                ("out_lo_off", C.c_size_t), ("bias", C.c_void_p), ("out", C.c_void_p), ("ldo", C.c_int), ("temperature", C.c_float),
+                ("partial", C.c_void_p), ("target", C.c_void_p), ("target_logit", C.c_void_p), ("ws", C.c_void_p),
+                ("ws_elems", C.c_size_t), ("splits", C.c_int), ("rest", C.c_char * 512)]
+
+
+@pytest.mark.parametrize("precise", [0, 1])
+@pytest.mark.parametrize("K", [64, 96, 256])
+def test_a_k_split_leaves_no_part_without_a_k_tile(K, precise):
+    """More parts than K tiles are refused (a part without one would add a K step of another); as many as K tiles pass this
+    check and fail for want of a device.  Never run beside a GPU: the operands are no memory."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("host-only check")
+    f = getattr(R.lib, "_Z13rl_gemm_partsRK8GemmArgsiP12ihipStream_t")
+    f.argtypes, f.restype = [C.c_void_p, C.c_int, C.c_void_p], C.c_int
+    tiles = (K + 63) // 64 * (2 if precise else 1)
+    for splits in range(2, tiles + 3):
+        g = GemmArgs(A=256, W=256, M=64, N=128, K=K, precise=precise, out=256, ldo=128, ws=256, ws_elems=1 << 20, splits=splits)
+        rc = f(C.byref(g), 7, None)
+        assert rc != 0 and (rc == 1) == (splits > tiles), (splits, rc)      # 1: hipErrorInvalidValue
