@@ -91,6 +91,25 @@ def reference_decoder(W: Weights, m, precise=0):
     return O.Decoder(W, m)
 
 
+# decode steps over hundreds of keys: a head size for each form of the attention kernel
+LONG_SHAPES = {
+    "neox-h64": ModelShape(ARCH_NEOX, 1, 128, 2, 2, 64, 128, 200, rotary_dim=16),
+    "llama-gqa2-h128": ModelShape(ARCH_LLAMA, 1, 256, 2, 1, 128, 64, 64, rotary_dim=128, rope_theta=500000.0),
+    "neox-h256": GPU_SHAPES["neox-h256"],
+}
+
+
+@functools.lru_cache(maxsize=None)
+def long_context_weights(name) -> Weights:
+    """Weights whose queries and keys are doubled: a query then heeds few of 800 keys, so that 32 keys lost or taken twice can
+    move a log-prob well beyond the tolerance (test_rounding_model.py shows by how much)."""
+    from workloads import bf16_bits_to_f32, f32_to_bf16_bits
+    m = LONG_SHAPES[name]
+    W = scaled_bf16_weights(m)
+    t = {k: f32_to_bf16_bits(2 * bf16_bits_to_f32(v)) if k.endswith((".wq", ".wk")) else v for k, v in W.tensors.items()}
+    return Weights(m, t, True)
+
+
 def make_policy(W: Weights, *, max_seqs, max_seq_len, max_kv_tokens=None, max_batch_tokens=0, share_prompt_kv=0, precise=0):
     r = R()
     if max_kv_tokens is None:

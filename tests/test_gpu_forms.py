@@ -1,14 +1,17 @@
 """GPU: the kernels' forms at the sizes where they can go wrong -- whole and ragged tiles of the matrix products with two to a
 few K steps, decode steps on either side of the rules that divide a product or an attention job inside a block, norms with a
 wave or a block to a row, and a joined output product whose K is not whole K blocks."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
 
 from oracle import decoder as O
 from workloads import ModelShape
-from gpu_util import (GPU_SHAPES, TOL_LOGITS, TOL_LOGPROB, R, dev_f32, dev_i32, make_policy, padded, reference_decoder,
-                      scaled_bf16_weights)
+from gpu_util import (GPU_SHAPES, LONG_SHAPES, TOL_LOGITS, TOL_LOGPROB, R, dev_f32, dev_i32, long_context_weights, make_policy, padded,
+                      reference_decoder, report, scaled_bf16_weights)
+from rounding_model import DEFAULT_FORMATS, RoundedDecoder
 
 pytestmark = pytest.mark.gpu
 
@@ -250,3 +253,38 @@ def test_swiglu_at_large_gates(precise):
     with np.errstate(over="ignore"):
         want = O.last_logits(dec, np.array([1, 2, 3]))
     assert np.abs(z[0] - want).max() < (TOL_LOGITS / 20 if precise else TOL_LOGITS)
+
+
+@pytest.mark.parametrize("share", [0, 1])
+@pytest.mark.parametrize("name,max_seqs,waves", [(n, s, w) for n in ("neox-h64", "llama-gqa2-h128", "neox-h256")
+                                                 for s, w in ((12, 8), (300, 4), (1100, 1))])
+def test_decode_attention_over_several_turns_of_the_key_loop(name, max_seqs, waves, share):
+    """A job's waves take super-blocks of 32 keys in turn and request one or two turns ahead: contexts of one turn of eight waves less,
+    exactly and more (255 to 257 keys), of two (513) and of three and a part (797, where the steps cross into a new super-block).
+    Tolerance: the reference rounds where the library does, and its own log-probs move by at most 1.3e-3 on these models when its
+    sums are taken in fp64 instead of fp32 (roundings that fall the other way); with two blocks of the Llama shape that is
+    1.1e-2, so it has one here."""
+    m = LONG_SHAPES[name]
+    r = R()
+    assert r.lib["_Z25rl_attention_decode_splitxi"](C.c_longlong(max_seqs * m.n_kv_heads), m.head_dim) == waves
+    W = long_context_weights(name)
+    dec = RoundedDecoder(W, m, DEFAULT_FORMATS)
+    rng = np.random.default_rng(41)
+    prompts = [rng.integers(0, m.vocab, size=n) for n in (31, 255, 256, 257, 513, 797)]
+    arr, lens = padded(prompts)
+    k, T = 2, 5
+    forced = rng.integers(0, m.vocab, size=(6, k, T)).astype(np.int32)
+    pol = make_policy(W, max_seqs=max_seqs, max_seq_len=832, max_kv_tokens=5000, max_batch_tokens=832, share_prompt_kv=share)
+    try:
+        _, lp = r.rlgen_generate(pol, dev_i32(arr), lens, k, T, 0.7, dev_f32(np.zeros((6, k, T))), dev_i32(forced))
+        assert r.rlgen_status(pol) == 0
+        lp = lp.cpu().numpy()
+    finally:
+        pol.close()
+    worst = 0.0
+    for b in range(6):
+        for j in range(k):
+            want = O.score(dec, np.concatenate([prompts[b], forced[b, j]]), 0.7, score_from=int(lens[b]))[lens[b]:]
+            worst = max(worst, np.abs(lp[b, j] - want).max())
+    report("decode-attention-turns", err=worst, waves=waves, h=m.head_dim, share=share)
+    assert worst < TOL_LOGPROB

@@ -1,6 +1,6 @@
 """What the library's storage formats cost on the Llama-3.1-8B-shaped workload, computed from the oracle alone.
 
-The benchmark spec's tolerances (raw logits 2e-2, token log-probs 1e-2) are met by the library's default formats (fp16
+The stated tolerances (raw logits 2e-2, token log-probs 1e-2) are met by the library's default formats (fp16
 matrix-product inputs, bf16 KV cache) on the GPT-NeoX-shaped workloads, but not on the Llama-shaped one: with N(0, 0.02)
 weights at d_model 4096 every block amplifies a perturbation of its input, so the 16-bit roundings grow with depth.
 These tests apply the formats to the oracle's own functions (tests/rounding_model.py) on that model shape (full width,
@@ -88,3 +88,34 @@ def test_bf16_pairs_at_every_point_stay_far_below_the_tolerance(llama8b_slices, 
     assert precise[8] < TOL_LOGITS / 50
     # extrapolated to the 32 layers like sqrt(depth), with a factor 4 to spare for the longer prompts and the full vocabulary
     assert 4 * precise[8] * np.sqrt(32 / 8) < TOL_LOGITS / 10
+
+
+class WithoutKeys(RoundedDecoder):
+    """The last `steps` queries of a pass do not see the keys of one super-block."""
+    lost, steps = None, 5
+
+    def _attend(self, q, k, v, qpos):
+        out = super()._attend(q, k, v, qpos)
+        if self.lost is None:
+            return out
+        keep = np.arange(len(k)) // 32 != self.lost
+        base = self.steps
+        out[-base:] = super()._attend(q[-base:], k[keep], v[keep], np.asarray(qpos)[-base:] - 32 * (np.asarray(qpos)[-base:] // 32 > self.lost))
+        return out
+
+
+@pytest.mark.parametrize("name", ["neox-h64", "llama-gqa2-h128", "neox-h256"])
+def test_a_lost_super_block_of_a_long_context_shows(name):
+    """The models that the decode attention's key loop is tested on: 32 keys of 800 that a decode step leaves out move the four
+    log-probs compared by several times the tolerance, in every turn of a loop that strides by eight super-blocks."""
+    from gpu_util import LONG_SHAPES, TOL_LOGPROB, long_context_weights
+    m = LONG_SHAPES[name]
+    dec = WithoutKeys(long_context_weights(name), m, DEFAULT_FORMATS)
+    seq = np.random.default_rng(3).integers(0, m.vocab, size=801)
+    whole = O.score(dec, seq, 0.7, score_from=797)[797:]
+    moved = []
+    for dec.lost in range(24):
+        moved.append(np.abs(O.score(dec, seq, 0.7, score_from=797)[797:] - whole).max())
+    moved = np.array(moved)
+    for turn in (slice(0, 8), slice(8, 16), slice(16, 24)):
+        assert (moved[turn] > 2 * TOL_LOGPROB).sum() >= 2 and moved[turn].max() > 5 * TOL_LOGPROB, moved[turn]
