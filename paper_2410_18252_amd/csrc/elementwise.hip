@@ -100,7 +100,8 @@ __global__ void embed_kernel(float* x, const uint16_t* E, const int* tokens, con
 // LayerNorm / RMSNorm; the row lives in registers.  Mean, then variance of the centred values (two passes over registers),
 // all in fp32; the normalised row is stored as fp16.  WIDE: four waves share a row, thread t holding its 16-byte pieces
 // t, t + 256, ...; otherwise a wave holds a row and lane l the pieces the lanes l of those four waves would hold, with one
-// sum for each of the four, so that both forms add in the same order and return the same bits.
+// sum for each of the four, so that both forms add in the same order and return the same bits (products that are added are
+// written as fmaf: of two products in a sum the compiler rounds one first, and not the same one in both forms).
 // A decode step's norms are bound by latency, not by bytes: one wave per row leaves most CUs empty and chains ten loads
 // (64 rows at d = 2560: 11.4 us, 4.9 with four waves to a row); from a few thousand rows on the one-wave form is at
 // the rate of memory and does without the barriers.  NV: 16-byte pieces per thread of the wide form.
@@ -178,7 +179,7 @@ __global__ __launch_bounds__(256) void norm_kernel(const float* x, const int* ro
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           v[i][w][e] -= mean;
-          sq[w] += v[i][w][e] * v[i][w][e];
+          sq[w] = fmaf(v[i][w][e], v[i][w][e], sq[w]);
         }
       }
     }
@@ -209,7 +210,7 @@ __global__ __launch_bounds__(256) void norm_kernel(const float* x, const int* ro
       f32x4 y;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        y[e] = v[i][w][e] * rstd * ga[e] + ba[e];
+        y[e] = fmaf(v[i][w][e] * rstd, ga[e], ba[e]);
         sat |= f16_out_of_range(y[e]);
       }
       put(out1, y, col);
@@ -219,7 +220,7 @@ __global__ __launch_bounds__(256) void norm_kernel(const float* x, const int* ro
         if (b2) bb = *(const f32x4*)(b2 + col);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          y[e] = v[i][w][e] * rstd * gb[e] + bb[e];
+          y[e] = fmaf(v[i][w][e] * rstd, gb[e], bb[e]);
           sat |= f16_out_of_range(y[e]);
         }
         put(out2, y, col);

@@ -86,18 +86,34 @@ def test_decode_forms_match_the_reference(name, max_seqs):
         assert np.abs(lp[b, 0] - want).max() < TOL_LOGPROB
 
 
-def test_norms_return_the_same_bits_with_a_wave_or_a_block_to_a_row():
-    """A sequence scored on its own (few rows: a block to each) and among others (1100 rows: a wave to each)."""
-    m = GPU_SHAPES["neox-h80"]
-    W = scaled_bf16_weights(m)
+# widths whose 16-byte pieces fill one wave's share and part of the next (80), the second round of all four (264) and the third (640);
+# the 1056-wide shapes end a K block half full.  1037 rows of 1056 cut the products into the residual in two or three parts
+NORM_SHAPES = {
+    "neox-d320": ModelShape(0, 2, 320, 5, 5, 64, 640, 300, rotary_dim=16),          # the output products are one
+    "neox-d1056": ModelShape(0, 2, 1056, 33, 33, 32, 1024, 300, rotary_dim=8),      # they are two
+    "llama-d1056": ModelShape(1, 2, 1056, 33, 11, 32, 1024, 300, rotary_dim=32, rope_theta=500000.0),
+    "neox-d2560": ModelShape(0, 2, 2560, 40, 40, 64, 512, 300, rotary_dim=16),
+}
+
+
+@pytest.mark.parametrize("precise", [0, 1])
+@pytest.mark.parametrize("name", list(NORM_SHAPES))
+def test_norms_return_the_same_bits_with_a_wave_or_a_block_to_a_row(name, precise):
+    """A sequence scored on its own (few rows: a block to each, which also adds up the parts of a split product) and among others
+    (1037 rows: a wave to each, and the parts are added by the product's second pass)."""
+    m = NORM_SHAPES[name]
+    W = scaled_bf16_weights(m, scale=1.5)
     rng = np.random.default_rng(29)
-    arr, lens = padded([rng.integers(0, m.vocab, size=n) for n in [100] * 10 + [37, 63]])
+    arr, lens = padded([rng.integers(0, m.vocab, size=n) for n in [100] * 10 + [37]])
     r = R()
-    pol = make_policy(W, max_seqs=12, max_seq_len=100, max_batch_tokens=1200)
+    pol = make_policy(W, max_seqs=12, max_seq_len=100, max_batch_tokens=1056, precise=precise)
     try:
+        assert r.rlgen_debug_get_gemm(pol, 1, 3)[1] > 1          # the product into the residual is split
         many = r.rlgen_score(pol, dev_i32(arr), lens, 1.0)
-        one = r.rlgen_score(pol, dev_i32(arr[10:11]), lens[10:11], 1.0)
-        assert torch.equal(many[10, :37], one[0, :37])
+        for i in (3, 10):
+            one = r.rlgen_score(pol, dev_i32(arr[i:i + 1]), lens[i:i + 1], 1.0)
+            assert torch.equal(many[i, :lens[i]], one[0, :lens[i]])
+        assert (many[10, 1:37] < 0).all()
     finally:
         pol.close()
 
