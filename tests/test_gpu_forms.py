@@ -304,3 +304,49 @@ def test_decode_attention_over_several_turns_of_the_key_loop(name, max_seqs, wav
             worst = max(worst, np.abs(lp[b, j] - want).max())
     report("decode-attention-turns", err=worst, waves=waves, h=m.head_dim, share=share)
     assert worst < TOL_LOGPROB
+
+
+# no decode layer of these divides K inside a block (more than 128 sequences, whole K blocks); FFN-down is cut into parts, and
+# the GPT-NeoX shape's FFN-up too
+DECODE_TILES = {
+    "neox-d512": ModelShape(0, 2, 512, 8, 8, 64, 1024, 515, rotary_dim=16),
+    "llama-d256": ModelShape(1, 2, 256, 4, 2, 64, 512, 700, rotary_dim=64, rope_theta=500000.0),
+}
+
+
+@pytest.mark.parametrize("precise", [0, 1])
+@pytest.mark.parametrize("name", list(DECODE_TILES))
+def test_decode_steps_return_the_same_bits_on_every_tile_shape(name, precise):
+    """Every tile shape forced on all layers of a decode step of 131 sequences (ragged in every tile), taken whole and as two
+    halves: the QKV product's writes into the cache, split and whole products, the LM head.  The same tokens and log-probs bit
+    for bit, and those within tolerance of the reference."""
+    m = DECODE_TILES[name]
+    W = scaled_bf16_weights(m, scale=2.0)
+    rng = np.random.default_rng(53)
+    prompts = [rng.integers(0, m.vocab, size=n) for n in rng.integers(1, 40, size=131)]
+    arr, lens = padded(prompts)
+    T = 5
+    u = dev_f32(rng.random((131, 1, T), dtype=np.float32))
+    r = R()
+    pol = make_policy(W, max_seqs=131, max_seq_len=45, precise=precise)
+    outs = []
+    try:
+        splits = [r.rlgen_debug_get_gemm(pol, 0, which)[1] for which in range(5)]
+        assert splits[3] > 1 and (m.arch == 1 or splits[2] > 1), splits
+        for v in [0, 3, 5, 7] if precise else range(11):
+            for halves in (0, 1):
+                r.rlgen_set_decode_split_min(pol, 2 if halves else 0)
+                for which in range(5):
+                    wide_only = which == 4 or (which == 2 and m.arch == 1)
+                    r.rlgen_debug_set_gemm(pol, 2 if halves else 0, which, 0 if wide_only and 6 <= v <= 9 else v)
+                outs.append(r.rlgen_generate(pol, dev_i32(arr), lens, 1, T, 0.7, u))
+        assert r.rlgen_status(pol) == 0
+    finally:
+        pol.close()
+    for t, lp in outs[1:]:
+        assert torch.equal(t, outs[0][0]) and torch.equal(lp, outs[0][1])
+    t, lp = (x.cpu().numpy() for x in outs[0])
+    dec = reference_decoder(W, m, precise)
+    for b in (0, 64, 130):
+        want = O.score(dec, np.concatenate([prompts[b], t[b, 0]]), 0.7, score_from=int(lens[b]))[lens[b]:]
+        assert np.abs(lp[b, 0] - want).max() < TOL_LOGPROB

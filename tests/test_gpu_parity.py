@@ -281,7 +281,9 @@ def test_results_do_not_depend_on_the_tile_shapes_a_context_picked(name):
     u = rng.random((5, 2, 7), dtype=np.float32)
     outs, picks = [], []
     # contexts 0-2: the measured choice, and that choice moved on by one and by two in the list of legal shapes; then
-    # (default formats) every layer that may take it forced onto the eight-wave small tile, and onto the sixteen-wave large one
+    # (default formats) every layer that may take it forced onto the eight-wave 64x128 ring, and onto the 256x128 ring.  With
+    # twelve sequences the default formats' decode layers divide K inside a block and have no shape to force:
+    # test_gpu_forms.py forces theirs on a larger batch
     for shift in (0, 1, 2) if precise else (0, 1, 2, -9, -10):
         pol = make_policy(W, max_seqs=12, max_seq_len=80, max_batch_tokens=80, precise=precise)
         try:
@@ -311,7 +313,9 @@ def test_results_do_not_depend_on_the_tile_shapes_a_context_picked(name):
     assert all([sp for _, sp in p] == [sp for _, sp in picks[0]] for p in picks[1:])                  # the K split is the rule's
     assert [v for v, _ in picks[0]] != [v for v, _ in picks[1]]
     if name == "neox-wide-ffn":
-        assert any(sp > 1 for _, sp in picks[0])                               # the test covers a split product
+        assert picks[0][5 + 3][1] > 1                      # the prompt pass's FFN-down: the test covers a split product
+        if precise:
+            assert picks[0][3][1] > 1                      # and the decode step's
     for o in outs[1:]:
         for a, b in zip(outs[0], o):
             assert torch.equal(a, b)
