@@ -214,8 +214,9 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
         v[i] = acc[i][j] + bias_n;
         if (any_rot) {
           const f32x4 cs = cs_n[i];
-          const float lo0 = v[i][0] * cs[0] - v[i][2] * cs[1], hi0 = v[i][2] * cs[0] + v[i][0] * cs[1];
-          const float lo1 = v[i][1] * cs[2] - v[i][3] * cs[3], hi1 = v[i][3] * cs[2] + v[i][1] * cs[3];
+          // (as fmaf: left to the compiler, which of the two products is rounded first could differ between tile shapes)
+          const float lo0 = fmaf(v[i][0], cs[0], -(v[i][2] * cs[1])), hi0 = fmaf(v[i][2], cs[0], v[i][0] * cs[1]);
+          const float lo1 = fmaf(v[i][1], cs[2], -(v[i][3] * cs[3])), hi1 = fmaf(v[i][3], cs[2], v[i][1] * cs[3]);
           v[i][0] = lo0; v[i][1] = lo1; v[i][2] = hi0; v[i][3] = hi1;
         }
       }
