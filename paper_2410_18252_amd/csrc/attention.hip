@@ -3,7 +3,8 @@
 //
 // One wave owns 16 "columns" (queries) and streams one (sequence, kv head) K/V stream in
 // super-blocks of 32 keys.  The matrix cores serve as dot-product engines fed straight from global
-// memory: no LDS, no cross-lane reduction over head_dim.
+// memory: the operands never pass through LDS (only what the waves of a shared job add up does), and there is no cross-lane
+// reduction over head_dim.
 //   S^T[key, col] = sum_d K[key, d] q[col, d]       2 x ceil(h/32) MFMA 16x16x32 per super-block
 //   O^T[d, col]  += sum_key V^T[d, key] P^T[key, col]   h/16 MFMA 16x16x32 per super-block
 // K and V are stored as bf16 and widened to fp16 in registers (exact for every value in fp16's
@@ -441,14 +442,20 @@ hipError_t rl_attention_decode(const AttnArgs& a, hipStream_t s) {
 }
 // Waves to a decode job: by what the context can hold, so that a sequence's sums do not depend on the batch it is in.  Where
 // the jobs alone give a SIMD a wave or two (wide heads need fewer, they hold more in registers), sharing one only costs the
-// meeting in LDS.  Measured, one wave / four waves to a job: 128 jobs at head size 256 50 / 21 us, 2048 at head size 64 37.8 /
-// 35.9 us, 2048 at head size 128 125 / 148 us.
+// meeting in LDS.  Measured, one wave / four waves to a job, the kernel alone: 128 jobs at head size 256 50 / 21 us, 2048 at head
+// size 64 37.8 / 35.9 us, 2048 at head size 128 125 / 148 us.  A decode layer on either side of the borders (us, 256 and 1500 keys):
+// twice the upper one, one wave / four: 1024 jobs of size 256 127 / 144 and 324 / 320, 3264 of size 80 155 / 157 and 345 / 337; twice
+// the lower one, four waves / eight: 1024 of size 64 50 / 49 and 100 / 96, 800 of size 80 102 / 110 and 150 / 158, 512 of size 128
+// 176 / 221 and 223 / 294; below it, four / eight: 384 of size 80 90 / 93 and 114 / 119, 128 of size 128 159 / 176 and 170 / 198 (there
+// four would do better).
 int rl_attention_decode_split(long long cap_jobs, int h) {
   const long long size = cap_jobs * (h > 64 ? h : 64);
   return size <= 32768 ? 8 : size <= 131072 ? 4 : 1;
 }
 // The same for a prompt pass of at most cap_rows rows: up to four jobs a CU (654 rows of 8 heads of size 256: 57 ->
-// 21 us a layer).
+// 21 us a layer).  A layer of prompts of 500 tokens, one wave / four (us): 512 jobs at 1B width 231 / 191, at 8B 312 / 286; 1024
+// jobs at 1B 330 / 315, at 2.8B 281 / 283, at 8B 313 / 284; 2048 jobs 623 / 586, 485 / 488, 512 / 509, and with prompts of 128
+// tokens 529 / 544, 470 / 486, 474 / 491.
 int rl_attention_prefill_split(int cap_rows, int Hq, int h) {
   const long long jobs = (long long)((cap_rows + 15) / 16) * Hq / rl_attention_prefill_qb(h);
   return jobs <= 1024 ? 4 : 1;

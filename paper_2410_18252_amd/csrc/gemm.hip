@@ -395,8 +395,8 @@ __device__ __forceinline__ f32x4 mfma16(f16x8 b, f16x8 a, f32x4 c) {
   else return __builtin_amdgcn_mfma_f32_16x16x32_f16(b, a, c, 0, 0, 0);
 }
 
-// NS = 0: tiles travel global -> registers -> LDS (two LDS stages).  NS >= 2: NS LDS stages filled by direct
-// global -> LDS loads, issued NS - 1 K steps ahead (needs K % 64 == 0).
+// Two LDS stages.  NS = 0: tiles travel global -> registers -> LDS.  NS = 2: by direct global -> LDS loads, issued one K step
+// ahead (needs K % 64 == 0).
 // PR: precise mode (see GemmArgs): bf16 operands, A as hi/lo pairs; every K block of W meets the hi and then the lo
 // block of A in two consecutive steps of the K loop.
 template <int BM, int BN, int WM, int WN, int EPI, bool KTAIL, int NS = 0, bool PR = false>
@@ -555,10 +555,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_f16_kernel(GemmArgs g) {
         __builtin_amdgcn_global_load_lds((gptr_t)(qb[i] + wk(kt) * kw), (lptr_t)(la + (BM + i * RPP) * BK), 16, 0, 0);
     };
     {
-      // Skewed by a quarter of a K step: the wait for the next stage and the barrier sit before the last of the four
-      // MFMA groups of a stage, whose fragments are in registers by then.  Behind the barrier nobody reads this
-      // stage's LDS any more, so its buffer is refilled at once, and the first fragments of the next stage are
-      // fetched while the last MFMA group runs: the matrix pipe does not drain at the stage boundary.
+      // Skewed by less than half a K step: the wait for the next stage and the barrier sit behind the first products of the
+      // second of a stage's two MFMA groups (one per K slice of 32), whose fragments are in registers by then.  Behind the
+      // barrier nobody reads this stage's LDS any more, so its buffer is refilled at once, and the first fragments of the
+      // next stage are fetched while the rest of the group runs: the matrix pipe does not drain at the stage boundary.
       f16x8 fa[2][TM], fb[2][TN];
       auto frags = [&](int buf, int kk, int slot) {
         const uint16_t* la = lds + buf * STAGE + (wm * (BM / WM)) * BK;
@@ -632,8 +632,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_f16_kernel(GemmArgs g) {
 // all the time, which covers the 1.3 us that the operand stream takes from HBM and the other XCDs' L2 under load.  One
 // barrier per phase: the half needed next has landed, and everybody has read the half that is about to be overwritten.
 // Measured (M = 32768, random operands, bursts of ten): N = 2560, K = 10240 1.28 PFLOP/s where the two-stage loop on eight
-// waves gave 1.01, N = 10240, K = 2560 with GELU 1.19 (0.90), N = 7680, K = 2560 1.16 (0.95).  The loop is bound by power:
-// 2420 clocks per K step (2048 of them matrix products) at 1.65 GHz; on zeros the clock stays at 2.4 GHz.
+// waves gave 1.01, N = 10240, K = 2560 with GELU 1.19 (0.90), N = 7680, K = 2560 1.16 (0.95; 1.04 in a whole prompt pass).  The
+// loop is bound by power: 2420 clocks per K step (2048 of them matrix products) at 1.65 GHz; on zeros the clock stays at 2.4 GHz.
+// The other products raise their waves' priority for the decode step's sake; this one need not (the LM head is all of a decode
+// step it takes: generate of 2.8B width on two streams 371.1 ms without, 370.3 with, 1B 137.3 and 137.4).
 template <int EPI, bool PR>
 __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmArgs g) {
   constexpr int TM = 8, TN = 8;                  // 16x16 tiles of a wave: 128 x 128
@@ -1121,8 +1123,8 @@ hipError_t launch_ring(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Whole K tiles take the direct-load pipeline with two LDS stages (more stages measured slower: the extra LDS
-// costs a resident block); a ragged K falls back to register staging, which can zero-fill the tail.
+// Whole K tiles take the direct-load pipeline with two LDS stages, which leave room for a second block on a CU (launches with fewer
+// blocks take the ring); a ragged K falls back to register staging, which can zero-fill the tail.
 template <int BM, int BN, int WM, int WN, int EPI, int NS = 2, bool PR = false>
 hipError_t launch(const GemmArgs& g, hipStream_t s) {
   return g.K % BK == 0 ? launch_k<BM, BN, WM, WN, EPI, false, NS, PR>(g, s) : launch_k<BM, BN, WM, WN, EPI, true, 0, PR>(g, s);
@@ -1210,7 +1212,11 @@ hipError_t rl_gemm_variant(const GemmArgs& g, int epi, int variant, hipStream_t 
 bool rl_gemm_skinny_pays(int cap_rows, int N, int K, int epi) {
   if (K % BK != 0 || N % 16 != 0 || (epi == EPI_SWIGLU_F16 && N % 64 != 0)) return false;
   if (epi != EPI_F32 && epi != EPI_RESID && epi != EPI_GELU_F16 && epi != EPI_SWIGLU_F16 && epi != EPI_QKV) return false;
-  // up to 16 rows on every width that was measured, beyond while a CU fetches no more than 256 KB (see the kernel)
+  // While a CU fetches no more than 256 KB (see the kernel), and up to 16 rows whatever it fetches.  A decode layer over 64 keys
+  // (us): of 16 rows with the long K divided inside the block / by tiles and split-K, Llama 3072 wide 104 / 110 and 4096 wide 163 /
+  // 161, GPT-NeoX 5120 wide 227 / 245, 2560 wide 87 / 86, 2048 wide 62 / 56 and 1024 wide 35 / 31; of 32 rows (within 256 KB /
+  // always divided) 63 / 75 at 2048, 91 / 104 at 2560 and 208 / 279 at 5120, but 124 / 109 and 175 / 169 for the Llama widths; of
+  // 128 rows 52 / 57, 98 / 123, 131 / 196 and 309 / 514, 149 / 192 and 202 / 320.
   return cap_rows <= 16 || (cap_rows <= 128 && skinny_tile(cap_rows, N, epi).cost * K * 2 <= 256 * 1024);
 }
 hipError_t rl_gemm_skinny(const GemmArgs& g, int epi, hipStream_t s) {

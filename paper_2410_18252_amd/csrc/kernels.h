@@ -92,7 +92,8 @@ struct GemmArgs {
 };
 // tile shape chosen from the problem size; g.splits >= 2 (with g.ws) cuts K into that many parts (rl_gemm_splitk)
 hipError_t rl_gemm(const GemmArgs& g, int epi, hipStream_t s);
-// the same with an explicit tile shape (tuning and tests): 0 = 128x128, 1 = 256x128, 2 = 256x256, ...
+// the same with an explicit tile shape (tuning and tests).  Two stages: 0 = 128x128, 1 = 256x128, 4 = 128x256 (four waves), 5 = 256x128
+// (eight), 7 = 64x128; 256x256 by hand: 3; rings: 2 = 128x128, 10 = 256x128, 6 = 64x64, 8 and 9 = 64x128 on four and eight waves
 hipError_t rl_gemm_variant(const GemmArgs& g, int epi, int variant, hipStream_t s);
 // needs g.ws and 2 <= g.splits <= K tiles of 64 (precise mode: twice as many)
 hipError_t rl_gemm_splitk(const GemmArgs& g, int epi, int variant, hipStream_t s);
