@@ -27,7 +27,7 @@ MFMA_F16_PEAK_TFLOPS = 2500.0        # dense fp16 / bf16 matrix peak of MI355X
 TRAFFIC_OVER_ALGORITHMIC = 1.039
 # The same for every kernel of the decode phase together, two-stream decode (profiles/decode_phase_c4_hbm_traffic.txt):
 # weights are read once per half batch, whole super-blocks are loaded, activations and partial sums pass through HBM.
-DECODE_TRAFFIC_OVER_ALGORITHMIC = 1.192
+DECODE_TRAFFIC_OVER_ALGORITHMIC = 1.187
 
 
 # every EVENT_EVERY-th decode-attention launch of the timed region is bracketed with HIP events (each bracket costs

@@ -15,7 +15,7 @@ MARGIN = 1e-3         # tokens must agree wherever the oracle's CDF margin excee
 
 
 def report(name, **vals):
-    """Appends measured errors to gpurun_out/parity.jsonl when that folder exists (diagnostics only)."""
+    """Appends measured errors to a file of its own where the folder for results exists (diagnostics only)."""
     import json, os
     d = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "gpurun_out")
     if os.path.isdir(d):
