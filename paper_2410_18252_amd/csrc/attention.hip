@@ -57,7 +57,7 @@ namespace {
 // QB = query blocks of 16 columns a wave carries through one pass over the keys (prompt pass only: two blocks halve
 // the key / value traffic per query; a.jobs then counts blocks of 16 QB tokens).
 template <int HD, bool DECODE, int QB = 1, bool PR = false, int SPLIT = 1>
-__global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= 128 && !PR && SPLIT == 1) ? ATTN_PROMPT_BLOCKS : 1) void attention_kernel(AttnArgs a) {
+__global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= (PR ? 80 : 128) && SPLIT == 1) ? ATTN_PROMPT_BLOCKS : 1) void attention_kernel(AttnArgs a) {
   static_assert(!DECODE || QB == 1, "decode has one query block");
   static_assert(SPLIT == 1 || SPLIT == 4 || (DECODE && SPLIT == 8), "a job is shared by all waves of a block");
   constexpr int NCH = HD / 8;            // 16-byte chunks per key row
@@ -170,6 +170,23 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= 128
     else return __builtin_amdgcn_mfma_f32_16x16x32_f16(x, y, acc, 0, 0, 0);
   };
 
+  // V^T fragment t (16 dims, of which lane c holds one, keys 8 g .. + 7): in a whole group of 64 dims tile 4 q + i has the dims
+  // 64 q + 4 c + i, and pair p of its keys sits in unit 4 q + p, dims i in the low or high halves of the words i / 2 and 2 + i / 2
+  constexpr int VG = PR ? 0 : HD / 64 * 4;        // tiles in whole groups
+  auto value_frag = [](const u32x4 (&raw)[VT], int t) {
+    if (t >= VG) return bf16x8_to_f16x8(raw[t]);
+    const int i = t & 3;
+    f16x8 r;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const uint32_t w0 = raw[(t & ~3) + p][i >> 1], w1 = raw[(t & ~3) + p][2 + (i >> 1)];
+      const auto h = i & 1 ? __builtin_amdgcn_cvt_pkrtz(__uint_as_float(w0 & 0xffff0000u), __uint_as_float(w1 & 0xffff0000u))
+                           : __builtin_amdgcn_cvt_pkrtz(__uint_as_float(w0 << 16), __uint_as_float(w1 << 16));
+      r[2 * p] = (f16_t)h[0];
+      r[2 * p + 1] = (f16_t)h[1];
+    }
+    return r;
+  };
   f32x4 o[QB][VT];
   float m[QB], lsum[QB];
 #pragma unroll
@@ -204,7 +221,9 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= 128
 #pragma unroll
       for (int i = 0; i < KSTEPS; ++i) {
         const int chunk = 4 * i + g;
-        kraw[t][i] = chunk < NCH ? ATTN_LOAD((const u32x4*)(kb + (((t * NCH + chunk) * 16 + c) << 3))) : u32x4{0, 0, 0, 0};
+        constexpr int LAST = HD % 32 ? HD / 32 : KSTEPS;          // a step of 16 dims
+        const int lane_at = PR ? ((4 * i + g) * 16 + c) * 8 : i * 512 + (c * (i == LAST ? 16 : 32) + 8 * g);
+        kraw[t][i] = chunk < NCH ? ATTN_LOAD((const u32x4*)(kb + (t * 16 * HD + lane_at))) : u32x4{0, 0, 0, 0};
       }
 #pragma unroll
     for (int t = 0; t < VT; ++t) vraw[t] = ATTN_LOAD((const u32x4*)(vb + ((((t * 4 + g) * 16) + c) << 3)));
@@ -237,14 +256,12 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= 128
     load_sb(sb, kraw, vraw);
 #endif
 
-    // the super-block's operands are widened once and serve every query block
-    f16x8 kf[2][KSTEPS], vf[VT];
+    // the super-block's keys are widened once and serve every query block, and so are its values below
+    f16x8 kf[2][KSTEPS];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int i = 0; i < KSTEPS; ++i) kf[t][i] = PR ? __builtin_bit_cast(f16x8, kraw[t][i]) : bf16x8_to_f16x8(kraw[t][i]);
-#pragma unroll
-    for (int t = 0; t < VT; ++t) vf[t] = PR ? __builtin_bit_cast(f16x8, vraw[t]) : bf16x8_to_f16x8(vraw[t]);
     // straight-line code over the query blocks: their chains (MFMA -> softmax -> MFMA) are independent, and the
     // scheduler interleaves them only if no branch separates them
     f32x4 sc[QB][2];
@@ -290,26 +307,37 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= 128
       }
       lsum[b] = lsum[b] * alpha[b] + psum;
     }
+    if constexpr (PR) {
 #pragma unroll
-    for (int b = 0; b < QB; ++b) {
-      f16x8 pf;
-      [[maybe_unused]] u32x4 plo;
-      if constexpr (PR) {
-        u32x4 phi;
+      for (int b = 0; b < QB; ++b) {
+        u32x4 phi, plo;
 #pragma unroll
         for (int e = 0; e < 4; ++e) SPLIT_BF16X2(p[b][2 * e], p[b][2 * e + 1], phi[e], plo[e]);
-        pf = __builtin_bit_cast(f16x8, phi);
-      } else {
+        const f16x8 pf = __builtin_bit_cast(f16x8, phi);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) pf[e] = (f16_t)p[b][e];
+        for (int t = 0; t < VT; ++t) {
+          const f16x8 vf = __builtin_bit_cast(f16x8, vraw[t]);
+          o[b][t] *= alpha[b];
+          o[b][t] = mfma(vf, pf, o[b][t]);
+          o[b][t] = mfma(__builtin_bit_cast(f16x8, vraw_lo[t]), pf, o[b][t]);
+          o[b][t] = mfma(vf, __builtin_bit_cast(f16x8, plo), o[b][t]);
+        }
       }
+    } else {
+      f16x8 pf[QB];
+#pragma unroll
+      for (int b = 0; b < QB; ++b)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pf[b][e] = (f16_t)p[b][e];
+      // (the values are widened here, where the keys' registers are free: with it at the top of the super-block head size 80
+      // needs 174 registers in the prompt pass instead of 159, two waves to a SIMD instead of three)
 #pragma unroll
       for (int t = 0; t < VT; ++t) {
-        o[b][t] *= alpha[b];
-        o[b][t] = mfma(vf[t], pf, o[b][t]);
-        if constexpr (PR) {
-          o[b][t] = mfma(__builtin_bit_cast(f16x8, vraw_lo[t]), pf, o[b][t]);
-          o[b][t] = mfma(vf[t], __builtin_bit_cast(f16x8, plo), o[b][t]);
+        const f16x8 vf = value_frag(vraw, t);
+#pragma unroll
+        for (int b = 0; b < QB; ++b) {
+          o[b][t] *= alpha[b];
+          o[b][t] = mfma(vf, pf[b], o[b][t]);
         }
       }
     }
@@ -335,10 +363,16 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= 128
 #endif
   }
   }   // segments
-  // column c's 4 VT values of head dims 16 t + 4 g .. + 3 leave for row qrow
+  // column c's 4 VT values leave for row qrow in runs of four head dims: piece t is tile t, or of a whole group of 64 dims row
+  // t % 4 of its four tiles
+  auto piece = [&](int b, int t) {
+    if (t >= VG) return o[b][t];
+    const int q = t & ~3, e = t & 3;
+    return f32x4{o[b][q][e], o[b][q + 1][e], o[b][q + 2][e], o[b][q + 3][e]};
+  };
   auto store = [&](int b, int t, f32x4 y) {
     u32x2 w;
-    uint16_t* dst = a.out + kblk_off(qrow[b], qhead * HD + 16 * t + 4 * g, a.out_rows);
+    uint16_t* dst = a.out + kblk_off(qrow[b], qhead * HD + (t < VG ? 16 * (t & ~3) + 16 * g + 4 * (t & 3) : 16 * t + 4 * g), a.out_rows);
     if constexpr (PR) {
       u32x2 wl;
       SPLIT_BF16X2(y[0], y[1], w[0], wl[0]);
@@ -369,7 +403,7 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= 128
       // a wave without keys has a maximum of -inf and contributes nothing (some wave has keys: M is finite)
       const float mine = __expf(m[b] - M);
 #pragma unroll
-      for (int t = 0; t < VT; ++t) part[wave][t][lane] = o[b][t] * mine;
+      for (int t = 0; t < VT; ++t) part[wave][t][lane] = piece(b, t) * mine;
       __syncthreads();
       const float inv = 1.0f / L;
       for (int t = wave; t < VT; t += SPLIT) {
@@ -383,7 +417,7 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= 128
       const float inv = 1.0f / ls;
       if (store_col[b]) {
 #pragma unroll
-        for (int t = 0; t < VT; ++t) store(b, t, o[b][t] * inv);
+        for (int t = 0; t < VT; ++t) store(b, t, piece(b, t) * inv);
       }
     }
   }

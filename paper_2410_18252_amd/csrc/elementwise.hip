@@ -229,6 +229,27 @@ __global__ __launch_bounds__(256) void norm_kernel(const float* x, const int* ro
   flag_f16_range(sat && lo_off == 0, status);        // bf16 pairs have fp32's range
 }
 
+// Four head dims (from dim on, a multiple of 4) of eight keys (from key on, a multiple of 8) into a value stream; b: one key each
+__device__ __forceinline__ void put_values(uint16_t* stream, const KvLayout& lay, int key, int dim, const u32x2 (&b)[8]) {
+  if (lay.v_grouped(dim)) {
+    uint16_t* dst = stream + lay.v_key_grouped(key) + lay.v_dim_grouped(dim);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) *(u32x4*)(dst + p * 512) = u32x4{b[2 * p][0], b[2 * p][1], b[2 * p + 1][0], b[2 * p + 1][1]};
+  } else {
+    uint16_t* dst = stream + lay.v_key_rest(key) + lay.v_dim_rest(dim);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      u32x4 w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t lo = b[2 * e][j >> 1], hi = b[2 * e + 1][j >> 1];
+        w[e] = (j & 1) ? ((lo >> 16) | (hi & 0xffff0000u)) : ((lo & 0xffffu) | (hi << 16));
+      }
+      *(u32x4*)(dst + j * 8) = w;
+    }
+  }
+}
+
 // One thread per (row, head slot, 8-dim chunk).  Head slots: Hq query heads, Hkv key heads, Hkv
 // value heads.  The pair (i, i + r/2) of the first r dims is rotated by the row's position.
 __global__ void rope_kv_kernel(RopeArgs a) {
@@ -285,31 +306,29 @@ __global__ void rope_kv_kernel(RopeArgs a) {
   }
 }
 
-// Prompt pass: values of 8 consecutive tokens of one sequence and one head dim form one 16-byte unit of
-// the cache layout, so one thread gathers them (coalesced across head dims) and writes the unit whole, to
-// every copy.  One block per 16-token job; slots past the prompt's end are written as zero (the decode
-// steps fill them later).
+// Prompt pass: a thread takes four head dims of eight consecutive tokens of one sequence and writes them, to every copy, as the
+// four 16-byte units they fill (see KvLayout).  One block per 16-token job; slots past the prompt's end are written as zero
+// (the decode steps fill them later).
 __global__ __launch_bounds__(256) void rope_v_prefill_kernel(RopeArgs a) {
   const AttnJob jb = a.jobs[blockIdx.x];
   const int slots = a.Hq + 2 * a.Hkv;
-  const int per_group = a.Hkv * a.h;
+  const int per_group = a.Hkv * a.h / 4;
   const size_t ld = (size_t)slots * a.h;
   for (int item = threadIdx.x; item < 2 * per_group; item += blockDim.x) {
-    const int grp = item / per_group, rem = item - grp * per_group;
+    const int grp = item / per_group, rem = 4 * (item - grp * per_group);
     const int head = rem / a.h, dim = rem - head * a.h;
     const int pos0 = jb.qblock * 16 + grp * 8;
     if (pos0 >= jb.len) continue;
     const float* src = a.qkv + (size_t)(jb.row0 + pos0) * ld + (size_t)(a.Hq + a.Hkv + head) * a.h + dim;
-    float v[8];
+    u32x2 b[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = pos0 + i < jb.len ? src[(size_t)i * ld] : 0.f;
-    u32x4 w;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) w[e] = pack_bf16x2(v[2 * e], v[2 * e + 1]);
+    for (int i = 0; i < 8; ++i) {
+      const f32x4 v = pos0 + i < jb.len ? *(const f32x4*)(src + (size_t)i * ld) : f32x4{0.f, 0.f, 0.f, 0.f};
+      b[i][0] = pack_bf16x2(v[0], v[1]); b[i][1] = pack_bf16x2(v[2], v[3]);
+    }
     for (int cpy = 0; cpy < a.ncopy; ++cpy) {
       const int s = jb.cache_seq + cpy;
-      uint16_t* st = a.kv + a.lay.stream(a.kv_off[s], a.kv_cap[s], head);
-      *(u32x4*)(st + a.lay.v_elem(pos0, dim)) = w;
+      put_values(a.kv + a.lay.stream(a.kv_off[s], a.kv_cap[s], head), a.lay, pos0, dim, b);
     }
   }
 }
@@ -326,13 +345,12 @@ __global__ __launch_bounds__(256) void kv_prefill_kernel(RopeArgs a) {
   const uint16_t* stage = a.kvstage + (size_t)(jb.row0 + jb.qblock * 16) * ld;
   // the job's items are spread over gridDim.y blocks: the copies are latency-bound, so more blocks in flight
   const int first = threadIdx.x + blockDim.x * blockIdx.y, step = blockDim.x * gridDim.y;
-  // keys: items ordered as the cache stores them -- (head, 8-dim chunk, t, row) with 8 rows of a 16-token job
-  // contiguous -- so that eight lanes write one 128-byte line; the staged rows are read in 16-byte pieces
+  // keys: four lanes take 32 head dims of a key (a row of the cache), the next ones the rows behind it
 #pragma unroll 2
-  for (int item = first; item < 16 * nch; item += step) {
-    const int r8 = item & 7, t = (item >> 3) & 1, unit = item >> 4;
+  for (int item = first; item < 16 * ((nch + 3) & ~3); item += step) {
+    const int r8 = (item >> 2) & 7, t = (item >> 5) & 1, unit = (item >> 6) * 4 + (item & 3);
     const int tok = 8 * (r8 >> 2) + 4 * t + (r8 & 3);
-    if (tok >= ntok) continue;
+    if (tok >= ntok || unit >= nch) continue;
     const int head = (int)(((float)(unit << 3) + 0.5f) * inv_h), dim = (unit << 3) - head * a.h;
     const u32x4 w = *(const u32x4*)(stage + (size_t)tok * ld + (unit << 3));
     const long long o = a.lay.k_elem(jb.qblock * 16 + tok, dim);
@@ -341,30 +359,18 @@ __global__ __launch_bounds__(256) void kv_prefill_kernel(RopeArgs a) {
       *(u32x4*)(a.kv + a.lay.stream(a.kv_off[s], a.kv_cap[s], head) + o) = w;
     }
   }
-  // values: a thread takes 8 head dims of 8 consecutive tokens (8 row-contiguous 16-byte loads), transposes them
-  // in registers and writes the 8 units (one per head dim, 8 keys each), which are 128 contiguous bytes
-  for (int item = first; item < 2 * nch; item += step) {
-    const int grp = item / nch, unit = item - grp * nch;
+  // values: a thread takes 4 head dims of 8 consecutive tokens (8 row-contiguous 8-byte loads)
+  for (int item = first; item < 4 * nch; item += step) {
+    const int grp = item / (2 * nch), unit = item - grp * 2 * nch;
     if (grp * 8 >= ntok) continue;
-    const int head = (int)(((float)(unit << 3) + 0.5f) * inv_h), dim = (unit << 3) - head * a.h;
-    u32x4 b[8];
+    const int head = (int)(((float)(unit << 2) + 0.5f) * inv_h), dim = (unit << 2) - head * a.h;
+    u32x2 b[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      b[i] = grp * 8 + i < ntok ? *(const u32x4*)(stage + (size_t)(grp * 8 + i) * ld + per_group + (unit << 3)) : u32x4{0, 0, 0, 0};
-    u32x4 w[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t lo = b[2 * e][j >> 1], hi = b[2 * e + 1][j >> 1];
-        w[j][e] = (j & 1) ? ((lo >> 16) | (hi & 0xffff0000u)) : ((lo & 0xffffu) | (hi << 16));
-      }
-    const long long o = a.lay.v_elem(jb.qblock * 16 + grp * 8, dim);
+      b[i] = grp * 8 + i < ntok ? *(const u32x2*)(stage + (size_t)(grp * 8 + i) * ld + per_group + (unit << 2)) : u32x2{0, 0};
     for (int cpy = 0; cpy < a.ncopy; ++cpy) {
       const int s = jb.cache_seq + cpy;
-      u32x4* dst = (u32x4*)(a.kv + a.lay.stream(a.kv_off[s], a.kv_cap[s], head) + o);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) dst[j] = w[j];
+      put_values(a.kv + a.lay.stream(a.kv_off[s], a.kv_cap[s], head), a.lay, jb.qblock * 16 + grp * 8, dim, b);
     }
   }
 }

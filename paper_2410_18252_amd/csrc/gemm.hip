@@ -150,8 +150,10 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
     const bool staged = STAGED || e.kvstage != nullptr;
     auto live = [&](int i) { return FULL || wrow0 + i * 16 + frow < g.M; };
     uint32_t rope[TM];       // byte offset of the row's angles: at most 2^20 positions of 128 pairs
-    [[maybe_unused]] long long k_at[STAGED ? 1 : TM], v_at[STAGED ? 1 : TM];     // the row's first key / value element in the cache
+    // a row's place in the cache: its stream's super-block, and the key's row and place in the two kinds of value units
+    [[maybe_unused]] long long kv_at[STAGED ? 1 : TM];
     [[maybe_unused]] int per_head[STAGED ? 1 : TM];                              // elements between kv heads
+    [[maybe_unused]] int slot[STAGED ? 1 : TM];
     {
       int pos[TM];
       [[maybe_unused]] int seq[TM], sub[TM];
@@ -171,8 +173,8 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
           if (!staged) {
             const long long base = e.lay.seq_base(e.kv_off[seq[i]]);
             per_head[i] = 2 * e.kv_cap[seq[i]] * e.h;
-            k_at[i] = base + e.lay.k_elem(pos[i] - sub[i], 0);
-            v_at[i] = base + e.lay.v_elem(pos[i] - sub[i], 0);
+            slot[i] = (pos[i] - sub[i]) & 31;
+            kv_at[i] = base + (long long)((pos[i] - sub[i]) >> 5) * 64 * e.h;
           }
         }
       }
@@ -261,21 +263,36 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
             *(u32x2*)(p + d0) = w;
           }
         } else if constexpr (!STAGED) {
+          uint16_t* st = e.kv + kv_at[i];
           if (c.head < e.Hq + e.Hkv) {
-            // eight dims of a key are 16 bytes, the next eight 256 bytes further
-            uint16_t* st = e.kv + k_at[i] + (long long)(c.head - e.Hq) * per_head[i];
-            *(uint32_t*)(st + ((d0 >> 3) << 7) + (d0 & 7)) = w01;
-            *(uint32_t*)(st + ((d1 >> 3) << 7) + (d1 & 7)) = w23;
-            if constexpr (PR) {
-              *(uint32_t*)(st + e.kv_lo_off + ((d0 >> 3) << 7) + (d0 & 7)) = wl[0];
-              *(uint32_t*)(st + e.kv_lo_off + ((d1 >> 3) << 7) + (d1 & 7)) = wl[1];
+            st += (long long)(c.head - e.Hq) * per_head[i] + ((slot[i] >> 2) & 1) * 16 * e.h;
+            const int r = e.lay.k_row(slot[i]);
+            uint16_t* s0 = st + e.lay.k_dim(d0) + r * e.lay.k_width(d0);
+            uint16_t* s1 = st + e.lay.k_dim(d1) + r * e.lay.k_width(d1);
+            if (any_rot) {
+              *(uint32_t*)s0 = w01;
+              *(uint32_t*)s1 = w23;
+              if constexpr (PR) {
+                *(uint32_t*)(s0 + e.kv_lo_off) = wl[0];
+                *(uint32_t*)(s1 + e.kv_lo_off) = wl[1];
+              }
+            } else {
+              *(u32x2*)s0 = u32x2{w01, w23};
+              if constexpr (PR) *(u32x2*)(s0 + e.kv_lo_off) = wl;
             }
           } else {
-            uint16_t* st = e.kv + v_at[i] + (long long)(c.head - e.Hq - e.Hkv) * per_head[i] + ((c.p0 >> 4) << 9) + ((c.p0 & 15) << 3);
-            st[0] = (uint16_t)w01; st[8] = (uint16_t)(w01 >> 16); st[16] = (uint16_t)w23; st[24] = (uint16_t)(w23 >> 16);
-            if constexpr (PR) {
-              st += e.kv_lo_off;
-              st[0] = (uint16_t)wl[0]; st[8] = (uint16_t)(wl[0] >> 16); st[16] = (uint16_t)wl[1]; st[24] = (uint16_t)(wl[1] >> 16);
+            st += (long long)(c.head - e.Hq - e.Hkv) * per_head[i];
+            if (e.lay.v_grouped(c.p0)) {
+              st += e.lay.v_key_grouped(slot[i]) + e.lay.v_dim_grouped(c.p0);
+              *(u32x2*)st = u32x2{w01, w23};
+              if constexpr (PR) *(u32x2*)(st + e.kv_lo_off) = wl;
+            } else {
+              st += e.lay.v_key_rest(slot[i]) + e.lay.v_dim_rest(c.p0);
+              st[0] = (uint16_t)w01; st[8] = (uint16_t)(w01 >> 16); st[16] = (uint16_t)w23; st[24] = (uint16_t)(w23 >> 16);
+              if constexpr (PR) {
+                st += e.kv_lo_off;
+                st[0] = (uint16_t)wl[0]; st[8] = (uint16_t)(wl[0] >> 16); st[16] = (uint16_t)wl[1]; st[24] = (uint16_t)(wl[1] >> 16);
+              }
             }
           }
         }

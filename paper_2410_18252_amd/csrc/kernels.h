@@ -8,28 +8,51 @@
 // decode step reads the stream front to back.  Inside a super-block the elements are ordered so
 // that every MFMA operand fragment the attention kernel needs is one 16-byte unit and every
 // wave-wide load instruction reads one contiguous kilobyte:
-//   K super-block: [t = 0..1][chunk = 0..h/8-1][r = 0..15][8 head dims]
-//                  holding key 8 (r / 4) + 4 t + r % 4, head dims 8 chunk .. 8 chunk + 7
-//   V super-block: [tile = 0..h/16-1][g = 0..3][r = 0..15][8 keys]
-//                  holding head dim 16 tile + r, keys 8 g .. 8 g + 7
+//   K super-block: [t = 0..1][step = 0..ceil(h/32)-1][r = 0..15][up to 32 head dims]
+//                  holding key 8 (r / 4) + 4 t + r % 4, head dims 32 step .. (the last step has 16 dims if h % 32 is 16)
+//   V super-block, whole groups of 64 head dims: [group][p = 0..3][g = 0..3][c = 0..15][2 keys][4 head dims]
+//                  holding keys 8 g + 2 p, + 1, head dims 64 group + 4 c .. + 3
+//   and the dims behind the last whole group: [tile of 16 dims][g = 0..3][r = 0..15][8 keys]
+//                  holding head dim r of the tile, keys 8 g .. 8 g + 7
+// A decode step writes one key and one value per stream, and every 64-byte sector it touches only in part is read, merged and
+// written back to HBM, so a token's dims lie close: h / 32 whole sectors of keys and h / 16 of values (with the 16-byte units
+// of 8 dims and of 8 keys in rows the token touched h / 8 + h / 4).
 // Streams of a sequence: head 0..Hkv-1; sequences follow each other at token offsets kv_off[s];
 // layers are max_kv_tokens * Hkv * h * 2 elements apart.
 struct KvLayout {
   int Hkv, h;
+  // Precise mode, whose prompt pass reads two planes and is 20 % slower on the rows above, keeps units of 8 dims and of 8 keys:
+  int kshift;              // a key's step has up to 2^kshift dims: 5, or 3
+  int vdims;               // head dims in whole groups of 64, or 0
   long long layer_stride;  // elements between layers
   __host__ __device__ long long seq_base(long long kv_off) const { return 2LL * kv_off * Hkv * h; }
   __host__ __device__ long long stream(long long kv_off, int cap, int head) const {
     return seq_base(kv_off) + (long long)head * 2 * cap * h;
   }
-  // element offset of key / value (key, dim) inside a stream
-  __host__ __device__ long long k_elem(int key, int dim) const {
-    const int sb = key >> 5, kk = key & 31;
-    const int r = 4 * (kk >> 3) + (kk & 3), t = (kk >> 2) & 1;
-    return (long long)sb * 64 * h + (((t * (h >> 3) + (dim >> 3)) * 16 + r) << 3) + (dim & 7);
+  // element offset of key / value (key, dim) inside a stream, as a part of the key's and one of the dim
+  __host__ __device__ static int k_row(int key) { return 4 * ((key & 31) >> 3) + (key & 3); }
+  __host__ __device__ int k_width(int dim) const {          // dims of a row in dim's step
+    const int w = 1 << kshift;
+    return (dim | (w - 1)) < h ? w : 16;
   }
+  __host__ __device__ int k_dim(int dim) const { return ((dim >> kshift) << (kshift + 4)) + (dim & ((1 << kshift) - 1)); }
+  __host__ __device__ long long k_elem(int key, int dim) const {
+    return (long long)(key >> 5) * 64 * h + ((key >> 2) & 1) * 16 * h + k_dim(dim) + k_row(key) * k_width(dim);
+  }
+  __host__ __device__ bool v_grouped(int dim) const { return dim < vdims; }
+  // of the key: super-block and place for a dim of a whole group / of the rest
+  __host__ __device__ long long v_key_grouped(int key) const {
+    const int kk = key & 31;
+    return (long long)(key >> 5) * 64 * h + 32 * h + ((((kk >> 1) & 3) * 4 + (kk >> 3)) << 7) + ((kk & 1) << 2);
+  }
+  __host__ __device__ long long v_key_rest(int key) const {
+    const int kk = key & 31;
+    return (long long)(key >> 5) * 64 * h + 32 * h + ((kk >> 3) << 7) + (kk & 7);
+  }
+  __host__ __device__ static int v_dim_grouped(int dim) { return ((dim >> 6) << 11) + (((dim >> 2) & 15) << 3) + (dim & 3); }
+  __host__ __device__ static int v_dim_rest(int dim) { return ((dim >> 4) << 9) + ((dim & 15) << 3); }      // (a whole group is four tiles long)
   __host__ __device__ long long v_elem(int key, int dim) const {
-    const int sb = key >> 5, kk = key & 31;
-    return (long long)sb * 64 * h + 32 * h + (((((dim >> 4) * 4 + (kk >> 3)) * 16) + (dim & 15)) << 3) + (kk & 7);
+    return v_grouped(dim) ? v_key_grouped(key) + v_dim_grouped(dim) : v_key_rest(key) + v_dim_rest(dim);
   }
 };
 

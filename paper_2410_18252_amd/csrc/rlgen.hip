@@ -210,6 +210,8 @@ size_t carve(rlgen_ctx* c, char* base) {
   c->rope = k.take<float2>(base, (size_t)m.max_seq_len * (m.rotary_dim / 2 > 0 ? m.rotary_dim / 2 : 1));
   c->lay.Hkv = m.n_kv_heads;
   c->lay.h = m.head_dim;
+  c->lay.kshift = m.precise ? 3 : 5;
+  c->lay.vdims = m.precise ? 0 : m.head_dim / 64 * 64;
   c->lay.layer_stride = 2LL * m.max_kv_tokens * m.n_kv_heads * m.head_dim;
   c->pw = m.precise ? 2 : 1;
   c->kv_plane = c->lay.layer_stride * m.n_layers;

@@ -350,3 +350,33 @@ def test_decode_steps_return_the_same_bits_on_every_tile_shape(name, precise):
     for b in (0, 64, 130):
         want = O.score(dec, np.concatenate([prompts[b], t[b, 0]]), 0.7, score_from=int(lens[b]))[lens[b]:]
         assert np.abs(lp[b, 0] - want).max() < TOL_LOGPROB
+
+
+# every way a key's and a value's head dims divide in the cache: steps of 32 dims with and without a rest of 16, whole groups of
+# 64 dims and 0 to 3 tiles behind them; rotary pairs inside a step and across steps
+@pytest.mark.parametrize("precise", [0, 1])
+@pytest.mark.parametrize("h, rot", [(16, 16), (32, 8), (48, 48), (64, 16), (64, 6), (80, 20), (96, 96), (112, 28), (128, 128), (256, 64)])
+def test_decode_steps_read_what_the_prompt_pass_and_they_wrote(h, rot, precise):
+    """Prompts of 27 and 32 tokens and 40 decoded ones (pairs, groups of eight and super-blocks begin and end in both): the
+    same log-probs as one prompt pass over all of them."""
+    if precise and (h == 256 or rot % 4):
+        pytest.skip("no precise mode for this shape")
+    m = ModelShape(0, 2, 2 * h, 2, 2, h, 128, 210, rotary_dim=rot)
+    W = scaled_bf16_weights(m)
+    rng = np.random.default_rng(41)
+    lens, T = [27, 32], 40
+    arr, lens = padded([rng.integers(0, m.vocab, size=n) for n in lens])
+    forced = rng.integers(0, m.vocab, size=(2, 1, T)).astype(np.int32)
+    r = R()
+    pol = make_policy(W, max_seqs=2, max_seq_len=72, precise=precise)
+    try:
+        _, lp = r.rlgen_generate(pol, dev_i32(arr), lens, 1, T, 0.7, dev_f32(np.zeros((2, 1, T))), dev_i32(forced))
+        full = np.zeros((2, 72), np.int32)
+        for b in range(2):
+            full[b, :lens[b] + T] = np.concatenate([arr[b, :lens[b]], forced[b, 0]])
+        sc = r.rlgen_score(pol, dev_i32(full), [n + T for n in lens], 0.7).cpu().numpy()
+        assert r.rlgen_status(pol) == 0
+    finally:
+        pol.close()
+    for b in range(2):
+        assert np.abs(lp.cpu().numpy()[b, 0] - sc[b, lens[b]:lens[b] + T]).max() < (TOL_LOGPROB / 20 if precise else TOL_LOGPROB)
