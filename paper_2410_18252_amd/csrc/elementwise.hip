@@ -146,15 +146,34 @@ __global__ __launch_bounds__(256) void norm_kernel(const float* x, const int* ro
   if constexpr (WIDE) {
     if (parts.ws) {
       // the row is still waiting for a split product: its parts in their order, the bias, the residual (as the split
-      // product's own second pass adds them), and back to the residual stream
+      // product's own second pass adds them), and back to the residual stream.  Four parts are requested at once: one behind
+      // the other they are eight waits for memory (16 rows at d = 2048, 8 parts: 9.9 us)
+      constexpr int AT_ONCE = NV <= 4 ? 4 : 2;
+      f32x4 y[NV];
+#pragma unroll
+      for (int i = 0; i < NV; ++i) y[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int sp0 = 0; sp0 < parts.splits; sp0 += AT_ONCE) {
+        f32x4 p[AT_ONCE][NV];
+#pragma unroll
+        for (int s = 0; s < AT_ONCE; ++s)
+          if (sp0 + s < parts.splits) {
+#pragma unroll
+            for (int i = 0; i < NV; ++i)
+              if (col_of(i, 0) < d) p[s][i] = *(const f32x4*)(parts.ws + ((size_t)(sp0 + s) * rows + row) * d + col_of(i, 0));
+          }
+#pragma unroll
+        for (int s = 0; s < AT_ONCE; ++s)
+          if (sp0 + s < parts.splits) {
+#pragma unroll
+            for (int i = 0; i < NV; ++i) y[i] += p[s][i];
+          }
+      }
 #pragma unroll
       for (int i = 0; i < NV; ++i) {
         const int col = col_of(i, 0);
         if (col >= d) continue;
-        f32x4 y = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int sp = 0; sp < parts.splits; ++sp) y += *(const f32x4*)(parts.ws + ((size_t)sp * rows + row) * d + col);
-        if (parts.bias) y += *(const f32x4*)(parts.bias + col);
-        v[i][0] += y;
+        if (parts.bias) y[i] += *(const f32x4*)(parts.bias + col);
+        v[i][0] += y[i];
         *(f32x4*)(parts.x + (size_t)row * d + col) = v[i][0];
       }
     }

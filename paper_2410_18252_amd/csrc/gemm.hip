@@ -5,11 +5,10 @@
 // block's tile is one contiguous run in memory and every MFMA operand fragment is one 16-byte LDS read.
 // A block of WM x WN waves owns a BM x BN tile; each wave a (BM/WM) x (BN/WN) sub-tile built from 16x16x32
 // MFMAs.  A and W tiles of depth 64 go from global memory straight into LDS (16-byte chunks, XOR-swizzled by
-// row so that fragment reads spread over all banks).  Four main loops share the epilogues and the matrix instruction,
+// row so that fragment reads spread over all banks).  Three main loops share the epilogues and the matrix instruction,
 // which walks K front to back in all of them: gemm_f16_kernel (two stages, one barrier per K step; a K that is not a
 // multiple of 64 takes its older path through registers, which can zero-fill the tail), gemm_big_kernel (256x256 on four
-// waves, for launches that fill the chip), gemm_ring_kernel (as many stages as LDS holds, for launches that do not) and
-// gemm_skinny_kernel (K divided among the waves of a block, for the fewest rows).
+// waves, for launches that fill the chip) and gemm_ring_kernel (a ring of stages, for launches that do not).
 #include "kernels.h"
 #include <algorithm>
 #include <type_traits>
@@ -779,17 +778,20 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmArgs g) {
 // the next stage and the only barrier of a K step sit between its two slices, where every wave holds fragments for the
 // second; behind the barrier nobody reads the stage before any more, whose slot is requested anew.  No branch in the loop.
 // What bounds these launches is the latency of the weights (1 us from another XCD's side of the chip, 1.8 us from HBM) over
-// the bytes a CU has in flight, so the ring takes most of LDS.  Measured with weights from HBM (us, the two-stage loop's best
-// tile in parentheses): 64x64 on four waves, 128 rows, N x K = 2560 x 2560 9.2 (15.2), 6144 x 2048 8.8 (13.6); 128x128 on
-// eight waves, 512 rows, 7680 x 2560 23.5 (29.8), 6144 x 4096 38.0 (54.7), 1024 rows, 2560 x 2560 19.5 (24.4); 256x128, 1024
-// rows, 7680 x 2560 43.9 (48.8); 64x128 on four waves as the parts of a K split, 128 rows, 2560 x 10240 21.7 (26.2).
+// the bytes a CU has in flight, and the number of CUs that have a block, so the shapes go from 32x32 (several blocks to a CU) to
+// 256x128 (most of LDS).  Measured with weights from HBM (us): 32x32, 16 rows, N x K = 3072 x 1024 4.8, 6144 x 2048 7.1, 6144 x
+// 4096 11.3 (64x64 6.8, 10.5, 18.9); 32x64, 64 rows, 6144 x 2048 9.5 (64x64 11.8); 64x64, 128 rows, 4096 x 1024 7.4 and as the 8
+// parts of a K split 1024 x 5120 6.6; 64x96 (64x128), 256 rows, 6144 x 4096 25.4 (28.4); 128x64, 256 rows, 8192 x 2048 16.4 (17.1);
+// 32x128, 16 rows, 28672 x 4096 38.2 (128x128 42.0); 256x128, 1024 rows, 7680 x 2560 43.9 (two-stage loop 48.8).  K divided among the waves of a block instead, operands straight to registers: 16
+// rows, 6144 x 2048 8.3, 2048 x 10240 21.2 (64x64 in 8 parts 9.5), 128 rows, 4096 x 1024 8.6: such operands are 64-byte pieces
+// of sixteen rows, which a CU takes in at a third of the rate of the kilobytes that go to LDS.
 template <int BM, int BN, int WM, int WN, int NS, int EPI, bool PR = false>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_ring_kernel(GemmArgs g) {
   constexpr int NW = WM * WN;                            // waves
   constexpr int TM = BM / WM / 16, TN = BN / WN / 16;    // 16x16 tiles of a wave
   constexpr int LA = BM / 8 / NW, LB = BN / 8 / NW, L = LA + LB;     // requests per wave and stage, 8 rows each
   constexpr int STAGE = (BM + BN) * BK;
-  static_assert(NS >= 3 && NS <= 6 && LA >= 1 && LB >= 1, "whole requests");
+  static_assert(NS >= 3 && (NS - 2) * L < 64 && BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "whole requests, as many as a wait can count");
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];   // NS stages
   __builtin_amdgcn_s_setprio(3);       // ahead of the other half's attention (see gemm_f16_kernel)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -847,21 +849,23 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_ring_kernel(GemmArgs g) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   constexpr int T = TM * TN, R = TM + TN;
-  static_assert(R <= T, "at most one read and one request behind a product");
-  static_assert(L <= T, "at most one request");
   auto slice = [&](int ks, auto&& rd, auto&& rq) {
 #pragma unroll
     for (int n = 0; n < T; ++n) {
       acc[n / TN][n % TN] = mfma16<PR>(fb[ks][n % TN], fa[ks][n / TN], acc[n / TN][n % TN]);
       SCHED_FENCE();
-      if ((n + 1) * R / T > n * R / T) rd(n * R / T);
-      if ((n + 1) * L / T > n * L / T) rq(n * L / T);
+#pragma unroll
+      for (int r = n * R / T; r < (n + 1) * R / T; ++r) rd(r);
+#pragma unroll
+      for (int l = n * L / T; l < (n + 1) * L / T; ++l) rq(l);
       SCHED_FENCE();
     }
   };
 #define RING_WAIT(N) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory")
   auto wait_younger = [&](int stages) {     // all but the `stages` youngest stages of this wave have landed; then everybody is here
-    if (stages >= 4) RING_WAIT(4 * L);
+    if (stages >= NS - 2) RING_WAIT((NS - 2) * L);
+    else if (NS > 10 && stages >= 8) RING_WAIT(8 * L);
+    else if (NS > 6 && stages >= 4) RING_WAIT(4 * L);
     else if (stages == 3) RING_WAIT(3 * L);
     else if (stages == 2) RING_WAIT(2 * L);
     else if (stages == 1) RING_WAIT(L);
@@ -903,107 +907,6 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_ring_kernel(GemmArgs g) {
   gemm_epilogue<TM, TN, EPI, PR>(g, acc, row0 + wm * (BM / WM), col0 + wn * (BN / WN), lane, split);
 }
 #undef RING_WAIT
-
-// Few rows (a decode step of a small batch): the product is bound by the time the weights take to arrive, and a 64x128
-// tile per block leaves most CUs without one.  Here a block owns a tile of 16 TM x 16 TN (16 to 64 on a side) and its eight
-// waves divide K among themselves, wave w taking the K blocks w, w + 8, ... straight from memory into matrix operands; the
-// eight partial tiles meet in LDS and are added in the order of the waves.  One launch with any epilogue, where the K split
-// over blocks takes a second one and has no form for QKV.  A sum's order depends on K alone, not on the tile or the rows.
-// Measured (weights from HBM, us): 16 rows, N x K = 3072 x 1024 4.2 (64x128 tiles 7.4), 6144 x 2048 8.7 (13.8), 8192 x 2048
-// 9.0 (split-K 12.9), 2560 x 10240 21.5 (23.2); 128 rows, 1024 x 1024 4.9 (8.6).  Operands that go to registers arrive at
-// about 34 bytes a nanosecond and CU, a third of what the direct loads to LDS reach, so the tiles win where a block has
-// more than 256 KB to fetch: 64 rows, 2560 x 10240 38 (split-K 24).
-template <int TM, int TN, int EPI>
-__global__ __launch_bounds__(SKINNY_WAVES * 64) void gemm_skinny_kernel(GemmArgs g) {
-  constexpr int NW = SKINNY_WAVES;
-  __builtin_amdgcn_s_setprio(3);       // as the other products: beside another half's attention the GEMM goes first
-  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
-  f32x4 (*red)[TM * TN][64] = (f32x4 (*)[TM * TN][64])lds;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int tiles_m = (g.M + 16 * TM - 1) / (16 * TM), tiles_n = (g.N + 16 * TN - 1) / (16 * TN);
-  int tile_m, tile_n, split;
-  tile_of_block(tiles_m, tiles_n, 1, tile_m, tile_n, split);
-  const int row0 = tile_m * 16 * TM, col0 = tile_n * 16 * TN;
-  const int frow = lane & 15, fq = lane >> 4;
-  const char* const a0 = (const char*)g.A + (size_t)row0 * 128;      // 32-bit distances stay inside the tile
-  const char* const w0 = (const char*)g.W + (size_t)col0 * 128;
-  uint32_t va[TM], vb[TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i) va[i] = (uint32_t)min(i * 16 + frow, g.M - 1 - row0) * 128 + fq * 16;
-#pragma unroll
-  for (int j = 0; j < TN; ++j) vb[j] = (uint32_t)min(j * 16 + frow, g.N - 1 - col0) * 128 + fq * 16;
-  const size_t ka = (size_t)g.M * 128, kw = (size_t)g.N * 128;
-  const int nkb = g.K / BK;
-  f16x8 fa[2][TM][2], fb[2][TN][2];
-  auto load = [&](int kb, int slot) {
-    const char* a = a0 + (size_t)kb * ka;
-    const char* w = w0 + (size_t)kb * kw;
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) fb[slot][j][s] = *(const f16x8*)(w + vb[j] + s * 64);
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int i = 0; i < TM; ++i) fa[slot][i][s] = *(const f16x8*)(a + va[i] + s * 64);
-  };
-  f32x4 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto mma = [&](int slot) {
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = mfma16<false>(fb[slot][j][s], fa[slot][i][s], acc[i][j]);
-  };
-  if (wave < nkb) {
-    load(wave, 0);
-    int kb = wave;
-#pragma unroll 1
-    for (; kb + 2 * NW < nkb; kb += 2 * NW) {
-      load(kb + NW, 1);
-      mma(0);
-      load(kb + 2 * NW, 0);
-      mma(1);
-    }
-    if (kb + NW < nkb) {
-      load(kb + NW, 1);
-      mma(0);
-      mma(1);
-    } else {
-      mma(0);
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) red[wave][i * TN + j][lane] = acc[i][j];
-  __syncthreads();
-  if constexpr (EPI == EPI_SWIGLU_F16) {
-    for (int i = wave; i < TM; i += NW) {
-      f32x4 v[1][TN];
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        v[0][j] = red[0][i * TN + j][lane];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) v[0][j] += red[w][i * TN + j][lane];
-      }
-      if (row0 + i * 16 < g.M) gemm_epilogue<1, TN, EPI, false>(g, v, row0 + i * 16, col0, lane, 0);
-    }
-  } else {
-    for (int t = wave; t < TM * TN; t += NW) {
-      f32x4 v[1][1];
-      v[0][0] = red[0][t][lane];
-#pragma unroll
-      for (int w = 1; w < NW; ++w) v[0][0] += red[w][t][lane];
-      if (row0 + t / TN * 16 < g.M && col0 + t % TN * 16 < g.N) gemm_epilogue<1, 1, EPI, false>(g, v, row0 + t / TN * 16, col0 + t % TN * 16, lane, 0);
-    }
-  }
-}
 
 // Second half of a split-K product: sums the partial results in split order (so the result does not depend
 // on scheduling) and applies the epilogue.
@@ -1073,56 +976,6 @@ hipError_t launch_big(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int TM, int TN, int EPI>
-hipError_t launch_skinny(const GemmArgs& g, hipStream_t s) {
-  constexpr int lds_bytes = SKINNY_WAVES * TM * TN * 64 * 16;
-  static bool configured_on[64] = {};       // once per device (a repeated call is harmless, so no lock)
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-  if (lds_bytes > 65536 && !configured_on[dev]) {
-    hipError_t e = hipFuncSetAttribute((const void*)gemm_skinny_kernel<TM, TN, EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-    if (e != hipSuccess) return e;
-    configured_on[dev] = true;
-  }
-  const int tiles = ((g.M + 16 * TM - 1) / (16 * TM)) * ((g.N + 16 * TN - 1) / (16 * TN));
-  hipLaunchKernelGGL((gemm_skinny_kernel<TM, TN, EPI>), dim3(tiles), dim3(SKINNY_WAVES * 64), lds_bytes, s, g);
-  return hipGetLastError();
-}
-
-// The tile that leaves the busiest CU the fewest rows and columns to fetch; of equals the largest.
-struct SkinnyTile { int tm, tn; long long cost; };      // cost: rows + columns over all blocks of the busiest CU
-SkinnyTile skinny_tile(int M, int N, int epi) {
-  SkinnyTile best{0, 0, 1LL << 60};
-  for (int tm = 1; tm <= 4; tm *= 2)
-    for (int tn = epi == EPI_SWIGLU_F16 ? 4 : 1; tn <= 4; tn *= 2) {      // SwiGLU: gates and ups of 32 features
-      const long long blocks = (long long)((M + 16 * tm - 1) / (16 * tm)) * ((N + 16 * tn - 1) / (16 * tn));
-      const long long cost = (blocks + 255) / 256 * 16 * (tm + tn);
-      if (cost <= best.cost) best = {tm, tn, cost};
-    }
-  return best;
-}
-
-template <int EPI>
-hipError_t launch_skinny_tile(const GemmArgs& g, hipStream_t s) {
-  const SkinnyTile t = skinny_tile(g.M, g.N, EPI);
-  switch (t.tm * 8 + t.tn) {
-    case 12: return launch_skinny<1, 4, EPI>(g, s);
-    case 20: return launch_skinny<2, 4, EPI>(g, s);
-    case 36: return launch_skinny<4, 4, EPI>(g, s);
-  }
-  if constexpr (EPI != EPI_SWIGLU_F16) {
-    switch (t.tm * 8 + t.tn) {
-      case 9: return launch_skinny<1, 1, EPI>(g, s);
-      case 10: return launch_skinny<1, 2, EPI>(g, s);
-      case 17: return launch_skinny<2, 1, EPI>(g, s);
-      case 18: return launch_skinny<2, 2, EPI>(g, s);
-      case 33: return launch_skinny<4, 1, EPI>(g, s);
-      case 34: return launch_skinny<4, 2, EPI>(g, s);
-    }
-  }
-  return hipErrorInvalidValue;
-}
-
 template <int BM, int BN, int WM, int WN, int NS, int EPI, bool PR = false>
 hipError_t launch_ring(const GemmArgs& g, hipStream_t s) {
   constexpr int lds_bytes = NS * (BM + BN) * BK * (int)sizeof(uint16_t);
@@ -1172,23 +1025,30 @@ hipError_t launch_variant(const GemmArgs& g, int variant, hipStream_t s) {
   const bool whole = g.K % BK == 0;
   switch (variant) {
     case 0: return launch<128, 128, 2, 2, EPI>(g, s);
-    case 1: return launch<256, 128, 2, 2, EPI>(g, s);
     case 2: return whole ? launch_ring<128, 128, 4, 2, 4, EPI>(g, s) : launch_k<128, 128, 2, 2, EPI, true, 0>(g, s);
     case 3:
       // (a K split is for shapes with few tiles: partial sums come from 256x128 at most, and so do a decode step's cache writes)
       if (EPI == EPI_PARTIAL || (EPI == EPI_QKV && !g.qe.kvstage)) return launch<256, 128, 4, 2, EPI>(g, s);
       if constexpr (EPI != EPI_PARTIAL) return launch_big<EPI, false>(g, s);
       break;
-    case 4: return launch<128, 256, 2, 2, EPI>(g, s);
     case 5: return launch<256, 128, 4, 2, EPI>(g, s);
     case 10: return whole ? launch_ring<256, 128, 4, 2, 3, EPI>(g, s) : launch_k<256, 128, 4, 2, EPI, true, 0>(g, s);
   }
-  if constexpr (!WIDE) {
+  if constexpr (WIDE) {
+    if (!whole) return launch_k<128, 128, 2, 2, EPI, true, 0>(g, s);
     switch (variant) {
-      case 6: return whole ? launch_ring<64, 64, 2, 2, 5, EPI>(g, s) : launch_k<64, 128, 1, 4, EPI, true, 0>(g, s);
-      case 7: return launch<64, 128, 1, 4, EPI>(g, s);
-      case 8: return whole ? launch_ring<64, 128, 2, 2, 6, EPI>(g, s) : launch_k<64, 128, 1, 4, EPI, true, 0>(g, s);
-      case 9: return whole ? launch_ring<64, 128, 2, 4, 6, EPI>(g, s) : launch_k<64, 128, 1, 4, EPI, true, 0>(g, s);
+      case 1: return launch_ring<32, 128, 2, 2, 7, EPI>(g, s);
+      case 4: return launch_ring<64, 128, 2, 2, 6, EPI>(g, s);
+    }
+  } else {
+    if (!whole) return launch_k<64, 128, 1, 4, EPI, true, 0>(g, s);
+    switch (variant) {
+      case 1: return launch_ring<32, 32, 2, 2, 8, EPI>(g, s);
+      case 4: return launch_ring<32, 64, 2, 2, 6, EPI>(g, s);
+      case 6: return launch_ring<64, 64, 2, 2, 5, EPI>(g, s);
+      case 7: return launch_ring<128, 64, 4, 2, 6, EPI>(g, s);
+      case 8: return launch_ring<64, 96, 2, 2, 7, EPI>(g, s);
+      case 9: return launch_ring<64, 128, 2, 4, 6, EPI>(g, s);
     }
   }
   return hipErrorInvalidValue;
@@ -1226,29 +1086,6 @@ hipError_t rl_gemm_variant(const GemmArgs& g, int epi, int variant, hipStream_t 
   return hipErrorInvalidValue;
 }
 
-bool rl_gemm_skinny_pays(int cap_rows, int N, int K, int epi) {
-  if (K % BK != 0 || N % 16 != 0 || (epi == EPI_SWIGLU_F16 && N % 64 != 0)) return false;
-  if (epi != EPI_F32 && epi != EPI_RESID && epi != EPI_GELU_F16 && epi != EPI_SWIGLU_F16 && epi != EPI_QKV) return false;
-  // While a CU fetches no more than 256 KB (see the kernel), and up to 16 rows whatever it fetches.  A decode layer over 64 keys
-  // (us): of 16 rows with the long K divided inside the block / by tiles and split-K, Llama 3072 wide 104 / 110 and 4096 wide 163 /
-  // 161, GPT-NeoX 5120 wide 227 / 245, 2560 wide 87 / 86, 2048 wide 62 / 56 and 1024 wide 35 / 31; of 32 rows (within 256 KB /
-  // always divided) 63 / 75 at 2048, 91 / 104 at 2560 and 208 / 279 at 5120, but 124 / 109 and 175 / 169 for the Llama widths; of
-  // 128 rows 52 / 57, 98 / 123, 131 / 196 and 309 / 514, 149 / 192 and 202 / 320.
-  return cap_rows <= 16 || (cap_rows <= 128 && skinny_tile(cap_rows, N, epi).cost * K * 2 <= 256 * 1024);
-}
-hipError_t rl_gemm_skinny(const GemmArgs& g, int epi, hipStream_t s) {
-  if (g.M <= 0 || g.N <= 0) return hipSuccess;
-  if (g.precise || g.K % BK != 0 || g.N % 16 != 0 || (epi == EPI_RESID && g.ldo % 4 != 0)) return hipErrorInvalidValue;
-  switch (epi) {
-    case EPI_F32: return launch_skinny_tile<EPI_F32>(g, s);
-    case EPI_RESID: return launch_skinny_tile<EPI_RESID>(g, s);
-    case EPI_GELU_F16: return launch_skinny_tile<EPI_GELU_F16>(g, s);
-    case EPI_SWIGLU_F16: return g.N % 64 == 0 ? launch_skinny_tile<EPI_SWIGLU_F16>(g, s) : hipErrorInvalidValue;
-    case EPI_QKV: return valid_qkv(g) ? launch_skinny_tile<EPI_QKV>(g, s) : hipErrorInvalidValue;
-  }
-  return hipErrorInvalidValue;
-}
-
 // Split-K: `splits` blocks per tile each take a share of K and write fp32 partial tiles to g.ws
 // ([splits, M, N]); a second kernel adds them in order and applies the epilogue.
 hipError_t rl_gemm_parts(const GemmArgs& g, int variant, hipStream_t s) {
@@ -1279,7 +1116,7 @@ hipError_t rl_gemm(const GemmArgs& g, int epi, hipStream_t s) {
   if (tiles(256, 256) >= 160) variant = 3;
   else if (tiles(256, 128) >= 200) variant = 5;
   else if (tiles(128, 128) >= 400 || wide_only) variant = 0;
-  else variant = 7;
-  if (g.splits >= 2 && g.ws) return rl_gemm_splitk(g, epi, wide_only ? 0 : 7, s);
+  else variant = g.precise ? 7 : 9;
+  if (g.splits >= 2 && g.ws) return rl_gemm_splitk(g, epi, wide_only ? 0 : g.precise ? 7 : 9, s);
   return rl_gemm_variant(g, epi, variant, s);
 }

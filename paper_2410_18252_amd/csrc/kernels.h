@@ -115,19 +115,15 @@ struct GemmArgs {
 };
 // tile shape chosen from the problem size; g.splits >= 2 (with g.ws) cuts K into that many parts (rl_gemm_splitk)
 hipError_t rl_gemm(const GemmArgs& g, int epi, hipStream_t s);
-// the same with an explicit tile shape (tuning and tests).  Two stages: 0 = 128x128, 1 = 256x128, 4 = 128x256 (four waves), 5 = 256x128
-// (eight), 7 = 64x128; 256x256 by hand: 3; rings: 2 = 128x128, 10 = 256x128, 6 = 64x64, 8 and 9 = 64x128 on four and eight waves
+// the same with an explicit tile shape (tuning and tests).  Two stages: 0 = 128x128, 5 = 256x128; 256x256 by hand: 3; rings: 2 =
+// 128x128, 10 = 256x128; rings of the epilogues whose waves must own 64 columns (SwiGLU, LM head): 1 = 32x128, 4 = 64x128; rings
+// of the others: 1 = 32x32, 4 = 32x64, 6 = 64x64, 7 = 128x64, 8 = 64x96, 9 = 64x128.  Precise mode: 0, 3, 5 and two stages 7 = 64x128
 hipError_t rl_gemm_variant(const GemmArgs& g, int epi, int variant, hipStream_t s);
 // needs g.ws and 2 <= g.splits <= K tiles of 64 (precise mode: twice as many)
 hipError_t rl_gemm_splitk(const GemmArgs& g, int epi, int variant, hipStream_t s);
 
 // the first half of rl_gemm_splitk alone: the parts stay in g.ws
 hipError_t rl_gemm_parts(const GemmArgs& g, int variant, hipStream_t s);
-// Few rows: K divided among the SKINNY_WAVES waves of a block (K a multiple of 64, N of 16; not in precise mode).  Whether a
-// layer of a context with room for cap_rows rows takes this form follows from its shape: the sums' order is the form's.
-constexpr int SKINNY_WAVES = 8;
-bool rl_gemm_skinny_pays(int cap_rows, int N, int K, int epi);
-hipError_t rl_gemm_skinny(const GemmArgs& g, int epi, hipStream_t s);
 
 // ------------------------------------------------------------------ attention
 // prefill: 16 queries [16 qblock, 16 qblock + 16) of one sequence.  pre_len > 0: the sequence continues a prefix held

@@ -131,7 +131,6 @@ struct rlgen_ctx {
   // tile shape and K split of each linear layer, measured at creation: [decode | prompt pass][which GEMM]
   // [decode of max_seqs rows | prompt pass | decode of half of max_seqs rows][which GEMM]
   struct GemmChoice { int variant, splits; } tuned[3][5];
-  bool skinny[5];         // decode steps take this linear layer with K divided inside the block (by rule: rl_gemm_skinny_pays)
   bool half_rows;         // the decode steps being enqueued cover half of the batch
   // precise mode (cfg.precise): 16-bit activations and cached keys/values are bf16 hi/lo pairs.  pw = 2 then (else 1):
   // 16-bit values per activation element; kv_plane = elements between the hi and the lo plane of the cache
@@ -394,7 +393,6 @@ hipError_t run_choice(const GemmArgs& g, int epi, int variant, int splits, hipSt
 }
 hipError_t gemm(rlgen_ctx* c, int which, bool decode, const GemmArgs& g, int epi, hipStream_t st) {
   const int mode = decode ? (c->half_rows ? 2 : 0) : 1;
-  if (decode && c->skinny[which]) return rl_gemm_skinny(g, epi, st);
   // the K split is that of the mode's family (decode / prompt pass) even where a mode was not tuned
   return run_choice(g, epi, c->tuned[mode][which].variant, c->tuned[decode ? 0 : 1][which].splits, st);
 }
@@ -405,12 +403,12 @@ hipError_t gemm(rlgen_ctx* c, int which, bool decode, const GemmArgs& g, int epi
 hipError_t gemm_resid(rlgen_ctx* c, int which, bool decode, const GemmArgs& g, NormParts* parts, hipStream_t st) {
   const int mode = decode ? (c->half_rows ? 2 : 0) : 1;
   const int splits = c->tuned[decode ? 0 : 1][which].splits, variant = c->tuned[mode][which].variant;
-  if ((decode && c->skinny[which]) || splits < 2 || !g.ws || !parts || g.M > NORM_WIDE_ROWS || g.ldo != g.N)
+  if (splits < 2 || !g.ws || !parts || g.M > NORM_WIDE_ROWS || g.ldo != g.N)
     return gemm(c, which, decode, g, EPI_RESID, st);
   GemmArgs h = g;
   h.splits = splits;
   *parts = NormParts{h.ws, splits, g.bias, (float*)g.out};
-  return rl_gemm_parts(h, variant < 0 ? 7 : variant, st);
+  return rl_gemm_parts(h, variant < 0 ? (g.precise ? 7 : 9) : variant, st);
 }
 
 QkvEpi qkv_epilogue(const rlgen_ctx* c, const RopeArgs& r, uint16_t* kvstage) {
@@ -612,6 +610,43 @@ int split_rule(int rows, int cap_rows, int N, int K, int epi, size_t ws_elems, b
   sp = std::min<long long>(sp, (long long)(ws_elems / ((size_t)cap_rows * N)));
   return sp >= 2 ? (int)sp : 1;
 }
+// The same for a decode step's products into the residual, whose parts the following norm adds up, when nothing runs beside them:
+// the number of parts for which the modelled time of the best of three tiles is shortest.  Time in us: rounds of 256 blocks x K
+// steps of a part x the tile's K step (64x64 0.34, 64x128 0.38, 128x128 0.585, with the ring's depth of requests), and 1 and
+// 2 for every million partial sums written and read.  Modelled, with 2 us for the launch, / measured: 1024 x 5120 at 128 rows 7.6 / 6.6 in
+// 8 parts; 2048 x 10240 at 64 rows 11.0 / 11.0 in 8, 128 rows 13.9 / 14.0 in 8, 256 rows 21.5 / 20.3 in 4 (21.7 in 6, 22.5 in 8);
+// 2560 x 12800 at 256 rows 29.9 / 29.3 in 6 (29.5 in 3); 4096 x 14336 at 256 rows 43.3 / 43.3 in 4 (47.4 in 2).
+int split_rule_decode(int rows, int cap_rows, int N, int K, int epi, size_t ws_elems) {
+  // the others take a second pass of their own (4 to 7 us), which pays only where 64x64 tiles leave three quarters of the CUs idle
+  if (epi != EPI_RESID) return (long long)((rows + 63) / 64) * ((N + 63) / 64) < 64 ? split_rule(rows, cap_rows, N, K, epi, ws_elems, false) : 1;
+  const int nk = (K + 63) / 64;
+  const int most = (int)std::min<long long>(std::min(8, nk / 4), (long long)(ws_elems / ((size_t)cap_rows * N)));
+  const struct { int bm, bn; double step; } tiles[] = {{64, 64, 0.34}, {64, 128, 0.38}, {128, 128, 0.585}};
+  int best = 1;
+  double best_us = 1e30;
+  for (int sp = 1; sp <= most; ++sp)
+    for (const auto& t : tiles) {
+      const long long blocks = (long long)((rows + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * sp;
+      const double us = (double)((blocks + 255) / 256) * ((nk + sp - 1) / sp) * t.step + (sp > 1 ? 1.0 + 2e-6 * sp * rows * N : 0.0);
+      if (us < best_us) { best_us = us; best = sp; }
+    }
+  return best;
+}
+
+// The smallest tile whose blocks the CUs take in one round, -1 if there is none.  A decode step or a short prompt pass that is alone on the GPU is
+// bound by the requests in flight for the weights: fewer, larger blocks leave CUs out of it, a second round doubles the wait.  Timed over
+// 16 shapes (410M to 8B width) at 16, 64, 128 and 256 rows this is the fastest shape or within 7 % of it (us, 64 rows: 3072 x
+// 1024 32x32 5.0, 32x64 6.0, 64x64 7.5; 6144 x 2048 32x64 9.5, 32x32 in two rounds 11.4, 64x64 11.8), where a timing of two
+// launches of 5 to 10 us, which the host can hardly enqueue as fast, picked shapes up to 25 % slower.
+int one_round_tile(int M, int N, int splits, bool wide) {
+  struct Tile { int variant, bm, bn; };
+  static const Tile narrow_tiles[] = {{1, 32, 32}, {4, 32, 64}, {6, 64, 64}, {8, 64, 96}, {7, 128, 64}, {9, 64, 128}, {2, 128, 128}};
+  static const Tile wide_tiles[] = {{1, 32, 128}, {4, 64, 128}, {2, 128, 128}};
+  const Tile* tiles = wide ? wide_tiles : narrow_tiles;
+  for (int i = 0; i < (wide ? 3 : 7); ++i)
+    if ((long long)((M + tiles[i].bm - 1) / tiles[i].bm) * ((N + tiles[i].bn - 1) / tiles[i].bn) * splits <= 256) return tiles[i].variant;
+  return -1;
+}
 
 struct Events3 {      // three timing events, destroyed on every path out of the tuner
   hipEvent_t e[3] = {nullptr, nullptr, nullptr};
@@ -731,13 +766,8 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
       const bool wide_only = epi == EPI_SWIGLU_F16 || epi == EPI_LMHEAD;
       // the K split: by rule, the same for every decode mode
       const int splits = !g.ws ? 1 : mode == 1 ? split_rule(c->R, c->R, g.N, g.K, epi, g.ws_elems, false)
-                                               : split_rule(dec_rows_eff, m.max_seqs, g.N, g.K, epi, g.ws_elems, tune_half);
-      if (mode != 1 && which != G_LMHEAD && !pr && rl_gemm_skinny_pays(m.max_seqs, g.N, g.K, epi)) {
-        // decode steps of every row count divide K inside the block: there is no tile shape to time
-        c->skinny[which] = true;
-        c->tuned[mode][which] = {0, SKINNY_WAVES};
-        continue;
-      }
+                         : tune_half || pr ? split_rule(dec_rows_eff, m.max_seqs, g.N, g.K, epi, g.ws_elems, tune_half)
+                                           : split_rule_decode(dec_rows_eff, m.max_seqs, g.N, g.K, epi, g.ws_elems);
       std::vector<int> cands;
       if (pr) {                                   // precise mode is compiled for four tile shapes
         cands = {0, 5};
@@ -745,18 +775,20 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
         if (!wide_only) cands.push_back(7);
       } else if (splits == 1 && (long long)(g.M / 256) * (g.N / 256) >= 1024) {
         cands = {3, 10, 5};                       // four large tiles to every CU: the small ones cannot win
+      } else if (!tune_half && one_round_tile(g.M, g.N, splits, wide_only) >= 0) {
+        cands = {one_round_tile(g.M, g.N, splits, wide_only)};
+      } else if (g.M <= 64) {
+        if (wide_only) cands = {1, 4};
+        else cands = {1, 4, 6, 8, 9};
       } else {
-        cands = {0, 2};
+        cands = {0, 2, 4};
         if (g.M > 128) {                          // 256 rows to a tile would be half padding below
           cands.push_back(5); cands.push_back(10);
           if (splits == 1) cands.push_back(3);
         }
-        if (mode == 2 && splits == 1) { cands.push_back(1); cands.push_back(4); }     // beside attention other shapes can win
-        if (!wide_only) {
-          cands.push_back(7);
-          // the small rings are for launches that leave CUs short of blocks
-          if ((long long)((g.M + 63) / 64) * ((g.N + 127) / 128) < 2048) { cands.push_back(6); cands.push_back(8); cands.push_back(9); }
-        }
+        // the small rings are for launches that leave CUs short of blocks
+        if (!wide_only && (long long)((g.M + 63) / 64) * ((g.N + 127) / 128) < 2048)
+          for (int v : {6, 7, 8, 9}) cands.push_back(v);
       }
       // clocks drift with load, so the candidates take turns: one warm-up each, then three rounds in which
       // every candidate is timed over two launches; the smallest total wins
@@ -768,6 +800,10 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
         const LayerW& l = c->layers[layer];
         a.W = which == G_QKV ? l.wqkv : which == G_O ? l.wo : which == G_UP ? l.wup : which == G_DOWN ? (c->joined_out ? l.wo : l.wdown) : c->lm_head;
       };
+      if (cands.size() == 1) {
+        c->tuned[mode][which] = {cands[0], splits};
+        continue;
+      }
       std::vector<float> total(cands.size(), 0.f);
       bool ok = true;
       for (size_t i = 0; ok && i < cands.size(); ++i) ok = run_choice(g, epi, cands[i], splits, st) == hipSuccess;

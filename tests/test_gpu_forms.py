@@ -1,5 +1,5 @@
 """GPU: the kernels' forms at the sizes where they can go wrong -- whole and ragged tiles of the matrix products with two to a
-few K steps, decode steps on either side of the rules that divide a product or an attention job inside a block, norms with a
+few K steps, decode steps on either side of the rules that divide an attention job inside a block, norms with a
 wave or a block to a row, and a joined output product whose K is not whole K blocks."""
 import ctypes as C
 
@@ -55,8 +55,7 @@ def test_every_tile_shape_returns_the_same_bits_on_whole_and_ragged_tiles(name, 
         assert np.abs(outs[0][0][n, :lens[n]].numpy() - O.score(dec, seqs[n], 0.7)).max() < TOL_LOGPROB
 
 
-# capacities on either side of the rules: products divide K inside a block up to 16 sequences, and up to 128 where little is
-# fetched; decode attention shares a job among eight or four waves while capacity x kv heads x max(head size, 64) is at most
+# capacities on either side of the rules: decode attention shares a job among eight or four waves while capacity x kv heads x max(head size, 64) is at most
 # 32768 or 131072
 @pytest.mark.parametrize("max_seqs", [6, 17, 128, 129, 300, 2100])
 @pytest.mark.parametrize("name", ["neox-h16-raggedV", "neox-h80", "neox-h256", "llama-gqa4-h16", "llama-gqa2-h128"])
@@ -306,8 +305,7 @@ def test_decode_attention_over_several_turns_of_the_key_loop(name, max_seqs, wav
     assert worst < TOL_LOGPROB
 
 
-# no decode layer of these divides K inside a block (more than 128 sequences, whole K blocks); FFN-down is cut into parts, and
-# the GPT-NeoX shape's FFN-up too
+# FFN-down is cut into parts, and the GPT-NeoX shape's FFN-up too
 DECODE_TILES = {
     "neox-d512": ModelShape(0, 2, 512, 8, 8, 64, 1024, 515, rotary_dim=16),
     "llama-d256": ModelShape(1, 2, 256, 4, 2, 64, 512, 700, rotary_dim=64, rope_theta=500000.0),

@@ -281,9 +281,7 @@ def test_results_do_not_depend_on_the_tile_shapes_a_context_picked(name):
     u = rng.random((5, 2, 7), dtype=np.float32)
     outs, picks = [], []
     # contexts 0-2: the measured choice, and that choice moved on by one and by two in the list of legal shapes; then
-    # (default formats) every layer that may take it forced onto the eight-wave 64x128 ring, and onto the 256x128 ring.  With
-    # twelve sequences the default formats' decode layers divide K inside a block and have no shape to force:
-    # test_gpu_forms.py forces theirs on a larger batch
+    # (default formats) every layer that may take it forced onto the eight-wave 64x128 ring, and onto the 256x128 ring
     for shift in (0, 1, 2) if precise else (0, 1, 2, -9, -10):
         pol = make_policy(W, max_seqs=12, max_seq_len=80, max_batch_tokens=80, precise=precise)
         try:
