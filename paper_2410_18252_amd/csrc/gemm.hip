@@ -395,8 +395,28 @@ __device__ __forceinline__ void gemm_epilogue_as(const GemmArgs& g, const f32x4 
     if constexpr ((EPI == EPI_GELU_F16 || EPI == EPI_SWIGLU_F16) && !PR) flag_f16_range(sat, g.status);
   }
 }
+// EPI_QKV_UP: tile columns behind the QKV product's belong to the second one, which takes the first one's place in the arguments
+template <int EPI, int BN>
+__device__ __forceinline__ bool take_second(GemmArgs& g, int& tile_n) {
+  if constexpr (EPI != EPI_QKV_UP) return false;
+  const int first = (g.N + BN - 1) / BN;
+  if (tile_n < first) return false;
+  tile_n -= first;
+  g.A = g.A2; g.W = g.W2; g.N = g.N2; g.bias = g.bias2;
+  return true;
+}
+// tile columns of a launch
+template <int EPI, int BN>
+__host__ __device__ __forceinline__ int tile_cols(const GemmArgs& g) {
+  return (g.N + BN - 1) / BN + (EPI == EPI_QKV_UP ? (g.N2 + BN - 1) / BN : 0);
+}
 template <int TM, int TN, int EPI, bool PR, bool STAGED = false>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, const f32x4 (&acc)[TM][TN], int wrow0, int wcol0, int lane, int split) {
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, const f32x4 (&acc)[TM][TN], int wrow0, int wcol0, int lane, int split, bool second = false) {
+  if constexpr (EPI == EPI_QKV_UP) {
+    if (second) gemm_epilogue<TM, TN, EPI_GELU_F16, PR>(g, acc, wrow0, wcol0, lane, split);
+    else gemm_epilogue<TM, TN, EPI_QKV, PR, STAGED>(g, acc, wrow0, wcol0, lane, split);
+    return;
+  }
   const bool fits = wrow0 + TM * 16 <= g.M && wcol0 + TN * 16 <= g.N && (EPI != EPI_F32 || (g.ldo & 3) == 0);
   if (fits) gemm_epilogue_as<TM, TN, EPI, PR, true, STAGED>(g, acc, wrow0, wcol0, lane, split);
   else gemm_epilogue_as<TM, TN, EPI, PR, false, STAGED>(g, acc, wrow0, wcol0, lane, split);
@@ -431,10 +451,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_f16_kernel(GemmArgs g) {
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
-  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = tile_cols<EPI, BN>(g);
   int tile_m, tile_n, split;
   const int splits = EPI == EPI_PARTIAL ? g.splits : 1;
   tile_of_block(tiles_m, tiles_n, splits, tile_m, tile_n, split);
+  const bool second = take_second<EPI, BN>(g, tile_n);
   const int row0 = tile_m * BM, col0 = tile_n * BN;
 
   // ---- global -> register staging: thread t covers chunk (t % 8) of rows (t / 8) + RPP i
@@ -637,7 +658,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_f16_kernel(GemmArgs g) {
     }
   }
 
-  gemm_epilogue<TM, TN, EPI, PR>(g, acc, row0 + wm * (BM / WM), col0 + wn * (BN / WN), lane, split);
+  gemm_epilogue<TM, TN, EPI, PR>(g, acc, row0 + wm * (BM / WM), col0 + wn * (BN / WN), lane, split, second);
 }
 
 // The 256x256 tile: four waves of 128x128, one per SIMD, K >= 128 (two K steps).  Every wave is its SIMD's only one, so the
@@ -660,9 +681,10 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];   // two stages
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int tiles_m = (g.M + 255) >> 8, tiles_n = (g.N + 255) >> 8;
+  const int tiles_m = (g.M + 255) >> 8, tiles_n = tile_cols<EPI, 256>(g);
   int tile_m, tile_n, split;
   tile_of_block(tiles_m, tiles_n, 1, tile_m, tile_n, split);
+  const bool second = take_second<EPI, 256>(g, tile_n);
   const int row0 = tile_m << 8, col0 = tile_n << 8;
 
   const int nkb = g.K / BK;                      // K blocks of W (and of each half of a hi/lo A)
@@ -769,7 +791,7 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmArgs g) {
   for (; kt < nk - 2; ++kt) step(kt, std::integral_constant<int, 0>{});
   step(kt, std::integral_constant<int, 1>{});
   step(kt + 1, std::integral_constant<int, 2>{});
-  gemm_epilogue<TM, TN, EPI, PR, true>(g, acc, row0 + wm * 128, col0 + wn * 128, lane, 0);
+  gemm_epilogue<TM, TN, EPI, PR, true>(g, acc, row0 + wm * 128, col0 + wn * 128, lane, 0, second);
 }
 #undef BIG_BAR
 
@@ -796,10 +818,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_ring_kernel(GemmArgs g) {
   __builtin_amdgcn_s_setprio(3);       // ahead of the other half's attention (see gemm_f16_kernel)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WN, wn = wave % WN;
-  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = tile_cols<EPI, BN>(g);
   int tile_m, tile_n, split;
   const int splits = EPI == EPI_PARTIAL ? g.splits : 1;
   tile_of_block(tiles_m, tiles_n, splits, tile_m, tile_n, split);
+  const bool second = take_second<EPI, BN>(g, tile_n);
   const int row0 = tile_m * BM, col0 = tile_n * BN;
   const int nkb = g.K / BK;
   const int nk_all = PR ? 2 * nkb : nkb;
@@ -904,7 +927,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_ring_kernel(GemmArgs g) {
     slice(0, [&](int n) { read(s, 1, n); }, [](int) {});
     slice(1, [](int) {}, [](int) {});
   }
-  gemm_epilogue<TM, TN, EPI, PR>(g, acc, row0 + wm * (BM / WM), col0 + wn * (BN / WN), lane, split);
+  gemm_epilogue<TM, TN, EPI, PR>(g, acc, row0 + wm * (BM / WM), col0 + wn * (BN / WN), lane, split, second);
 }
 #undef RING_WAIT
 
@@ -953,7 +976,7 @@ hipError_t launch_k(const GemmArgs& g, hipStream_t s) {
     }
     configured = true;
   }
-  const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * (EPI == EPI_PARTIAL ? g.splits : 1);
+  const int tiles = ((g.M + BM - 1) / BM) * tile_cols<EPI, BN>(g) * (EPI == EPI_PARTIAL ? g.splits : 1);
   hipLaunchKernelGGL((gemm_f16_kernel<BM, BN, WM, WN, EPI, KTAIL, NS, PR>), dim3(tiles), dim3(WM * WN * 64), lds_bytes, s, g);
   return hipGetLastError();
 }
@@ -971,7 +994,7 @@ hipError_t launch_big(const GemmArgs& g, hipStream_t s) {
     if (e != hipSuccess) return e;
     configured_on[dev] = true;
   }
-  const int tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
+  const int tiles = ((g.M + 255) / 256) * tile_cols<EPI, 256>(g);
   hipLaunchKernelGGL((gemm_big_kernel<EPI, PR>), dim3(tiles), dim3(256), lds_bytes, s, g);
   return hipGetLastError();
 }
@@ -988,7 +1011,7 @@ hipError_t launch_ring(const GemmArgs& g, hipStream_t s) {
     if (e != hipSuccess) return e;
     configured_on[dev] = true;
   }
-  const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN) * (EPI == EPI_PARTIAL ? g.splits : 1);
+  const int tiles = ((g.M + BM - 1) / BM) * tile_cols<EPI, BN>(g) * (EPI == EPI_PARTIAL ? g.splits : 1);
   hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WM, WN, NS, EPI, PR>), dim3(tiles), dim3(WM * WN * 64), lds_bytes, s, g);
   return hipGetLastError();
 }
@@ -1020,7 +1043,11 @@ hipError_t launch_variant_precise(const GemmArgs& g, int variant, hipStream_t s)
 // the tile shapes by number; a K that is not whole K tiles takes the register-staged form of the same or the nearest tile
 template <int EPI>
 hipError_t launch_variant(const GemmArgs& g, int variant, hipStream_t s) {
-  if (g.precise) return launch_variant_precise<EPI>(g, variant, s);
+  if constexpr (EPI == EPI_QKV_UP) {
+    if (g.precise) return hipErrorInvalidValue;
+  } else {
+    if (g.precise) return launch_variant_precise<EPI>(g, variant, s);
+  }
   constexpr bool WIDE = EPI == EPI_SWIGLU_F16 || EPI == EPI_LMHEAD;      // a wave must own 64 columns
   const bool whole = g.K % BK == 0;
   switch (variant) {
@@ -1028,7 +1055,7 @@ hipError_t launch_variant(const GemmArgs& g, int variant, hipStream_t s) {
     case 2: return whole ? launch_ring<128, 128, 4, 2, 4, EPI>(g, s) : launch_k<128, 128, 2, 2, EPI, true, 0>(g, s);
     case 3:
       // (a K split is for shapes with few tiles: partial sums come from 256x128 at most, and so do a decode step's cache writes)
-      if (EPI == EPI_PARTIAL || (EPI == EPI_QKV && !g.qe.kvstage)) return launch<256, 128, 4, 2, EPI>(g, s);
+      if (EPI == EPI_PARTIAL || ((EPI == EPI_QKV || EPI == EPI_QKV_UP) && !g.qe.kvstage)) return launch<256, 128, 4, 2, EPI>(g, s);
       if constexpr (EPI != EPI_PARTIAL) return launch_big<EPI, false>(g, s);
       break;
     case 5: return launch<256, 128, 4, 2, EPI>(g, s);
@@ -1079,6 +1106,9 @@ hipError_t rl_gemm_variant(const GemmArgs& g, int epi, int variant, hipStream_t 
         return g.precise ? launch<128, 128, 2, 2, EPI_LMHEAD_EXACT, 2, true>(g, s) : launch<128, 128, 2, 2, EPI_LMHEAD_EXACT>(g, s);
       return launch_variant<EPI_LMHEAD>(g, variant, s);
     case EPI_PARTIAL: return launch_variant<EPI_PARTIAL>(g, variant, s);
+    case EPI_QKV_UP:
+      if (!valid_qkv(g) || !g.A2 || !g.W2 || !g.out || g.N2 <= 0 || g.N2 % 4 != 0) return hipErrorInvalidValue;
+      return launch_variant<EPI_QKV_UP>(g, variant, s);
     case EPI_QKV: {
       return valid_qkv(g) ? launch_variant<EPI_QKV>(g, variant, s) : hipErrorInvalidValue;
     }
@@ -1110,7 +1140,8 @@ hipError_t rl_gemm_splitk(const GemmArgs& g, int epi, int variant, hipStream_t s
 // Tile shape by problem size (measured on MI355X): the largest tile that still gives every CU work.  The K split is
 // the caller's (g.splits >= 2 with g.ws set), never chosen here: it fixes the order of the sums.
 hipError_t rl_gemm(const GemmArgs& g, int epi, hipStream_t s) {
-  auto tiles = [&](int bm, int bn) { return (long long)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
+  const int cols = g.N + (epi == EPI_QKV_UP ? g.N2 : 0);
+  auto tiles = [&](int bm, int bn) { return (long long)((g.M + bm - 1) / bm) * ((cols + bn - 1) / bn); };
   const bool wide_only = (epi == EPI_SWIGLU_F16 || epi == EPI_LMHEAD);   // a wave must own 64 columns
   int variant;
   if (tiles(256, 256) >= 160) variant = 3;

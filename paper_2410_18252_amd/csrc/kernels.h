@@ -58,7 +58,8 @@ struct KvLayout {
 
 // ------------------------------------------------------------------ GEMM
 enum { EPI_F32 = 0, EPI_RESID = 1, EPI_GELU_F16 = 2, EPI_SWIGLU_F16 = 3, EPI_LMHEAD = 4, EPI_PARTIAL = 5, EPI_QKV = 6,
-       EPI_LMHEAD_EXACT = 7 };      // EPI_LMHEAD at temperatures near the end of fp32's range, chosen inside rl_gemm_variant
+       EPI_LMHEAD_EXACT = 7,        // EPI_LMHEAD at temperatures near the end of fp32's range, chosen inside rl_gemm_variant
+       EPI_QKV_UP = 8 };            // EPI_QKV and, in the same launch, a second product of as many rows and the same K into EPI_GELU_F16
 
 // Epilogue of the fused QKV projection (EPI_QKV): bias, rotary embedding and the writes of q (fp16) and of k, v
 // (bf16, into the cache) happen on the accumulators.  For that the weight rows of every query and key head are
@@ -110,6 +111,8 @@ struct GemmArgs {
   // split-K scratch (nullable: no split-K): fp32 [splits, M, N], ws_elems floats available
   float* ws; size_t ws_elems; int splits;
   QkvEpi qe;                    // EPI_QKV only (out / ldo unused)
+  // EPI_QKV_UP only: A2 [M, K] . W2 [N2, K]^T + bias2 through GELU into out (not in precise mode)
+  const void *A2, *W2; int N2; const float* bias2;
   unsigned* status;             // nullable: receives RLGEN_FAULT_RANGE when an fp16 (or cached bf16, later read as fp16)
                                 // output of the epilogue exceeds fp16's range and is clamped
 };

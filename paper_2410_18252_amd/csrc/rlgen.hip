@@ -87,6 +87,9 @@ struct rlgen_ctx {
   // Parallel residual (NeoX): attention output and FFN-down add to the same residual, so they are one product over K = Hq h + F:
   // the two weight matrices and the two activation matrices follow each other in memory (whole K blocks: Hq h % 64 == 0)
   bool joined_out;
+  // and both norms of a block read the same rows, so that the QKV and FFN-up products do not wait for each other: one launch, where
+  // FFN-up is not cut into parts ([decode | prompt pass]; fused_qkv, not in precise mode)
+  bool joined_in[2];
   bool fused_qkv;         // rotary_dim % 4 == 0: rotary embedding and cache writes run in the QKV GEMM's epilogue
   int score_groups;       // k > 1: rlgen_score treats every k consecutive sequences as one prompt with k completions
   int eos_token;          // -1: completions never end early (rlgen_set_eos)
@@ -442,6 +445,7 @@ int run_layers(rlgen_ctx* c, int rows, bool decode, int t, int ncopy, bool use_c
   const int d = m.d_model, F = m.d_ffn, h = m.head_dim;
   const int qd = m.n_q_heads * h, nqkv = qd + 2 * m.n_kv_heads * h;
   NormParts parts;           // a product the next norm has to add to the residual first
+  const bool joined_in = c->joined_in[decode ? 0 : 1];
   for (int l = 0; l < m.n_layers; ++l) {
     const LayerW& L = c->layers[l];
     uint16_t* kvl = c->kv + (use_cache_layers ? (size_t)c->lay.layer_stride * l : 0);
@@ -471,7 +475,12 @@ int run_layers(rlgen_ctx* c, int rows, bool decode, int t, int ncopy, bool use_c
       // the prompt pass leaves k and v as bf16 rows in the (otherwise unused) fp32 qkv buffer for the block-wise writer
       g.qe = qkv_epilogue(c, r, decode ? nullptr : (uint16_t*)c->qkv);
       g.ws = nullptr;
-      HIPCHK(gemm(c, G_QKV, decode, g, EPI_QKV, st));
+      if (joined_in) {
+        g.A2 = c->n2; g.W2 = L.wup; g.N2 = F; g.bias2 = L.bup; g.out = act;
+        HIPCHK(gemm(c, G_QKV, decode, g, EPI_QKV_UP, st));
+      } else {
+        HIPCHK(gemm(c, G_QKV, decode, g, EPI_QKV, st));
+      }
       if (!decode) {
         r.kvstage = (const uint16_t*)c->qkv;
         HIPCHK(rl_kv_prefill(r, st));
@@ -530,12 +539,14 @@ int run_layers(rlgen_ctx* c, int rows, bool decode, int t, int ncopy, bool use_c
       HIPCHK(rl_norm(c->x, nullptr, rows, d, m.norm_eps, L.n2g, nullptr, c->n2, nullptr, nullptr, nullptr, rows, 0, c->status, st, lo_off(d), parts));
       parts = NormParts{};
     }
-    g = GemmArgs{};
-    g.precise = pr; g.out_lo_off = lo_off(act_K);
-    g.A = c->n2; g.W = L.wup; g.M = rows; g.N = llama ? 2 * F : F; g.K = d;
-    g.bias = llama ? nullptr : L.bup; g.out = act; g.ldo = F; g.ws = c->splitk; g.ws_elems = c->splitk_elems;
-    g.status = c->status;
-    HIPCHK(gemm(c, G_UP, decode, g, llama ? EPI_SWIGLU_F16 : EPI_GELU_F16, st));
+    if (!joined_in) {
+      g = GemmArgs{};
+      g.precise = pr; g.out_lo_off = lo_off(act_K);
+      g.A = c->n2; g.W = L.wup; g.M = rows; g.N = llama ? 2 * F : F; g.K = d;
+      g.bias = llama ? nullptr : L.bup; g.out = act; g.ldo = F; g.ws = c->splitk; g.ws_elems = c->splitk_elems;
+      g.status = c->status;
+      HIPCHK(gemm(c, G_UP, decode, g, llama ? EPI_SWIGLU_F16 : EPI_GELU_F16, st));
+    }
     g = GemmArgs{};
     g.precise = pr;
     g.A = c->joined_out ? c->attn : act; g.W = c->joined_out ? L.wo : L.wdown; g.M = rows; g.N = d; g.K = act_K;
@@ -638,13 +649,14 @@ int split_rule_decode(int rows, int cap_rows, int N, int K, int epi, size_t ws_e
 // 16 shapes (410M to 8B width) at 16, 64, 128 and 256 rows this is the fastest shape or within 7 % of it (us, 64 rows: 3072 x
 // 1024 32x32 5.0, 32x64 6.0, 64x64 7.5; 6144 x 2048 32x64 9.5, 32x32 in two rounds 11.4, 64x64 11.8), where a timing of two
 // launches of 5 to 10 us, which the host can hardly enqueue as fast, picked shapes up to 25 % slower.
-int one_round_tile(int M, int N, int splits, bool wide) {
+int one_round_tile(int M, int N, int N2, int splits, bool wide) {      // N2: columns of a second product in the launch
   struct Tile { int variant, bm, bn; };
   static const Tile narrow_tiles[] = {{1, 32, 32}, {4, 32, 64}, {6, 64, 64}, {8, 64, 96}, {7, 128, 64}, {9, 64, 128}, {2, 128, 128}};
   static const Tile wide_tiles[] = {{1, 32, 128}, {4, 64, 128}, {2, 128, 128}};
   const Tile* tiles = wide ? wide_tiles : narrow_tiles;
   for (int i = 0; i < (wide ? 3 : 7); ++i)
-    if ((long long)((M + tiles[i].bm - 1) / tiles[i].bm) * ((N + tiles[i].bn - 1) / tiles[i].bn) * splits <= 256) return tiles[i].variant;
+    if ((long long)((M + tiles[i].bm - 1) / tiles[i].bm) * ((N + tiles[i].bn - 1) / tiles[i].bn + (N2 + tiles[i].bn - 1) / tiles[i].bn) * splits <= 256)
+      return tiles[i].variant;
   return -1;
 }
 
@@ -698,6 +710,20 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
   // rows a decode launch is sized for
   const int dec_rows_eff = tune_half ? (m.max_seqs + 1) / 2 : m.max_seqs;
   for (int which = 0; which < 5; ++which) c->tuned[2][which] = {-1, 1};
+  auto splits_of = [&](int mode, int N, int K, int epi) {
+    if (mode == 1 && (epi == EPI_RESID || pr)) return split_rule(c->R, c->R, N, K, epi, c->splitk_elems, false);
+    if (mode != 1 && (tune_half || pr)) return split_rule(dec_rows_eff, m.max_seqs, N, K, epi, c->splitk_elems, tune_half);
+    return mode == 1 ? split_rule_decode(c->R, c->R, N, K, epi, c->splitk_elems) : split_rule_decode(dec_rows_eff, m.max_seqs, N, K, epi, c->splitk_elems);
+  };
+  // One launch for QKV and FFN-up while the two are short of blocks (up to five rounds of 128x128 tiles): 654 rows at 1B width 87 us
+  // as two launches, 67 as one, 384 rows at 2.8B width 66 and 54, 128 rows at 410M 16 and 10; 32768 rows at 2.8B width 2750 and 2840
+  // (two operands more in the caches).  Beside attention one round: generate of 1B width with halves of 256 rows 131.0 ms apart,
+  // 129.2 joined, of 2.8B width with 512 rows 355.8 and 361.3
+  for (int prompt = 0; prompt < 2; ++prompt) {
+    const long long rows = prompt ? c->R : dec_rows_eff;
+    c->joined_in[prompt] = !llama && c->fused_qkv && !pr && splits_of(prompt, F, d, EPI_GELU_F16) == 1 &&
+                           (rows + 127) / 128 * ((nqkv + F + 127) / 128) <= (!prompt && tune_half ? 256 : 5 * 256);
+  }
   // The neighbour of the half-batch timing runs: the decode attention of the other half, over half a full batch of
   // sequences that each hold their share of the cache (all zeros), twice in a row.  Its three per-sequence arrays
   // live in the (idle) index area of EOS compaction and are uploaded from that feature's pinned buffer.
@@ -729,7 +755,7 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
   for (int mi = tune_half ? 0 : 1; mi < 3 && rc == RLGEN_OK; ++mi) {
     const int mode = modes[mi];
     for (int which = 0; which < 5 && rc == RLGEN_OK; ++which) {
-      if (which == G_O && c->joined_out) {      // no launch of its own
+      if ((which == G_O && c->joined_out) || (which == G_UP && c->joined_in[mode == 1])) {      // no launch of its own
         c->tuned[mode][which] = {0, 1};
         continue;
       }
@@ -752,6 +778,10 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
             g.qe = qkv_epilogue(c, r, mode != 1 ? nullptr : (uint16_t*)c->qkv);
             g.ws = nullptr;          // the fused epilogue has no split-K form
             epi = EPI_QKV;
+            if (c->joined_in[mode == 1]) {
+              g.A2 = c->n2; g.W2 = L.wup; g.N2 = F; g.bias2 = L.bup; g.out = c->joined_out ? c->attn : c->act;
+              epi = EPI_QKV_UP;
+            }
           }
           break;
         case G_O: g.A = c->attn; g.W = L.wo; g.N = d; g.K = qd; g.bias = llama ? nullptr : L.bo; g.out = c->x; g.ldo = d; epi = EPI_RESID; break;
@@ -765,18 +795,16 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
       }
       const bool wide_only = epi == EPI_SWIGLU_F16 || epi == EPI_LMHEAD;
       // the K split: by rule, the same for every decode mode
-      const int splits = !g.ws ? 1 : mode == 1 ? split_rule(c->R, c->R, g.N, g.K, epi, g.ws_elems, false)
-                         : tune_half || pr ? split_rule(dec_rows_eff, m.max_seqs, g.N, g.K, epi, g.ws_elems, tune_half)
-                                           : split_rule_decode(dec_rows_eff, m.max_seqs, g.N, g.K, epi, g.ws_elems);
+      const int splits = !g.ws ? 1 : splits_of(mode, g.N, g.K, epi);
       std::vector<int> cands;
       if (pr) {                                   // precise mode is compiled for four tile shapes
         cands = {0, 5};
         if (splits == 1) cands.push_back(3);
         if (!wide_only) cands.push_back(7);
-      } else if (splits == 1 && (long long)(g.M / 256) * (g.N / 256) >= 1024) {
+      } else if (splits == 1 && (long long)(g.M / 256) * ((g.N + g.N2) / 256) >= 1024) {
         cands = {3, 10, 5};                       // four large tiles to every CU: the small ones cannot win
-      } else if (!tune_half && one_round_tile(g.M, g.N, splits, wide_only) >= 0) {
-        cands = {one_round_tile(g.M, g.N, splits, wide_only)};
+      } else if (!tune_half && one_round_tile(g.M, g.N, g.N2, splits, wide_only) >= 0) {
+        cands = {one_round_tile(g.M, g.N, g.N2, splits, wide_only)};
       } else if (g.M <= 64) {
         if (wide_only) cands = {1, 4};
         else cands = {1, 4, 6, 8, 9};
@@ -787,7 +815,7 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
           if (splits == 1) cands.push_back(3);
         }
         // the small rings are for launches that leave CUs short of blocks
-        if (!wide_only && (long long)((g.M + 63) / 64) * ((g.N + 127) / 128) < 2048)
+        if (!wide_only && (long long)((g.M + 63) / 64) * ((g.N + g.N2 + 127) / 128) < 2048)
           for (int v : {6, 7, 8, 9}) cands.push_back(v);
       }
       // clocks drift with load, so the candidates take turns: one warm-up each, then three rounds in which
@@ -798,6 +826,7 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
       auto next_layer = [&](GemmArgs& a) {
         layer = layer + 1 == m.n_layers ? 0 : layer + 1;
         const LayerW& l = c->layers[layer];
+        a.W2 = l.wup;
         a.W = which == G_QKV ? l.wqkv : which == G_O ? l.wo : which == G_UP ? l.wup : which == G_DOWN ? (c->joined_out ? l.wo : l.wdown) : c->lm_head;
       };
       if (cands.size() == 1) {

@@ -378,3 +378,35 @@ def test_decode_steps_read_what_the_prompt_pass_and_they_wrote(h, rot, precise):
         pol.close()
     for b in range(2):
         assert np.abs(lp.cpu().numpy()[b, 0] - sc[b, lens[b]:lens[b] + T]).max() < (TOL_LOGPROB / 20 if precise else TOL_LOGPROB)
+
+
+# one launch for QKV and FFN-up: widths of both that are no multiple of any tile, with and without a joined output product, prompt
+# pass and decode; the Llama shape has no such launch
+@pytest.mark.parametrize("m", [ModelShape(0, 2, 192, 4, 4, 48, 608, 333, rotary_dim=12), ModelShape(0, 1, 256, 1, 1, 256, 1056, 130, rotary_dim=64),
+                               ModelShape(0, 1, 96, 2, 2, 48, 160, 100, rotary_dim=12)])
+def test_qkv_and_ffn_up_in_one_launch_match_the_reference(m):
+    W = scaled_bf16_weights(m)
+    dec = reference_decoder(W, m)
+    rng = np.random.default_rng(61)
+    lens = [1, 63, 64, 65, 130]
+    arr, lens = padded([rng.integers(0, m.vocab, size=n) for n in lens])
+    T = 6
+    forced = rng.integers(0, m.vocab, size=(5, 1, T)).astype(np.int32)
+    r = R()
+    outs = []
+    for shape in (None, 1, 6, 2, 3):             # the rule's tile, the smallest, 64x64, 128x128, 256x256
+        pol = make_policy(W, max_seqs=5, max_seq_len=140)
+        try:
+            if shape is not None:
+                for mode in (0, 1):
+                    r.rlgen_debug_set_gemm(pol, mode, 0, shape)
+            _, lp = r.rlgen_generate(pol, dev_i32(arr), lens, 1, T, 0.7, dev_f32(np.zeros((5, 1, T))), dev_i32(forced))
+            assert r.rlgen_status(pol) == 0
+            outs.append(lp.cpu())
+        finally:
+            pol.close()
+    for o in outs[1:]:
+        assert torch.equal(o, outs[0])
+    for b in range(5):
+        want = O.score(dec, np.concatenate([arr[b, :lens[b]], forced[b, 0]]), 0.7, score_from=int(lens[b]))[lens[b]:]
+        assert np.abs(outs[0].numpy()[b, 0] - want).max() < TOL_LOGPROB
