@@ -30,10 +30,9 @@
 #ifndef ATTN_PREFETCH2
 #define ATTN_PREFETCH2 1
 #endif
-// The prompt pass is not bound by memory but by the latency of a wave's serial chain (load, convert, MFMA, softmax,
-// MFMA): it is compiled for at least ATTN_PROMPT_BLOCKS blocks per CU (256 registers), and without the register
-// prefetch of the next super-block it needs 162 registers at head size 80, so three waves share a SIMD and hide
-// each other's L2 latency (measured on the 2.8B shape: 596 -> 345 us with two blocks, -> 312 us without the prefetch).
+// The prompt pass of contexts whose jobs do not fill the chip, and of precise mode, is not bound by memory but by the latency of a
+// wave's serial chain (load, convert, MFMA, softmax, MFMA): it does without the register prefetch of the next super-block, so that
+// two waves share a SIMD and hide each other's L2 latency.
 #ifndef ATTN_PROMPT_NOPF
 #define ATTN_PROMPT_NOPF 1
 #endif
@@ -68,10 +67,7 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= (PR
   constexpr bool PF = (DECODE || !ATTN_PROMPT_NOPF) && !PR;
   constexpr int NP = PR ? 2 : 1;         // cache planes: hi, lo
   const int lane = threadIdx.x & 63;
-  // A wave number known to be common to the wave makes the job's addresses scalar.  Not for the two-block prompt pass: there
-  // the compiler then keeps more in registers (181 instead of 162 at head size 80: two waves per SIMD instead of three; at
-  // head size 64 109 -> 128 us), while wide heads gain (256: 163 -> 142 us).
-  const int wave = DECODE || HD >= 112 || SPLIT > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : (int)(threadIdx.x >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);         // (common to the wave: the job's addresses are scalar)
   const int c = lane & 15, g = lane >> 4;
   const int Hkv = a.lay.Hkv, G = a.Hq / Hkv;
   const int job = SPLIT > 1 ? blockIdx.x : blockIdx.x * 4 + wave;
@@ -423,6 +419,190 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= (PR
   }
 }
 
+// The prompt pass of large contexts: the four waves of a block share every super-block.  Each takes a quarter of it from memory,
+// widens it to fp16 and leaves it in LDS as the fragments the products want (a kilobyte each, read back linearly), while the one before
+// is consumed; one barrier a super-block.  The waves differ in the query head (groups of four or two heads to a kv head), else in
+// the block of 16 queries.  One wave alone streamed everything itself: keys and values crossed L2 four times and were widened
+// four times (a layer of 32768 rows, us: head size 256, mean prompt 320 723 -> 235, 128 with four heads to a kv head, 640, 947 ->
+// 514, 80, 384, 377 -> 325; 22700 rows of size 64 109 -> 78).  Two query blocks to a wave read LDS half as often and are slower all
+// the same: 490 at 80, 897 at 128 (fewer waves, and a completion of 64 tokens leaves half of them idle).
+// Masks only where the diagonal is, sums rescaled only where a maximum rose: the values are those of attention_kernel.
+template <int HD>
+__global__ __launch_bounds__(256) void attention_prompt_kernel(AttnArgs a, int heads_per_block) {
+  constexpr int KF = HD / 32, KHALF = HD % 32 ? 1 : 0;      // key steps of 32 dims, and one of 16
+  constexpr int KSTEPS = KF + KHALF, VT = HD / 16, NQ = HD / 64, VG = 4 * NQ, VR = VT - VG;
+  constexpr int NKF = 2 * KF + KHALF;                        // key fragments: two to a step, the half step's two share one
+  constexpr int FRAGS = NKF + VT;
+  // What the waves fetch: groups of 64 value dims (four units to a lane, wave w the groups w, w + 4, ...) and single fragments, the
+  // latter dealt out so that no wave has more than LEVEL units to a lane unless its groups alone are more
+  constexpr int SINGLES = NKF + VR, GW = (NQ + 3) / 4;
+  auto room = [](int level, int w) constexpr { const int n = level - 4 * ((NQ - w + 3) / 4); return n > 0 ? n : 0; };
+  constexpr int LEVEL = [&room] {
+    int level = 1;
+    while (room(level, 0) + room(level, 1) + room(level, 2) + room(level, 3) < SINGLES) ++level;
+    return level;
+  }();
+  __shared__ __attribute__((aligned(16))) uint16_t lds[2][FRAGS * 512];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c = lane & 15, g = lane >> 4;
+  const int Hkv = a.lay.Hkv, G = a.Hq / Hkv;
+  const int tw = 4 / heads_per_block;                        // waves along the tokens
+  const int hgroups = a.Hq / heads_per_block;
+  const int job = blockIdx.x / hgroups, hg = blockIdx.x - job * hgroups;
+  const int qhead = hg * heads_per_block + wave % heads_per_block, kvh = qhead / G;
+  const AttnJob jb = a.jobs[job * tw];
+  const int q0 = (jb.qblock + wave / heads_per_block) * 16;  // the wave's first query
+  const bool store_col = q0 + c < jb.len;
+  const int qpos = min(q0 + c, jb.len - 1), qrow = jb.row0 + qpos;
+  const int wave_keys = q0 < jb.len ? min(q0 + 16, jb.len) : 0;
+  const int block_keys = min((jb.qblock + tw) * 16, jb.len);
+  f16x8 qf[KSTEPS];
+  const uint16_t* qp = a.q + (size_t)qrow * a.q_ld + qhead * HD;
+#pragma unroll
+  for (int i = 0; i < KSTEPS; ++i) {
+    const int d0 = 32 * i + 8 * g;
+    if (d0 < HD) qf[i] = *(const f16x8*)(qp + d0);
+    else
+#pragma unroll
+      for (int e = 0; e < 8; ++e) qf[i][e] = (f16_t)0.f;
+  }
+  f32x4 o[VT];
+#pragma unroll
+  for (int t = 0; t < VT; ++t) o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, lsum = 0.f;
+  // this wave's single fragments: their lane offsets in a super-block and their places in LDS
+  int first = 0, singles = 0;
+  {
+    int at = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const int n = min(room(LEVEL, w), SINGLES - at);
+      if (w == wave) { first = at; singles = n; }
+      at += n;
+    }
+  }
+  uint32_t from[LEVEL];
+#pragma unroll
+  for (int l = 0; l < LEVEL; ++l) {
+    const int f = min(first + l, SINGLES - 1);
+    if (f < 2 * KF) from[l] = (f >= KF ? 16 * HD + (f - KF) * 512 : f * 512) + c * 32 + 8 * g;
+    else if (f < NKF) from[l] = (g >> 1) * 16 * HD + KF * 512 + c * 16 + 8 * (g & 1);
+    else from[l] = 32 * HD + NQ * 2048 + (f - NKF) * 512 + lane * 8;
+  }
+  u32x4 group[GW > 0 ? GW : 1][4], single[LEVEL];
+  const int nseg = jb.pre_len > 0 ? 2 : 1;
+  int buf = 0;
+  for (int seg = 0; seg < nseg; ++seg) {
+    const bool prefix = nseg == 2 && seg == 0;               // a shared prompt: every key visible
+    const int cache_seq = prefix ? jb.pre_seq : jb.cache_seq, nkeys = prefix ? jb.pre_len : block_keys;
+    const int own_keys = prefix ? (wave_keys > 0 ? nkeys : 0) : wave_keys;
+    const uint16_t* __restrict__ st = a.kv + a.lay.stream(a.kv_off[cache_seq], a.kv_cap[cache_seq], kvh);
+    const int nsb = (nkeys + 31) >> 5;
+    auto fetch = [&](int sb) {
+      const uint16_t* kb = st + (size_t)sb * 64 * HD;
+#pragma unroll
+      for (int q = 0; q < GW; ++q)
+        if (wave + 4 * q < NQ) {
+#pragma unroll
+          for (int p = 0; p < 4; ++p) group[q][p] = *(const u32x4*)(kb + (uint32_t)(32 * HD + (wave + 4 * q) * 2048 + p * 512 + lane * 8));
+        }
+#pragma unroll
+      for (int l = 0; l < LEVEL; ++l)
+        if (l < singles) single[l] = *(const u32x4*)(kb + from[l]);
+    };
+    auto put = [&](int to) {
+#pragma unroll
+      for (int q = 0; q < GW; ++q)
+        if (wave + 4 * q < NQ) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            f16x8 r;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+              const uint32_t w0 = group[q][p][i >> 1], w1 = group[q][p][2 + (i >> 1)];
+              const auto h = i & 1 ? __builtin_amdgcn_cvt_pkrtz(__uint_as_float(w0 & 0xffff0000u), __uint_as_float(w1 & 0xffff0000u))
+                                   : __builtin_amdgcn_cvt_pkrtz(__uint_as_float(w0 << 16), __uint_as_float(w1 << 16));
+              r[2 * p] = (f16_t)h[0];
+              r[2 * p + 1] = (f16_t)h[1];
+            }
+            *(f16x8*)(&lds[to][(NKF + 4 * (wave + 4 * q) + i) * 512 + lane * 8]) = r;
+          }
+        }
+#pragma unroll
+      for (int l = 0; l < LEVEL; ++l)
+        if (l < singles) *(f16x8*)(&lds[to][(first + l < NKF ? first + l : first + l + VG) * 512 + lane * 8]) = bf16x8_to_f16x8(single[l]);
+    };
+    fetch(0);
+    for (int sb = 0; sb < nsb; ++sb) {
+      put(buf);
+      if (sb + 1 < nsb) fetch(sb + 1);
+      // (requests for the next super-block stay on their way across the barrier; behind it nobody reads the other buffer any more)
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      const uint16_t* fr = lds[buf] + lane * 8;
+      const uint16_t* half = lds[buf] + 2 * KF * 512 + ((g & 1) * 16 + c) * 8;
+      buf ^= 1;
+      if (sb * 32 >= own_keys) continue;
+      f32x4 sc[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        sc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < KSTEPS; ++i) {
+          // (the half step: two lane groups read their chunk, the others read the same again against queries of zero)
+          const f16x8 kf = i < KF ? *(const f16x8*)(fr + (t * KF + i) * 512) : *(const f16x8*)(half + t * 256);
+          sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qf[i], sc[t], 0, 0, 0);
+        }
+      }
+      const int klimit = prefix ? nkeys - 1 : qpos;
+      float p[8], bmax = -INFINITY;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) p[e] = sc[e >> 2][e & 3] * a.scale;
+      if (sb * 32 + 31 > (prefix ? nkeys - 1 : q0)) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (sb * 32 + 8 * g + e > klimit) p[e] = -INFINITY;
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) bmax = fmaxf(bmax, p[e]);
+      bmax = fmaxf(bmax, __shfl_xor(bmax, 16, WAVE));
+      bmax = fmaxf(bmax, __shfl_xor(bmax, 32, WAVE));
+      const float mnew = fmaxf(m, bmax);
+      const bool rose = mnew > m;
+      // a column that has seen no key yet (m and mnew both -inf) keeps alpha = 1 and p = 0
+      const float alpha = mnew == -INFINITY ? 1.f : __expf(m - mnew);
+      m = mnew;
+      float psum = 0.f;
+      f16x8 pf;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        p[e] = mnew == -INFINITY ? 0.f : __expf(p[e] - mnew);
+        psum += p[e];
+        pf[e] = (f16_t)p[e];
+      }
+      lsum = lsum * alpha + psum;
+      if (__any(rose)) {
+#pragma unroll
+        for (int t = 0; t < VT; ++t) o[t] *= alpha;
+      }
+#pragma unroll
+      for (int t = 0; t < VT; ++t) o[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(*(const f16x8*)(fr + (NKF + t) * 512), pf, o[t], 0, 0, 0);
+    }
+  }
+  lsum += __shfl_xor(lsum, 16, WAVE);
+  lsum += __shfl_xor(lsum, 32, WAVE);
+  const float inv = 1.0f / lsum;
+  if (!store_col) return;
+#pragma unroll
+  for (int t = 0; t < VT; ++t) {
+    const int q = t & ~3, e = t & 3;
+    const f32x4 y = (t >= VG ? o[t] : f32x4{o[q][e], o[q + 1][e], o[q + 2][e], o[q + 3][e]}) * inv;
+    u32x2 w;
+    w[0] = pack_f16x2(y[0], y[1]);
+    w[1] = pack_f16x2(y[2], y[3]);
+    *(u32x2*)(a.out + kblk_off(qrow, qhead * HD + (t < VG ? 16 * q + 16 * g + 4 * e : 16 * t + 4 * g), a.out_rows)) = w;
+  }
+}
+
 template <int HD, bool DECODE, int QB, bool PR, int SPLIT>
 hipError_t launch(const AttnArgs& a, int jobs, hipStream_t s) {
   constexpr int lds_bytes = SPLIT > 1 ? SPLIT * (HD / 16 * 64 * 16 + 16 * (int)sizeof(float2)) : 0;
@@ -447,7 +627,8 @@ hipError_t launch_split(const AttnArgs& a, int jobs, hipStream_t s) {
     if (a.split >= 8 && HD <= 128 && !PR) return launch<HD, DECODE, QB, PR, (HD <= 128 && !PR) ? 8 : 4>(a, jobs, s);
   }
   if (a.split >= 4) return launch<HD, DECODE, QB, PR, 4>(a, jobs, s);
-  return launch<HD, DECODE, QB, PR, 1>(a, jobs, s);
+  if constexpr (DECODE || PR) return launch<HD, DECODE, QB, PR, 1>(a, jobs, s);
+  return hipErrorInvalidValue;
 }
 template <bool DECODE, int QB>
 hipError_t dispatch(const AttnArgs& a, int jobs, hipStream_t s) {
@@ -491,14 +672,30 @@ int rl_attention_decode_split(long long cap_jobs, int h) {
 // jobs at 1B 330 / 315, at 2.8B 281 / 283, at 8B 313 / 284; 2048 jobs 623 / 586, 485 / 488, 512 / 509, and with prompts of 128
 // tokens 529 / 544, 470 / 486, 474 / 491.
 int rl_attention_prefill_split(int cap_rows, int Hq, int h) {
-  const long long jobs = (long long)((cap_rows + 15) / 16) * Hq / rl_attention_prefill_qb(h);
+  const long long jobs = (long long)((cap_rows + 15) / 16) * Hq / (h <= 80 ? 2 : 1);
   return jobs <= 1024 ? 4 : 1;
 }
-// a.jobs: 16-token blocks; every sequence must contribute a multiple of rl_attention_prefill_qb(h) of them (blocks
-// past its end are allowed), since a wave takes that many consecutive blocks
-int rl_attention_prefill_qb(int h) { return h <= 80 ? 2 : 1; }
+// waves of a block of attention_prompt_kernel that differ in the query head
+static int prompt_heads(int G) { return G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1; }
+int rl_attention_prefill_jobs(int cap_rows, int Hq, int Hkv, int h, int precise) {
+  if (precise || rl_attention_prefill_split(cap_rows, Hq, h) > 1) return h <= 80 ? 2 : 1;
+  return 4 / prompt_heads(Hq / Hkv);
+}
 hipError_t rl_attention_prefill(const AttnArgs& a, hipStream_t s) {
-  const int qb = rl_attention_prefill_qb(a.lay.h);
-  if (a.njobs % qb != 0) return hipErrorInvalidValue;
-  return dispatch<false, 2>(a, a.njobs / qb * a.Hq, s);
+  if (a.precise || a.split > 1) {
+    const int qb = a.lay.h <= 80 ? 2 : 1;
+    if (a.njobs % qb != 0) return hipErrorInvalidValue;
+    return dispatch<false, 2>(a, a.njobs / qb * a.Hq, s);
+  }
+  if (a.njobs <= 0) return hipSuccess;
+  const int hb = prompt_heads(a.Hq / a.lay.Hkv), per = 4 / hb;
+  if (a.njobs % per != 0) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)((long long)a.njobs / per * (a.Hq / hb)));
+  switch (a.lay.h) {
+#define CASE(H) case H: hipLaunchKernelGGL((attention_prompt_kernel<H>), grid, dim3(256), 0, s, a, hb); break;
+    CASE(16) CASE(32) CASE(48) CASE(64) CASE(80) CASE(96) CASE(112) CASE(128) CASE(256)
+#undef CASE
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }

@@ -160,8 +160,9 @@ hipError_t rl_attention_decode(const AttnArgs& a, hipStream_t s);
 int rl_attention_decode_split(long long cap_jobs, int h);
 int rl_attention_prefill_split(int cap_rows, int Hq, int h);
 hipError_t rl_attention_prefill(const AttnArgs& a, hipStream_t s);
-// 16-token blocks a prompt-pass attention wave takes at once for head size h; a.jobs must list a multiple of it per sequence
-int rl_attention_prefill_qb(int h);
+// 16-token blocks that a wave or the waves of a block take at once in a context of cap_rows rows; a.jobs must list a multiple of it
+// per sequence, and nothing else (blocks past the sequence's end do nothing)
+int rl_attention_prefill_jobs(int cap_rows, int Hq, int Hkv, int h, int precise);
 
 // ------------------------------------------------------------------ element-wise and small kernels
 // dst bf16 <- src (fp32 rounded to nearest even, or bf16 copied); n elements

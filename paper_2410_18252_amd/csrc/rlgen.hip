@@ -227,7 +227,7 @@ size_t carve(rlgen_ctx* c, char* base) {
   c->d_cmp = k.take<int>(base, 8 * S); c->d_lists = k.take<int>(base, 3 * S);
   c->d_tok_index = k.take<int>(base, R); c->d_pos = k.take<int>(base, R); c->d_dst_seq = k.take<int>(base, R);
   c->d_lm_row = k.take<int>(base, R); c->d_target = k.take<int>(base, R); c->d_out_index = k.take<int>(base, R);
-  c->d_jobs = k.take<AttnJob>(base, R / 16 + 4 * S + 2);
+  c->d_jobs = k.take<AttnJob>(base, R / 16 + 8 * S + 2);       // up to 4 blocks more for each of 2 S streams
   c->Sg = (2 * m.max_seqs + 2) / 3 + 1;        // the larger half: ceil(B / 2) prompts of B >= 2, k samples each
   for (int i = 0; i < 3; ++i) {
     const size_t rows = i == 0 ? R : (size_t)c->Sg, lm = i == 0 ? LM : (size_t)c->Sg;
@@ -380,7 +380,8 @@ __global__ void clamp_targets_kernel(int* target, int n, int vocab, unsigned* st
 struct Chunk { int first, count, rows, jobs, lm_rows; };
 // 16-token blocks of a sequence of `len` tokens in the job list: rounded up to what one attention wave takes
 int jobs_of(const rlgen_ctx* c, int len) {
-  const int per = 16 * rl_attention_prefill_qb(c->cfg.head_dim);
+  const rlgen_model_cfg& m = c->cfg;
+  const int per = 16 * rl_attention_prefill_jobs(c->R, m.n_q_heads, m.n_kv_heads, m.head_dim, m.precise);
   return (len + per - 1) / per * (per / 16);
 }
 
@@ -957,7 +958,7 @@ int stage_upload(rlgen_ctx* c, const Staged& s, int nmeta, int nseq, int nstream
 int expand(rlgen_ctx* c, const Chunk& ch, const int* tokens, bool scoring, hipStream_t st) {
   hipLaunchKernelGGL(expand_kernel, dim3(ch.count), dim3(256), 0, st, c->d_meta, ch.first, tokens, c->d_tok_index, c->d_pos,
                      c->d_dst_seq, c->d_jobs, c->d_lm_row, c->d_target, c->d_out_index, scoring ? 1 : 0,
-                     rl_attention_prefill_qb(c->cfg.head_dim), c->status);
+                     jobs_of(c, 1), c->status);
   HIPCHK(hipGetLastError());
   return RLGEN_OK;
 }

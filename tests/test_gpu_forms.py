@@ -410,3 +410,41 @@ def test_qkv_and_ffn_up_in_one_launch_match_the_reference(m):
     for b in range(5):
         want = O.score(dec, np.concatenate([arr[b, :lens[b]], forced[b, 0]]), 0.7, score_from=int(lens[b]))[lens[b]:]
         assert np.abs(outs[0].numpy()[b, 0] - want).max() < TOL_LOGPROB
+
+
+# contexts with room for enough rows that the waves of a block share the super-blocks of a prompt pass: every division of the head
+# dims among them, waves along the tokens, the heads of a group or both; a group of three has no heads to share
+@pytest.mark.parametrize("hq, hkv, h", [(4, 4, 16), (3, 3, 32), (2, 2, 48), (2, 2, 64), (2, 2, 80), (2, 2, 96), (2, 2, 112), (2, 2, 128), (1, 1, 256),
+                                        (4, 1, 64), (4, 2, 80), (3, 1, 32), (8, 2, 128), (4, 1, 112), (2, 1, 256)])
+def test_prompt_attention_with_shared_super_blocks_matches_the_reference(hq, hkv, h):
+    """Sequences of 1 to 200 tokens (ends inside and at the end of query blocks, blocks of waves and super-blocks), on their own and as
+    completions behind a shared prompt."""
+    m = ModelShape(0 if hq == hkv else 1, 1, hq * h, hq, hkv, h, 96, 150, rotary_dim=h // 4 * 4 if h < 64 else 16 if hq == hkv else h)
+    W = scaled_bf16_weights(m)
+    dec = RoundedDecoder(W, m, DEFAULT_FORMATS)       # with the formats applied: on widths of 64 and 96 they alone are up to 0.012 off
+    rng = np.random.default_rng(67)
+    lens = [1, 15, 16, 17, 32, 33, 64, 65, 127, 128, 129, 200]
+    arr, lens = padded([rng.integers(0, m.vocab, size=n) for n in lens])
+    r = R()
+    pol = make_policy(W, max_seqs=12, max_seq_len=300, max_kv_tokens=12 * 320, max_batch_tokens=40000)
+    try:
+        lp = r.rlgen_score(pol, dev_i32(arr), lens, 0.7).cpu().numpy()
+        for n in range(12):
+            if lens[n] > 1:
+                assert np.abs(lp[n, :lens[n]] - O.score(dec, arr[n, :lens[n]], 0.7)).max() < TOL_LOGPROB
+        P, tails = 77, [1, 16, 33, 90]
+        full = np.zeros((4, P + 90), np.int32)
+        full[:, :P] = arr[11, :P]
+        for j, n in enumerate(tails):
+            full[j, P:P + n] = rng.integers(0, m.vocab, size=n)
+        total = [P + n for n in tails]
+        plain = r.rlgen_score(pol, dev_i32(full), total, 0.7, [P] * 4).cpu().numpy()
+        r.rlgen_set_score_groups(pol, 4)
+        grouped = r.rlgen_score(pol, dev_i32(full), total, 0.7, [P] * 4).cpu().numpy()
+        assert r.rlgen_status(pol) == 0
+    finally:
+        pol.close()
+    for j, n in enumerate(tails):
+        want = O.score(dec, full[j, :P + n], 0.7, score_from=P)[P:]
+        assert np.abs(plain[j, P:P + n] - want).max() < TOL_LOGPROB
+        assert np.abs(grouped[j, P:P + n] - want).max() < TOL_LOGPROB
