@@ -122,12 +122,13 @@ def _check(code: int, where: str):
         raise RlgenError(code, where)
 
 
+# plain integers (the argument types make pointers of them) and the raw stream: the objects in between cost a short call 1 to 2 us
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _host_i32(a):
@@ -280,7 +281,7 @@ def rlgen_sequence_logprob(token_logprobs: torch.Tensor, start: torch.Tensor, le
     N, stride = token_logprobs.shape
     assert token_logprobs.dtype == torch.float32 and token_logprobs.is_contiguous()
     assert start.dtype == torch.int32 and lens.dtype == torch.int32
-    out = torch.empty(N, dtype=torch.float32, device=token_logprobs.device)
+    out = token_logprobs.new_empty(N)
     _check(lib.rlgen_sequence_logprob(_ptr(token_logprobs), _ptr(start), _ptr(lens), N, stride, _ptr(out), _stream()),
            "rlgen_sequence_logprob")
     return out
@@ -290,7 +291,7 @@ def rlgen_dpo_loss(pol_pos, ref_pos, pol_neg, ref_neg, beta: float):
     P = pol_pos.numel()
     for t in (pol_pos, ref_pos, pol_neg, ref_neg):
         assert t.dtype == torch.float32 and t.is_contiguous() and t.numel() == P
-    out = torch.empty(P, dtype=torch.float32, device=pol_pos.device)
+    out = pol_pos.new_empty(P)
     _check(lib.rlgen_dpo_loss(_ptr(pol_pos), _ptr(ref_pos), _ptr(pol_neg), _ptr(ref_neg), P, beta, _ptr(out), _stream()),
            "rlgen_dpo_loss")
     return out
@@ -302,7 +303,7 @@ def rlgen_proximal_rloo(pol_logprob, old_logprob, rewards, epsilon: float):
     B, k = rewards.shape
     for t in (pol_logprob, old_logprob, rewards):
         assert t.dtype == torch.float32 and t.is_contiguous() and tuple(t.shape) == (B, k)
-    out = torch.empty(B, k, dtype=torch.float32, device=rewards.device)
+    out = rewards.new_empty((B, k))
     _check(lib.rlgen_proximal_rloo(_ptr(pol_logprob), _ptr(old_logprob), _ptr(rewards), B, k, epsilon, _ptr(out), _stream()),
            "rlgen_proximal_rloo")
     return out
@@ -312,8 +313,7 @@ def rlgen_select_pairs(rewards):
     """rewards [B, k] fp32 on the device -> (idx_pos, idx_neg), each [B] int32."""
     assert rewards.dtype == torch.float32 and rewards.is_contiguous() and rewards.dim() == 2
     B, k = rewards.shape
-    pos = torch.empty(B, dtype=torch.int32, device=rewards.device)
-    neg = torch.empty(B, dtype=torch.int32, device=rewards.device)
+    pos, neg = rewards.new_empty(B, dtype=torch.int32), rewards.new_empty(B, dtype=torch.int32)
     _check(lib.rlgen_select_pairs(_ptr(rewards), B, k, _ptr(pos), _ptr(neg), _stream()), "rlgen_select_pairs")
     return pos, neg
 
