@@ -98,3 +98,13 @@ __device__ __forceinline__ float wave_max(float v) {
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, WAVE));
   return v;
 }
+// eight bf16 values to fp32
+__device__ __forceinline__ void widen_bf16x8(float* dst, u32x4 v) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    f32x4 y;
+    y[0] = __uint_as_float(v[2 * h] << 16); y[1] = __uint_as_float(v[2 * h] & 0xffff0000u);
+    y[2] = __uint_as_float(v[2 * h + 1] << 16); y[3] = __uint_as_float(v[2 * h + 1] & 0xffff0000u);
+    *(f32x4*)(dst + 4 * h) = y;
+  }
+}

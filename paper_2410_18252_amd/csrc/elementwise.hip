@@ -86,14 +86,7 @@ __global__ void embed_kernel(float* x, const uint16_t* E, const int* tokens, con
   const uint16_t* e = E + (size_t)tok * d;
   float* xr = x + (size_t)row * d;
   for (int i = threadIdx.x * 8; i < d; i += blockDim.x * 8) {
-    const u32x4 v = *(const u32x4*)(e + i);
-    f32x4 lo, hi;
-    lo[0] = __uint_as_float(v[0] << 16); lo[1] = __uint_as_float(v[0] & 0xffff0000u);
-    lo[2] = __uint_as_float(v[1] << 16); lo[3] = __uint_as_float(v[1] & 0xffff0000u);
-    hi[0] = __uint_as_float(v[2] << 16); hi[1] = __uint_as_float(v[2] & 0xffff0000u);
-    hi[2] = __uint_as_float(v[3] << 16); hi[3] = __uint_as_float(v[3] & 0xffff0000u);
-    *(f32x4*)(xr + i) = lo;
-    *(f32x4*)(xr + i + 4) = hi;
+    widen_bf16x8(xr + i, *(const u32x4*)(e + i));
   }
 }
 

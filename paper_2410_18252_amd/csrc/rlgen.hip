@@ -579,7 +579,7 @@ int lm_head_stats(rlgen_ctx* c, const uint16_t* hfin, int rows, float temperatur
 // temperature 0 selects greedy decoding: arg max of the logits, log-prob under softmax(z)
 int sample_rows(rlgen_ctx* c, int rows, float temperature, const float* uniforms, const int* forced, int io_stride,
                 int io_add, int* tokens, float* logprobs, int* next_token, hipStream_t st, int* finished = nullptr,
-                const int* io_index = nullptr) {
+                const int* io_index = nullptr, float* x = nullptr) {
   const bool greedy = temperature == 0.f;
   if (greedy) temperature = 1.f;
   int rc = lm_head_stats(c, c->hfin, rows, temperature, nullptr, st);
@@ -590,6 +590,7 @@ int sample_rows(rlgen_ctx* c, int rows, float temperature, const float* uniforms
   s.lm_head = c->lm_head; s.vocab = c->cfg.vocab; s.temperature = temperature;
   s.uniforms = uniforms; s.forced = forced; s.io_index = io_index; s.io_stride = io_stride; s.io_add = io_add;
   s.tokens = tokens; s.logprobs = logprobs; s.next_token = next_token; s.R = rows; s.status = c->status;
+  s.embed = c->embed; s.x = x;
   s.greedy = greedy ? 1 : 0; s.eos = c->eos_token; s.finished = c->eos_token >= 0 ? finished : nullptr;
   HIPCHK(rl_sample(s, st));
   return RLGEN_OK;
@@ -1299,21 +1300,22 @@ int rlgen_generate(rlgen_ctx* c, const int32_t* prompts, const int32_t* prompt_l
   }
   if (c->timed) HIPCHK(hipEventRecord(c->ev_mid, st));
   if (c->eos_token >= 0) HIPCHK(rl_fill_zero(c->d_finished, align_up((size_t)S * 4, 16), st));
-  rc = sample_rows(c, S, temperature, uniforms, forced, max_new, 0, tokens, token_logprobs, c->d_next_token, st, c->d_finished);
+  rc = sample_rows(c, S, temperature, uniforms, forced, max_new, 0, tokens, token_logprobs, c->d_next_token, st, c->d_finished, nullptr, c->x);
   if (rc) return rc;
-  // one decode step of sequences g0 .. g0 + n - 1 on stream gs, with the activation set in use
-  auto decode_step = [&](int t, DecView dv, int n, hipStream_t gs) -> int {
-    HIPCHK(rl_embed(c->x, c->embed, dv.row_seq ? dv.row_next : c->d_next_token + dv.g0, nullptr, n, m.d_model, m.vocab, c->status, gs));
+  // One decode step of sequences g0 .. g0 + n - 1 on stream gs, with the activation set in use.  A step's sampling leaves the
+  // embedded tokens in that set's rows for the next one; `fresh`: they are not there (the first step of a half, or rows moved)
+  auto decode_step = [&](int t, DecView dv, int n, hipStream_t gs, bool fresh) -> int {
+    if (fresh) HIPCHK(rl_embed(c->x, c->embed, dv.row_seq ? dv.row_next : c->d_next_token + dv.g0, nullptr, n, m.d_model, m.vocab, c->status, gs));
     NormParts parts;
     int r2 = run_layers(c, n, true, t, 1, true, 0, gs, dv, &parts);
     if (r2) return r2;
     r2 = final_norm(c, nullptr, n, n, 0, gs, parts);
     if (r2) return r2;
     if (dv.row_seq)       // row i reads and writes the entries of sequence row_seq[i]
-      return sample_rows(c, n, temperature, uniforms, forced, max_new, t, tokens, token_logprobs, dv.row_next, gs, dv.row_fin, dv.row_seq);
+      return sample_rows(c, n, temperature, uniforms, forced, max_new, t, tokens, token_logprobs, dv.row_next, gs, dv.row_fin, dv.row_seq, c->x);
     const size_t o = (size_t)dv.g0 * max_new;
     return sample_rows(c, n, temperature, uniforms + o, forced ? forced + o : nullptr, max_new, t, tokens + o, token_logprobs + o,
-                       c->d_next_token + dv.g0, gs, c->d_finished + dv.g0);
+                       c->d_next_token + dv.g0, gs, c->d_finished + dv.g0, nullptr, c->x);
   };
   if (ngroups == 2 && max_new > 1) {
     HIPCHK(hipEventRecord(c->ev_fork, st));
@@ -1323,7 +1325,7 @@ int rlgen_generate(rlgen_ctx* c, const int32_t* prompts, const int32_t* prompt_l
         use_set(c, 1 + gi);
         c->half_rows = c->tuned[2][0].variant >= 0;
         const int b0 = gi == 0 ? 0 : Bh, nb = gi == 0 ? Bh : B - Bh;
-        rc = decode_step(t, DecView{b0 * k, b0, B}, nb * k, c->gstream[gi]);
+        rc = decode_step(t, DecView{b0 * k, b0, B}, nb * k, c->gstream[gi], t == 1);
       }
     use_set(c, 0);
     c->half_rows = false;
@@ -1344,6 +1346,7 @@ int rlgen_generate(rlgen_ctx* c, const int32_t* prompts, const int32_t* prompt_l
     dv.row_order = c->use_order ? c->d_order : nullptr;
     int rows = S, side = 0;
     for (int t = 1; t < max_new && rows > 0; ++t) {
+      bool moved = false;
       if (t % c->eos_every == 0) {
         HIPCHK(hipMemcpyAsync(c->h_fin, dv.row_fin, (size_t)rows * 4, hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
@@ -1376,15 +1379,16 @@ int rlgen_generate(rlgen_ctx* c, const int32_t* prompts, const int32_t* prompt_l
             side ^= 1;
           }
           rows = kept;
+          moved = true;
           if (rows == 0) break;
         }
       }
-      rc = decode_step(t, dv, rows, st);
+      rc = decode_step(t, dv, rows, st, moved);
       if (rc) return rc;
     }
   } else {
     for (int t = 1; t < max_new; ++t) {
-      rc = decode_step(t, DecView{0, 0, B}, S, st);
+      rc = decode_step(t, DecView{0, 0, B}, S, st, false);
       if (rc) return rc;
     }
   }

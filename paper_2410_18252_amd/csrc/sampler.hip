@@ -40,12 +40,19 @@ __global__ __launch_bounds__(256) void sample_kernel(SampleArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int row = blockIdx.x;
   const size_t idx = (size_t)(a.io_index ? a.io_index[row] : row) * a.io_stride + a.io_add;
+  // the token's row of the embedding is where the next step starts: taken along here (first .. by step, 8 dims each), it is a launch
+  // and a hand-over less per step
+  auto embed = [&](int tok, int first, int step) {
+    if (a.x == nullptr) return;
+    for (int i = 8 * first; i < a.d; i += 8 * step) widen_bf16x8(a.x + (size_t)row * a.d + i, *(const u32x4*)(a.embed + (size_t)tok * a.d + i));
+  };
   if (a.finished && a.finished[row]) {            // the completion ended at an earlier step
     if (threadIdx.x == 0) {
       a.tokens[idx] = a.eos;
       a.logprobs[idx] = 0.f;
       if (a.next_token) a.next_token[row] = a.eos;
     }
+    embed(a.eos, threadIdx.x, 256);
     return;
   }
   float u = a.greedy ? 0.f : a.uniforms[idx];
@@ -226,6 +233,7 @@ __global__ __launch_bounds__(256) void sample_kernel(SampleArgs a) {
     if (a.next_token) a.next_token[row] = tok;
     if (a.finished && tok == a.eos) a.finished[row] = 1;
   }
+  embed(tok, lane, 64);
 }
 
 __global__ __launch_bounds__(256) void score_finalize_kernel(const float2* partial, int ngroups, const float* target_logit,
