@@ -661,11 +661,13 @@ hipError_t rl_attention_decode(const AttnArgs& a, hipStream_t s) {
 // size 64 37.8 / 35.9 us, 2048 at head size 128 125 / 148 us.  A decode layer on either side of the borders (us, 256 and 1500 keys):
 // twice the upper one, one wave / four: 1024 jobs of size 256 127 / 144 and 324 / 320, 3264 of size 80 155 / 157 and 345 / 337; twice
 // the lower one, four waves / eight: 1024 of size 64 50 / 49 and 100 / 96, 800 of size 80 102 / 110 and 150 / 158, 512 of size 128
-// 176 / 221 and 223 / 294; below it, four / eight: 384 of size 80 90 / 93 and 114 / 119, 128 of size 128 159 / 176 and 170 / 198 (there
-// four would do better).
+// 176 / 221 and 223 / 294.  Eight waves leave a wave 256 registers, in which the wider heads' super-blocks hardly fit: for those the
+// lower border is half as high.  Four / eight there: 384 of size 80 69.8 / 72.6 and 93.2 / 98.1, 256 of size 128 136.2 / 144.9 and
+// 160.3 / 174.2, 240 of size 128 177.2 / 185.9 and 199.5 / 212.3; below it 128 of size 80 65.5 / 64.6 and 79.1 / 75.6, 64 of size 128
+// 127.5 / 130.2 and 146.7 / 146.8, 8 of size 128 128.7 / 129.5 and 145.8 / 143.8.
 int rl_attention_decode_split(long long cap_jobs, int h) {
   const long long size = cap_jobs * (h > 64 ? h : 64);
-  return size <= 32768 ? 8 : size <= 131072 ? 4 : 1;
+  return size <= (h > 64 ? 16384 : 32768) ? 8 : size <= 131072 ? 4 : 1;
 }
 // The same for a prompt pass of at most cap_rows rows: up to four jobs a CU (654 rows of 8 heads of size 256: 57 ->
 // 21 us a layer).  A layer of prompts of 500 tokens, one wave / four (us): 512 jobs at 1B width 231 / 191, at 8B 312 / 286; 1024

@@ -832,6 +832,8 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
         a.W = which == G_QKV ? l.wqkv : which == G_O ? l.wo : which == G_UP ? l.wup : which == G_DOWN ? (c->joined_out ? l.wo : l.wdown) : c->lm_head;
       };
       if (cands.size() == 1) {
+        // (launched once all the same: the kernel is loaded and configured here and not in the first call, which may be captured)
+        if (run_choice(g, epi, cands[0], splits, st) != hipSuccess) { rc = RLGEN_ERR_DEVICE; break; }
         c->tuned[mode][which] = {cands[0], splits};
         continue;
       }
