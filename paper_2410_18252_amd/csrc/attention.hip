@@ -670,9 +670,11 @@ int rl_attention_decode_split(long long cap_jobs, int h) {
   return size <= (h > 64 ? 16384 : 32768) ? 8 : size <= 131072 ? 4 : 1;
 }
 // The same for a prompt pass of at most cap_rows rows: up to four jobs a CU (654 rows of 8 heads of size 256: 57 ->
-// 21 us a layer).  A layer of prompts of 500 tokens, one wave / four (us): 512 jobs at 1B width 231 / 191, at 8B 312 / 286; 1024
-// jobs at 1B 330 / 315, at 2.8B 281 / 283, at 8B 313 / 284; 2048 jobs 623 / 586, 485 / 488, 512 / 509, and with prompts of 128
-// tokens 529 / 544, 470 / 486, 474 / 491.
+// 21 us a layer).  A layer of prompts of 500 / 128 tokens, the waves of a block sharing super-blocks against sharing jobs (us): 256 jobs
+// at 1B width 122 / 101 against 107 / 99, at 2.8B 156 / 105 and 150 / 104, at 410M 58 / 49 and 50 / 47; 512 jobs at 1B 171 / 151 and
+// 167 / 155, at 410M 74 / 66 and 69 / 66, at 8B 280 / 190 both; 1024 jobs at 1B 277 / 262 and 297 / 275, else within 1 %; 2048 jobs
+// 495 / 478 and 566 / 517, at 2.8B 451 / 448 and 467 / 465, at 8B 479 / 467 and 489 / 472.  (The border is by what a context can
+// hold; calls that fill half of it lie where sharing jobs is ahead.)
 int rl_attention_prefill_split(int cap_rows, int Hq, int h) {
   const long long jobs = (long long)((cap_rows + 15) / 16) * Hq / (h <= 80 ? 2 : 1);
   return jobs <= 1024 ? 4 : 1;
