@@ -36,9 +36,6 @@
 #ifndef ATTN_PROMPT_NOPF
 #define ATTN_PROMPT_NOPF 1
 #endif
-#ifndef ATTN_PROMPT_BLOCKS
-#define ATTN_PROMPT_BLOCKS 2
-#endif
 #ifndef ATTN_NT
 #define ATTN_NT 1
 #endif
@@ -56,7 +53,7 @@ namespace {
 // QB = query blocks of 16 columns a wave carries through one pass over the keys (prompt pass only: two blocks halve
 // the key / value traffic per query; a.jobs then counts blocks of 16 QB tokens).
 template <int HD, bool DECODE, int QB = 1, bool PR = false, int SPLIT = 1>
-__global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= (PR ? 80 : 128) && SPLIT == 1) ? ATTN_PROMPT_BLOCKS : 1) void attention_kernel(AttnArgs a) {
+__global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, 1) void attention_kernel(AttnArgs a) {
   static_assert(!DECODE || QB == 1, "decode has one query block");
   static_assert(SPLIT == 1 || SPLIT == 4 || (DECODE && SPLIT == 8), "a job is shared by all waves of a block");
   constexpr int NCH = HD / 8;            // 16-byte chunks per key row
@@ -67,7 +64,9 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= (PR
   constexpr bool PF = (DECODE || !ATTN_PROMPT_NOPF) && !PR;
   constexpr int NP = PR ? 2 : 1;         // cache planes: hi, lo
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);         // (common to the wave: the job's addresses are scalar)
+  // A wave number known to be common to the wave makes the job's addresses scalar.  Not for two query blocks to a wave: the compiler
+  // then orders their loop worse (precise mode, head size 48, 16 prompts of 500 tokens, 20 heads: 117 -> 123 us)
+  const int wave = QB == 1 || SPLIT > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : (int)(threadIdx.x >> 6);
   const int c = lane & 15, g = lane >> 4;
   const int Hkv = a.lay.Hkv, G = a.Hq / Hkv;
   const int job = SPLIT > 1 ? blockIdx.x : blockIdx.x * 4 + wave;
@@ -245,6 +244,10 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= (PR
     else {
       load_sb(sb, kraw, vraw);
       if constexpr (PR) load_sb(sb, kraw_lo, vraw_lo, 1);
+      // Left to itself the scheduler puts requests back to save registers, for a wave more that cannot come, and the chain waits for
+      // each.  A wave of four to a job, with two to a SIMD at most, asks for both planes at once (us a layer: decode of 8 sequences of
+      // 600 keys, head size 64 16.6 -> 11.6, 128 27.5 -> 17.6; 300 rows of size 128 15.0 -> 10.1; not two query blocks: 9.0 -> 9.6 at 64)
+      if constexpr (PR && SPLIT > 1 && QB == 1) __builtin_amdgcn_sched_barrier(0);
     }
 #elif ATTN_PREFETCH
     if (sb + SPLIT < nsb) load_sb(sb + SPLIT, knext, vnext);
@@ -275,6 +278,9 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, (!DECODE && HD <= (PR
           }
         }
       }
+    // ... and one wave to a job in the prompt pass has its values on their way before the softmax (24 sequences of 514 tokens, 32
+    // heads of size 128 on 8: 619 -> 520 us a layer, 536 with two waves to a SIMD prescribed; all requests first: 548 and more)
+    if constexpr (PR && SPLIT == 1 && !DECODE && QB == 1) __builtin_amdgcn_sched_barrier(0);
     // lane (c, g) now holds the scores of keys 32 sb + 8 g + 4 t + j against column c
     float p[QB][8], alpha[QB];
 #pragma unroll
