@@ -448,3 +448,38 @@ def test_prompt_attention_with_shared_super_blocks_matches_the_reference(hq, hkv
         want = O.score(dec, full[j, :P + n], 0.7, score_from=P)[P:]
         assert np.abs(plain[j, P:P + n] - want).max() < TOL_LOGPROB
         assert np.abs(grouped[j, P:P + n] - want).max() < TOL_LOGPROB
+
+
+@pytest.mark.parametrize("h", [16, 48, 80, 112])
+def test_both_prompt_forms_agree_on_queries_that_an_infinite_key_does_not_reach(h):
+    """Queries and keys are biases alone, the keys' large enough that the rotation (by the position itself, theta is 1) takes them
+    beyond bf16 at some positions: the head's last dim at position 1, its partner h / 2 before it at 2.  The queries of the first
+    four positions score such keys at minus infinity, weight zero, and their rows stay what they are without them: in a small
+    context, where the waves of a block share a job, and in a large one, where they share super-blocks and head sizes that are no
+    multiple of 32 end on half a step."""
+    from workloads import f32_to_bf16_bits
+    m = ModelShape(0, 1, 2 * h, 2, 2, h, 96, 150, rotary_dim=h, rope_theta=1.0)
+    W = scaled_bf16_weights(m)
+    pair = [h // 2 - 1, h - 1]
+    bq, bk = np.zeros(2 * h, np.float32), np.zeros(2 * h, np.float32)
+    bq[pair] = np.cos(-3.2), np.sin(-3.2)
+    bk[pair] = 2.9e38
+    zero = f32_to_bf16_bits(np.zeros((2 * h, 2 * h), np.float32))
+    W.tensors.update({"layers.0.wq": zero, "layers.0.wk": zero, "layers.0.bq": f32_to_bf16_bits(bq), "layers.0.bk": f32_to_bf16_bits(bk)})
+    pos = np.arange(4)
+    k0, k2 = 2.9 * (np.cos(pos) - np.sin(pos)), 2.9 * (np.cos(pos) + np.sin(pos))
+    q0, q2 = np.cos(pos - 3.2), np.sin(pos - 3.2)
+    assert list(np.abs(k0) > 3.39) == [False, False, True, False] and list(np.abs(k2) > 3.39) == [False, True, False, False]
+    assert (q2[1:] * k2[1] < 0).all() and (q0[2:] * k0[2] < 0).all()
+    rng = np.random.default_rng(71)
+    seqs = dev_i32(rng.integers(0, m.vocab, size=(6, 5)))
+    r = R()
+    outs = []
+    for rows in (64, 40000):
+        pol = make_policy(W, max_seqs=6, max_seq_len=32, max_batch_tokens=rows)
+        try:
+            outs.append(r.rlgen_score(pol, seqs, [5] * 6, 0.7).cpu().numpy())
+            assert r.rlgen_status_bits(pol) == 8
+        finally:
+            pol.close()
+    assert np.isfinite(outs[0]).all() and np.abs(outs[1][:, 1:] - outs[0][:, 1:]).max() < TOL_LOGPROB
