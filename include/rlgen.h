@@ -278,13 +278,14 @@ int rlgen_set_decode_split_min(rlgen_ctx *ctx, int32_t min_seqs);
 
 /* The tile shape (`variant`, an index into the library's list of GEMM tilings) and the K split the context uses for
  * linear layer `which` (0 QKV, 1 attention output, 2 FFN up, 3 FFN down, 4 LM head) in `mode` (0: decode of the whole
- * batch, 1: prompt pass and scoring, 2: decode of half a batch).  variant -1 = chosen per call from the problem size.
+ * batch, 1: prompt pass and scoring, 2: decode of half a batch).  variant -1 = chosen per call from the problem size; -2
+ * (FFN up of a GPT-NeoX block only) = computed in QKV's launch, with QKV's tile shape.
  * rlgen_debug_set_gemm replaces the tile shape (testing and measurement); the K split cannot be set: it is a function
- * of the configuration.  A decode layer of few rows whose K is divided among the waves of a block reports that division
- * (8) and has no tile shape to replace; with the GPT-NeoX block (n_q_heads * head_dim a multiple of 64) the attention
- * output is part of FFN down's product and `which` 1 has no launch of its own: replacing either's tile shape changes
- * nothing.  Errors: NULL, BAD_ARG (mode, which or variant out of range, or a tile shape this layer's epilogue does not
- * support). */
+ * of the configuration.  A shape set for an FFN up in QKV's launch gives it a launch of its own, and -2 takes it back where
+ * the context had it there.  With the GPT-NeoX block (n_q_heads * head_dim a multiple of 64) the attention output is part of
+ * FFN down's product and `which` 1 has no launch of its own: replacing its tile shape changes nothing.  Errors: NULL, BAD_ARG
+ * (mode, which or variant out of range, -2 where the context has no such launch, or a tile shape this layer's epilogue
+ * does not support). */
 int rlgen_debug_get_gemm(rlgen_ctx *ctx, int32_t mode, int32_t which, int32_t *variant, int32_t *splits);
 int rlgen_debug_set_gemm(rlgen_ctx *ctx, int32_t mode, int32_t which, int32_t variant);
 

@@ -90,6 +90,7 @@ struct rlgen_ctx {
   // and both norms of a block read the same rows, so that the QKV and FFN-up products do not wait for each other: one launch, where
   // FFN-up is not cut into parts ([decode | prompt pass]; fused_qkv, not in precise mode)
   bool joined_in[2];
+  bool apart[3];          // rlgen_debug_set_gemm gave a mode's FFN-up a tile shape, and with it a launch of its own again
   bool fused_qkv;         // rotary_dim % 4 == 0: rotary embedding and cache writes run in the QKV GEMM's epilogue
   int score_groups;       // k > 1: rlgen_score treats every k consecutive sequences as one prompt with k completions
   int eos_token;          // -1: completions never end early (rlgen_set_eos)
@@ -169,6 +170,9 @@ int check_cfg(const rlgen_model_cfg* c) {
   if (c->precise != 0 && (c->precise != 1 || c->rotary_dim % 4 != 0 || h > 128)) return RLGEN_ERR_BAD_CFG;
   return RLGEN_OK;
 }
+
+// do the QKV and FFN-up products of a mode (as in rlgen_debug_get_gemm) share a launch
+bool one_launch_in(const rlgen_ctx* c, int mode) { return c->joined_in[mode == 1] && !c->apart[mode]; }
 
 void use_set(rlgen_ctx* c, int i) {
   const rlgen_ctx::Bufs& b = c->set[i];
@@ -446,7 +450,7 @@ int run_layers(rlgen_ctx* c, int rows, bool decode, int t, int ncopy, bool use_c
   const int d = m.d_model, F = m.d_ffn, h = m.head_dim;
   const int qd = m.n_q_heads * h, nqkv = qd + 2 * m.n_kv_heads * h;
   NormParts parts;           // a product the next norm has to add to the residual first
-  const bool joined_in = c->joined_in[decode ? 0 : 1];
+  const bool joined_in = one_launch_in(c, decode ? (c->half_rows ? 2 : 0) : 1);
   for (int l = 0; l < m.n_layers; ++l) {
     const LayerW& L = c->layers[l];
     uint16_t* kvl = c->kv + (use_cache_layers ? (size_t)c->lay.layer_stride * l : 0);
@@ -1559,18 +1563,24 @@ int rlgen_set_decode_split_min(rlgen_ctx* c, int32_t min_seqs) {
 int rlgen_debug_get_gemm(rlgen_ctx* c, int32_t mode, int32_t which, int32_t* variant, int32_t* splits) {
   if (!c) return RLGEN_ERR_NULL;
   if (mode < 0 || mode > 2 || which < 0 || which > 4) return RLGEN_ERR_BAD_ARG;
-  if (variant) *variant = c->tuned[mode][which].variant;
+  if (variant) *variant = which == G_UP && one_launch_in(c, mode) ? -2 : c->tuned[mode][which].variant;
   if (splits) *splits = c->tuned[mode == 1 ? 1 : 0][which].splits;
   return RLGEN_OK;
 }
 
 int rlgen_debug_set_gemm(rlgen_ctx* c, int32_t mode, int32_t which, int32_t variant) {
   if (!c) return RLGEN_ERR_NULL;
-  if (mode < 0 || mode > 2 || which < 0 || which > 4 || variant < -1 || variant > 10) return RLGEN_ERR_BAD_ARG;
+  if (mode < 0 || mode > 2 || which < 0 || which > 4 || variant < -2 || variant > 10) return RLGEN_ERR_BAD_ARG;
+  if (variant == -2) {
+    if (which != G_UP || !c->joined_in[mode == 1]) return RLGEN_ERR_BAD_ARG;
+    c->apart[mode] = false;
+    return RLGEN_OK;
+  }
   // the fused gate/up and LM-head epilogues need a wave to own 64 columns: not the 64-column-per-wave-pair shapes
   const bool wide_only = which == G_LMHEAD || (which == G_UP && c->cfg.arch == RLGEN_ARCH_LLAMA);
   if (wide_only && variant >= 6 && variant <= 9) return RLGEN_ERR_BAD_ARG;
   if (c->cfg.precise && variant != -1 && variant != 0 && variant != 3 && variant != 5 && variant != 7) return RLGEN_ERR_BAD_ARG;
+  if (which == G_UP && c->joined_in[mode == 1]) c->apart[mode] = true;
   c->tuned[mode][which].variant = variant;
   return RLGEN_OK;
 }

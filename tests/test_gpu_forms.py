@@ -397,8 +397,9 @@ def test_qkv_and_ffn_up_in_one_launch_match_the_reference(m):
     for shape in (None, 1, 6, 2, 3):             # the rule's tile, the smallest, 64x64, 128x128, 256x256
         pol = make_policy(W, max_seqs=5, max_seq_len=140)
         try:
-            if shape is not None:
-                for mode in (0, 1):
+            for mode in (0, 1):
+                assert r.rlgen_debug_get_gemm(pol, mode, 2)[0] == -2          # (FFN-up has no launch of its own)
+                if shape is not None:
                     r.rlgen_debug_set_gemm(pol, mode, 0, shape)
             _, lp = r.rlgen_generate(pol, dev_i32(arr), lens, 1, T, 0.7, dev_f32(np.zeros((5, 1, T))), dev_i32(forced))
             assert r.rlgen_status(pol) == 0
@@ -483,3 +484,46 @@ def test_both_prompt_forms_agree_on_queries_that_an_infinite_key_does_not_reach(
         finally:
             pol.close()
     assert np.isfinite(outs[0]).all() and np.abs(outs[1][:, 1:] - outs[0][:, 1:]).max() < TOL_LOGPROB
+
+
+@pytest.mark.parametrize("name", ["neox-d128", "neox-d192", "llama-d320"])
+def test_a_tile_shape_for_ffn_up_takes_it_out_of_the_qkv_launch(name):
+    """Small GPT-NeoX contexts report FFN-up as part of QKV's launch.  A shape set for it gives it a launch of its own, -2 takes it
+    back, and every shape of either form returns the same bits: prompt pass (611 rows) and decode, whole and in halves."""
+    m = TILES[name]
+    W = scaled_bf16_weights(m)
+    rng = np.random.default_rng(73)
+    arr, lens = padded([rng.integers(0, m.vocab, size=n) for n in (256, 1, 255, 99)])
+    T = 3
+    forced = dev_i32(rng.integers(0, m.vocab, size=(4, 1, T)))
+    u = dev_f32(np.zeros((4, 1, T)))
+    r = R()
+    pol = make_policy(W, max_seqs=4, max_seq_len=256 + T, max_batch_tokens=1024)
+    try:
+        if m.arch == 1:
+            for mode in range(3):
+                assert r.rlgen_debug_get_gemm(pol, mode, 2)[0] != -2
+                with pytest.raises(r.RlgenError):
+                    r.rlgen_debug_set_gemm(pol, mode, 2, -2)
+            return
+        with pytest.raises(r.RlgenError):
+            r.rlgen_debug_set_gemm(pol, 1, 0, -2)
+        outs = []
+        for v in range(11):
+            for joined in (1, 0):
+                for mode in range(3):
+                    r.rlgen_debug_set_gemm(pol, mode, 0, v)
+                    assert r.rlgen_debug_get_gemm(pol, mode, 2) == (-2, 1)
+                    if not joined:
+                        r.rlgen_debug_set_gemm(pol, mode, 2, v)
+                        assert r.rlgen_debug_get_gemm(pol, mode, 2) == (v, 1)
+                for halves in (0, 2):
+                    r.rlgen_set_decode_split_min(pol, halves)
+                    outs.append(r.rlgen_generate(pol, dev_i32(arr), lens, 1, T, 0.7, u, forced)[1].cpu())
+                for mode in range(3):
+                    r.rlgen_debug_set_gemm(pol, mode, 2, -2)
+        assert r.rlgen_status(pol) == 0
+    finally:
+        pol.close()
+    for o in outs[1:]:
+        assert torch.equal(o, outs[0])
