@@ -132,7 +132,7 @@ struct rlgen_ctx {
   int profiling;          // n > 0: every n-th decode-attention launch is bracketed with events
   std::vector<hipEvent_t> prof_events;
   size_t prof_used;
-  // tile shape and K split of each linear layer, measured at creation: [decode | prompt pass][which GEMM]
+  // tile shape and K split of each linear layer, fixed at creation (tune_gemms):
   // [decode of max_seqs rows | prompt pass | decode of half of max_seqs rows][which GEMM]
   struct GemmChoice { int variant, splits; } tuned[3][5];
   bool half_rows;         // the decode steps being enqueued cover half of the batch
@@ -683,10 +683,10 @@ bool capacity_splits_decode(const rlgen_ctx* c) {
   return 4.0 * m.n_kv_heads * m.head_dim * (double)m.max_kv_tokens * m.n_layers >= 4.0 * weight_bytes_of(m);
 }
 
-// Fixes the K split of every linear layer by split_rule, then times the tile shapes on each layer at the row counts it
-// will see -- max_seqs rows (or half of them) for a decode step, a full chunk for the prompt pass -- and keeps the
-// fastest.  Tile shape does not change the order of any sum.  Inputs are the activation scratch buffers filled with
-// pseudo-random fp16; outputs land in scratch.
+// Fixes the K split of every linear layer by split_rule and split_rule_decode; then its tile shape at the row counts it will see --
+// max_seqs rows (or half of them) for a decode step, a full chunk for the prompt pass -- by one_round_tile where that has one
+// and else by timing the candidates; and whether QKV and FFN-up share a launch.  Nothing but the split changes the order of a
+// sum.  Inputs are the activation scratch buffers filled with pseudo-random fp16; outputs land in scratch.
 int tune_gemms(rlgen_ctx* c, hipStream_t st) {
   const rlgen_model_cfg& m = c->cfg;
   const bool llama = m.arch == RLGEN_ARCH_LLAMA;
@@ -721,10 +721,13 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
     if (mode != 1 && (tune_half || pr)) return split_rule(dec_rows_eff, m.max_seqs, N, K, epi, c->splitk_elems, tune_half);
     return mode == 1 ? split_rule_decode(c->R, c->R, N, K, epi, c->splitk_elems) : split_rule_decode(dec_rows_eff, m.max_seqs, N, K, epi, c->splitk_elems);
   };
-  // One launch for QKV and FFN-up while the two are short of blocks (up to five rounds of 128x128 tiles): 654 rows at 1B width 87 us
-  // as two launches, 67 as one, 384 rows at 2.8B width 66 and 54, 128 rows at 410M 16 and 10; 32768 rows at 2.8B width 2750 and 2840
-  // (two operands more in the caches).  Beside attention one round: generate of 1B width with halves of 256 rows 131.0 ms apart,
-  // 129.2 joined, of 2.8B width with 512 rows 355.8 and 361.3
+  // One launch for QKV and FFN-up while the two are short of blocks (up to five rounds of 128x128 tiles).  Which form's tiles come out in
+  // whole rounds decides there, and either can win (us a layer, apart / joined: prompt passes at 1B width 768 rows 175 / 158, 1024 176 /
+  // 163, 1408 274 / 248; at 2.8B width 640 rows 202 / 185, 896 252 / 244, 960 249 / 258, 1024 256 / 274, 1152 295 / 287; decode of
+  // 512 sequences at 2.8B width 185 / 193), so where more than one tile shape is timed the two products are timed apart as well.
+  // Beyond the border two operands more in the caches cost up to 4 % (2048 rows at 2.8B width 451 / 469 a layer, 32768 2750 / 2840 for
+  // the two).  Beside attention one round: generate of 1B width with halves of 256 rows 131.0 ms apart, 129.2 joined, of 2.8B width with
+  // 512 rows 355.8 and 361.3
   for (int prompt = 0; prompt < 2; ++prompt) {
     const long long rows = prompt ? c->R : dec_rows_eff;
     c->joined_in[prompt] = !llama && c->fused_qkv && !pr && splits_of(prompt, F, d, EPI_GELU_F16) == 1 &&
@@ -758,6 +761,9 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
     }
   }
   const int modes[3] = {2, 0, 1};
+  bool comparing = false;                      // the shapes of QKV and FFN-up in one launch are chosen, and now those of the two apart
+  GemmArgs joined_g{}, qkv_g{};
+  rlgen_ctx::GemmChoice joined_choice{};
   for (int mi = tune_half ? 0 : 1; mi < 3 && rc == RLGEN_OK; ++mi) {
     const int mode = modes[mi];
     for (int which = 0; which < 5 && rc == RLGEN_OK; ++which) {
@@ -835,10 +841,11 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
         a.W2 = l.wup;
         a.W = which == G_QKV ? l.wqkv : which == G_O ? l.wo : which == G_UP ? l.wup : which == G_DOWN ? (c->joined_out ? l.wo : l.wdown) : c->lm_head;
       };
-      if (cands.size() == 1) {
+      if (cands.size() == 1 && !(comparing && which == G_UP)) {
         // (launched once all the same: the kernel is loaded and configured here and not in the first call, which may be captured)
         if (run_choice(g, epi, cands[0], splits, st) != hipSuccess) { rc = RLGEN_ERR_DEVICE; break; }
         c->tuned[mode][which] = {cands[0], splits};
+        if (which == G_QKV) qkv_g = g;
         continue;
       }
       std::vector<float> total(cands.size(), 0.f);
@@ -919,6 +926,46 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
       // cheaper in company
       if (score[bi] > 0.985f * score[alone]) bi = alone;
       c->tuned[mode][which] = {cands[bi], splits};
+      if (which == G_QKV && comparing) {
+        qkv_g = g;
+      } else if (which == G_QKV && c->joined_in[mode == 1] && (mode == 1 || !tune_half)) {
+        comparing = true;
+        joined_g = g;
+        joined_choice = c->tuned[mode][G_QKV];
+        c->joined_in[mode == 1] = false;
+        --which;
+      } else if (which == G_UP && comparing) {
+        // the two forms take turns over the same weights: each product's alone may fit the cache in front of HBM where both do not
+        comparing = false;
+        const rlgen_ctx::GemmChoice qkv = c->tuned[mode][G_QKV], up = c->tuned[mode][G_UP];
+        float form_ms[2] = {0.f, 0.f};                          // apart, joined
+        for (int turn = 0; ok && turn < 8; ++turn) {            // (the first turn of each warms up)
+          ok = hipEventRecord(e0, st) == hipSuccess;
+          for (int r = 0; ok && r < 2; ++r) {
+            next_layer(g);
+            const LayerW& l = c->layers[layer];
+            if (turn & 1) {
+              joined_g.W = l.wqkv;
+              joined_g.W2 = l.wup;
+              ok = run_choice(joined_g, EPI_QKV_UP, joined_choice.variant, 1, st) == hipSuccess;
+            } else {
+              qkv_g.W = l.wqkv;
+              ok = run_choice(qkv_g, EPI_QKV, qkv.variant, 1, st) == hipSuccess && run_choice(g, epi, up.variant, splits, st) == hipSuccess;
+            }
+          }
+          if (ok) ok = hipEventRecord(e1, st) == hipSuccess && hipEventSynchronize(e1) == hipSuccess;
+          float ms = 0.f;
+          if (ok) ok = hipEventElapsedTime(&ms, e0, e1) == hipSuccess;
+          if (turn >= 2) form_ms[turn & 1] += ms;
+        }
+        if (!ok) { rc = RLGEN_ERR_DEVICE; break; }
+        // (near a tie one launch: timed 1280 rows at 410M width 38.5 joined and 37.1 apart, in a layer 97.4 and 100.9)
+        c->joined_in[mode == 1] = form_ms[1] <= 1.04f * form_ms[0];
+        if (c->joined_in[mode == 1]) {
+          c->tuned[mode][G_QKV] = joined_choice;
+          c->tuned[mode][G_UP] = {0, 1};
+        }
+      }
     }
   }
   return rc;
