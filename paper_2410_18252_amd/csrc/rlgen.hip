@@ -727,10 +727,13 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
   // 512 sequences at 2.8B width 185 / 193), so where more than one tile shape is timed the two products are timed apart as well.
   // Beyond the border two operands more in the caches cost up to 4 % (2048 rows at 2.8B width 451 / 469 a layer, 32768 2750 / 2840 for
   // the two).  Beside attention one round: generate of 1B width with halves of 256 rows 131.0 ms apart, 129.2 joined, of 2.8B width with
-  // 512 rows 355.8 and 361.3
+  // 512 rows 355.8 and 361.3.
+  // Up to 64 rows also where FFN-up alone would be cut into parts (narrow models): two launches less (a decode layer of 1, 4, 64 sequences,
+  // cut and apart / whole and joined: 512 wide 25.9, 26.6, 29.8 / 22.9, 23.6, 24.4; 768 wide 28.4, 28.9, 34.2 / 24.6, 25.3, 26.9).  With
+  // more rows only FFNs narrower than four times the model are cut
   for (int prompt = 0; prompt < 2; ++prompt) {
     const long long rows = prompt ? c->R : dec_rows_eff;
-    c->joined_in[prompt] = !llama && c->fused_qkv && !pr && splits_of(prompt, F, d, EPI_GELU_F16) == 1 &&
+    c->joined_in[prompt] = !llama && c->fused_qkv && !pr && (rows <= 64 || splits_of(prompt, F, d, EPI_GELU_F16) == 1) &&
                            (rows + 127) / 128 * ((nqkv + F + 127) / 128) <= (!prompt && tune_half ? 256 : 5 * 256);
   }
   // The neighbour of the half-batch timing runs: the decode attention of the other half, over half a full batch of

@@ -527,3 +527,26 @@ def test_a_tile_shape_for_ffn_up_takes_it_out_of_the_qkv_launch(name):
         pol.close()
     for o in outs[1:]:
         assert torch.equal(o, outs[0])
+
+
+@pytest.mark.parametrize("max_seqs", [1, 64])
+def test_narrow_models_of_few_rows_take_ffn_up_whole(max_seqs):
+    """An FFN of a few tile columns, which would be cut into parts on its own, shares QKV's launch in decode steps of up to 64 rows."""
+    m = ModelShape(0, 2, 512, 8, 8, 64, 2048, 200, rotary_dim=16)
+    W = scaled_bf16_weights(m)
+    dec = reference_decoder(W, m)
+    rng = np.random.default_rng(79)
+    B, T = min(max_seqs, 3), 5
+    arr, lens = padded([rng.integers(0, m.vocab, size=n) for n in (33, 1, 20)[:B]])
+    forced = rng.integers(0, m.vocab, size=(B, 1, T)).astype(np.int32)
+    r = R()
+    pol = make_policy(W, max_seqs=max_seqs, max_seq_len=40)
+    try:
+        assert r.rlgen_debug_get_gemm(pol, 0, 2) == (-2, 1)
+        _, lp = r.rlgen_generate(pol, dev_i32(arr), lens, 1, T, 0.7, dev_f32(np.zeros((B, 1, T))), dev_i32(forced))
+        assert r.rlgen_status(pol) == 0
+    finally:
+        pol.close()
+    for b in range(B):
+        want = O.score(dec, np.concatenate([arr[b, :lens[b]], forced[b, 0]]), 0.7, score_from=int(lens[b]))[lens[b]:]
+        assert np.abs(lp.cpu().numpy()[b, 0] - want).max() < TOL_LOGPROB
