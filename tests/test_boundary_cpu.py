@@ -105,3 +105,10 @@ def test_a_k_split_leaves_no_part_without_a_k_tile(K, precise):
         g = GemmArgs(A=256, W=256, M=64, N=128, K=K, precise=precise, out=256, ldo=128, ws=256, ws_elems=1 << 20, splits=splits)
         rc = f(C.byref(g), 7, None)
         assert rc != 0 and (rc == 1) == (splits > tiles), (splits, rc)      # 1: hipErrorInvalidValue
+
+
+def test_the_stream_is_found_without_the_private_name(monkeypatch):
+    from types import SimpleNamespace
+    monkeypatch.setattr(R, "_raw_stream", None)
+    monkeypatch.setattr(R.torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=7))
+    assert R._stream() == 7
