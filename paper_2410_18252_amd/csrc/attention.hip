@@ -32,7 +32,8 @@
 #endif
 // The prompt pass of contexts whose jobs do not fill the chip, and of precise mode, is not bound by memory but by the latency of a
 // wave's serial chain (load, convert, MFMA, softmax, MFMA): it does without the register prefetch of the next super-block, so that
-// two waves share a SIMD and hide each other's L2 latency.
+// two or three waves share a SIMD (one at head size 256) and hide each other's L2 latency: with the prefetch 3000 rows, 8 heads of
+// size 80, 25.9 us instead of 17.8.
 #ifndef ATTN_PROMPT_NOPF
 #define ATTN_PROMPT_NOPF 1
 #endif
@@ -52,8 +53,10 @@ namespace {
 // CU several jobs: a wave's walk over its keys is a serial chain of loads and products, 2.8 us a super-block at head size 256.
 // QB = query blocks of 16 columns a wave carries through one pass over the keys (prompt pass only: two blocks halve
 // the key / value traffic per query; a.jobs then counts blocks of 16 QB tokens).
+// Three waves to a SIMD are prescribed where the prompt pass of small contexts would miss them by a few registers (654 tokens, 32 heads
+// of size 64 on 8: 16.8 -> 14.5 us; 1300 rows, 8 heads of size 112: 16.4 -> 13.5).
 template <int HD, bool DECODE, int QB = 1, bool PR = false, int SPLIT = 1>
-__global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, 1) void attention_kernel(AttnArgs a) {
+__global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, !DECODE && !PR && SPLIT == 4 && (HD == 64 || HD == 112) ? 3 : 1) void attention_kernel(AttnArgs a) {
   static_assert(!DECODE || QB == 1, "decode has one query block");
   static_assert(SPLIT == 1 || SPLIT == 4 || (DECODE && SPLIT == 8), "a job is shared by all waves of a block");
   constexpr int NCH = HD / 8;            // 16-byte chunks per key row
@@ -278,9 +281,11 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, 1) void attention_ker
           }
         }
       }
-    // ... and one wave to a job in the prompt pass has its values on their way before the softmax (24 sequences of 514 tokens, 32
-    // heads of size 128 on 8: 619 -> 520 us a layer, 536 with two waves to a SIMD prescribed; all requests first: 548 and more)
-    if constexpr (PR && SPLIT == 1 && !DECODE && QB == 1) __builtin_amdgcn_sched_barrier(0);
+    // ... and the prompt pass of one query block to a wave has its values on their way before the softmax: in precise mode one wave to
+    // a job (24 sequences of 514 tokens, 32 heads of size 128 on 8: 619 -> 520 us a layer, 536 with two waves to a SIMD prescribed;
+    // all requests first: 548 and more), else four (654 tokens, 8 heads of size 96 / 128 / 256: 13.5 / 14.5 / 35.4 -> 11.4 / 12.9 / 25.9
+    // us, all requests first 12.3 / 17.2 / 22.8; 250 tokens, 32 heads of size 128 on 8: 9.7 -> 8.5, all first 11.6)
+    if constexpr (!DECODE && QB == 1 && (!PR || SPLIT == 1)) __builtin_amdgcn_sched_barrier(0);
     // lane (c, g) now holds the scores of keys 32 sb + 8 g + 4 t + j against column c
     float p[QB][8], alpha[QB];
 #pragma unroll
@@ -331,8 +336,8 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, 1) void attention_ker
       for (int b = 0; b < QB; ++b)
 #pragma unroll
         for (int e = 0; e < 8; ++e) pf[b][e] = (f16_t)p[b][e];
-      // (the values are widened here, where the keys' registers are free: with it at the top of the super-block head size 80
-      // needs 174 registers in the prompt pass instead of 159, two waves to a SIMD instead of three)
+      // (the values are widened here, where the keys' registers are free: with it at the top of the super-block the prompt pass of
+      // head size 80 needs 202 registers instead of 188, 654 and 1300 rows of 8 heads 14.4 and 14.1 us instead of 14.0 and 13.8)
 #pragma unroll
       for (int t = 0; t < VT; ++t) {
         const f16x8 vf = value_frag(vraw, t);
