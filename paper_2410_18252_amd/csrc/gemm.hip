@@ -1076,6 +1076,10 @@ hipError_t launch_variant(const GemmArgs& g, int variant, hipStream_t s) {
       case 7: return launch_ring<128, 64, 4, 2, 6, EPI>(g, s);
       case 8: return launch_ring<64, 96, 2, 2, 7, EPI>(g, s);
       case 9: return launch_ring<64, 128, 2, 4, 6, EPI>(g, s);
+      // (two stages leave room for three blocks to a CU, a ring of 64x128 for one: where the tiles make a round and a half to three, us:
+      // 1300 rows, 1024 x 5120 in 3 parts 25.8 (rings 27.0 and more), 300 rows, 2560 x 12800 in 5 parts 37.8 (42.1), 10240 x 2560,
+      // 420 rows 41.7 (43.7))
+      case 11: return launch<64, 128, 1, 4, EPI>(g, s);
     }
   }
   return hipErrorInvalidValue;

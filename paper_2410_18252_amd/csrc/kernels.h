@@ -119,8 +119,8 @@ struct GemmArgs {
 // tile shape chosen from the problem size; g.splits >= 2 (with g.ws) cuts K into that many parts (rl_gemm_splitk)
 hipError_t rl_gemm(const GemmArgs& g, int epi, hipStream_t s);
 // the same with an explicit tile shape (tuning and tests).  Two stages: 0 = 128x128, 5 = 256x128; 256x256 by hand: 3; rings: 2 =
-// 128x128, 10 = 256x128; rings of the epilogues whose waves must own 64 columns (SwiGLU, LM head): 1 = 32x128, 4 = 64x128; rings
-// of the others: 1 = 32x32, 4 = 32x64, 6 = 64x64, 7 = 128x64, 8 = 64x96, 9 = 64x128.  Precise mode: 0, 3, 5 and two stages 7 = 64x128
+// 128x128, 10 = 256x128; rings of the epilogues whose waves must own 64 columns (SwiGLU, LM head): 1 = 32x128, 4 = 64x128; of the
+// others rings 1 = 32x32, 4 = 32x64, 6 = 64x64, 7 = 128x64, 8 = 64x96, 9 = 64x128 and two stages 11 = 64x128.  Precise mode: 0, 3, 5 and two stages 7 = 64x128
 hipError_t rl_gemm_variant(const GemmArgs& g, int epi, int variant, hipStream_t s);
 // needs g.ws and 2 <= g.splits <= K tiles of 64 (precise mode: twice as many)
 hipError_t rl_gemm_splitk(const GemmArgs& g, int epi, int variant, hipStream_t s);

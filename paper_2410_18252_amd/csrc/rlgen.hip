@@ -829,6 +829,7 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
           cands.push_back(5); cands.push_back(10);
           if (splits == 1) cands.push_back(3);
         }
+        if (!wide_only) cands.push_back(11);
         // the small rings are for launches that leave CUs short of blocks
         if (!wide_only && (long long)((g.M + 63) / 64) * ((g.N + g.N2 + 127) / 128) < 2048)
           for (int v : {6, 7, 8, 9}) cands.push_back(v);
@@ -1620,15 +1621,15 @@ int rlgen_debug_get_gemm(rlgen_ctx* c, int32_t mode, int32_t which, int32_t* var
 
 int rlgen_debug_set_gemm(rlgen_ctx* c, int32_t mode, int32_t which, int32_t variant) {
   if (!c) return RLGEN_ERR_NULL;
-  if (mode < 0 || mode > 2 || which < 0 || which > 4 || variant < -2 || variant > 10) return RLGEN_ERR_BAD_ARG;
+  if (mode < 0 || mode > 2 || which < 0 || which > 4 || variant < -2 || variant > 11) return RLGEN_ERR_BAD_ARG;
   if (variant == -2) {
     if (which != G_UP || !c->joined_in[mode == 1]) return RLGEN_ERR_BAD_ARG;
     c->apart[mode] = false;
     return RLGEN_OK;
   }
-  // the fused gate/up and LM-head epilogues need a wave to own 64 columns: not the 64-column-per-wave-pair shapes
+  // the fused gate/up and LM-head epilogues need a wave to own 64 columns: not the shapes whose waves own fewer
   const bool wide_only = which == G_LMHEAD || (which == G_UP && c->cfg.arch == RLGEN_ARCH_LLAMA);
-  if (wide_only && variant >= 6 && variant <= 9) return RLGEN_ERR_BAD_ARG;
+  if (wide_only && ((variant >= 6 && variant <= 9) || variant == 11)) return RLGEN_ERR_BAD_ARG;
   if (c->cfg.precise && variant != -1 && variant != 0 && variant != 3 && variant != 5 && variant != 7) return RLGEN_ERR_BAD_ARG;
   if (which == G_UP && c->joined_in[mode == 1]) c->apart[mode] = true;
   c->tuned[mode][which].variant = variant;

@@ -550,3 +550,38 @@ def test_narrow_models_of_few_rows_take_ffn_up_whole(max_seqs):
     for b in range(B):
         want = O.score(dec, np.concatenate([arr[b, :lens[b]], forced[b, 0]]), 0.7, score_from=int(lens[b]))[lens[b]:]
         assert np.abs(lp.cpu().numpy()[b, 0] - want).max() < TOL_LOGPROB
+
+
+@pytest.mark.parametrize("name", ["neox-d128", "neox-d192", "llama-d320", "neox-d512"])
+def test_the_two_stage_tile_of_64_rows_returns_the_same_bits(name):
+    """Two stages of 64x128 (no shape of the SwiGLU and LM-head products) on every layer that takes it, against 128x128: a prompt
+    pass of 611 rows and decode steps, FFN-up in QKV's launch and on its own; 611 rows end in a ragged tile, 512 x 1536 is cut
+    into parts."""
+    m = {**TILES, **DECODE_TILES}[name]
+    W = scaled_bf16_weights(m)
+    rng = np.random.default_rng(83)
+    arr, lens = padded([rng.integers(0, m.vocab, size=n) for n in (256, 1, 255, 99)])
+    T = 3
+    forced, u = dev_i32(rng.integers(0, m.vocab, size=(4, 1, T))), dev_f32(np.zeros((4, 1, T)))
+    r = R()
+    pol = make_policy(W, max_seqs=4, max_seq_len=256 + T, max_batch_tokens=1024)
+    outs = []
+    try:
+        with pytest.raises(r.RlgenError):
+            r.rlgen_debug_set_gemm(pol, 1, 4, 11)
+        for v in (0, 11):
+            for apart in (0, 1):
+                for mode in range(3):
+                    for which in (0, 1, 2, 3):
+                        if which == 2 and not (apart and m.arch == 0):
+                            continue
+                        r.rlgen_debug_set_gemm(pol, mode, which, v)
+                outs.append((r.rlgen_generate(pol, dev_i32(arr), lens, 1, T, 0.7, u, forced)[1].cpu(), r.rlgen_score(pol, dev_i32(arr), lens, 0.7).cpu()))
+                for mode in range(3):
+                    if m.arch == 0 and apart:
+                        r.rlgen_debug_set_gemm(pol, mode, 2, -2)
+        assert r.rlgen_status(pol) == 0
+    finally:
+        pol.close()
+    for o in outs[1:]:
+        assert torch.equal(o[0], outs[0][0]) and torch.equal(o[1], outs[0][1])
