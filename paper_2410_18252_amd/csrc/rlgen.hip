@@ -634,7 +634,10 @@ int split_rule(int rows, int cap_rows, int N, int K, int epi, size_t ws_elems, b
 // 8 parts; 2048 x 10240 at 64 rows 11.0 / 11.0 in 8, 128 rows 13.9 / 14.0 in 8, 256 rows 21.5 / 20.3 in 4 (21.7 in 6, 22.5 in 8);
 // 2560 x 12800 at 256 rows 29.9 / 29.3 in 6 (29.5 in 3); 4096 x 14336 at 256 rows 43.3 / 43.3 in 4 (47.4 in 2).
 int split_rule_decode(int rows, int cap_rows, int N, int K, int epi, size_t ws_elems) {
-  // the others take a second pass of their own (4 to 7 us), which pays only where 64x64 tiles leave three quarters of the CUs idle
+  // the others take a second pass of their own (4 to 7 us), which pays only where 64x64 tiles leave three quarters of the CUs idle, and
+  // not up to 64 rows, where 32x32 tiles are many and quick (1 / 64 sequences at 410M width with a QKV product apart from its
+  // rotation, a decode layer with that product in 4 parts 34.1 / 45.4 us, whole 31.6 / 41.3)
+  if (epi != EPI_RESID && rows <= 64) return 1;
   if (epi != EPI_RESID) return (long long)((rows + 63) / 64) * ((N + 63) / 64) < 64 ? split_rule(rows, cap_rows, N, K, epi, ws_elems, false) : 1;
   const int nk = (K + 63) / 64;
   const int most = (int)std::min<long long>(std::min(8, nk / 4), (long long)(ws_elems / ((size_t)cap_rows * N)));
@@ -728,7 +731,7 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
   // Beyond the border two operands more in the caches cost up to 4 % (2048 rows at 2.8B width 451 / 469 a layer, 32768 2750 / 2840 for
   // the two).  Beside attention one round: generate of 1B width with halves of 256 rows 131.0 ms apart, 129.2 joined, of 2.8B width with
   // 512 rows 355.8 and 361.3.
-  // Up to 64 rows also where FFN-up alone would be cut into parts (narrow models): two launches less (a decode layer of 1, 4, 64 sequences,
+  // Up to 64 rows FFN-up is whole (beside attention, where alone it would be cut, too): two launches less (a decode layer of 1, 4, 64 sequences,
   // cut and apart / whole and joined: 512 wide 25.9, 26.6, 29.8 / 22.9, 23.6, 24.4; 768 wide 28.4, 28.9, 34.2 / 24.6, 25.3, 26.9).  With
   // more rows only FFNs narrower than four times the model are cut
   for (int prompt = 0; prompt < 2; ++prompt) {

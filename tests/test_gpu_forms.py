@@ -585,3 +585,26 @@ def test_the_two_stage_tile_of_64_rows_returns_the_same_bits(name):
         pol.close()
     for o in outs[1:]:
         assert torch.equal(o[0], outs[0][0]) and torch.equal(o[1], outs[0][1])
+
+
+@pytest.mark.parametrize("max_seqs", [1, 64, 65])
+def test_an_unfused_qkv_product_of_few_rows_stays_whole(max_seqs):
+    """A rotary dim that is no multiple of 4 keeps QKV apart from its rotation; up to 64 rows its K is not cut."""
+    m = ModelShape(0, 2, 512, 8, 8, 64, 1024, 200, rotary_dim=6)
+    W = scaled_bf16_weights(m)
+    dec = reference_decoder(W, m)
+    rng = np.random.default_rng(89)
+    B, T = min(max_seqs, 3), 5
+    arr, lens = padded([rng.integers(0, m.vocab, size=n) for n in (33, 1, 20)[:B]])
+    forced = rng.integers(0, m.vocab, size=(B, 1, T)).astype(np.int32)
+    r = R()
+    pol = make_policy(W, max_seqs=max_seqs, max_seq_len=40)
+    try:
+        assert (r.rlgen_debug_get_gemm(pol, 0, 0)[1] == 1) == (max_seqs <= 64)
+        _, lp = r.rlgen_generate(pol, dev_i32(arr), lens, 1, T, 0.7, dev_f32(np.zeros((B, 1, T))), dev_i32(forced))
+        assert r.rlgen_status(pol) == 0
+    finally:
+        pol.close()
+    for b in range(B):
+        want = O.score(dec, np.concatenate([arr[b, :lens[b]], forced[b, 0]]), 0.7, score_from=int(lens[b]))[lens[b]:]
+        assert np.abs(lp.cpu().numpy()[b, 0] - want).max() < TOL_LOGPROB
