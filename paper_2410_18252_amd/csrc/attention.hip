@@ -66,6 +66,10 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, !DECODE && !PR && SPL
   // and loads them at the top of the iteration instead)
   constexpr bool PF = (DECODE || !ATTN_PROMPT_NOPF) && !PR;
   constexpr int NP = PR ? 2 : 1;         // cache planes: hi, lo
+  // Decode of heads whose wave has a SIMD to itself whatever it holds: values are widened with the keys, off the chain behind the
+  // softmax (8 heads, us: size 256, 16 sequences of 1000 keys 36.4 -> 33.3, 40 75.4 -> 73.3; size 112, 64 sequences 46.3 -> 45.1).
+  // Elsewhere it costs registers: size 64, eight waves to a job, 64 sequences 25.6 -> 28.1; 128, 24 sequences of 2000 keys 36.8 -> 37.2
+  constexpr bool V_EARLY = DECODE && !PR && SPLIT <= 4 && (HD == 112 || HD == 256);
   const int lane = threadIdx.x & 63;
   // A wave number known to be common to the wave makes the job's addresses scalar.  Not for two query blocks to a wave: the compiler
   // then orders their loop worse (precise mode, head size 48, 16 prompts of 500 tokens, 20 heads: 117 -> 123 us)
@@ -264,6 +268,11 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, !DECODE && !PR && SPL
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int i = 0; i < KSTEPS; ++i) kf[t][i] = PR ? __builtin_bit_cast(f16x8, kraw[t][i]) : bf16x8_to_f16x8(kraw[t][i]);
+    [[maybe_unused]] f16x8 vwide[V_EARLY ? VT : 1];
+    if constexpr (V_EARLY) {
+#pragma unroll
+      for (int t = 0; t < VT; ++t) vwide[t] = value_frag(vraw, t);
+    }
     // straight-line code over the query blocks: their chains (MFMA -> softmax -> MFMA) are independent, and the
     // scheduler interleaves them only if no branch separates them
     f32x4 sc[QB][2];
@@ -336,11 +345,13 @@ __global__ __launch_bounds__(SPLIT > 4 ? SPLIT * 64 : 256, !DECODE && !PR && SPL
       for (int b = 0; b < QB; ++b)
 #pragma unroll
         for (int e = 0; e < 8; ++e) pf[b][e] = (f16_t)p[b][e];
-      // (the values are widened here, where the keys' registers are free: with it at the top of the super-block the prompt pass of
+      // (but for V_EARLY the values are widened here, where the keys' registers are free: with it at the top of the super-block the prompt pass of
       // head size 80 needs 202 registers instead of 188, 654 and 1300 rows of 8 heads 14.4 and 14.1 us instead of 14.0 and 13.8)
 #pragma unroll
       for (int t = 0; t < VT; ++t) {
-        const f16x8 vf = value_frag(vraw, t);
+        f16x8 vf;
+        if constexpr (V_EARLY) vf = vwide[t];
+        else vf = value_frag(vraw, t);
 #pragma unroll
         for (int b = 0; b < QB; ++b) {
           o[b][t] *= alpha[b];
