@@ -686,13 +686,14 @@ hipError_t rl_attention_decode(const AttnArgs& a, hipStream_t s) {
 // size 64 37.8 / 35.9 us, 2048 at head size 128 125 / 148 us.  A decode layer on either side of the borders (us, 256 and 1500 keys):
 // twice the upper one, one wave / four: 1024 jobs of size 256 127 / 144 and 324 / 320, 3264 of size 80 155 / 157 and 345 / 337; twice
 // the lower one, four waves / eight: 1024 of size 64 50 / 49 and 100 / 96, 800 of size 80 102 / 110 and 150 / 158, 512 of size 128
-// 176 / 221 and 223 / 294.  Eight waves leave a wave 256 registers, in which the wider heads' super-blocks hardly fit: for those the
-// lower border is half as high.  Four / eight there: 384 of size 80 69.8 / 72.6 and 93.2 / 98.1, 256 of size 128 136.2 / 144.9 and
-// 160.3 / 174.2, 240 of size 128 177.2 / 185.9 and 199.5 / 212.3; below it 128 of size 80 65.5 / 64.6 and 79.1 / 75.6, 64 of size 128
-// 127.5 / 130.2 and 146.7 / 146.8, 8 of size 128 128.7 / 129.5 and 145.8 / 143.8.
+// 176 / 221 and 223 / 294.  Of head sizes 80 and 96 a CU holds one block of eight waves: they pay while every job has a CU (the kernel
+// alone, four / eight, 1000 and 2000 keys: 224 jobs of size 80 17.2 / 17.4 and 28.6 / 27.3 us, 256 18.0 / 18.4 and 29.5 / 30.2, 288
+// 22.6 / 28.2 and 37.6 / 45.9; of size 96 192 jobs 18.6 / 17.3 and 30.3 / 27.9, 256 21.4 / 20.8 and 35.2 / 34.9, 288 27.4 / 31.5 and
+// 47.4 / 51.9).  Eight waves leave a wave 256 registers, in which the super-blocks of wider heads hardly fit (300 and 2000 keys: 64 jobs
+// of size 128 10.3 / 11.0 and 32.2 / 30.4, 128 10.7 / 12.0 and 34.3 / 33.2, 192 12.0 / 13.3 and 36.6 / 42.8): half as many there.
 int rl_attention_decode_split(long long cap_jobs, int h) {
   const long long size = cap_jobs * (h > 64 ? h : 64);
-  return size <= (h > 64 ? 16384 : 32768) ? 8 : size <= 131072 ? 4 : 1;
+  return size <= (h <= 64 ? 32768 : h <= 96 ? 256 * h : 16384) ? 8 : size <= 131072 ? 4 : 1;
 }
 // The same for a prompt pass of at most cap_rows rows: up to four jobs a CU (654 rows of 8 heads of size 256: 57 ->
 // 21 us a layer).  A layer of prompts of 500 / 128 tokens, the waves of a block sharing super-blocks against sharing jobs (us): 256 jobs

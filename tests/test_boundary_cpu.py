@@ -112,3 +112,10 @@ def test_the_stream_is_found_without_the_private_name(monkeypatch):
     monkeypatch.setattr(R, "_raw_stream", None)
     monkeypatch.setattr(R.torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=7))
     assert R._stream() == 7
+
+
+@pytest.mark.parametrize("h, eight, four", [(16, 512, 2048), (64, 512, 2048), (80, 256, 1638), (96, 256, 1365), (112, 146, 1170), (128, 128, 1024)])
+def test_the_waves_of_a_decode_job_follow_from_jobs_and_head_size(h, eight, four):
+    f = getattr(R.lib, "_Z25rl_attention_decode_splitxi")
+    f.argtypes, f.restype = [C.c_longlong, C.c_int], C.c_int
+    assert [f(n, h) for n in (1, eight, eight + 1, four, four + 1)] == [8, 8, 4, 4, 1]

@@ -56,7 +56,7 @@ def test_every_tile_shape_returns_the_same_bits_on_whole_and_ragged_tiles(name, 
 
 
 # capacities on either side of the rules: decode attention shares a job among eight or four waves while capacity x kv heads x
-# max(head size, 64) is at most 32768 (16384 for heads wider than 64) or 131072
+# max(head size, 64) is at most 32768 (256 jobs of head sizes 80 and 96, 16384 for wider heads) or 131072
 @pytest.mark.parametrize("max_seqs", [6, 17, 128, 129, 300, 2100])
 @pytest.mark.parametrize("name", ["neox-h16-raggedV", "neox-h80", "neox-h256", "llama-gqa4-h16", "llama-gqa2-h128"])
 def test_decode_forms_match_the_reference(name, max_seqs):
