@@ -804,9 +804,10 @@ __global__ __launch_bounds__(256, 1) void gemm_big_kernel(GemmArgs g) {
 // 256x128 (most of LDS).  Measured with weights from HBM (us): 32x32, 16 rows, N x K = 3072 x 1024 4.8, 6144 x 2048 7.1, 6144 x
 // 4096 11.3 (64x64 6.8, 10.5, 18.9); 32x64, 64 rows, 6144 x 2048 9.5 (64x64 11.8); 64x64, 128 rows, 4096 x 1024 7.4 and as the 8
 // parts of a K split 1024 x 5120 6.6; 64x96 (64x128), 256 rows, 6144 x 4096 25.4 (28.4); 128x64, 256 rows, 8192 x 2048 16.4 (17.1);
-// 32x128, 16 rows, 28672 x 4096 38.2 (128x128 42.0); 256x128, 1024 rows, 7680 x 2560 43.9 (two-stage loop 48.8).  K divided among the waves of a block instead, operands straight to registers: 16
-// rows, 6144 x 2048 8.3, 2048 x 10240 21.2 (64x64 in 8 parts 9.5), 128 rows, 4096 x 1024 8.6: such operands are 64-byte pieces
-// of sixteen rows, which a CU takes in at a third of the rate of the kilobytes that go to LDS.
+// 32x128, 16 rows, 28672 x 4096 38.2 (128x128 42.0); 256x128, 1024 rows, 7680 x 2560 43.9 (two-stage loop 48.8).  K divided
+// among the waves of a block instead, operands straight to registers: 16 rows, 6144 x 2048 8.3, 2048 x 10240 21.2 (64x64 in 8
+// parts 9.5), 128 rows, 4096 x 1024 8.6: such operands are 64-byte pieces of sixteen rows, which a CU takes in at a third of the
+// rate of the kilobytes that go to LDS.
 template <int BM, int BN, int WM, int WN, int NS, int EPI, bool PR = false>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_ring_kernel(GemmArgs g) {
   constexpr int NW = WM * WN;                            // waves
@@ -887,7 +888,6 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_ring_kernel(GemmArgs g) {
 #define RING_WAIT(N) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(N) : "memory")
   auto wait_younger = [&](int stages) {     // all but the `stages` youngest stages of this wave have landed; then everybody is here
     if (stages >= NS - 2) RING_WAIT((NS - 2) * L);
-    else if (NS > 10 && stages >= 8) RING_WAIT(8 * L);
     else if (NS > 6 && stages >= 4) RING_WAIT(4 * L);
     else if (stages == 3) RING_WAIT(3 * L);
     else if (stages == 2) RING_WAIT(2 * L);

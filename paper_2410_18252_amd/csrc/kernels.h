@@ -15,8 +15,9 @@
 //   and the dims behind the last whole group: [tile of 16 dims][g = 0..3][r = 0..15][8 keys]
 //                  holding head dim r of the tile, keys 8 g .. 8 g + 7
 // A decode step writes one key and one value per stream, and every 64-byte sector it touches only in part is read, merged and
-// written back to HBM, so a token's dims lie close: h / 32 whole sectors of keys and h / 16 of values (with the 16-byte units
-// of 8 dims and of 8 keys in rows the token touched h / 8 + h / 4).
+// written back to HBM, so a token's dims lie close: one sector for every 32 dims of its key (a step of 16 dims half of one), four for
+// every 64 dims of its value in whole groups and for every 16 behind them (head size 80: 3 + 8; with the 16-byte units of 8 dims
+// and of 8 keys in rows, as precise mode has them, a token touches h / 8 + h / 4).
 // Streams of a sequence: head 0..Hkv-1; sequences follow each other at token offsets kv_off[s];
 // layers are max_kv_tokens * Hkv * h * 2 elements apart.
 struct KvLayout {

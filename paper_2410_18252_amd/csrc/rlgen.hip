@@ -630,9 +630,10 @@ int split_rule(int rows, int cap_rows, int N, int K, int epi, size_t ws_elems, b
 // The same for a decode step's products into the residual, whose parts the following norm adds up, when nothing runs beside them:
 // the number of parts for which the modelled time of the best of three tiles is shortest.  Time in us: rounds of 256 blocks x K
 // steps of a part x the tile's K step (64x64 0.34, 64x128 0.38, 128x128 0.585, with the ring's depth of requests), and 1 and
-// 2 for every million partial sums written and read.  Modelled, with 2 us for the launch, / measured: 1024 x 5120 at 128 rows 7.6 / 6.6 in
-// 8 parts; 2048 x 10240 at 64 rows 11.0 / 11.0 in 8, 128 rows 13.9 / 14.0 in 8, 256 rows 21.5 / 20.3 in 4 (21.7 in 6, 22.5 in 8);
-// 2560 x 12800 at 256 rows 29.9 / 29.3 in 6 (29.5 in 3); 4096 x 14336 at 256 rows 43.3 / 43.3 in 4 (47.4 in 2).
+// 2 for every million partial sums written and read.  Modelled / the product's launch measured: 1024 x 5120 at 128 rows 6.5 / 6.2 in
+// 8 parts; 2048 x 10240 at 64 rows 9.9 / 11.4 in 8, 128 rows 12.8 / 14.4 in 8, 256 rows 20.4 / 20.8 in 4; 2560 x 12800 at 256 rows
+// 28.8 / 28.1 in 6; 4096 x 14336 at 256 rows 42.1 / 42.2 in 4.  (Beyond NORM_WIDE_ROWS rows the parts take a pass of their own, which
+// the model leaves out: contexts that large decode in halves unless their caches are short.)
 int split_rule_decode(int rows, int cap_rows, int N, int K, int epi, size_t ws_elems) {
   // the others take a second pass of their own (4 to 7 us), which pays only where 64x64 tiles leave three quarters of the CUs idle, and
   // not up to 64 rows, where 32x32 tiles are many and quick (1 / 64 sequences at 410M width with a QKV product apart from its
@@ -654,10 +655,11 @@ int split_rule_decode(int rows, int cap_rows, int N, int K, int epi, size_t ws_e
 }
 
 // The smallest tile whose blocks the CUs take in one round, -1 if there is none.  A decode step or a short prompt pass that is alone on the GPU is
-// bound by the requests in flight for the weights: fewer, larger blocks leave CUs out of it, a second round doubles the wait.  Timed over
-// 16 shapes (410M to 8B width) at 16, 64, 128 and 256 rows this is the fastest shape or within 7 % of it (us, 64 rows: 3072 x
-// 1024 32x32 5.0, 32x64 6.0, 64x64 7.5; 6144 x 2048 32x64 9.5, 32x32 in two rounds 11.4, 64x64 11.8), where a timing of two
-// launches of 5 to 10 us, which the host can hardly enqueue as fast, picked shapes up to 25 % slower.
+// bound by the requests in flight for the weights: fewer, larger blocks leave CUs out of it, a second round doubles the wait.  Every
+// tile timed over 16 shapes (410M to 8B width) at 16 to 2000 rows (profiles/one_round_tiles.txt): of the 115 that have such a tile
+// it is the fastest for 98 and within 6 % of it for all but four, 3072 and 4096 x 1024 at 300 and 420 rows (64x96 9 and 11 % behind
+// 64x128) and 4096 x 4096 in 8 parts at 16 and 64 rows (64x128 11.0 and 12.7 us, 32x64 8.9, 64x64 10.7: parts of 8 K steps, two blocks to
+// a CU).  A timing of two launches of 5 to 10 us, which the host can hardly enqueue as fast, picked shapes up to 25 % slower.
 int one_round_tile(int M, int N, int N2, int splits, bool wide) {      // N2: columns of a second product in the launch
   struct Tile { int variant, bm, bn; };
   static const Tile narrow_tiles[] = {{1, 32, 32}, {4, 32, 64}, {6, 64, 64}, {8, 64, 96}, {7, 128, 64}, {9, 64, 128}, {2, 128, 128}};

@@ -267,7 +267,7 @@ WIDE_FFN = ModelShape(0, 2, 64, 4, 4, 16, 1024, 200, rotary_dim=4)
 
 @pytest.mark.parametrize("name", ["neox-h80", "llama-gqa4-h16", "neox-wide-ffn", "llama-gqa4-h16/precise", "neox-wide-ffn/precise"])
 def test_results_do_not_depend_on_the_tile_shapes_a_context_picked(name):
-    """A context chooses its GEMM tile shapes by timing them, so two contexts may choose differently; how a sum over the
+    """A context chooses some of its GEMM tile shapes by timing them, so two contexts may choose differently; how a sum over the
     inner dimension is cut and ordered is fixed by the configuration.  Two contexts with the same weights are forced onto
     different tile shapes for every linear layer and every mode: tokens and log-probs must agree bit for bit."""
     name, _, mode = name.partition("/")
