@@ -465,10 +465,6 @@ __global__ __launch_bounds__(256) void attention_prompt_kernel(AttnArgs a, int h
     return level;
   }();
   __shared__ __attribute__((aligned(16))) uint16_t lds[2][FRAGS * 512];
-  // What the lane groups without dims of the half step read as their key's: zeros, since a query of zero does not cancel an infinity (the
-  // other groups' values there: 303 us a layer of 32000 rows at head size 80, zeros 307, as a fragment of zeros behind the step's 309)
-  __shared__ __attribute__((aligned(16))) uint16_t idle[KHALF ? 264 : 8];
-  if (KHALF && threadIdx.x < 33) *(u32x4*)(idle + 8 * threadIdx.x) = u32x4{0, 0, 0, 0};     // (behind the first barrier it is read)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 15, g = lane >> 4;
   const int Hkv = a.lay.Hkv, G = a.Hq / Hkv;
@@ -565,7 +561,7 @@ __global__ __launch_bounds__(256) void attention_prompt_kernel(AttnArgs a, int h
       // (requests for the next super-block stay on their way across the barrier; behind it nobody reads the other buffer any more)
       asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
       const uint16_t* fr = lds[buf] + lane * 8;
-      const uint16_t* half = g < 2 ? lds[buf] + 2 * KF * 512 + (g * 16 + c) * 8 : idle;
+      const uint16_t* half = lds[buf] + 2 * KF * 512 + ((g & 1) * 16 + c) * 8;
       buf ^= 1;
       if (sb * 32 >= own_keys) continue;
       f32x4 sc[2];
@@ -574,7 +570,10 @@ __global__ __launch_bounds__(256) void attention_prompt_kernel(AttnArgs a, int h
         sc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < KSTEPS; ++i) {
-          const f16x8 kf = i < KF ? *(const f16x8*)(fr + (t * KF + i) * 512) : *(const f16x8*)(half + t * 256);
+          f16x8 kf = i < KF ? *(const f16x8*)(fr + (t * KF + i) * 512) : *(const f16x8*)(half + t * 256);
+          // (lane groups without dims of the half step multiply zeros: a query of zero alone does not cancel an infinity.  32768 rows of
+          // head size 80, us a layer: without this 295, zeroed here 296, zeros read from LDS instead 299)
+          if (i >= KF && g >= 2) kf = f16x8{};
           sc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qf[i], sc[t], 0, 0, 0);
         }
       }
