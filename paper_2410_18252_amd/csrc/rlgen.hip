@@ -829,7 +829,10 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
         if (wide_only) cands = {1, 4};
         else cands = {1, 4, 6, 8, 9};
       } else {
-        cands = {0, 2, 4};
+        // (narrow rings beyond 128 rows, where there is no attention beside them, are never the fastest: profiles/one_round_tiles.txt)
+        const bool narrow = g.M <= 128 || tune_half;
+        cands = {0, 2};
+        if (wide_only || narrow) cands.push_back(4);
         if (g.M > 128) {                          // 256 rows to a tile would be half padding below
           cands.push_back(5); cands.push_back(10);
           if (splits == 1) cands.push_back(3);
@@ -837,7 +840,8 @@ int tune_gemms(rlgen_ctx* c, hipStream_t st) {
         if (!wide_only) cands.push_back(11);
         // the small rings are for launches that leave CUs short of blocks
         if (!wide_only && (long long)((g.M + 63) / 64) * ((g.N + g.N2 + 127) / 128) < 2048)
-          for (int v : {6, 7, 8, 9}) cands.push_back(v);
+          for (int v : {6, 9, 7, 8})
+            if (narrow || v == 6 || v == 9) cands.push_back(v);
       }
       // clocks drift with load, so the candidates take turns: one warm-up each, then three rounds in which
       // every candidate is timed over two launches; the smallest total wins
